@@ -670,12 +670,7 @@ tbn_status launch_conv_taps(const ConvArgs &a, const ConvMfmaParams &P, const Co
 
 bool conv_mfma_supported(const ConvArgs &a) { return plan_conv(a).ok; }
 
-tbn_status launch_conv_mfma(const ConvArgs &a) {
-    const ConvPlan pl = plan_conv(a);
-    if (!pl.ok) {
-        set_error("tbn_conv2d_forward: shape not supported by the matrix-core kernel");
-        return TBN_ERR_UNSUPPORTED;
-    }
+static ConvMfmaParams make_conv_params(const ConvArgs &a, const ConvPlan &pl) {
     ConvMfmaParams P;
     P.N = a.N; P.C = a.C; P.H = a.H; P.W = a.W; P.O = a.O; P.Ho = a.Ho; P.Wo = a.Wo;
     P.kh = a.kh; P.kw = a.kw; P.sh = a.sh; P.sw = a.sw; P.ph = a.ph; P.pw = a.pw;
@@ -690,18 +685,15 @@ tbn_status launch_conv_mfma(const ConvArgs &a) {
     P.n_colblk = pl.n_colblk;
     P.PR = pl.PR; P.PC = pl.PC;
     P.plane_bytes = pl.PR * pl.PC * kPixStride;
-    const int64_t fblocks = (P.R + 16 * pl.nft - 1) / (16 * pl.nft);
-    if (fblocks > 65535) {
-        set_error("tbn_conv2d_forward: too many distinct filters for one launch");
-        return TBN_ERR_UNSUPPORTED;
-    }
-    const dim3 grid(static_cast<unsigned>(pl.nblk * pl.n_colblk), static_cast<unsigned>(a.N), static_cast<unsigned>(fblocks));
-    tbn_status st = (a.dt == TBN_F32) ? launch_conv_taps<float>(a, P, pl, grid) : launch_conv_taps<uint16_t>(a, P, pl, grid);
-    if (st != TBN_OK) return st;
-    if (a.n_alpha == 1 || P.aligned) return TBN_OK;
-    // Channels whose filter contains a tile start are scaled by two alphas: a second pass of the same kernel over
-    // pairs of masked filters, 16 such channels per workgroup, where the doubled filter-bit area still fits the LDS
-    // (else the plain kernel for those channels).
+    return P;
+}
+
+// Channels whose filter contains a tile start are scaled by two alphas: a pass over pairs of masked filters, 16 such
+// channels per workgroup, where the doubled filter-bit area still fits the LDS (else the plain kernel for those
+// channels).  Runs behind a main pass that has written the channel with the alpha of its first weight.
+tbn_status launch_conv_tile_ends(const ConvArgs &a) {
+    const ConvPlan pl = plan_conv(a);
+    if (!pl.ok) return launch_conv_generic_tile_ends(a);
     ConvPlan fp = pl;
     fp.fix = true;
     fp.nft = kFtSmall;
@@ -711,8 +703,27 @@ tbn_status launch_conv_mfma(const ConvArgs &a) {
     const int64_t pairs_per_blk = 16 * kFtSmall / 2;
     const int64_t fix_blocks = (int64_t(a.k) - 1 + pairs_per_blk - 1) / pairs_per_blk;
     if (fp.lds > size_t(kPlanLdsMax) || fix_blocks > 65535 || a.C % kCK != 0) return launch_conv_generic_tile_ends(a);
+    const ConvMfmaParams P = make_conv_params(a, pl);
     const dim3 fgrid(static_cast<unsigned>(pl.nblk * pl.n_colblk), static_cast<unsigned>(a.N), static_cast<unsigned>(fix_blocks));
     return (a.dt == TBN_F32) ? launch_conv_taps<float>(a, P, fp, fgrid) : launch_conv_taps<uint16_t>(a, P, fp, fgrid);
+}
+
+tbn_status launch_conv_mfma(const ConvArgs &a) {
+    const ConvPlan pl = plan_conv(a);
+    if (!pl.ok) {
+        set_error("tbn_conv2d_forward: shape not supported by the matrix-core kernel");
+        return TBN_ERR_UNSUPPORTED;
+    }
+    const ConvMfmaParams P = make_conv_params(a, pl);
+    const int64_t fblocks = (P.R + 16 * pl.nft - 1) / (16 * pl.nft);
+    if (fblocks > 65535) {
+        set_error("tbn_conv2d_forward: too many distinct filters for one launch");
+        return TBN_ERR_UNSUPPORTED;
+    }
+    const dim3 grid(static_cast<unsigned>(pl.nblk * pl.n_colblk), static_cast<unsigned>(a.N), static_cast<unsigned>(fblocks));
+    const tbn_status st = (a.dt == TBN_F32) ? launch_conv_taps<float>(a, P, pl, grid) : launch_conv_taps<uint16_t>(a, P, pl, grid);
+    if (st != TBN_OK || a.n_alpha == 1 || P.aligned) return st;
+    return launch_conv_tile_ends(a);
 }
 
 }  // namespace tbn

@@ -1,0 +1,65 @@
+"""The convolution kernel with one wave per block of output pixels, at the edges of its blocks: exact arithmetic
+(activations in {-1, 0, +1}, alphas powers of two: every output is one float32 number whatever the order of the sums),
+so it has to equal the oracle bit for bit."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import tbn_oracle as orc
+from paper_2407_12075_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+# N, C, H, W, O, window, stride, pad, k, n_alpha
+CASES = [
+    (2, 9, 7, 7, 8, 3, 1, 1, 2, 2),          # 49 pixels in one block, a short chunk, fewer filters than a tile of 16
+    (1, 33, 14, 14, 34, 3, 1, 1, 2, 2),      # 17 distinct filters, one channel in the second chunk
+    (2, 64, 9, 65, 66, 3, 1, 1, 2, 1),       # 33 filters; 65 columns: a last column block of few pixels
+    (1, 40, 5, 91, 16, 3, 1, 1, 1, 1),       # odd rows: bfloat16 stores at 2-byte alignment
+    (3, 16, 13, 2, 64, 3, 1, 1, 64, 64),     # two columns (one pair of pixels), one distinct filter, 64 replicas
+    (1, 12, 3, 3, 130, 3, 1, 1, 65, 65),     # more replicas than lanes
+    (2, 48, 15, 17, 96, 3, 2, 1, 1, 1),      # stride 2, 96 filters: three tiles of 32
+    (1, 128, 11, 13, 260, 3, (2, 1), (0, 2), 2, 2),   # 130 filters, unequal strides and paddings, 4 or 8 channel slices
+    (1, 512, 4, 4, 32, 3, 1, 1, 1, 1),       # eight channel slices of several chunks
+    (1, 64, 14, 14, 48, 3, 1, 1, 3, 3),      # whole filters
+    (1, 32, 10, 12, 40, 3, 1, 1, 9, 9),      # tile ends inside filters: windows that wrap, repaired channels
+    (1, 32, 10, 12, 40, 3, 1, 1, 9, 1),
+    (2, 24, 8, 8, 6, 1, 1, 0, 2, 1),         # 1x1
+    (2, 56, 15, 15, 70, 1, 2, 0, 2, 2),      # 1x1 with stride 2
+    (1, 272, 9, 9, 128, 1, 1, 1, 1, 1),      # 1x1 with padding, 128 filters, a half chunk at the end
+    (1, 64, 8, 24, 45, 1, 1, 0, 8, 8),       # 1x1, tile ends inside filters
+]
+
+
+@pytest.fixture(scope="module")
+def tbn():
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    from paper_2407_12075_amd import tbn as binding
+    binding.lib()
+    return binding
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("N,C,H,W,O,ks,stride,pad,k,n_alpha", CASES)
+def test_conv_wave_blocks_exact(tbn, N, C, H, W, O, ks, stride, pad, k, n_alpha, dtype):
+    stride = stride if isinstance(stride, tuple) else (stride, stride)
+    pad = pad if isinstance(pad, tuple) else (pad, pad)
+    rng = np.random.default_rng(C * 1000 + O)
+    p = O * C * ks * ks // k
+    tile_ref = rng.integers(0, 2 ** 32, size=(p + 31) // 32, dtype=np.uint64).astype(np.uint32)
+    if p % 32:
+        tile_ref[-1] &= np.uint32((1 << (p % 32)) - 1)
+    alpha_ref = np.asarray([2.0 ** ((i % 5) - 2) for i in range(n_alpha)], dtype=np.float32)
+    x = rng.integers(-1, 2, size=(N, C, H, W)).astype(np.float32)
+    ref = orc.conv2d_forward(x, tile_ref, alpha_ref, O, ks, ks, k, stride=stride, pad=pad).astype(np.float32)
+    ref = np.maximum(ref, 0.0)
+    xd = torch.from_numpy(x).cuda()
+    if dtype == "bf16":
+        xd = xd.bfloat16()
+        ref = wl.bf16_bits_to_f32(wl.f32_to_bf16_bits(ref)).reshape(ref.shape)
+    y = tbn.tbn_conv2d_forward(xd, torch.from_numpy(tile_ref.view(np.int32)).cuda(), torch.from_numpy(alpha_ref).cuda(), O, ks, ks, k,
+                               stride=stride, pad=pad, flags=tbn.TBN_FLAG_RELU)
+    torch.cuda.synchronize()
+    got = y.float().cpu().numpy()
+    bad = np.argwhere(got != ref)
+    assert bad.size == 0, f"{len(bad)} of {got.size} outputs differ, first at {tuple(bad[0])}: {got[tuple(bad[0])]} against {ref[tuple(bad[0])]}"
