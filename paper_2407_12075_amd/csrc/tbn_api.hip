@@ -69,8 +69,9 @@ static LinearKernel choose_linear(const LinearArgs &a) {
         if (!(a.flags & TBN_FLAG_LARGE_BATCH) && linear_decode_supported(a) &&
             (a.M * (a.p / a.in) <= 16384 || !linear_skinny_supported(a)))
             return LinearKernel::Decode;
-        if (!(a.flags & (TBN_FLAG_BLOCK_KERNEL | TBN_FLAG_STREAM_KERNEL)) && linear_tile_preferred(a)) return LinearKernel::Tile;
-        if (linear_skinny_supported(a)) return LinearKernel::Skinny;
+        if (!(a.flags & (TBN_FLAG_BLOCK_KERNEL | TBN_FLAG_STREAM_KERNEL)) && linear_tile_preferred(a))
+            return linear_direct_preferred(a, true, false) ? LinearKernel::Direct : LinearKernel::Tile;
+        if (linear_skinny_supported(a)) return linear_direct_preferred(a, false, true) ? LinearKernel::Direct : LinearKernel::Skinny;
         if (!(a.flags & TBN_FLAG_BLOCK_KERNEL)) {
             // bfloat16, tile of whole rows: 128 x 128 blocks with load waves; the streaming kernel (64-row half
             // tiles, twice the workgroups) where the blocks would leave half of the CUs or more idle
@@ -90,9 +91,9 @@ static LinearKernel choose_linear(const LinearArgs &a) {
             // 1024 distinct columns 57 us against 84, 8192 x 4096 -> 8192 distinct columns 1379 against 1672)
             if (a.dt == TBN_F32 && linear_tile_supported(a)) return LinearKernel::Tile;
         }
-        if (linear_mfma_supported(a)) return LinearKernel::Mfma;
+        if (linear_mfma_supported(a)) return linear_direct_preferred(a, false, false) ? LinearKernel::Direct : LinearKernel::Mfma;
         if (linear_rows_supported(a)) return LinearKernel::Rows;
-        // row lengths and alignments that none of the kernels above takes (in no multiple of 8), tile of whole rows
+        // tile of whole rows, row lengths and alignments that none of the kernels above takes
         if (linear_direct_supported(a)) return LinearKernel::Direct;
     }
     return LinearKernel::Generic;

@@ -1,109 +1,437 @@
-// Fully-connected tiled-bit layer for row lengths the matrix-core kernels do not take (in no multiple of 8, or
-// activations that are not 16-byte aligned: the 196-token mixing layers of an MLP-Mixer, 300- or 2050-wide rows),
-// with a tile of whole weight rows.
+// Fully-connected tiled-bit layer with a tile of whole weight rows, any row length and alignment: what the other
+// matrix-core kernels do not take (in no multiple of 8, activations that are not 16-byte aligned: the 196-token mixing
+// layers of an MLP-Mixer, 300- or 2050-wide rows), and the small and middle-sized layers it is faster on.
 //
 // What is computed (Section "Method", Eq. 4-5 and the scaling after Eq. 8): with p a multiple of `in` the weight is
 // the U = p / in rows of the tile stacked k times, copy t scaled by alpha[t]; Z = X * T^T is formed once and
 // Y[:, t*U + u] = alpha[t] * Z[:, u].
 //
-// A thread owns one batch row and 16 distinct columns: it walks its row of X one or two elements at a time (a lane's
-// loads hit the same cache line many times in a row, whatever the row's alignment) and feeds every element to 16 sums with
-// +-1 values that all lanes read from the same LDS address.  The +-1 weights of the workgroup's 16 tile rows pass
-// through LDS as float32, 512 positions of K at a time.  Vector-ALU work, an order of magnitude above one thread per
-// output element (8192 x 196 -> 384, k = 4: 34 us against 382; 8192 x 2050 -> 1026, k = 2: 0.50 ms against 8.9).
+// What bounds it: such layers are small (8192 x 196 -> 384 moves 19 MB), so the time goes into latency: how many waves
+// have loads in flight and how few dependent steps lie between the launch and the stores.  The waves of a workgroup share
+// 32 batch rows and up to 128 distinct columns and take the 256-byte chunks of K in turn; each stages its chunk
+// through 8 KiB of LDS of its own (no barrier in the K loop) into the operand layout of v_mfma_f32_32x32x16_bf16.
+//   * Rows start at any element: activations are read 16 bytes per lane at element alignment.  The last chunk of a row
+//     reads its last pieces at the row's end instead of past it and shifts them into place, zeros behind: no load
+//     leaves its row and no load is conditional.
+//   * The +-1 operand: 32 or 64 tile bits per lane, column and chunk at any bit position (two or three words and a
+//     funnel shift; the shift never changes), a byte of them through a 256-entry table in LDS.
+//   * float32 activations are split exactly into three bfloat16 terms, every product is exact and the sums are float32.
+//   * The waves leave their sums in LDS as rows of 32 columns; all threads of the workgroup add them in wave order (the
+//     result does not depend on timing) and store four (float32) or eight (bfloat16) columns of a row at once.
+//
+// Microseconds per call (graph replays), before (a batch row and 16 columns per thread on the vector ALUs) / now:
+// float32 8192 x 196 -> 384, k = 4: 32.9 / 7.8; 12608 x 197 -> 96, k = 4: 27.6 / 5.7; 8192 x 1199 -> 1024, k = 2:
+// 330 / 41; bfloat16 8192 x 2050 -> 1026, k = 2: 490 / 44; 16 x 4095 -> 4096, k = 8: 275 / 13; 8192 x 4096 -> 4096,
+// k = 8 with activations at an odd element: 1077 / 72.  Its relative error in float32 against 64-bit sums at the first of
+// these: 2.5e-7 / 5.6e-8.
 #include "tbn_common.h"
+
+#include <type_traits>
 
 namespace tbn {
 
 namespace {
 
-constexpr int kFG = 16;       // distinct columns per workgroup
-constexpr int kRows = 128;    // batch rows per workgroup, one per thread
-constexpr int kStage = 512;   // positions of K staged per pass
+typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
+typedef float f32x16_t __attribute__((ext_vector_type(16)));
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
+typedef float f32x2_t __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
+
+// 16 bytes at the alignment of an element
+template <typename XT> struct Piece;
+template <> struct Piece<float> { typedef uint32_t type __attribute__((ext_vector_type(4), aligned(4))); };
+template <> struct Piece<uint16_t> { typedef uint32_t type __attribute__((ext_vector_type(4), aligned(2))); };
+
+union Frag {
+    bf16x8_t v;
+    u32x4_t q;
+};
+
+constexpr int kChunkBytes = 256;   // bytes of a row per chunk: 64 floats (four MFMA steps) or 128 bfloat16 (eight)
+constexpr int kMaxNT = 4;          // column tiles of 32 per workgroup
 
 struct DirectLinearParams {
-    int64_t M, in, out, U;
+    int64_t M, out;
+    int32_t in, U;
+    int32_t chunks;       // ceil(in / elements per chunk)
+    uint32_t last_word;   // of the tile
     int32_t reps, n_alpha, relu;
+    uint32_t groups;      // groups of NT * 32 distinct columns
+    uint32_t row_tiles;   // tiles of 32 batch rows
 };
 
-// VEC consecutive activations with one load (the caller has checked the alignment)
-template <typename T, int VEC> struct XVec;
-template <> struct XVec<float, 1> { static __device__ __forceinline__ void load(const float *p, float (&v)[1]) { v[0] = *p; } };
-template <> struct XVec<float, 2> {
-    static __device__ __forceinline__ void load(const float *p, float (&v)[2]) {
-        const float2 t = *reinterpret_cast<const float2 *>(p);
-        v[0] = t.x; v[1] = t.y;
-    }
-};
-template <> struct XVec<uint16_t, 1> { static __device__ __forceinline__ void load(const uint16_t *p, float (&v)[1]) { v[0] = bf16_bits_to_f32(*p); } };
-template <> struct XVec<uint16_t, 2> {
-    static __device__ __forceinline__ void load(const uint16_t *p, float (&v)[2]) {
-        const uint32_t t = *reinterpret_cast<const uint32_t *>(p);
-        v[0] = __uint_as_float(t << 16); v[1] = __uint_as_float(t & 0xffff0000u);
-    }
-};
+__device__ __forceinline__ uint32_t pack2(float a, float b) {
+    const f32x2_t f = {a, b};
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(f, bf16x2_t));   // round to nearest even in hardware
+}
 
-template <typename T, int VEC>
-__global__ __launch_bounds__(kRows) void linear_direct_kernel(const T *__restrict__ x, T *__restrict__ y,
-                                                             const uint32_t *__restrict__ tile,
-                                                             const float *__restrict__ alpha, DirectLinearParams P) {
-    __shared__ __attribute__((aligned(16))) float w_lds[kStage][kFG];   // +1 / -1
-    const int tid = threadIdx.x;
-    const int64_t m = int64_t(blockIdx.x) * kRows + tid;
-    const int64_t u0 = int64_t(blockIdx.y) * kFG;
-    const bool live = m < P.M;
-    const T *xr = x + (live ? m : P.M - 1) * P.in;   // rows past M repeat the last one; never written
-
-    float acc[kFG];
+// Truncation split of eight floats into three bf16x8 operands (8 + 8 + 8 significand bits: exact).  An infinity is all in
+// the first term (infinity minus itself would put a NaN in the others); a NaN stays one in the second.
+__device__ __forceinline__ void split8(const float (&x)[8], Frag (&t)[3]) {
+    uint32_t h[3][8];
+    float top = 0.f;
 #pragma unroll
-    for (int f = 0; f < kFG; ++f) acc[f] = 0.f;
-
-    for (int64_t j0 = 0; j0 < P.in; j0 += kStage) {
-        const int32_t n = static_cast<int32_t>(P.in - j0 < kStage ? P.in - j0 : kStage);
-        __syncthreads();   // the previous pass is done with the staged weights
-        for (int32_t e = tid; e < n; e += kRows) {
+    for (int i = 0; i < 8; ++i) {
+        const uint32_t t0 = __float_as_uint(x[i]) & 0xffff0000u;
+        const float r1 = x[i] - __uint_as_float(t0);
+        const uint32_t t1 = __float_as_uint(r1) & 0xffff0000u;
+        const float r2 = r1 - __uint_as_float(t1);
+        h[0][i] = t0; h[1][i] = t1; h[2][i] = __float_as_uint(r2);
+        top = fmaxf(top, fabsf(x[i]));
+    }
+    if (__builtin_expect(__any(top == __builtin_inff()), 0)) {
 #pragma unroll
-            for (int f = 0; f < kFG; ++f) {
-                const int64_t u = u0 + f < P.U ? u0 + f : P.U - 1;   // columns past U repeat the last one; never written
-                const int64_t bit = u * P.in + j0 + e;               // < p
-                w_lds[e][f] = ((tile[bit >> 5] >> (bit & 31)) & 1u) ? 1.f : -1.f;
+        for (int i = 0; i < 8; ++i)
+            if (fabsf(x[i]) == __builtin_inff()) h[1][i] = h[2][i] = 0u;
+    }
+#pragma unroll
+    for (int j = 0; j < 3; ++j)
+#pragma unroll
+        for (int v = 0; v < 4; ++v)   // high halves of two words in one: (lo >> 16) | (hi & 0xffff0000)
+            t[j].q[v] = __builtin_amdgcn_perm(h[j][2 * v + 1], h[j][2 * v], 0x07060302u);
+}
+
+// drops the first `bits` bits (a multiple of 16) of a piece and moves the rest down, zeros on top
+__device__ __forceinline__ u32x4_t shift_down(u32x4_t v, uint32_t bits) {
+    const uint32_t words = bits >> 5, odd = bits & 16u;
+    uint32_t w[5] = {v[0], v[1], v[2], v[3], 0u};
+    if (words & 1) { w[0] = w[1]; w[1] = w[2]; w[2] = w[3]; w[3] = 0u; }
+    if (words & 2) { w[0] = w[2]; w[1] = w[3]; w[2] = w[3] = 0u; }
+    if (words >= 4) w[0] = w[1] = w[2] = w[3] = 0u;
+    u32x4_t r;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) r[i] = __funnelshift_r(w[i], w[i + 1], odd);
+    return r;
+}
+
+template <int NT, int KW>
+struct Lds {
+    static constexpr int kRegion = NT * 4096 > 8192 ? NT * 4096 : 8192;   // a wave's chunk of X, later its sums
+    static constexpr int kBytes = 4096 + KW * kRegion;
+};
+
+template <typename XT, int NT, int KW>
+__global__ __launch_bounds__(64 * KW) __attribute__((amdgpu_waves_per_eu(2))) void linear_direct_kernel(const XT *__restrict__ x, XT *__restrict__ y,
+                                                               const uint32_t *__restrict__ tile,
+                                                               const float *__restrict__ alpha, DirectLinearParams P) {
+    typedef Lds<NT, KW> L;
+    typedef typename Piece<XT>::type piece_t;
+    constexpr bool kF32 = std::is_same<XT, float>::value;
+    constexpr int kCE = kChunkBytes / static_cast<int>(sizeof(XT));   // elements of K per chunk
+    constexpr int kEP = 16 / static_cast<int>(sizeof(XT));            // elements per piece
+    constexpr int kSteps = kCE / 16;                                  // MFMA steps per chunk
+    constexpr int kWords = kCE / 64;                                  // 32-bit windows per lane half, column and chunk
+    extern __shared__ __attribute__((aligned(16))) unsigned char s_raw[];
+    u32x4_t *s_table = reinterpret_cast<u32x4_t *>(s_raw);
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int ln = lane & 31, lg = lane >> 5;
+    unsigned char *region = s_raw + 4096 + wave * L::kRegion;   // this wave's
+
+    // the column groups of a row tile take consecutive slots of one XCD (ids are dealt round-robin to the eight of them):
+    // the rows of X they share come from HBM once
+    uint32_t rt, cg;
+    {
+        const uint32_t bid = blockIdx.x, xcd = bid & 7, slot = bid >> 3, full = (P.row_tiles / 8) * P.groups;
+        if (slot < full) {
+            const uint32_t q = slot / P.groups;
+            cg = slot - q * P.groups;
+            rt = q * 8 + xcd;
+        } else {   // the remaining row tiles: plain order
+            const uint32_t rest = bid - full * 8, q = rest / P.groups;
+            cg = rest - q * P.groups;
+            rt = (P.row_tiles / 8) * 8 + q;
+        }
+    }
+    const int64_t m0 = int64_t(rt) * 32;
+    const int32_t u0 = static_cast<int32_t>(cg) * (NT * 32);
+
+    // loads: piece (i, h) of a chunk is row 8i + lane/8, bytes 128h + 16*(lane%8) .. + 15: eight lanes read 128 bytes in
+    // a row.  Rows past M repeat the last one; they are never written.
+    const unsigned char *x_blk = reinterpret_cast<const unsigned char *>(x + m0 * P.in);
+    const int rows_last = static_cast<int>(P.M - 1 - m0 < 31 ? P.M - 1 - m0 : 31);
+    uint32_t ld_off[4];      // bytes from x_blk
+    // byte positions in the wave's region: 256 bytes per row, piece p of row r at place p ^ (r % 16); piece (i, h) is at
+    // 2048 i + st_pos[(i + h) % 2]
+    uint32_t st_pos[2];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int r = 8 * i + (lane >> 3);
+        ld_off[i] = static_cast<uint32_t>(r < rows_last ? r : rows_last) * static_cast<uint32_t>(P.in) * static_cast<uint32_t>(sizeof(XT));
+    }
+    st_pos[0] = static_cast<uint32_t>((lane >> 3) * 256 + (((lane & 7) ^ (lane >> 3)) << 4));
+    st_pos[1] = st_pos[0] ^ 128u;
+    const int e_lane = (lane & 7) * kEP;   // first element of piece h in a chunk: e_lane + h * kCE / 2
+
+    u32x4_t xr[8];   // the chunk in flight: [i][h]
+    auto load_chunk = [&](int32_t c) {
+        if ((c + 1) * kCE <= P.in) {
+            const unsigned char *src = x_blk + int64_t(c) * kChunkBytes;
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int h = 0; h < 2; ++h)
+                    xr[2 * i + h] = *reinterpret_cast<const piece_t *>(src + (ld_off[i] + 16 * (lane & 7)) + h * (kChunkBytes / 2));
+        } else if (P.in >= kEP) {   // the last chunk: pieces that would leave the row are read at its end
+            const int32_t lim = P.in - kEP;
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const int32_t e = c * kCE + e_lane + h * (kCE / 2);
+                const uint32_t off = static_cast<uint32_t>(e < lim ? e : lim) * static_cast<uint32_t>(sizeof(XT));
+#pragma unroll
+                for (int i = 0; i < 4; ++i) xr[2 * i + h] = *reinterpret_cast<const piece_t *>(x_blk + (ld_off[i] + off));
+            }
+        } else {   // rows shorter than a piece
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const XT *row = reinterpret_cast<const XT *>(x_blk + ld_off[i]);
+                u32x4_t v = {0u, 0u, 0u, 0u};
+#pragma unroll
+                for (int j = 0; j < kEP - 1; ++j) {
+                    if (j >= P.in) break;
+                    if constexpr (kF32) v[j] = __float_as_uint(row[j]);
+                    else v[j / 2] |= uint32_t(row[j]) << (16 * (j & 1));
+                }
+                xr[2 * i] = (lane & 7) == 0 ? v : u32x4_t{0u, 0u, 0u, 0u};
+                xr[2 * i + 1] = u32x4_t{0u, 0u, 0u, 0u};
             }
         }
-        __syncthreads();
-        const T *xs = xr + j0;
-#pragma unroll 4
-        for (int32_t e = 0; e < n; e += VEC) {   // n is a multiple of VEC: `in` is, and so is the stage
-            float xv[VEC];
-            XVec<T, VEC>::load(xs + e, xv);
+    };
+
+    // tile words of this lane's column in every column tile: bit u * in + k, lane half lg covers kWords windows per chunk
+    uint32_t word0[NT], sh[NT];
 #pragma unroll
-            for (int i = 0; i < VEC; ++i) {
-                const float4 *wv = reinterpret_cast<const float4 *>(w_lds[e + i]);
+    for (int t = 0; t < NT; ++t) {
+        const int32_t u = u0 + 32 * t + ln < P.U ? u0 + 32 * t + ln : P.U - 1;   // columns past U repeat the last one; never written
+        const uint64_t bit = uint64_t(u) * static_cast<uint32_t>(P.in) + static_cast<uint32_t>(lg * (kCE / 2));
+        word0[t] = static_cast<uint32_t>(bit >> 5);
+        sh[t] = static_cast<uint32_t>(bit & 31);
+    }
+    uint32_t wr[NT][kWords + 1];
+    auto load_words = [&](int32_t c) {   // words past the tile's end belong to positions past the row's end: any value will do
 #pragma unroll
-                for (int g = 0; g < kFG / 4; ++g) {
-                    const float4 s = wv[g];
-                    acc[4 * g + 0] = fmaf(xv[i], s.x, acc[4 * g + 0]);
-                    acc[4 * g + 1] = fmaf(xv[i], s.y, acc[4 * g + 1]);
-                    acc[4 * g + 2] = fmaf(xv[i], s.z, acc[4 * g + 2]);
-                    acc[4 * g + 3] = fmaf(xv[i], s.w, acc[4 * g + 3]);
+        for (int t = 0; t < NT; ++t)
+#pragma unroll
+            for (int w = 0; w <= kWords; ++w) {
+                const uint32_t i = word0[t] + static_cast<uint32_t>(c * (kCE / 32) + w);
+                wr[t][w] = tile[i < P.last_word ? i : P.last_word];
+            }
+    };
+
+    if (wave < P.chunks) {
+        load_chunk(wave);
+        load_words(wave);
+    }
+    // sign table: entry e, element i is +1 if bit i of e is set, else -1
+    for (int e = tid; e < 256; e += 64 * KW) {
+        u32x4_t t;
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+            t[v] = (((e >> (2 * v)) & 1) ? 0x3f80u : 0xbf80u) | ((((e >> (2 * v + 1)) & 1) ? 0x3f80u : 0xbf80u) << 16);
+        s_table[e] = t;
+    }
+    __syncthreads();
+
+    // float32: the two small terms of the split have sums of their own, so that they are not rounded to the large sum's
+    // last place at every step (relative error at in = 1199: 5.6e-8, against 2.3e-7 with one sum)
+    f32x16_t acc[NT], low[kF32 ? NT : 1];
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+            acc[t][e] = 0.f;
+            if constexpr (kF32) low[t][e] = 0.f;
+        }
+
+    for (int32_t c = wave; c < P.chunks; c += KW) {
+        int steps = kSteps;
+        if ((c + 1) * kCE > P.in) {   // the last chunk of a row that does not fill it
+            const int tail = P.in - c * kCE;
+            if (tail < kCE / 2) steps = (tail + 7) / 8;   // step s takes elements 8s .. + 7 of both halves of the chunk
+            if (P.in >= kEP) {
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const int past = e_lane + h * (kCE / 2) - (tail - kEP);   // elements that the load was moved back by
+                    const uint32_t bits = past > 0 ? static_cast<uint32_t>(past) * (8u * sizeof(XT)) : 0u;
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) xr[2 * i + h] = shift_down(xr[2 * i + h], bits);
                 }
             }
         }
+        uint32_t wc[NT][kWords];
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+#pragma unroll
+            for (int w = 0; w < kWords; ++w) wc[t][w] = __funnelshift_r(wr[t][w], wr[t][w + 1], sh[t]);
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) *reinterpret_cast<u32x4_t *>(region + st_pos[(i + h) & 1] + 2048 * i) = xr[2 * i + h];
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();   // lanes read what other lanes of the wave wrote (LDS operations of a wave stay in order)
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        if (c + KW < P.chunks) {
+            load_chunk(c + KW);
+            load_words(c + KW);
+        }
+        // operands of row ln.  float32: step s of lane half lg takes floats 32*lg + 8*s .. + 7, pieces 8*lg + 2*s and + 1;
+        // bfloat16: elements 64*lg + 8*s .. + 7, piece 8*lg + s
+        auto sign = [&](int t, int s) {
+            Frag sg;
+            sg.q = s_table[(wc[t][s / 4] >> (8 * (s % 4))) & 0xffu];
+            return sg.v;
+        };
+#pragma unroll
+        for (int s = 0; s < kSteps; ++s) {
+            if (s >= steps) break;
+            if constexpr (kF32) {
+                const f32x4_t a = *reinterpret_cast<const f32x4_t *>(region + ln * 256 + (((8 * lg + 2 * s) ^ (ln & 15)) << 4));
+                const f32x4_t b = *reinterpret_cast<const f32x4_t *>(region + ln * 256 + (((8 * lg + 2 * s + 1) ^ (ln & 15)) << 4));
+                const float xs[8] = {a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
+                Frag terms[3];
+                split8(xs, terms);
+#pragma unroll
+                for (int t = 0; t < NT; ++t) {
+                    const bf16x8_t sg = sign(t, s);
+                    acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(sg, terms[0].v, acc[t], 0, 0, 0);
+                    low[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(sg, terms[2].v, low[t], 0, 0, 0);
+                    low[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(sg, terms[1].v, low[t], 0, 0, 0);
+                }
+            } else {
+                Frag xt;
+                xt.q = *reinterpret_cast<const u32x4_t *>(region + ln * 256 + (((8 * lg + s) ^ (ln & 15)) << 4));
+#pragma unroll
+                for (int t = 0; t < NT; ++t) acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(sign(t, s), xt.v, acc[t], 0, 0, 0);
+            }
+        }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();   // the next chunk overwrites the region
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     }
 
-    if (!live) return;
-    T *yr = y + m * P.out;
-    for (int32_t t = 0; t < P.reps; ++t) {
-        const float al = alpha[P.n_alpha == 1 ? 0 : t];
+    if constexpr (kF32) {
 #pragma unroll
-        for (int f = 0; f < kFG; ++f) {
-            const int64_t u = u0 + f;
-            if (u < P.U) {
-                float v = al * acc[f];
-                if (P.relu) v = fmaxf(v, 0.f);
-                ElemIO<T>::store(yr + int64_t(t) * P.U + u, v);
+        for (int t = 0; t < NT; ++t) acc[t] += low[t];
+    }
+    // The wave's sums, 32 rows of 32 columns per tile: register 4q + e is column 8q + 4lg + e of row ln; the four columns of
+    // group g of row r sit at group g ^ (r & 7).
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            *reinterpret_cast<f32x4_t *>(region + t * 4096 + ln * 128 + (((2 * q + lg) ^ (ln & 7)) << 4)) =
+                f32x4_t{acc[t][4 * q], acc[t][4 * q + 1], acc[t][4 * q + 2], acc[t][4 * q + 3]};
+    __syncthreads();
+
+    // y[m, u + t*U] = alpha[t] * Z[m, u]: a thread adds and writes kEP adjacent columns of a row, neighbouring threads
+    // neighbouring columns
+    constexpr int kGroupsPerRow = NT * 32 / kEP;
+    for (int unit = tid; unit < 32 * kGroupsPerRow; unit += 64 * KW) {
+        const int r = unit / kGroupsPerRow, g = unit - r * kGroupsPerRow;
+        const int64_t m = m0 + r;
+        const int32_t u = u0 + g * kEP;
+        if (m >= P.M || u >= P.U) continue;
+        const int t = g * kEP / 32, g4 = (g * kEP % 32) / 4;
+        f32x4_t z[kEP / 4];
+#pragma unroll
+        for (int w = 0; w < KW; ++w)
+#pragma unroll
+            for (int j = 0; j < kEP / 4; ++j) {
+                const f32x4_t v = *reinterpret_cast<const f32x4_t *>(s_raw + 4096 + w * L::kRegion + t * 4096 + r * 128 + (((g4 + j) ^ (r & 7)) << 4));
+                z[j] = w == 0 ? v : z[j] + v;
+            }
+        XT *dst = y + m * P.out + u;
+        const bool whole = u + kEP <= P.U;
+        for (int32_t rep = 0; rep < P.reps; ++rep, dst += P.U) {
+            const float al = alpha[P.n_alpha == 1 ? 0 : rep];
+            float v[kEP];
+#pragma unroll
+            for (int e = 0; e < kEP; ++e) {
+                v[e] = al * z[e / 4][e % 4];
+                if (P.relu) v[e] = fmaxf(v[e], 0.f);
+            }
+            if (whole) {
+                u32x4_t pk;
+                if constexpr (kF32) pk = u32x4_t{__float_as_uint(v[0]), __float_as_uint(v[1]), __float_as_uint(v[2]), __float_as_uint(v[3])};
+                else pk = u32x4_t{pack2(v[0], v[1]), pack2(v[2], v[3]), pack2(v[4 % kEP], v[5 % kEP]), pack2(v[6 % kEP], v[7 % kEP])};
+                *reinterpret_cast<piece_t *>(dst) = pk;
+            } else {
+#pragma unroll
+                for (int e = 0; e < kEP; ++e)
+                    if (u + e < P.U) ElemIO<XT>::store(dst + e, v[e]);
             }
         }
     }
+}
+
+template <typename XT, int NT, int KW>
+tbn_status launch_one(const LinearArgs &a, const DirectLinearParams &P) {
+    typedef Lds<NT, KW> L;
+    // dynamic LDS above the default limit has to be allowed once per kernel (thread-safe static initialisation)
+    static const hipError_t attr = L::kBytes > 65536
+        ? hipFuncSetAttribute(reinterpret_cast<const void *>(&linear_direct_kernel<XT, NT, KW>),
+                              hipFuncAttributeMaxDynamicSharedMemorySize, L::kBytes)
+        : hipSuccess;
+    if (attr != hipSuccess) {
+        set_error("tbn_linear_forward: cannot reserve %d bytes of LDS", L::kBytes);
+        return TBN_ERR_DEVICE;
+    }
+    hipLaunchKernelGGL((linear_direct_kernel<XT, NT, KW>), dim3(P.row_tiles * P.groups), dim3(64 * KW), L::kBytes, a.stream,
+                       static_cast<const XT *>(a.x), static_cast<XT *>(a.y), a.tile, a.alpha, P);
+    return check_launch("tbn_linear_forward (direct kernel)");
+}
+
+template <typename XT, int NT>
+tbn_status launch_kw(const LinearArgs &a, const DirectLinearParams &P, int kw) {
+    switch (kw) {
+        case 8: return launch_one<XT, NT, 8>(a, P);
+        case 4: return launch_one<XT, NT, 4>(a, P);
+        case 2: return launch_one<XT, NT, 2>(a, P);
+    }
+    return launch_one<XT, NT, 1>(a, P);
+}
+
+template <typename XT>
+tbn_status launch_nt(const LinearArgs &a, const DirectLinearParams &P, int nt, int kw) {
+    switch (nt) {
+        case 4: return launch_kw<XT, 4>(a, P, kw);
+        case 3: return launch_kw<XT, 3>(a, P, kw);
+        case 2: return launch_kw<XT, 2>(a, P, kw);
+    }
+    return launch_kw<XT, 1>(a, P, kw);
+}
+
+struct DirectPlan {
+    int nt, kw;
+    int64_t groups, row_tiles, chunks;
+};
+
+// W = 32 x 32 tiles of Z.  Up to 1024 of them a workgroup takes one and as many waves as bring the chip to 3072 (12 per
+// CU; 8192 x 196 -> 96: 8.0 us with four waves, 9.0 with two, 10.9 with eight).  Beyond that float32 takes four column
+// tiles and at least four waves: more columns share the split of an activation (2500 x 520 -> 1400: 23.5 us against 27.7
+// with two tiles; 6000 x 2504 -> 640: 65.8 against 80.1).  bfloat16 takes two (12000 x 520 -> 152: 10.8 us against 13.4
+// with four), and above 4096 as many as leave the fewest empty ones (8192 x 2050 -> 513: 41.9 us with three, 45.3 with
+// four).
+DirectPlan plan(const LinearArgs &a) {
+    DirectPlan pl;
+    const bool f32 = a.dt == TBN_F32;
+    const int64_t tiles = (a.p / a.in + 31) / 32;
+    const int64_t ce = f32 ? kChunkBytes / 4 : kChunkBytes / 2;
+    pl.row_tiles = (a.M + 31) / 32;
+    pl.chunks = (a.in + ce - 1) / ce;
+    const int64_t W = pl.row_tiles * tiles;
+    int nt = kMaxNT;
+    if (W <= 1024) nt = 1;
+    else if (!f32 && W <= 4096) nt = 2;
+    else if (!f32)
+        for (int cand = kMaxNT - 1; cand >= 2; --cand)
+            if ((tiles + cand - 1) / cand * cand < (tiles + nt - 1) / nt * nt) nt = cand;
+    pl.groups = (tiles + nt - 1) / nt;
+    pl.nt = static_cast<int>((tiles + pl.groups - 1) / pl.groups);
+    pl.kw = 8;
+    while (pl.kw > (f32 ? 4 : 1) && pl.row_tiles * pl.groups * pl.kw > 3072) pl.kw /= 2;
+    return pl;
 }
 
 }  // namespace
@@ -114,33 +442,59 @@ bool linear_direct_supported(const LinearArgs &a) {
     if (a.M < 1 || a.in < 1 || a.p % a.in != 0) return false;
     const int64_t U = a.p / a.in;
     if (U < 1 || U > a.out || a.out % U != 0 || a.out / U > (1 << 30)) return false;
+    // offsets inside 32 rows, columns and tile words are kept in 32 bits
+    if (a.in > (1 << 25) - 1 || U > (1 << 30) || a.p >= (int64_t(1) << 36)) return false;
     if (a.n_alpha != 1 && a.n_alpha != a.out / U) return false;
-    if ((a.M + kRows - 1) / kRows > 0x7fffffffLL || (U + kFG - 1) / kFG > 65535) return false;
-    return true;
+    const DirectPlan pl = plan(a);
+    return pl.row_tiles <= 0x7fffffffLL && pl.row_tiles * pl.groups <= 0x7fffffffLL;
+}
+
+// Where this kernel beats the one that would otherwise take a call with rows in multiples of 8 and 16-byte aligned
+// activations.  Graph replays, microseconds per call, the other kernel / this one; W is the number of 32 x 32 tiles of Z.
+bool linear_direct_preferred(const LinearArgs &a, bool tile, bool small_batch) {
+    if ((a.flags & ~uint32_t(TBN_FLAG_RELU)) || !linear_direct_supported(a)) return false;   // flags that steer to another kernel
+    const bool f32 = a.dt == TBN_F32;
+    const int64_t U = a.p / a.in, W = ((a.M + 31) / 32) * ((U + 31) / 32);
+    if (tile) {
+        // the tile kernel splits K among waves in whole slices: rows that do not divide leave it one wave per tile (bfloat16
+        // 1297 x 3840 -> 64: 23.0 / 8.8; 500 x 512 -> 256: 6.1 / 4.6; 9926 x 512 -> 32: 7.5 / 7.9; float32 817 x 640 -> 476:
+        // 15.5 / 8.4); float32 and few tiles, where it takes four columns tiles per wave (200 x 4096 -> 512: 23.5 / 15.5;
+        // 600 x 4096 -> 512: 25.1 / 29.4)
+        if (f32 && W <= 256) return true;
+        return linear_tile_k_slices(a) == 1 && W <= 1024 && a.in > kChunkBytes / (f32 ? 4 : 2) && (f32 || a.M <= 4096);
+    }
+    if (small_batch) {
+        // more than one workgroup of the small-batch kernel per CU (bfloat16 530 x 2600 -> 190: 12.3 / 8.1; float32
+        // 1000 x 776 -> 250: 20.3 / 6.7); below that rows of whole lines (bfloat16 in = 384 / 768 / 1280 / 5120 at 64 x 512
+        // columns: 4.6 / 4.1, 6.4 / 4.5, 7.6 / 5.3, 13.4 / 9.6, but 8.7 / 8.1 at 4096, left where it was, and in = 888,
+        // 1168: 5.6 / 6.9, 7.1 / 9.7; float32 in = 512 / 1024 / 1536: 5.6 / 5.0, 8.0 / 6.5, 7.7 / 8.1)
+        if (W <= 1024 && ((U + 15) / 16) * ((a.M + 15) / 16) > 256) return true;
+        if (U % 8 != 0 || a.in < 384) return false;
+        return f32 ? a.in % 64 == 0 && a.in <= 1280 : a.in % 128 == 0 && a.in % 4096 != 0;
+    }
+    // the general kernel's 128 x 128 blocks: few of them (bfloat16 200 x 520 -> 640: 11.1 / 4.6; 12000 x 520 -> 152: 13.0 /
+    // 10.6; 2500 x 2504 -> 640: 20.0 / 20.2; 2500 x 1000 -> 1400: 15.9 / 19.4; float32 300 x 200 -> 250: 21.6 / 4.4; 6000 x
+    // 2504 -> 640: 75 / 66; 12000 x 520 -> 640: 51 / 50), and columns that it stores one by one (bfloat16 8364 x 376 -> 1076:
+    // 54 / 24; 5338 x 1024 -> 2564: 74 / 60)
+    if (U % 8 != 0) return W <= 16384;
+    if (f32) return W <= 4096;
+    return W <= 1024 || (W <= 2048 && a.in <= 2048);
 }
 
 tbn_status launch_linear_direct(const LinearArgs &a) {
+    const DirectPlan pl = plan(a);
     DirectLinearParams P;
-    P.M = a.M; P.in = a.in; P.out = a.out;
-    P.U = a.p / a.in;
-    P.reps = static_cast<int32_t>(a.out / P.U);
+    P.M = a.M; P.out = a.out;
+    P.in = static_cast<int32_t>(a.in);
+    P.U = static_cast<int32_t>(a.p / a.in);
+    P.last_word = static_cast<uint32_t>((a.p + 31) / 32 - 1);
+    P.chunks = static_cast<int32_t>(pl.chunks);
+    P.reps = static_cast<int32_t>(a.out / (a.p / a.in));
     P.n_alpha = a.n_alpha;
     P.relu = (a.flags & TBN_FLAG_RELU) ? 1 : 0;
-    const dim3 grid(static_cast<unsigned>((a.M + kRows - 1) / kRows), static_cast<unsigned>((P.U + kFG - 1) / kFG));
-    // activations per load: two where the row length and the alignment of x allow
-    const size_t esz = a.dt == TBN_F32 ? 4 : 2;
-    const uintptr_t xa = reinterpret_cast<uintptr_t>(a.x);
-    const int vec = (a.in % 2 == 0 && xa % (2 * esz) == 0) ? 2 : 1;   // (four per load measured slower: 48 us against 37 at in = 196)
-#define TBN_DIRECT_LAUNCH(T, V)                                                                                          \
-    hipLaunchKernelGGL((linear_direct_kernel<T, V>), grid, dim3(kRows), 0, a.stream, static_cast<const T *>(a.x),           \
-                       static_cast<T *>(a.y), a.tile, a.alpha, P)
-    if (a.dt == TBN_F32) {
-        if (vec == 2) TBN_DIRECT_LAUNCH(float, 2); else TBN_DIRECT_LAUNCH(float, 1);
-    } else {
-        if (vec == 2) TBN_DIRECT_LAUNCH(uint16_t, 2); else TBN_DIRECT_LAUNCH(uint16_t, 1);
-    }
-#undef TBN_DIRECT_LAUNCH
-    return check_launch("tbn_linear_forward (direct kernel)");
+    P.groups = static_cast<uint32_t>(pl.groups);
+    P.row_tiles = static_cast<uint32_t>(pl.row_tiles);
+    return a.dt == TBN_F32 ? launch_nt<float>(a, P, pl.nt, pl.kw) : launch_nt<uint16_t>(a, P, pl.nt, pl.kw);
 }
 
 }  // namespace tbn

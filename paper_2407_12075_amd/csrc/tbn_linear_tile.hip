@@ -484,6 +484,12 @@ bool linear_tile_preferred(const LinearArgs &a) {
     return a.M > 64 && small_grid > 256 && waves1 <= 512;
 }
 
+int linear_tile_k_slices(const LinearArgs &a) {
+    int nt, groups, kw;
+    plan(a, nt, groups, kw);
+    return kw;
+}
+
 tbn_status launch_linear_tile(const LinearArgs &a) {
     TileParams P;
     P.M = a.M;

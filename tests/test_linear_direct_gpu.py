@@ -1,0 +1,81 @@
+"""The fully-connected kernel for any row length and alignment, at the edges of its chunks, row tiles and column tiles:
+exact arithmetic (activations in {-1, 0, +1}, alphas powers of two: every output is one float32 number whatever the
+order of the sums), so it has to equal the oracle bit for bit."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import tbn_oracle as orc
+from paper_2407_12075_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+# M, in, out, k, n_alpha, element offset of the activations
+CASES = [
+    (1, 1, 1, 1, 1, 0), (33, 3, 30, 2, 1, 1), (37, 5, 33, 1, 1, 0), (40, 7, 8, 8, 8, 3),       # rows shorter than a load
+    (31, 63, 96, 3, 3, 0), (32, 65, 64, 2, 1, 0), (97, 127, 66, 2, 2, 1), (64, 129, 31, 1, 1, 0),   # edges of a chunk
+    (1, 257, 1000, 4, 4, 0), (300, 301, 520, 8, 8, 0), (5, 4095, 4096, 8, 8, 0),
+    (2500, 196, 384, 4, 1, 0),                       # one column tile per workgroup, four waves
+    (4001, 91, 1024, 4, 1, 0),                       # more than 1024 tiles of 32 x 32: two or four column tiles
+    (8200, 67, 1026, 2, 2, 0),                       # more than 4096: three or four column tiles, 513 columns
+    (200, 4096, 128, 2, 1, 1), (130, 256, 72, 3, 3, 5),   # whole chunks at unaligned addresses
+    # aligned rows that other kernels could take as well
+    (500, 512, 512, 2, 1, 0), (64, 768, 2048, 4, 4, 0), (1000, 200, 500, 2, 1, 0), (200, 1024, 1024, 2, 1, 0),
+    (817, 640, 952, 2, 2, 0), (700, 3840, 128, 2, 1, 0), (2000, 520, 608, 2, 1, 0),
+]
+
+
+@pytest.fixture(scope="module")
+def tbn():
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    from paper_2407_12075_amd import tbn as binding
+    binding.lib()
+    return binding
+
+
+def _at_offset(values, offset):
+    """A device tensor of these values whose first element sits `offset` elements after a 256-byte boundary."""
+    buf = torch.empty(values.numel() + offset, dtype=values.dtype, device="cuda")
+    buf[offset:].copy_(values.reshape(-1))
+    return buf[offset:].view(values.shape)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("M,cin,cout,k,n_alpha,offset", CASES)
+def test_direct_exact(tbn, M, cin, cout, k, n_alpha, offset, dtype):
+    rng = np.random.default_rng(M * 10000 + cin)
+    p = cin * cout // k
+    tile_ref = rng.integers(0, 2 ** 32, size=(p + 31) // 32, dtype=np.uint64).astype(np.uint32)
+    if p % 32:
+        tile_ref[-1] &= np.uint32((1 << (p % 32)) - 1)
+    alpha_ref = np.asarray([2.0 ** ((i % 5) - 2) for i in range(n_alpha)], dtype=np.float32)
+    x = rng.integers(-1, 2, size=(M, cin)).astype(np.float32)
+    ref = np.maximum(orc.linear_forward(x, tile_ref, alpha_ref, cout, k).astype(np.float32), 0.0)
+    xd = torch.from_numpy(x)
+    if dtype == "bf16":
+        xd = xd.bfloat16()
+        ref = wl.bf16_bits_to_f32(wl.f32_to_bf16_bits(ref)).reshape(ref.shape)
+    xd = _at_offset(xd, offset)
+    tile, alpha = torch.from_numpy(tile_ref.view(np.int32)).cuda(), torch.from_numpy(alpha_ref).cuda()
+    y = _at_offset(torch.full((M, cout), 7.0, dtype=xd.dtype), offset)
+    tbn.tbn_linear_forward(xd, tile, alpha, cout, k, y=y, flags=tbn.TBN_FLAG_RELU)
+    torch.cuda.synchronize()
+    got = y.float().cpu().numpy()
+    bad = np.argwhere(got != ref)
+    assert bad.size == 0, f"{len(bad)} of {got.size} outputs differ, first at {tuple(bad[0])}: {got[tuple(bad[0])]} against {ref[tuple(bad[0])]}"
+
+
+def test_direct_infinities_and_nan(tbn):
+    """An infinity or a NaN reaches the outputs of its own row only, as in the one-thread-per-output kernel."""
+    g = torch.Generator().manual_seed(1)
+    for dt in (torch.float32, torch.bfloat16):
+        x = torch.randn(70, 67, generator=g).to(dt)
+        x[3, 5], x[8, 66], x[40, 0] = float("inf"), float("-inf"), float("nan")
+        x[50, 1], x[50, 2] = float("inf"), float("inf")
+        x = x.cuda()
+        tile, alpha = tbn.tbn_pack_tile(torch.randn(67 * 64, generator=g).cuda(), 4)
+        y = tbn.tbn_linear_forward(x, tile, alpha, 64, 4).float()
+        ref = tbn.tbn_linear_forward(x, tile, alpha, 64, 4, flags=tbn.TBN_FLAG_FORCE_GENERIC).float()
+        torch.cuda.synchronize()
+        assert torch.equal(torch.isnan(y), torch.isnan(ref))
+        assert torch.equal(torch.isinf(y), torch.isinf(ref)) and torch.equal(y[torch.isinf(y)], ref[torch.isinf(ref)])
