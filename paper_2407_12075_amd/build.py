@@ -15,6 +15,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(CSRC, "_build")
 LIB = os.path.join(HERE, "libtbn.so")
+HOST = os.path.join(HERE, "_tbn_host.so")   # extension module: the binding's everyday calls on C++ tensors
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 # The compiler the hand-scheduled kernels were validated with.  Several kernels read LDS through inline assembly
@@ -48,11 +49,28 @@ def _compile(src: str) -> str:
     return obj
 
 
+def _compile_host() -> str:
+    import sysconfig
+    import torch
+    root = os.path.dirname(torch.__file__)
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           "-isystem", f"{root}/include", "-isystem", f"{root}/include/torch/csrc/api/include", "-isystem", "/opt/rocm/include",
+           "-isystem", sysconfig.get_paths()["include"], os.path.join(CSRC, "tbn_host.cpp"), "-o", HOST,
+           f"-L{root}/lib", "-ltorch_python", "-ltorch_cpu", "-ltorch", "-lc10", "-lc10_hip"]
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    if res.returncode != 0:
+        raise RuntimeError(f"g++ failed for tbn_host.cpp:\n{res.stderr}")
+    return HOST
+
+
 def build(verbose: bool = True) -> str:
     os.makedirs(OBJ, exist_ok=True)
     srcs = sorted(glob.glob(os.path.join(CSRC, "*.hip")))
     with ThreadPoolExecutor(max_workers=min(8, len(srcs))) as ex:
+        host = ex.submit(_compile_host)
         objs = list(ex.map(_compile, srcs))
+        host.result()
     cmd = [HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-fno-gpu-rdc", *objs, "-o", LIB]
     subprocess.run(cmd, check=True)
     if verbose:

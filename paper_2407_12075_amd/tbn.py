@@ -1,6 +1,8 @@
 """Thin ctypes binding of libtbn (include/tbn.h).  Argument marshalling only: every step of the
 computation runs in the HIP kernels of the library.  PyTorch supplies device memory and the
-stream; tensors must live on the current CUDA (HIP) device and be contiguous.
+stream; tensors must live on the current CUDA (HIP) device and be contiguous.  The plain form of the
+everyday calls is made by the extension module ``_tbn_host`` (csrc/tbn_host.cpp), which answers None
+to every other form; the code of the wrappers then runs.
 
 There is no CPU fallback: if ``libtbn.so`` is missing the import of a symbol raises.
 """
@@ -29,6 +31,7 @@ _STATUS = {1: "TBN_ERR_NULL", 2: "TBN_ERR_SHAPE", 3: "TBN_ERR_UNSUPPORTED", 4: "
 
 _LIB_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)), "libtbn.so")
 _lib = None
+_host = None   # the extension module, once lib() has loaded the library
 
 _c_i64, _c_i32, _c_u32, _c_vp, _c_sz = ctypes.c_int64, ctypes.c_int32, ctypes.c_uint32, ctypes.c_void_p, ctypes.c_size_t
 
@@ -96,7 +99,12 @@ def lib() -> ctypes.CDLL:
         L.tbn_diag_mfma.argtypes = [_c_i32, _c_i32, _c_vp, _c_vp]
         L.tbn_diag_mfma_fp4.restype = ctypes.c_int
         L.tbn_diag_mfma_fp4.argtypes = [_c_i32, _c_i32, _c_vp, _c_vp]
-        _lib = L
+        global _host
+        from . import _tbn_host
+        _tbn_host.init(_raise, {name: ctypes.cast(getattr(L, name), _c_vp).value for name in (
+            "tbn_pack_workspace_bytes", "tbn_pack_tile", "tbn_linear_forward", "tbn_conv2d_forward", "tbn_sign_pack",
+            "tbn_linear_coltiled_workspace_bytes", "tbn_linear_coltiled_forward", "tbn_linear_forward_binact")})
+        _lib, _host = L, _tbn_host
     return _lib
 
 
@@ -204,6 +212,10 @@ def tbn_pack_tile(w_real: torch.Tensor, k: int, n_alpha: int = 1, a_real: Option
                   tile_out: Optional[torch.Tensor] = None, alpha_out: Optional[torch.Tensor] = None,
                   workspace: Optional[torch.Tensor] = None, stream=None) -> Tuple[torch.Tensor, torch.Tensor]:
     """Tile (int32 tensor holding the 32-bit words) and alpha (float32) from real weights."""
+    if _host is not None and a_real is None and tile_out is None and alpha_out is None and workspace is None and stream is None and _recording is None:
+        r = _host.pack_tile(w_real, k, n_alpha)
+        if r is not None:
+            return r
     n = w_real.numel()
     words = tbn_tile_words(n, k)
     dev = w_real.device
@@ -246,6 +258,10 @@ def tbn_pack_tile_noalloc(w_real: torch.Tensor, k: int, n_alpha: int, tile_out: 
 def tbn_linear_forward(x: torch.Tensor, tile: torch.Tensor, alpha: torch.Tensor, out_features: int, k: int,
                        y: Optional[torch.Tensor] = None, flags: int = 0, stream=None) -> torch.Tensor:
     """Y = X * B_hat^T for x of shape (M, in); y has shape (M, out_features) and x's dtype."""
+    if _host is not None and y is None and stream is None and _recording is None:
+        r = _host.linear_forward(x, tile, alpha, out_features, k, flags)
+        if r is not None:
+            return r
     if x.dim() != 2:
         raise ValueError("x must be (M, in)")
     M, cin = x.shape
@@ -331,6 +347,10 @@ def tbn_linear_coltiled_forward(x: torch.Tensor, tile: torch.Tensor, alpha: torc
                                 y: Optional[torch.Tensor] = None, flags: int = 0,
                                 workspace: Optional[torch.Tensor] = None, stream=None) -> torch.Tensor:
     """Column-tiled layer: W_hat[o, c*q + j] = alpha[c] * t[o, j]; y has shape (M, out_features) and x's dtype."""
+    if _host is not None and y is None and workspace is None and stream is None and _recording is None:
+        r = _host.linear_coltiled_forward(x, tile, alpha, out_features, k, flags)
+        if r is not None:
+            return r
     if x.dim() != 2:
         raise ValueError("x must be (M, in)")
     M, cin = x.shape
@@ -354,6 +374,10 @@ def tbn_conv2d_forward(x: torch.Tensor, tile: torch.Tensor, alpha: torch.Tensor,
                        kw: int, k: int, stride=(1, 1), pad=(0, 0), y: Optional[torch.Tensor] = None,
                        flags: int = 0, stream=None) -> torch.Tensor:
     """NCHW convolution with the implicit (O, C, kh, kw) tiled-bit weight."""
+    if _host is not None and y is None and stream is None and _recording is None:
+        r = _host.conv2d_forward(x, tile, alpha, out_channels, kh, kw, k, stride, pad, flags)
+        if r is not None:
+            return r
     if x.dim() != 4:
         raise ValueError("x must be (N, C, H, W)")
     N, C, H, W = x.shape
@@ -377,6 +401,10 @@ def tbn_sign_row_words(cin: int) -> int:
 
 def tbn_sign_pack(x: torch.Tensor, xbits: Optional[torch.Tensor] = None, stream=None) -> torch.Tensor:
     """Rows of sign bits of x (M, in): int32 (M, ceil(in / 32)), bit j % 32 of word j // 32 set where x[m, j] > 0."""
+    if _host is not None and xbits is None and stream is None and _recording is None:
+        r = _host.sign_pack(x)
+        if r is not None:
+            return r
     if x.dim() != 2:
         raise ValueError("x must be (M, in)")
     M, cin = x.shape
@@ -395,6 +423,10 @@ def tbn_linear_forward_binact(xbits: torch.Tensor, cin: int, tile: torch.Tensor,
                               k: int, dtype: torch.dtype = torch.float32, y: Optional[torch.Tensor] = None, flags: int = 0,
                               stream=None) -> torch.Tensor:
     """The layer on rows of sign bits (M, ceil(in / 32)); y has shape (M, out_features) and the given dtype."""
+    if _host is not None and y is None and stream is None and (dtype is torch.float32 or dtype is torch.bfloat16) and _recording is None:
+        r = _host.linear_forward_binact(xbits, cin, tile, alpha, out_features, k, dtype is torch.bfloat16, flags)
+        if r is not None:
+            return r
     if xbits.dim() != 2 or xbits.shape[1] != tbn_sign_row_words(cin):
         raise ValueError("xbits must be (M, ceil(in / 32))")
     M = xbits.shape[0]
