@@ -57,7 +57,7 @@ static tbn_status check_tiling(int64_t n, int32_t k, int32_t n_alpha) {
 
 // The kernel family that serves a fully-connected call (host arithmetic only: shapes, alignment of the pointers, the
 // number of CUs of the current device).
-enum class LinearKernel { Decode, Tile, Skinny, Stream, Block, Mfma, Rows, Direct, Generic };
+enum class LinearKernel { Decode, Tile, Skinny, Stream, Block, Mfma, Rows, Direct, Short, Generic };
 
 static LinearKernel choose_linear(const LinearArgs &a) {
     if (!(a.flags & TBN_FLAG_FORCE_GENERIC)) {
@@ -71,6 +71,8 @@ static LinearKernel choose_linear(const LinearArgs &a) {
             return LinearKernel::Decode;
         if (!(a.flags & (TBN_FLAG_BLOCK_KERNEL | TBN_FLAG_STREAM_KERNEL)) && linear_tile_preferred(a))
             return linear_direct_preferred(a, true, false) ? LinearKernel::Direct : LinearKernel::Tile;
+        // bfloat16, rows of at most 576 elements and many distinct columns: the rows of a block stay in LDS
+        if (linear_short_preferred(a)) return LinearKernel::Short;
         if (linear_skinny_supported(a)) return linear_direct_preferred(a, false, true) ? LinearKernel::Direct : LinearKernel::Skinny;
         if (!(a.flags & TBN_FLAG_BLOCK_KERNEL)) {
             // bfloat16, tile of whole rows: 128 x 128 blocks with load waves; the streaming kernel (64-row half
@@ -109,6 +111,7 @@ static const char *linear_kernel_name(LinearKernel kn) {
         case LinearKernel::Mfma: return "general";
         case LinearKernel::Rows: return "rows";
         case LinearKernel::Direct: return "direct";
+        case LinearKernel::Short: return "short-rows";
         case LinearKernel::Generic: return "generic";
     }
     return "generic";
@@ -125,6 +128,7 @@ static tbn_status dispatch_linear(const LinearArgs &a) {
         case LinearKernel::Mfma: return launch_linear_mfma(a);
         case LinearKernel::Rows: return launch_linear_rows(a);
         case LinearKernel::Direct: return launch_linear_direct(a);
+        case LinearKernel::Short: return launch_linear_short(a);
         case LinearKernel::Generic: break;
     }
     return launch_linear_generic(a);

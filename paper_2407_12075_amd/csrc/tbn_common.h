@@ -59,6 +59,9 @@ bool linear_direct_supported(const LinearArgs &a);   // tile of whole rows, any 
 int linear_tile_k_slices(const LinearArgs &a);   // K slices per workgroup of the tile kernel's plan
 bool linear_direct_preferred(const LinearArgs &a, bool tile, bool small_batch);   // over the tile, small-batch or general kernel
 tbn_status launch_linear_direct(const LinearArgs &a);
+bool linear_short_supported(const LinearArgs &a);    // bfloat16, short rows resident in LDS, many distinct columns
+bool linear_short_preferred(const LinearArgs &a);
+tbn_status launch_linear_short(const LinearArgs &a);
 bool linear_skinny_supported(const LinearArgs &a); // small-batch (decode-shaped) matrix-core kernel
 tbn_status launch_linear_skinny(const LinearArgs &a);
 bool linear_decode_supported(const LinearArgs &a); // at most 16 batch rows, tile of whole rows: latency-built GEMV kernel
