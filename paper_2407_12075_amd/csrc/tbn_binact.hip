@@ -9,9 +9,13 @@
 //   * binact_mfma (tile of whole weight rows, in % 256 == 0): Z = S T^T on the matrix cores in the 4-bit float
 //     format (E2M1 holds +1 and -1 exactly; v_mfma_f32_32x32x64_f8f6f4, the form without block scales, multiplies 64
 //     elements of K per instruction, four times the bfloat16 rate; the float32 sums of +-1 products are exact).
-//     A lane's operand for one instruction is 32 sign bits; each byte of them becomes eight 4-bit values through a
-//     256-entry table in LDS that is stored once per lane (entry e of lane l at byte 256 e + 4 l: every read is
-//     free of bank conflicts and its address is one v_perm_b32 of the bits and the lane offset).  Both operands
+//     A lane's operand for one instruction is 32 sign bits, which four shifts and and-ors (seven instructions) spread into
+//     four registers of eight 4-bit values: bit 4n + j is the sign of value n of register j.  (Before, each byte was looked
+//     up in a table of 64 KiB in LDS, four address and four read instructions and a table to fill per workgroup:
+//     8192 x 4096 -> 4096, k = 8, sign bits out 17.4 us against 15.1, bfloat16 out 23.8 against 21.2; one row 13.2 against 9.4;
+//     8192 x 256 -> 4096, k = 2, sign bits out 20.6 against 12.5.)  What bounds it now is the loads of the bits, 16 bytes from
+//     each of 32 rows per instruction; sending them through LDS in stages of 1024 bits measured the same at 4096 columns
+//     (141 us against 150 at 16384, k = 2) and 2 us slower at one row, fetching them three super-steps ahead 1 us slower.  Both operands
 //     use the same assignment of K to lanes and registers, so a dot product does not depend on what that
 //     assignment is.  The distinct columns are computed once and every replica is written as alpha[t] * Z in whole
 //     128-byte lines after a turn through LDS (Section "CNN Architectures": only one of the tile computations needs
@@ -285,10 +289,9 @@ __global__ __launch_bounds__(kDirRows) void binact_direct_kernel(const uint32_t 
 
 // ---- matrix-core forward --------------------------------------------------------------------------------
 
-constexpr int kTableBytes = 256 * 256;            // [entry][lane] words
 constexpr int kTurnStride = 68;                   // floats per row of a wave's 64 x 64 sums in LDS
 constexpr int kTurnBytes = 64 * kTurnStride * 4;  // per wave
-constexpr int kMfmaLds = 4 * kTurnBytes > kTableBytes ? 4 * kTurnBytes : kTableBytes;
+constexpr int kMfmaLds = 4 * kTurnBytes;
 
 struct BinactMfmaParams {
     int64_t M;
@@ -337,17 +340,6 @@ __global__ __launch_bounds__(256, 2) void binact_mfma_kernel(const uint32_t *__r
     // alpha of replica t in lane t (replicas past the 64th are fetched one by one in the epilogue)
     const float alpha_lanes = alpha[P.n_alpha == 1 ? 0 : (lane < P.reps ? lane : P.reps - 1)];
 
-    // table: entry e holds, for bit i of e, the 4-bit float +1.0 (0x2) or -1.0 (0xA) at bits 4i .. 4i+3
-    {
-        uint32_t v = 0;
-#pragma unroll
-        for (int i = 0; i < 8; ++i) v |= (((tid >> i) & 1) ? 0x2u : 0xAu) << (4 * i);
-        const u32x4_t vv = {v, v, v, v};
-        u32x4_t *dst = reinterpret_cast<u32x4_t *>(lds + tid * 256);
-#pragma unroll
-        for (int i = 0; i < 16; ++i) dst[i] = vv;
-    }
-
     // Operand rows.  Activations (second operand): lane (ln, lh) supplies batch row 32*tm + ln.  Tile rows (first
     // operand): lane ln supplies distinct column 32*tn + 16*((ln >> 2) & 1) + 4*(ln >> 3) + (ln & 3); the
     // instruction leaves row 8*(r / 4) + 4*lh + r % 4 of its result in register r, so that register r of a lane
@@ -369,14 +361,13 @@ __global__ __launch_bounds__(256, 2) void binact_mfma_kernel(const uint32_t *__r
         r[2] = *reinterpret_cast<const u32x4_t *>(b_row[0] + S * 32);
         r[3] = *reinterpret_cast<const u32x4_t *>(b_row[1] + S * 32);
     };
-    // The table starts at LDS address 0 (the kernel has no other LDS object), so the looked-up address needs no base.
-    typedef __attribute__((address_space(3))) const int lds_word_t;
-    const uint32_t lane_off = static_cast<uint32_t>(lane) * 4u;
-    auto expand = [&](i32x8_t &f, uint32_t word) {   // 32 sign bits -> 32 four-bit floats: entry (byte i of word), this lane's copy
-        f[0] = *reinterpret_cast<lds_word_t *>(__builtin_amdgcn_perm(word, lane_off, 0x0c0c0400u));
-        f[1] = *reinterpret_cast<lds_word_t *>(__builtin_amdgcn_perm(word, lane_off, 0x0c0c0500u));
-        f[2] = *reinterpret_cast<lds_word_t *>(__builtin_amdgcn_perm(word, lane_off, 0x0c0c0600u));
-        f[3] = *reinterpret_cast<lds_word_t *>(__builtin_amdgcn_perm(word, lane_off, 0x0c0c0700u));
+    // 32 sign bits -> 32 four-bit floats: bit 4n + j becomes the sign of value n of register j (0x2 is +1.0, 0xA is -1.0).
+    // A set bit gives -1 in both operands alike, so their products are those of the signs.
+    uint32_t sign_bits = 0x88888888u, one_bits = 0x22222222u;
+    asm volatile("" : "+v"(sign_bits), "+v"(one_bits));   // registers: an and-or takes no constants of this size
+    auto expand = [&](i32x8_t &f, uint32_t word) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) f[j] = static_cast<int>(((word << (3 - j)) & sign_bits) | one_bits);
     };
 
     f32x16_t acc[2][2];
@@ -393,32 +384,24 @@ __global__ __launch_bounds__(256, 2) void binact_mfma_kernel(const uint32_t *__r
     u32x4_t raw[3][4];
     load(raw[0], 0);
     load(raw[1], 1 < last ? 1 : last);
-    __syncthreads();   // the table is written
-    i32x8_t F[3][4] = {};   // [operand set][A0, A1, B0, B1]; the upper four words of an operand are not read in this format
+    i32x8_t F[2][4] = {};   // [operand set][A0, A1, B0, B1]; the upper four words of an operand are not read in this format
 #pragma unroll
-    for (int f = 0; f < 4; ++f) {
-        expand(F[0][f], raw[0][f][0]);
-        expand(F[1][f], raw[0][f][1]);
-    }
+    for (int f = 0; f < 4; ++f) expand(F[0][f], raw[0][f][0]);
     constexpr int kOne = 0;   // both scale operands zero: the compiler takes the form of the instruction without block scales
-    // One super-step: four groups of four instructions.  In front of each instruction one operand of the group after
-    // the next is looked up (a lookup takes longer to arrive than two instructions take to run, so one group ahead is
-    // not enough), in the order in which that group needs them (A0, B0, B1, A1).  Three operand sets rotate with the
-    // groups.  The last super-step loads itself once more and looks up operands nobody multiplies: the body stays one
-    // straight line of code, which is what keeps the order written here.
+    // One super-step: four groups of four instructions.  In front of each instruction one operand of the next group is
+    // expanded (seven vector instructions, 28 of the 32 cycles the matrix instruction before it runs).  The last
+    // super-step loads itself once more and expands operands nobody multiplies: the body stays one straight line of code.
     auto step = [&](auto c_c, int32_t S) __attribute__((always_inline)) {
         constexpr int C = decltype(c_c)::value, N1 = (C + 1) % 3, N2 = (C + 2) % 3;
         load(raw[N2], S + 2 < last ? S + 2 : last);
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            const int s = (C + i) % 3, n = (C + i + 2) % 3;   // group 4 S + i uses set (4 S + i) % 3 = (C + i) % 3
+            const int s = i & 1, n = s ^ 1;
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 constexpr int kOrder[4] = {0, 2, 3, 1};
                 const int f = kOrder[q];
-                expand(F[n][f], i < 2 ? raw[C][f][i + 2] : raw[N1][f][i - 2]);
-                __builtin_amdgcn_sched_group_barrier(0x2, 4, 0);     // the four addresses, then the four reads: a read
-                __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);   // does not follow its own address directly
+                expand(F[n][f], i < 3 ? raw[C][f][i + 1] : raw[N1][f][0]);
                 __builtin_amdgcn_sched_barrier(0);
                 const int tm = q >> 1, tn = q & 1;
                 acc[tm][tn] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(F[s][2 + tn], F[s][tm], acc[tm][tn], 4, 4, 0, kOne, 0, kOne);
@@ -437,8 +420,7 @@ __global__ __launch_bounds__(256, 2) void binact_mfma_kernel(const uint32_t *__r
         if (S + 1 < P.n_super) step(std::integral_constant<int, 1>{}, S + 1);
     }
 
-    // ---- turn the sums round through LDS (the table is no longer needed) and write every replica ----------
-    __syncthreads();
+    // ---- turn the sums round through the wave's own LDS and write every replica ----------------------------
     float *zt = reinterpret_cast<float *>(lds + wave * kTurnBytes);
 #pragma unroll
     for (int tm = 0; tm < 2; ++tm)
