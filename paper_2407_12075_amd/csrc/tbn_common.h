@@ -59,6 +59,8 @@ bool linear_direct_supported(const LinearArgs &a);   // tile of whole rows, any 
 int linear_tile_k_slices(const LinearArgs &a);   // K slices per workgroup of the tile kernel's plan
 bool linear_direct_preferred(const LinearArgs &a, bool tile, bool small_batch);   // over the tile, small-batch or general kernel
 tbn_status launch_linear_direct(const LinearArgs &a);
+bool linear_direct_ends_supported(const LinearArgs &a);   // repair pass: the columns whose weight row holds a tile start, two alphas
+tbn_status launch_linear_direct_ends(const LinearArgs &a);
 bool linear_short_supported(const LinearArgs &a);    // bfloat16, short rows resident in LDS, many distinct columns
 bool linear_short_preferred(const LinearArgs &a);
 tbn_status launch_linear_short(const LinearArgs &a);

@@ -60,7 +60,20 @@ struct DirectLinearParams {
     int32_t reps, n_alpha, relu;
     uint32_t groups;      // groups of NT * 32 distinct columns
     uint32_t row_tiles;   // tiles of 32 batch rows
+    int64_t p;            // ENDS: tile bits
+    int32_t k;            // ENDS: tile repeats
 };
+
+// Row of the weight that contains the start of tile number c, and the start's position in it (0: the tile starts with the
+// row).  c * p < 2^53, so that the float64 quotient is off by at most one.
+__device__ __forceinline__ int32_t tile_start_row(const DirectLinearParams &P, int32_t c, int32_t &j_e) {
+    const int64_t f = int64_t(c) * P.p;
+    int64_t q = static_cast<int64_t>(static_cast<double>(f) / static_cast<double>(P.in)), r = f - q * P.in;
+    if (r < 0) { r += P.in; --q; }
+    if (r >= P.in) { r -= P.in; ++q; }
+    j_e = static_cast<int32_t>(r);
+    return static_cast<int32_t>(q);
+}
 
 __device__ __forceinline__ uint32_t pack2(float a, float b) {
     const f32x2_t f = {a, b};
@@ -112,7 +125,12 @@ struct Lds {
     static constexpr int kBytes = 4096 + KW * kRegion;
 };
 
-template <typename XT, int NT, int KW>
+// ENDS (NT = 1): the columns whose weight row contains a tile start, sixteen per workgroup, each as two rows of the operand:
+// row c has the weights before the start (the tile's last bits) and zeros, row 16 + c zeros and the weights from it on (the
+// tile's first bits); y = alpha[c - 1] * first + alpha[c] * second.  The pass is a read of X: 8192 x 3000 in bfloat16 19.4 us
+// in the small-batch kernel's form (16 rows per workgroup, 64 bytes of a row per load instruction), 14.6 here; 12000 x 264
+// 9.2 against 4.7.
+template <typename XT, int NT, int KW, bool ENDS = false>
 __global__ __launch_bounds__(64 * KW) __attribute__((amdgpu_waves_per_eu(2))) void linear_direct_kernel(const XT *__restrict__ x, XT *__restrict__ y,
                                                                const uint32_t *__restrict__ tile,
                                                                const float *__restrict__ alpha, DirectLinearParams P) {
@@ -125,6 +143,7 @@ __global__ __launch_bounds__(64 * KW) __attribute__((amdgpu_waves_per_eu(2))) vo
     constexpr int kWords = kCE / 64;                                  // 32-bit windows per lane half, column and chunk
     extern __shared__ __attribute__((aligned(16))) unsigned char s_raw[];
     u32x4_t *s_table = reinterpret_cast<u32x4_t *>(s_raw);
+    u32x4_t *s_keep = reinterpret_cast<u32x4_t *>(s_raw + 4096 + KW * L::kRegion);   // ENDS: element masks of a byte
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int ln = lane & 31, lg = lane >> 5;
     unsigned char *region = s_raw + 4096 + wave * L::kRegion;   // this wave's
@@ -201,15 +220,26 @@ __global__ __launch_bounds__(64 * KW) __attribute__((amdgpu_waves_per_eu(2))) vo
 
     // tile words of this lane's column in every column tile: bit u * in + k, lane half lg covers kWords windows per chunk
     uint32_t word0[NT], sh[NT];
+    int32_t split = 0;   // ENDS: first element of the row that belongs to the tile that starts in it
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
-        const int32_t u = u0 + 32 * t + ln < P.U ? u0 + 32 * t + ln : P.U - 1;   // columns past U repeat the last one; never written
-        const uint64_t bit = uint64_t(u) * static_cast<uint32_t>(P.in) + static_cast<uint32_t>(lg * (kCE / 2));
-        word0[t] = static_cast<uint32_t>(bit >> 5);
-        sh[t] = static_cast<uint32_t>(bit & 31);
+        if constexpr (ENDS) {   // bit of element 0 (before the tile's start, where it is masked, for the second row)
+            const int32_t tc = static_cast<int32_t>(cg) * 16 + (ln & 15) + 1;
+            tile_start_row(P, tc < P.k ? tc : 1, split);
+            const int64_t bit = (ln < 16 ? P.p - split : int64_t(-split)) + lg * (kCE / 2);
+            word0[t] = static_cast<uint32_t>(bit >> 5);   // may be "negative": see load_words
+            sh[t] = static_cast<uint32_t>(bit & 31);
+        } else {
+            const int32_t u = u0 + 32 * t + ln < P.U ? u0 + 32 * t + ln : P.U - 1;   // columns past U repeat the last one; never written
+            const uint64_t bit = uint64_t(u) * static_cast<uint32_t>(P.in) + static_cast<uint32_t>(lg * (kCE / 2));
+            word0[t] = static_cast<uint32_t>(bit >> 5);
+            sh[t] = static_cast<uint32_t>(bit & 31);
+        }
     }
     uint32_t wr[NT][kWords + 1];
-    auto load_words = [&](int32_t c) {   // words past the tile's end belong to positions past the row's end: any value will do
+    // words past the tile's end belong to positions past the row's end (ENDS: past the first part), words before its start
+    // (as unsigned numbers past it as well) to positions before the second part: any value will do
+    auto load_words = [&](int32_t c) {
 #pragma unroll
         for (int t = 0; t < NT; ++t)
 #pragma unroll
@@ -230,6 +260,11 @@ __global__ __launch_bounds__(64 * KW) __attribute__((amdgpu_waves_per_eu(2))) vo
         for (int v = 0; v < 4; ++v)
             t[v] = (((e >> (2 * v)) & 1) ? 0x3f80u : 0xbf80u) | ((((e >> (2 * v + 1)) & 1) ? 0x3f80u : 0xbf80u) << 16);
         s_table[e] = t;
+        if constexpr (ENDS) {
+#pragma unroll
+            for (int v = 0; v < 4; ++v) t[v] = (((e >> (2 * v)) & 1) ? 0xffffu : 0u) | (((e >> (2 * v + 1)) & 1) ? 0xffff0000u : 0u);
+            s_keep[e] = t;
+        }
     }
     __syncthreads();
 
@@ -280,6 +315,12 @@ __global__ __launch_bounds__(64 * KW) __attribute__((amdgpu_waves_per_eu(2))) vo
         auto sign = [&](int t, int s) {
             Frag sg;
             sg.q = s_table[(wc[t][s / 4] >> (8 * (s % 4))) & 0xffu];
+            if constexpr (ENDS) {
+                int32_t n = split - (c * kCE + lg * (kCE / 2) + 8 * s);   // of the eight elements, those before the start
+                n = n < 0 ? 0 : n > 8 ? 8 : n;
+                const uint32_t before = (1u << n) - 1u;
+                sg.q &= s_keep[ln < 16 ? before : 0xffu ^ before];
+            }
             return sg.v;
         };
 #pragma unroll
@@ -324,6 +365,28 @@ __global__ __launch_bounds__(64 * KW) __attribute__((amdgpu_waves_per_eu(2))) vo
                 f32x4_t{acc[t][4 * q], acc[t][4 * q + 1], acc[t][4 * q + 2], acc[t][4 * q + 3]};
     __syncthreads();
 
+    if constexpr (ENDS) {   // 32 rows x 16 columns, neighbouring threads neighbouring columns
+        for (int unit = tid; unit < 512; unit += 64 * KW) {
+            const int r = unit >> 4, c = unit & 15;
+            const int32_t tc = static_cast<int32_t>(cg) * 16 + c + 1;
+            if (m0 + r >= P.M || tc >= P.k) continue;
+            int32_t j_e;
+            const int32_t o = tile_start_row(P, tc, j_e);
+            if (j_e == 0) continue;   // the tile starts with the row: nothing to repair
+            float z[2] = {0.f, 0.f};
+#pragma unroll
+            for (int w = 0; w < KW; ++w)
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const int col = 16 * h + c;
+                    z[h] += *reinterpret_cast<const float *>(s_raw + 4096 + w * L::kRegion + r * 128 + (((col >> 2) ^ (r & 7)) << 4) + 4 * (col & 3));
+                }
+            float v = alpha[tc - 1] * z[0] + alpha[tc] * z[1];
+            if (P.relu) v = fmaxf(v, 0.f);
+            ElemIO<XT>::store(y + (m0 + r) * P.out + o, v);
+        }
+        return;
+    }
     // y[m, u + t*U] = alpha[t] * Z[m, u]: a thread adds and writes kEP adjacent columns of a row, neighbouring threads
     // neighbouring columns
     constexpr int kGroupsPerRow = NT * 32 / kEP;
@@ -479,6 +542,43 @@ bool linear_direct_preferred(const LinearArgs &a, bool tile, bool small_batch) {
     if (U % 8 != 0) return W <= 16384;
     if (f32) return W <= 4096;
     return W <= 1024 || (W <= 2048 && a.in <= 2048);
+}
+
+template <typename XT>
+static tbn_status launch_ends(const LinearArgs &a, const DirectLinearParams &P) {
+    constexpr int kLds = Lds<1, 8>::kBytes + 4096;
+    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(&linear_direct_kernel<XT, 1, 8, true>),
+                                                       hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
+    if (attr != hipSuccess) {
+        set_error("tbn_linear_forward: cannot reserve %d bytes of LDS", kLds);
+        return TBN_ERR_DEVICE;
+    }
+    hipLaunchKernelGGL((linear_direct_kernel<XT, 1, 8, true>), dim3(P.row_tiles * P.groups), dim3(512), kLds, a.stream,
+                       static_cast<const XT *>(a.x), static_cast<XT *>(a.y), a.tile, a.alpha, P);
+    return check_launch("tbn_linear_forward (columns that hold a tile start)");
+}
+
+bool linear_direct_ends_supported(const LinearArgs &a) {
+    if (a.dt != TBN_F32 && a.dt != TBN_BF16) return false;
+    // at most one tile start per row; word numbers before the tile's start, as unsigned numbers, lie past its end
+    if (a.M < 1 || a.p < a.in || a.in > (1 << 21) || a.p >= (int64_t(1) << 31) || a.n_alpha != a.k || a.out > (1 << 30)) return false;
+    return (a.M + 31) / 32 * ((int64_t(a.k) + 14) / 16) <= 0x7fffffffLL;
+}
+
+tbn_status launch_linear_direct_ends(const LinearArgs &a) {
+    if (a.k < 2) return TBN_OK;
+    DirectLinearParams P = {};
+    P.M = a.M; P.out = a.out;
+    P.in = static_cast<int32_t>(a.in);
+    P.p = a.p;
+    P.k = a.k;
+    P.last_word = static_cast<uint32_t>((a.p + 31) / 32 - 1);
+    const int32_t ce = a.dt == TBN_F32 ? kChunkBytes / 4 : kChunkBytes / 2;
+    P.chunks = (P.in + ce - 1) / ce;
+    P.relu = (a.flags & TBN_FLAG_RELU) ? 1 : 0;
+    P.groups = static_cast<uint32_t>((a.k - 1 + 15) / 16);
+    P.row_tiles = static_cast<uint32_t>((a.M + 31) / 32);
+    return a.dt == TBN_F32 ? launch_ends<float>(a, P) : launch_ends<uint16_t>(a, P);
 }
 
 tbn_status launch_linear_direct(const LinearArgs &a) {

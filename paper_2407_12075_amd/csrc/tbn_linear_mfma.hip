@@ -33,8 +33,8 @@
 //     epilogue scales by alpha, turns the block round through LDS so that eight lanes hold a whole
 //     row of the wave's 64 columns, and writes the replicated column blocks with 16-byte stores.
 // Rows whose weights straddle a tile end use two different alphas when one alpha per tile is
-// given; those few columns are recomputed afterwards in one pass over X (see tbn_linear_skinny.hip,
-// launch_linear_tile_ends).
+// given; those few columns are recomputed afterwards in one pass over X (see tbn_linear_direct.hip,
+// launch_linear_direct_ends).
 #include "tbn_common.h"
 
 #include <type_traits>

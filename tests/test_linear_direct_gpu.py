@@ -79,3 +79,31 @@ def test_direct_infinities_and_nan(tbn):
         torch.cuda.synchronize()
         assert torch.equal(torch.isnan(y), torch.isnan(ref))
         assert torch.equal(torch.isinf(y), torch.isinf(ref)) and torch.equal(y[torch.isinf(y)], ref[torch.isinf(ref)])
+
+
+# tile starts inside rows, an alpha per tile: M, in, out, k
+ENDS = [(33, 264, 520, 11), (1000, 3000, 3072, 9), (64, 1000, 312, 16), (17, 1016, 123, 24), (40, 136, 45, 6), (700, 520, 1000, 64)]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("M,cin,cout,k", ENDS)
+def test_tile_starts_inside_rows_exact(tbn, M, cin, cout, k, dtype):
+    n = cin * cout
+    assert n % k == 0 and (n // k) % cin != 0
+    p = n // k
+    rng = np.random.default_rng(k)
+    tile_ref = rng.integers(0, 2 ** 32, size=(p + 31) // 32, dtype=np.uint64).astype(np.uint32)
+    if p % 32:
+        tile_ref[-1] &= np.uint32((1 << (p % 32)) - 1)
+    alpha_ref = np.asarray([2.0 ** (i % 5 - 2) for i in range(k)], dtype=np.float32)
+    x = rng.integers(-1, 2, size=(M, cin)).astype(np.float32)
+    ref = orc.linear_forward(x, tile_ref, alpha_ref, cout, k).astype(np.float32)
+    xd = torch.from_numpy(x).cuda()
+    if dtype == "bf16":
+        xd = xd.bfloat16()
+        ref = wl.bf16_bits_to_f32(wl.f32_to_bf16_bits(ref)).reshape(ref.shape)
+    y = tbn.tbn_linear_forward(xd, torch.from_numpy(tile_ref.view(np.int32)).cuda(), torch.from_numpy(alpha_ref).cuda(), cout, k)
+    torch.cuda.synchronize()
+    got = y.float().cpu().numpy()
+    bad = np.argwhere(got != ref)
+    assert bad.size == 0, f"{len(bad)} of {got.size} outputs differ, first at {tuple(bad[0])}: {got[tuple(bad[0])]} against {ref[tuple(bad[0])]}"
