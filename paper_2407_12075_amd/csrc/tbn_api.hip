@@ -70,10 +70,10 @@ static LinearKernel choose_linear(const LinearArgs &a) {
             (a.M * (a.p / a.in) <= 16384 || !linear_skinny_supported(a)))
             return LinearKernel::Decode;
         if (!(a.flags & (TBN_FLAG_BLOCK_KERNEL | TBN_FLAG_STREAM_KERNEL)) && linear_tile_preferred(a))
-            return linear_direct_preferred(a, true, false) ? LinearKernel::Direct : LinearKernel::Tile;
+            return linear_direct_preferred(a, DirectOver::Tile) ? LinearKernel::Direct : LinearKernel::Tile;
         // bfloat16, rows of at most 576 elements and many distinct columns: the rows of a block stay in LDS
         if (linear_short_preferred(a)) return LinearKernel::Short;
-        if (linear_skinny_supported(a)) return linear_direct_preferred(a, false, true) ? LinearKernel::Direct : LinearKernel::Skinny;
+        if (linear_skinny_supported(a)) return linear_direct_preferred(a, DirectOver::SmallBatch) ? LinearKernel::Direct : LinearKernel::Skinny;
         if (!(a.flags & TBN_FLAG_BLOCK_KERNEL)) {
             // bfloat16, tile of whole rows: 128 x 128 blocks with load waves; the streaming kernel (64-row half
             // tiles, twice the workgroups) where the blocks would leave half of the CUs or more idle
@@ -82,18 +82,18 @@ static LinearKernel choose_linear(const LinearArgs &a) {
             const int64_t blocks = ((a.M + 127) / 128) * ((U + 127) / 128);
             if ((a.flags & TBN_FLAG_TILE_KERNEL) && linear_tile_supported(a)) return LinearKernel::Tile;
             const bool stream = (a.flags & TBN_FLAG_STREAM_KERNEL) || blocks <= 128;   // (batch 4096: 25.2 us against 28.3)
-            if (stream && linear_stream_supported(a)) return LinearKernel::Stream;
+            if (stream && linear_stream_supported(a)) return linear_direct_preferred(a, DirectOver::Block) ? LinearKernel::Direct : LinearKernel::Stream;
             // (rows of 256: two rounds per block, too few for the persistent form; on grids of more than two blocks per CU
             // the general kernel with two workgroups per CU is 10 - 25 % faster: 8192 x 256 -> 4096 distinct columns 36 us
             // against 43)
             const bool short_rows = a.in < 512 && blocks > 512 && linear_mfma_supported(a);
-            if (!short_rows && linear_block_supported(a)) return LinearKernel::Block;
+            if (!short_rows && linear_block_supported(a)) return linear_direct_preferred(a, DirectOver::Block) ? LinearKernel::Direct : LinearKernel::Block;
             // float32, tile of whole rows: one wave per 32 batch rows (every shape measured, up to 8192 distinct columns
             // at batch 8192, runs 15 - 70 % faster than in the 128 x 128 blocks of the general kernel: 8192 x 1024 ->
             // 1024 distinct columns 57 us against 84, 8192 x 4096 -> 8192 distinct columns 1379 against 1672)
             if (a.dt == TBN_F32 && linear_tile_supported(a)) return LinearKernel::Tile;
         }
-        if (linear_mfma_supported(a)) return linear_direct_preferred(a, false, false) ? LinearKernel::Direct : LinearKernel::Mfma;
+        if (linear_mfma_supported(a)) return linear_direct_preferred(a, DirectOver::General) ? LinearKernel::Direct : LinearKernel::Mfma;
         if (linear_rows_supported(a)) return LinearKernel::Rows;
         // tile of whole rows, row lengths and alignments that none of the kernels above takes
         if (linear_direct_supported(a)) return LinearKernel::Direct;

@@ -57,7 +57,8 @@ tbn_status launch_pack_noalloc(const float *w, const float *a, int64_t n, int32_
 tbn_status launch_linear_generic(const LinearArgs &a);
 bool linear_direct_supported(const LinearArgs &a);   // tile of whole rows, any row length and alignment
 int linear_tile_k_slices(const LinearArgs &a);   // K slices per workgroup of the tile kernel's plan
-bool linear_direct_preferred(const LinearArgs &a, bool tile, bool small_batch);   // over the tile, small-batch or general kernel
+enum class DirectOver { Tile, SmallBatch, Block, General };   // the kernel that would otherwise take the call (Block: or the streaming one)
+bool linear_direct_preferred(const LinearArgs &a, DirectOver other);
 tbn_status launch_linear_direct(const LinearArgs &a);
 bool linear_direct_ends_supported(const LinearArgs &a);   // repair pass: the columns whose weight row holds a tile start, two alphas
 tbn_status launch_linear_direct_ends(const LinearArgs &a);

@@ -514,19 +514,19 @@ bool linear_direct_supported(const LinearArgs &a) {
 
 // Where this kernel beats the one that would otherwise take a call with rows in multiples of 8 and 16-byte aligned
 // activations.  Graph replays, microseconds per call, the other kernel / this one; W is the number of 32 x 32 tiles of Z.
-bool linear_direct_preferred(const LinearArgs &a, bool tile, bool small_batch) {
+bool linear_direct_preferred(const LinearArgs &a, DirectOver other) {
     if ((a.flags & ~uint32_t(TBN_FLAG_RELU)) || !linear_direct_supported(a)) return false;   // flags that steer to another kernel
     const bool f32 = a.dt == TBN_F32;
     const int64_t U = a.p / a.in, W = ((a.M + 31) / 32) * ((U + 31) / 32);
-    if (tile) {
+    if (other == DirectOver::Tile) {
         // the tile kernel splits K among waves in whole slices: rows that do not divide leave it one wave per tile (bfloat16
         // 1297 x 3840 -> 64: 23.0 / 8.8; 500 x 512 -> 256: 6.1 / 4.6; 9926 x 512 -> 32: 7.5 / 7.9; float32 817 x 640 -> 476:
-        // 15.5 / 8.4); float32 and few tiles, where it takes four columns tiles per wave (200 x 4096 -> 512: 23.5 / 15.5;
+        // 15.5 / 8.4); float32 and few tiles, where it takes four column tiles per wave (200 x 4096 -> 512: 23.5 / 15.5;
         // 600 x 4096 -> 512: 25.1 / 29.4)
         if (f32 && W <= 256) return true;
         return linear_tile_k_slices(a) == 1 && W <= 1024 && a.in > kChunkBytes / (f32 ? 4 : 2) && (f32 || a.M <= 4096);
     }
-    if (small_batch) {
+    if (other == DirectOver::SmallBatch) {
         // more than one workgroup of the small-batch kernel per CU (bfloat16 530 x 2600 -> 190: 12.3 / 8.1; float32
         // 1000 x 776 -> 250: 20.3 / 6.7); below that rows of whole lines (bfloat16 in = 384 / 768 / 1280 / 5120 at 64 x 512
         // columns: 4.6 / 4.1, 6.4 / 4.5, 7.6 / 5.3, 13.4 / 9.6, but 8.7 / 8.1 at 4096, left where it was, and in = 888,
@@ -535,6 +535,10 @@ bool linear_direct_preferred(const LinearArgs &a, bool tile, bool small_batch) {
         if (U % 8 != 0 || a.in < 384) return false;
         return f32 ? a.in % 64 == 0 && a.in <= 1280 : a.in % 128 == 0 && a.in % 4096 != 0;
     }
+    // short rows in few blocks of the block or the streaming kernel (bfloat16 8961 x 256 -> 96: 8.1 / 5.7; 1289 x 256 -> 848:
+    // 6.4 / 5.3; 1810 x 512 -> 528: 8.8 / 5.7; 6395 x 512 -> 168: 9.2 / 6.7; with activations at an odd element, 1226 x 256 ->
+    // 1248 (W = 1521): 8.7 / 9.0; 2736 x 768 -> 376: 8.9 / 10.9)
+    if (other == DirectOver::Block) return a.in <= 512 && W <= 1200;
     // the general kernel's 128 x 128 blocks: few of them (bfloat16 200 x 520 -> 640: 11.1 / 4.6; 12000 x 520 -> 152: 13.0 /
     // 10.6; 2500 x 2504 -> 640: 20.0 / 20.2; 2500 x 1000 -> 1400: 15.9 / 19.4; float32 300 x 200 -> 250: 21.6 / 4.4; 6000 x
     // 2504 -> 640: 75 / 66; 12000 x 520 -> 640: 51 / 50), and columns that it stores one by one (bfloat16 8364 x 376 -> 1076:

@@ -22,6 +22,7 @@ CASES = [
     # aligned rows that other kernels could take as well
     (500, 512, 512, 2, 1, 0), (64, 768, 2048, 4, 4, 0), (1000, 200, 500, 2, 1, 0), (200, 1024, 1024, 2, 1, 0),
     (817, 640, 952, 2, 2, 0), (700, 3840, 128, 2, 1, 0), (2000, 520, 608, 2, 1, 0),
+    (1306, 256, 832, 1, 1, 0), (2500, 512, 832, 2, 2, 0),
 ]
 
 
