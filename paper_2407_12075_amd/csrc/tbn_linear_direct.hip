@@ -60,6 +60,7 @@ struct DirectLinearParams {
     int32_t reps, n_alpha, relu;
     uint32_t groups;      // groups of NT * 32 distinct columns
     uint32_t row_tiles;   // tiles of 32 batch rows
+    uint32_t grid_x;      // workgroups per grid row
     int64_t p;            // ENDS: tile bits
     int32_t k;            // ENDS: tile repeats
 };
@@ -152,7 +153,8 @@ __global__ __launch_bounds__(64 * KW) __attribute__((amdgpu_waves_per_eu(2))) vo
     // the rows of X they share come from HBM once
     uint32_t rt, cg;
     {
-        const uint32_t bid = blockIdx.x, xcd = bid & 7, slot = bid >> 3, full = (P.row_tiles / 8) * P.groups;
+        const uint32_t bid = blockIdx.y * P.grid_x + blockIdx.x, xcd = bid & 7, slot = bid >> 3, full = (P.row_tiles / 8) * P.groups;
+        if (bid >= P.row_tiles * P.groups) return;   // the last grid row
         if (slot < full) {
             const uint32_t q = slot / P.groups;
             cg = slot - q * P.groups;
@@ -428,8 +430,18 @@ __global__ __launch_bounds__(64 * KW) __attribute__((amdgpu_waves_per_eu(2))) vo
     }
 }
 
+// A launch has fewer than 2^32 threads along x (beyond that the count wraps and the workgroups behind it never run): the
+// workgroups are dealt to rows of 2^22.
+constexpr uint32_t kGridX = 1u << 22;
+static_assert(uint64_t(kGridX) * 512 < (uint64_t(1) << 32), "threads per grid row");
+dim3 grid_of(DirectLinearParams &P) {
+    const uint32_t n = P.row_tiles * P.groups;   // < 2^31
+    P.grid_x = n < kGridX ? n : kGridX;
+    return dim3(P.grid_x, (n + P.grid_x - 1) / P.grid_x);
+}
+
 template <typename XT, int NT, int KW>
-tbn_status launch_one(const LinearArgs &a, const DirectLinearParams &P) {
+tbn_status launch_one(const LinearArgs &a, DirectLinearParams P) {
     typedef Lds<NT, KW> L;
     // dynamic LDS above the default limit has to be allowed once per kernel (thread-safe static initialisation)
     static const hipError_t attr = L::kBytes > 65536
@@ -440,7 +452,8 @@ tbn_status launch_one(const LinearArgs &a, const DirectLinearParams &P) {
         set_error("tbn_linear_forward: cannot reserve %d bytes of LDS", L::kBytes);
         return TBN_ERR_DEVICE;
     }
-    hipLaunchKernelGGL((linear_direct_kernel<XT, NT, KW>), dim3(P.row_tiles * P.groups), dim3(64 * KW), L::kBytes, a.stream,
+    const dim3 grid = grid_of(P);
+    hipLaunchKernelGGL((linear_direct_kernel<XT, NT, KW>), grid, dim3(64 * KW), L::kBytes, a.stream,
                        static_cast<const XT *>(a.x), static_cast<XT *>(a.y), a.tile, a.alpha, P);
     return check_launch("tbn_linear_forward (direct kernel)");
 }
@@ -549,7 +562,7 @@ bool linear_direct_preferred(const LinearArgs &a, DirectOver other) {
 }
 
 template <typename XT>
-static tbn_status launch_ends(const LinearArgs &a, const DirectLinearParams &P) {
+static tbn_status launch_ends(const LinearArgs &a, DirectLinearParams P) {
     constexpr int kLds = Lds<1, 8>::kBytes + 4096;
     static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(&linear_direct_kernel<XT, 1, 8, true>),
                                                        hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
@@ -557,7 +570,8 @@ static tbn_status launch_ends(const LinearArgs &a, const DirectLinearParams &P) 
         set_error("tbn_linear_forward: cannot reserve %d bytes of LDS", kLds);
         return TBN_ERR_DEVICE;
     }
-    hipLaunchKernelGGL((linear_direct_kernel<XT, 1, 8, true>), dim3(P.row_tiles * P.groups), dim3(512), kLds, a.stream,
+    const dim3 grid = grid_of(P);
+    hipLaunchKernelGGL((linear_direct_kernel<XT, 1, 8, true>), grid, dim3(512), kLds, a.stream,
                        static_cast<const XT *>(a.x), static_cast<XT *>(a.y), a.tile, a.alpha, P);
     return check_launch("tbn_linear_forward (columns that hold a tile start)");
 }

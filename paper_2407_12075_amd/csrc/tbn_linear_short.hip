@@ -332,7 +332,8 @@ bool linear_short_supported(const LinearArgs &a) {
     const int64_t U = a.p / a.in;
     if (U > a.out || a.out % U != 0 || U % 8 != 0 || a.out > (1 << 22) || a.p >= (int64_t(1) << 36)) return false;
     if ((reinterpret_cast<uintptr_t>(a.x) | reinterpret_cast<uintptr_t>(a.y)) & 15u) return false;
-    return a.M >= 1 && (a.M + kRows - 1) / kRows * ((U + kCols - 1) / kCols) <= 0x7fffffffLL;
+    // (a launch has fewer than 2^32 threads along x)
+    return a.M >= 1 && (a.M + kRows - 1) / kRows * ((U + kCols - 1) / kCols) < (int64_t(1) << 32) / kThreads;
 }
 
 // Where this kernel beats the block and the general kernel (graph replays, microseconds per call, the other kernel / this

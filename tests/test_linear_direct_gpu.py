@@ -108,3 +108,35 @@ def test_tile_starts_inside_rows_exact(tbn, M, cin, cout, k, dtype):
     got = y.float().cpu().numpy()
     bad = np.argwhere(got != ref)
     assert bad.size == 0, f"{len(bad)} of {got.size} outputs differ, first at {tuple(bad[0])}: {got[tuple(bad[0])]} against {ref[tuple(bad[0])]}"
+
+
+def _signs(tile, n):
+    """The first n entries of a tile as +1 / -1 in float32."""
+    bits = np.unpackbits(tile.cpu().numpy().view(np.uint8), bitorder="little")[:n]
+    return torch.from_numpy(bits.astype(np.float32) * 2 - 1).cuda()
+
+
+def test_more_workgroups_than_a_grid_row_holds(tbn):
+    """2^24 + 2 row tiles of four waves: more than 2^32 threads, which one grid dimension cannot count."""
+    M, cin = (1 << 29) + 33, 3
+    assert tbn.tbn_linear_forward_kernel(torch.float32, M, cin, 1, 1) == "direct"
+    x = torch.empty(M, cin, device="cuda").random_(0, 3, generator=torch.Generator(device="cuda").manual_seed(1)).sub_(1)
+    tile = torch.tensor([5], dtype=torch.int32, device="cuda")
+    y = torch.full((M, 1), 7.0, device="cuda")
+    tbn.tbn_linear_forward(x, tile, torch.ones(1, device="cuda"), 1, 1, y=y)
+    want = (x * _signs(tile, cin)).sum(1, keepdim=True)   # integers: exact in any order
+    assert torch.equal(y, want)
+
+
+def test_repair_pass_with_more_workgroups_than_a_grid_row_holds(tbn):
+    """29,132 row tiles x 288 groups of tile starts, eight waves each."""
+    M, cin, cout, k = 932200, 144, 6144, 4608
+    p = cin * cout // k
+    g = torch.Generator(device="cuda").manual_seed(2)
+    x = torch.empty(M, cin, device="cuda").random_(0, 3, generator=g).sub_(1).bfloat16()
+    tile = torch.randint(-2 ** 31, 2 ** 31, (p // 32,), generator=g, device="cuda", dtype=torch.int64).int()
+    alpha = torch.exp2((torch.arange(k, device="cuda") % 5 - 2).float())
+    y = tbn.tbn_linear_forward(x, tile, alpha, cout, k)
+    for rows in (slice(0, 4000), slice(M - 20000, M)):
+        want = tbn.tbn_linear_forward(x[rows], tile, alpha, cout, k, flags=tbn.TBN_FLAG_FORCE_GENERIC)
+        assert torch.equal(y[rows], want)
