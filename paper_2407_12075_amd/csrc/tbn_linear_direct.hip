@@ -82,9 +82,11 @@ __device__ __forceinline__ uint32_t pack2(float a, float b) {
 }
 
 // Truncation split of eight floats into three bf16x8 operands (8 + 8 + 8 significand bits: exact).  An infinity is all in
-// the first term (infinity minus itself would put a NaN in the others); a NaN stays one in the second.
-__device__ __forceinline__ void split8(const float (&x)[8], Frag (&t)[3]) {
-    uint32_t h[3][8];
+// the first term (infinity minus itself would put a NaN in the others); a NaN stays one in the second.  A bfloat16 has no
+// bits below 2^-133: what an activation has there (the low 16 bits of the third term, activations below 2^-110 only) is left
+// out and `lost` set.
+__device__ __forceinline__ void split8(const float (&x)[8], Frag (&t)[3], bool &lost) {
+    uint32_t h[3][8], low = 0u;
     float top = 0.f;
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
@@ -94,8 +96,10 @@ __device__ __forceinline__ void split8(const float (&x)[8], Frag (&t)[3]) {
         const float r2 = r1 - __uint_as_float(t1);
         h[0][i] = t0; h[1][i] = t1; h[2][i] = __float_as_uint(r2);
         top = fmaxf(top, fabsf(x[i]));
+        low |= h[2][i];
     }
-    if (__builtin_expect(__any(top == __builtin_inff()), 0)) {
+    if (__builtin_expect(__any(top == __builtin_inff() || (low << 16) != 0u), 0)) {
+        lost = true;
 #pragma unroll
         for (int i = 0; i < 8; ++i)
             if (fabsf(x[i]) == __builtin_inff()) h[1][i] = h[2][i] = 0u;
@@ -105,6 +109,24 @@ __device__ __forceinline__ void split8(const float (&x)[8], Frag (&t)[3]) {
 #pragma unroll
         for (int v = 0; v < 4; ++v)   // high halves of two words in one: (lo >> 16) | (hi & 0xffff0000)
             t[j].q[v] = __builtin_amdgcn_perm(h[j][2 * v + 1], h[j][2 * v], 0x07060302u);
+}
+
+// What split8 leaves out of eight floats, scaled by 2^64: at most 16 bits each, two operands.
+__device__ __forceinline__ void rest8(const float (&x)[8], Frag (&t)[2]) {
+    uint32_t h[2][8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        const float r1 = x[i] - __uint_as_float(__float_as_uint(x[i]) & 0xffff0000u);
+        const float r2 = r1 - __uint_as_float(__float_as_uint(r1) & 0xffff0000u);
+        float r3 = (r2 - __uint_as_float(__float_as_uint(r2) & 0xffff0000u)) * 0x1p64f;
+        r3 = fabsf(x[i]) < 1.f ? r3 : 0.f;   // infinities and NaN are in the terms already
+        h[0][i] = __float_as_uint(r3) & 0xffff0000u;
+        h[1][i] = __float_as_uint(r3 - __uint_as_float(h[0][i]));
+    }
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) t[j].q[v] = __builtin_amdgcn_perm(h[j][2 * v + 1], h[j][2 * v], 0x07060302u);
 }
 
 // drops the first `bits` bits (a multiple of 16) of a piece and moves the rest down, zeros on top
@@ -206,7 +228,9 @@ __global__ __launch_bounds__(64 * KW) __attribute__((amdgpu_waves_per_eu(2))) vo
         } else {   // rows shorter than a piece
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                const XT *row = reinterpret_cast<const XT *>(x_blk + ld_off[i]);
+                uint32_t off = ld_off[i];
+                asm volatile("" : "+v"(off));   // the address is formed here, not kept in registers through the loops
+                const XT *row = reinterpret_cast<const XT *>(x_blk + off);
                 u32x4_t v = {0u, 0u, 0u, 0u};
 #pragma unroll
                 for (int j = 0; j < kEP - 1; ++j) {
@@ -281,7 +305,8 @@ __global__ __launch_bounds__(64 * KW) __attribute__((amdgpu_waves_per_eu(2))) vo
             if constexpr (kF32) low[t][e] = 0.f;
         }
 
-    for (int32_t c = wave; c < P.chunks; c += KW) {
+    // the chunk in flight into the region; returns its MFMA steps
+    auto stage = [&](int32_t c) __attribute__((always_inline)) {
         int steps = kSteps;
         if ((c + 1) * kCE > P.in) {   // the last chunk of a row that does not fill it
             const int tail = P.in - c * kCE;
@@ -296,11 +321,6 @@ __global__ __launch_bounds__(64 * KW) __attribute__((amdgpu_waves_per_eu(2))) vo
                 }
             }
         }
-        uint32_t wc[NT][kWords];
-#pragma unroll
-        for (int t = 0; t < NT; ++t)
-#pragma unroll
-            for (int w = 0; w < kWords; ++w) wc[t][w] = __funnelshift_r(wr[t][w], wr[t][w + 1], sh[t]);
 #pragma unroll
         for (int i = 0; i < 4; ++i)
 #pragma unroll
@@ -308,23 +328,40 @@ __global__ __launch_bounds__(64 * KW) __attribute__((amdgpu_waves_per_eu(2))) vo
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();   // lanes read what other lanes of the wave wrote (LDS operations of a wave stay in order)
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        return steps;
+    };
+    auto release = [] {   // the next chunk overwrites the region
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    };
+    // the +-1 operand from a byte of tile bits whose first element is e of the chunk
+    auto operand = [&](uint32_t byte, int32_t c, int e) __attribute__((always_inline)) {
+        Frag sg;
+        sg.q = s_table[byte & 0xffu];
+        if constexpr (ENDS) {
+            int32_t n = split - (c * kCE + lg * (kCE / 2) + e);   // of the eight elements, those before the start
+            n = n < 0 ? 0 : n > 8 ? 8 : n;
+            const uint32_t before = (1u << n) - 1u;
+            sg.q &= s_keep[ln < 16 ? before : 0xffu ^ before];
+        }
+        return sg;
+    };
+    bool lost = false;
+    for (int32_t c = wave; c < P.chunks; c += KW) {
+        uint32_t wc[NT][kWords];
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+#pragma unroll
+            for (int w = 0; w < kWords; ++w) wc[t][w] = __funnelshift_r(wr[t][w], wr[t][w + 1], sh[t]);
+        const int steps = stage(c);
         if (c + KW < P.chunks) {
             load_chunk(c + KW);
             load_words(c + KW);
         }
         // operands of row ln.  float32: step s of lane half lg takes floats 32*lg + 8*s .. + 7, pieces 8*lg + 2*s and + 1;
         // bfloat16: elements 64*lg + 8*s .. + 7, piece 8*lg + s
-        auto sign = [&](int t, int s) {
-            Frag sg;
-            sg.q = s_table[(wc[t][s / 4] >> (8 * (s % 4))) & 0xffu];
-            if constexpr (ENDS) {
-                int32_t n = split - (c * kCE + lg * (kCE / 2) + 8 * s);   // of the eight elements, those before the start
-                n = n < 0 ? 0 : n > 8 ? 8 : n;
-                const uint32_t before = (1u << n) - 1u;
-                sg.q &= s_keep[ln < 16 ? before : 0xffu ^ before];
-            }
-            return sg.v;
-        };
+        auto sign = [&](int t, int s) { return operand(wc[t][s / 4] >> (8 * (s % 4)), c, 8 * s).v; };
 #pragma unroll
         for (int s = 0; s < kSteps; ++s) {
             if (s >= steps) break;
@@ -333,7 +370,7 @@ __global__ __launch_bounds__(64 * KW) __attribute__((amdgpu_waves_per_eu(2))) vo
                 const f32x4_t b = *reinterpret_cast<const f32x4_t *>(region + ln * 256 + (((8 * lg + 2 * s + 1) ^ (ln & 15)) << 4));
                 const float xs[8] = {a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
                 Frag terms[3];
-                split8(xs, terms);
+                split8(xs, terms, lost);
 #pragma unroll
                 for (int t = 0; t < NT; ++t) {
                     const bf16x8_t sg = sign(t, s);
@@ -348,14 +385,54 @@ __global__ __launch_bounds__(64 * KW) __attribute__((amdgpu_waves_per_eu(2))) vo
                 for (int t = 0; t < NT; ++t) acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(sign(t, s), xt.v, acc[t], 0, 0, 0);
             }
         }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();   // the next chunk overwrites the region
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        release();
     }
 
     if constexpr (kF32) {
 #pragma unroll
         for (int t = 0; t < NT; ++t) acc[t] += low[t];
+        // activations with bits below 2^-133: the wave goes through its chunks again, one column tile at a time, and adds
+        // those bits, scaled by 2^64, times signs scaled by 2^-64
+        if (__builtin_expect(lost, 0)) {
+#pragma unroll 1
+            for (int tt = 0; tt < NT; ++tt) {
+                uint32_t first = word0[0], shift = sh[0];
+#pragma unroll
+                for (int t = 1; t < NT; ++t)
+                    if (tt == t) { first = word0[t]; shift = sh[t]; }
+                f32x16_t sum;
+#pragma unroll
+                for (int e = 0; e < 16; ++e) sum[e] = 0.f;
+#pragma unroll 1
+                for (int32_t c = wave; c < P.chunks; c += KW) {
+                    load_chunk(c);
+                    uint32_t w[2];
+#pragma unroll
+                    for (int j = 0; j < 2; ++j) {
+                        const uint32_t i = first + static_cast<uint32_t>(c * (kCE / 32) + j);
+                        w[j] = tile[i < P.last_word ? i : P.last_word];
+                    }
+                    const uint32_t window = __funnelshift_r(w[0], w[1], shift);
+                    const int steps = stage(c);
+#pragma unroll 1
+                    for (int s = 0; s < steps; ++s) {
+                        const f32x4_t a = *reinterpret_cast<const f32x4_t *>(region + ln * 256 + (((8 * lg + 2 * s) ^ (ln & 15)) << 4));
+                        const f32x4_t b = *reinterpret_cast<const f32x4_t *>(region + ln * 256 + (((8 * lg + 2 * s + 1) ^ (ln & 15)) << 4));
+                        const float xs[8] = {a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
+                        Frag rest[2];
+                        rest8(xs, rest);
+                        Frag sg = operand(window >> (8 * s), c, 8 * s);
+                        sg.q &= 0xdfffdfffu;   // 1 -> 2^-64
+                        sum = __builtin_amdgcn_mfma_f32_32x32x16_bf16(sg.v, rest[1].v, sum, 0, 0, 0);
+                        sum = __builtin_amdgcn_mfma_f32_32x32x16_bf16(sg.v, rest[0].v, sum, 0, 0, 0);
+                    }
+                    release();
+                }
+#pragma unroll
+                for (int t = 0; t < NT; ++t)
+                    if (tt == t) acc[t] += sum;
+            }
+        }
     }
     // The wave's sums, 32 rows of 32 columns per tile: register 4q + e is column 8q + 4lg + e of row ln; the four columns of
     // group g of row r sit at group g ^ (r & 7).

@@ -26,6 +26,12 @@ CASES = [
 ]
 
 
+def _signs(tile, n):
+    """The first n entries of a tile as +1 / -1 in float32."""
+    bits = np.unpackbits(tile.cpu().numpy().view(np.uint8), bitorder="little")[:n]
+    return torch.from_numpy(bits.astype(np.float32) * 2 - 1).cuda()
+
+
 @pytest.fixture(scope="module")
 def tbn():
     assert torch.cuda.is_available(), "GPU tests need a GPU"
@@ -82,6 +88,44 @@ def test_direct_infinities_and_nan(tbn):
         assert torch.equal(torch.isinf(y), torch.isinf(ref)) and torch.equal(y[torch.isinf(y)], ref[torch.isinf(ref)])
 
 
+@pytest.mark.parametrize("M,cin,cout,k,ends", [(300, 196, 384, 4, False), (37, 5, 64, 2, False), (2500, 1199, 1024, 2, False),
+                                              (70, 264, 520, 11, True)])
+def test_small_activations_keep_all_their_bits(tbn, M, cin, cout, k, ends):
+    """Activations down to the smallest float32 numbers.  In float32 sums each of the `cin` additions is off by at most 2^-24
+    of the partial sum (at most the sum of the magnitudes) or, among subnormal numbers, exact; alpha is 1, with tile ends
+    a power of two, whose products of subnormal sums are rounded once more."""
+    g = torch.Generator().manual_seed(cin)
+    x0 = torch.randn(M, cin, generator=g)
+    x0[1::3] *= torch.exp2(torch.randint(-20, 1, (1, cin), generator=g).float())   # rows of mixed magnitudes
+    p = cin * cout // k
+    tile = torch.randint(-2 ** 31, 2 ** 31, ((p + 31) // 32,), generator=g).int().cuda()
+    alpha = torch.exp2((torch.arange(k) % 3 - 1).float()).cuda() if ends else torch.ones(1).cuda()
+    sign = _signs(tile, p).double().repeat(k).view(cout, cin)
+    scale = (alpha.double().repeat_interleave(p) if ends else torch.ones(cin * cout, device="cuda")).view(cout, cin)
+    cols = torch.arange(cout, device="cuda")
+    if ends:   # the columns of the repair pass: the other kernel's are not looked at here
+        starts = torch.arange(1, k, device="cuda") * p
+        cols = (starts // cin)[starts % cin != 0]
+        assert len(cols) == k - 1
+    else:
+        assert tbn.tbn_linear_forward_kernel(torch.float32, M, cin, cout, k) == "direct"
+    for e in (0, -90, -105, -112, -118, -124, -128, -134, -142):
+        x = (x0.double() * 2.0 ** e).float().cuda()
+        y = tbn.tbn_linear_forward(x, tile, alpha, cout, k)[:, cols].double()
+        want = x.double() @ (sign * scale)[cols].t()
+        bound = cin * 2.0 ** -24 * (x.double().abs() @ scale[cols].t().double()) + 3 * 2.0 ** -149
+        worst = float(((y - want).abs() / bound).max())
+        assert worst <= 1.0, (e, worst)
+    if not ends:   # an infinity and small activations in the same row tile
+        x = (x0.double() * 2.0 ** -118).float().cuda()
+        want = tbn.tbn_linear_forward(x, tile, alpha, cout, k)
+        x[2, 1] = float("inf")
+        y = tbn.tbn_linear_forward(x, tile, alpha, cout, k)
+        assert torch.isinf(y[2]).all() and torch.equal(torch.sign(y[2]), sign[:, 1].float())
+        want[2] = y[2]
+        assert torch.equal(y, want)
+
+
 # tile starts inside rows, an alpha per tile: M, in, out, k
 ENDS = [(33, 264, 520, 11), (1000, 3000, 3072, 9), (64, 1000, 312, 16), (17, 1016, 123, 24), (40, 136, 45, 6), (700, 520, 1000, 64)]
 
@@ -108,12 +152,6 @@ def test_tile_starts_inside_rows_exact(tbn, M, cin, cout, k, dtype):
     got = y.float().cpu().numpy()
     bad = np.argwhere(got != ref)
     assert bad.size == 0, f"{len(bad)} of {got.size} outputs differ, first at {tuple(bad[0])}: {got[tuple(bad[0])]} against {ref[tuple(bad[0])]}"
-
-
-def _signs(tile, n):
-    """The first n entries of a tile as +1 / -1 in float32."""
-    bits = np.unpackbits(tile.cpu().numpy().view(np.uint8), bitorder="little")[:n]
-    return torch.from_numpy(bits.astype(np.float32) * 2 - 1).cuda()
 
 
 def test_more_workgroups_than_a_grid_row_holds(tbn):
