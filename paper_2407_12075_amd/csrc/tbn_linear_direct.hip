@@ -460,6 +460,15 @@ __global__ __launch_bounds__(64 * KW) __attribute__((amdgpu_waves_per_eu(2))) vo
                     const int col = 16 * h + c;
                     z[h] += *reinterpret_cast<const float *>(s_raw + 4096 + w * L::kRegion + r * 128 + (((col >> 2) ^ (r & 7)) << 4) + 4 * (col & 3));
                 }
+            if (__builtin_expect(z[0] != z[0] || z[1] != z[1], 0)) {   // 0 x infinity in a masked operand, or a NaN: by elements
+                const XT *row = x + (m0 + r) * P.in;
+                z[0] = z[1] = 0.f;
+                for (int32_t j = 0; j < P.in; ++j) {
+                    const int64_t bit = (j < j_e ? P.p : 0) + j - j_e;
+                    const float e = ElemIO<XT>::load(row + j), w = ((tile[bit >> 5] >> (bit & 31)) & 1u) ? e : -e;
+                    if (j < j_e) z[0] += w; else z[1] += w;
+                }
+            }
             float v = alpha[tc - 1] * z[0] + alpha[tc] * z[1];
             if (P.relu) v = fmaxf(v, 0.f);
             ElemIO<XT>::store(y + (m0 + r) * P.out + o, v);

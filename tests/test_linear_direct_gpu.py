@@ -154,6 +154,25 @@ def test_tile_starts_inside_rows_exact(tbn, M, cin, cout, k, dtype):
     assert bad.size == 0, f"{len(bad)} of {got.size} outputs differ, first at {tuple(bad[0])}: {got[tuple(bad[0])]} against {ref[tuple(bad[0])]}"
 
 
+@pytest.mark.parametrize("dt", [torch.float32, torch.bfloat16])
+def test_tile_starts_inside_rows_infinities_and_nan(tbn, dt):
+    """An infinity on one side of a tile start leaves the other side's sum alone."""
+    M, cin, cout, k = 70, 264, 520, 11
+    g = torch.Generator().manual_seed(3)
+    tile, alpha = tbn.tbn_pack_tile(torch.randn(cin * cout, generator=g).cuda(), k, k)
+    x = torch.randn(M, cin, generator=g)
+    x[5, 7], x[6, cin - 1], x[33, 100], x[40, 9] = float("inf"), float("-inf"), float("inf"), float("nan")
+    x[50, 0], x[50, cin - 1] = float("inf"), float("inf")
+    x = x.to(dt).cuda()
+    starts = torch.arange(1, k, device="cuda") * (cin * cout // k)
+    cols = (starts // cin)[starts % cin != 0]
+    y = tbn.tbn_linear_forward(x, tile, alpha, cout, k)[:, cols].float()
+    ref = tbn.tbn_linear_forward(x, tile, alpha, cout, k, flags=tbn.TBN_FLAG_FORCE_GENERIC)[:, cols].float()
+    assert torch.isinf(ref).sum() >= 3 * len(cols)
+    assert torch.equal(torch.isnan(y), torch.isnan(ref))
+    assert torch.equal(torch.isinf(y), torch.isinf(ref)) and torch.equal(y[torch.isinf(y)], ref[torch.isinf(ref)])
+
+
 def test_more_workgroups_than_a_grid_row_holds(tbn):
     """2^24 + 2 row tiles of four waves: more than 2^32 threads, which one grid dimension cannot count."""
     M, cin = (1 << 29) + 33, 3
