@@ -224,7 +224,7 @@ __global__ __launch_bounds__(64 * kMaxWaves, (wave_bound(sizeof(XT) == 4, MT, T,
                 b += c0 + g * 8 + j + 1 < P.C ? hwb : 0;   // past the last channel: that one again, dropped below
             }
     };
-    auto store_chunk = [&](int chunk, auto set_c) {
+    auto store_chunk = [&](int chunk, auto set_c) __attribute__((always_inline)) {
         auto &st = staged[decltype(set_c)::value];
         const int c_left = P.C - chunk * CK;
         if (c_left < CK) {   // channels past the last one are zeros
@@ -251,15 +251,27 @@ __global__ __launch_bounds__(64 * kMaxWaves, (wave_bound(sizeof(XT) == 4, MT, T,
                 } else {   // exact three-term split: the top 8 significand bits, the next 8, the rest
                     unsigned char *dst = region + loff[it][0] + g * kGroup;
                     u32x4_t v0, v1, v2;
+                    float top = 0.f;
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
                         const float a = __uint_as_float(s[2 * e]), b = __uint_as_float(s[2 * e + 1]);
                         const float a1 = a - __uint_as_float(s[2 * e] & 0xffff0000u), b1 = b - __uint_as_float(s[2 * e + 1] & 0xffff0000u);
                         const float a2 = a1 - __uint_as_float(__float_as_uint(a1) & 0xffff0000u);
                         const float b2 = b1 - __uint_as_float(__float_as_uint(b1) & 0xffff0000u);
+                        top = fmaxf(top, fmaxf(fabsf(a), fabsf(b)));
                         v0[e] = pack_hi16(s[2 * e], s[2 * e + 1]);
                         v1[e] = pack_hi16(__float_as_uint(a1), __float_as_uint(b1));
                         v2[e] = pack_hi16(__float_as_uint(a2), __float_as_uint(b2));
+                    }
+                    if (__builtin_expect(__any(top == __builtin_inff()), 0)) {   // all in the first term (infinity minus itself is a NaN)
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            uint32_t keep = 0xffffffffu;
+                            if (fabsf(__uint_as_float(s[2 * e])) == __builtin_inff()) keep &= 0xffff0000u;
+                            if (fabsf(__uint_as_float(s[2 * e + 1])) == __builtin_inff()) keep &= 0x0000ffffu;
+                            v1[e] &= keep;
+                            v2[e] &= keep;
+                        }
                     }
                     *reinterpret_cast<u32x4_t *>(dst) = v0;
                     *reinterpret_cast<u32x4_t *>(dst + kPlane) = v1;

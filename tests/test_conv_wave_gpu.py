@@ -63,3 +63,24 @@ def test_conv_wave_blocks_exact(tbn, N, C, H, W, O, ks, stride, pad, k, n_alpha,
     got = y.float().cpu().numpy()
     bad = np.argwhere(got != ref)
     assert bad.size == 0, f"{len(bad)} of {got.size} outputs differ, first at {tuple(bad[0])}: {got[tuple(bad[0])]} against {ref[tuple(bad[0])]}"
+
+
+# float32: N, C, H, W, O, window, stride, pad, k
+SPECIAL = [(2, 64, 14, 14, 64, 3, 1, 1, 4), (1, 40, 9, 65, 66, 3, 1, 1, 2), (2, 48, 15, 17, 96, 3, 2, 1, 1), (1, 272, 9, 9, 128, 1, 1, 0, 1),
+           (1, 3500, 6, 6, 32, 3, 1, 1, 2)]   # the last one: more channels than tbn_conv_mfma.hip takes
+
+
+@pytest.mark.parametrize("N,C,H,W,O,ks,stride,pad,k", SPECIAL)
+def test_conv_wave_infinities_and_nan(tbn, N, C, H, W, O, ks, stride, pad, k):
+    """An infinity or a NaN reaches the outputs whose window holds it, as in the one-thread-per-output kernel."""
+    g = torch.Generator().manual_seed(C)
+    x = torch.randn(N, C, H, W, generator=g)
+    x[0, 3, 0, 1], x[0, C - 1, H - 1, W - 1], x[N - 1, 9, 4, 4] = float("inf"), float("-inf"), float("nan")
+    x[0, 1, 2, 5], x[0, 2, 2, 5] = float("inf"), float("inf")
+    x = x.cuda()
+    tile, alpha = tbn.tbn_pack_tile(torch.randn(O * C * ks * ks, generator=g).cuda(), k)
+    y = tbn.tbn_conv2d_forward(x, tile, alpha, O, ks, ks, k, stride=(stride, stride), pad=(pad, pad))
+    ref = tbn.tbn_conv2d_forward(x, tile, alpha, O, ks, ks, k, stride=(stride, stride), pad=(pad, pad), flags=tbn.TBN_FLAG_FORCE_GENERIC)
+    assert torch.isinf(ref).any() and torch.isnan(ref).any()
+    assert torch.equal(torch.isnan(y), torch.isnan(ref))
+    assert torch.equal(torch.isinf(y), torch.isinf(ref)) and torch.equal(y[torch.isinf(y)], ref[torch.isinf(ref)])
