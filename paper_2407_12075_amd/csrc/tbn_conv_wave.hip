@@ -127,9 +127,9 @@ template <> struct Acc<16> {
 };
 
 // XT: input and output type; MT: filters (and pixels) of an MFMA tile; T: taps; PW: pixels per wave; NFT: filter tiles
-// per wave; kCap: LDS pixels of a patch
-template <typename XT, int MT, int T, int PW, int NFT, int kCap>
-__global__ __launch_bounds__(64 * kMaxWaves, (wave_bound(sizeof(XT) == 4, MT, T, PW, NFT, kCap))) void conv_wave_kernel(const XT *__restrict__ x, XT *__restrict__ y,
+// per wave; kCap: LDS pixels of a patch; ALL: float32, add what the split of small activations leaves out
+template <typename XT, int MT, int T, int PW, int NFT, int kCap, bool ALL = false>
+__global__ __launch_bounds__(64 * kMaxWaves, (wave_bound(sizeof(XT) == 4, MT, T, PW, NFT, kCap) - (ALL ? 1 : 0))) void conv_wave_kernel(const XT *__restrict__ x, XT *__restrict__ y,
                                                                                          const uint32_t *__restrict__ tile,
                                                                                          const float *__restrict__ alpha, WaveConvParams P) {
     constexpr int NP = WTraits<XT>::planes;
@@ -224,6 +224,7 @@ __global__ __launch_bounds__(64 * kMaxWaves, (wave_bound(sizeof(XT) == 4, MT, T,
                 b += c0 + g * 8 + j + 1 < P.C ? hwb : 0;   // past the last channel: that one again, dropped below
             }
     };
+    uint32_t low_bits = 0u;   // ALL: of the third terms; the low 16 have no place in a bfloat16 (activations below 2^-110)
     auto store_chunk = [&](int chunk, auto set_c) __attribute__((always_inline)) {
         auto &st = staged[decltype(set_c)::value];
         const int c_left = P.C - chunk * CK;
@@ -259,6 +260,7 @@ __global__ __launch_bounds__(64 * kMaxWaves, (wave_bound(sizeof(XT) == 4, MT, T,
                         const float a2 = a1 - __uint_as_float(__float_as_uint(a1) & 0xffff0000u);
                         const float b2 = b1 - __uint_as_float(__float_as_uint(b1) & 0xffff0000u);
                         top = fmaxf(top, fmaxf(fabsf(a), fabsf(b)));
+                        if (ALL) low_bits |= __float_as_uint(a2) | __float_as_uint(b2);
                         v0[e] = pack_hi16(s[2 * e], s[2 * e + 1]);
                         v1[e] = pack_hi16(__float_as_uint(a1), __float_as_uint(b1));
                         v2[e] = pack_hi16(__float_as_uint(a2), __float_as_uint(b2));
@@ -463,6 +465,15 @@ __global__ __launch_bounds__(64 * kMaxWaves, (wave_bound(sizeof(XT) == 4, MT, T,
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
     };
+    bool small = false;   // an activation of the workgroup has bits below 2^-133
+    if constexpr (ALL) {
+        uint32_t *flag = reinterpret_cast<uint32_t *>(lds_raw);
+        lds_barrier();
+        if (lane == 0) flag[wave] = 0u;
+        if ((low_bits << 16) != 0u) flag[wave] = 1u;   // (LDS operations of a wave stay in order)
+        lds_barrier();
+        for (int w = 0; w < static_cast<int>(blockDim.x >> 6); ++w) small = small || flag[w] != 0u;
+    }
     for (int ft = 0; ft < NFT; ++ft) {   // (a real loop around everything but the registers: the code is fetched once)
         lds_barrier();
         float *mine = red + ks * (MT * PW);
@@ -485,6 +496,30 @@ __global__ __launch_bounds__(64 * kMaxWaves, (wave_bound(sizeof(XT) == 4, MT, T,
             for (int s = 1; s < KS; ++s)
 #pragma unroll
                 for (int e = 0; e < PG; ++e) v[e] += red[s * (MT * PW) + f * PW + px + e];
+            if (ALL && __builtin_expect(small, 0)) {   // those bits, one output at a time
+#pragma unroll 1
+                for (int e = 0; e < PG; ++e) {
+                    const int oy = P.d_cols.div(px + e), ox = px + e - oy * P.cols;
+                    if (px + e >= PX || ox >= cols) continue;
+                    const int iy0 = (row0 + oy) * P.sh - P.ph, ix0 = (col0 + ox) * P.sw - P.pw;
+                    int64_t bit = u * P.F % P.p;
+                    float sum = 0.f;
+                    for (int c = 0; c < P.C; ++c)
+                        for (int tap = 0; tap < T; ++tap) {
+                            const int iy = iy0 + tap / 3, ix = ix0 + tap % 3;
+                            if (iy >= 0 && iy < P.H && ix >= 0 && ix < P.W) {
+                                const float a = *reinterpret_cast<const float *>(x_img + c * hwb + (int64_t(iy) * P.W + ix) * 4);
+                                const float a1 = a - __uint_as_float(__float_as_uint(a) & 0xffff0000u);
+                                const float a2 = a1 - __uint_as_float(__float_as_uint(a1) & 0xffff0000u);
+                                const float r = fabsf(a) < 1.f ? a2 - __uint_as_float(__float_as_uint(a2) & 0xffff0000u) : 0.f;
+                                sum += ((tile[bit >> 5] >> (bit & 31)) & 1u) ? r : -r;
+                            }
+                            if (++bit == P.p) bit = 0;
+                        }
+#pragma unroll
+                    for (int i = 0; i < PG; ++i) v[i] += i == e ? sum : 0.f;
+                }
+            }
             const int yo = whole_rows ? 0 : P.d_cols.div(px), xo = px - yo * P.cols;
             const bool run = whole_rows ? px + PG <= PX : xo + PG <= cols;   // all of them exist and are consecutive in memory
             XT *dst0 = y + (img * P.O + u) * P.plane_out + int64_t(row0 + yo) * P.Wo + col0 + xo;
@@ -529,6 +564,7 @@ struct WavePlan {
     int mt, pw, nft, cap, rows, cols, n_colblk, n_rowblk, PR, PC, ks_log2, ps, n_chunks, waves;
     size_t lds;
     int64_t total_waves;
+    bool all_bits;
 };
 
 WavePlan plan_wave_for(const ConvArgs &a, int nft) {
@@ -637,8 +673,12 @@ WavePlan search_wave(const ConvArgs &a) {
     if (a.kh < 1 || a.kh != a.kw || a.p < 1) return WavePlan{};
     const int64_t R = unique_rows(a.O, a.C * a.kh * a.kw, a.p);
     WavePlan pl{};
+    // Float32 layers that are too large for tbn_conv_mfma.hip (more channels than its LDS holds filters for, maps wider than
+    // its blocks) were float32 FMAs before and keep every bit of their activations; the others never had those below 2^-133.
+    const bool all_bits = a.dt == TBN_F32 && !conv_mfma_supported(a);
     for (int nft = R <= 32 ? 1 : R <= 64 || (a.dt == TBN_F32 && a.kh == 3) ? 2 : 4; nft >= 1; nft /= 2) {
         pl = plan_wave_for(a, nft);
+        pl.all_bits = all_bits;
         if (pl.ok && (a.kh == 1 ? pl.total_waves >> pl.ks_log2 >= 2048 : pl.total_waves >= 1024)) break;   // (1x1: rather more filter blocks than channel slices)
     }
     return pl;
@@ -665,15 +705,17 @@ WavePlan plan_wave(const ConvArgs &a) {
     return e.plan;
 }
 
-template <typename XT, int MT, int T, int PW, int NFT, int CAP>
+template <typename XT, int MT, int T, int PW, int NFT, int CAP, bool ALL = false>
 tbn_status launch_wave_t(const ConvArgs &a, const WaveConvParams &P, const WavePlan &pl, dim3 grid) {
-    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(&conv_wave_kernel<XT, MT, T, PW, NFT, CAP>),
+    if constexpr (sizeof(XT) == 4 && !ALL)
+        if (pl.all_bits) return launch_wave_t<XT, MT, T, PW, NFT, CAP, true>(a, P, pl, grid);
+    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(&conv_wave_kernel<XT, MT, T, PW, NFT, CAP, ALL>),
                                                        hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     if (attr != hipSuccess) {
         set_error("tbn_conv2d_forward: cannot reserve %zu bytes of LDS", pl.lds);
         return TBN_ERR_DEVICE;
     }
-    hipLaunchKernelGGL((conv_wave_kernel<XT, MT, T, PW, NFT, CAP>), grid, dim3(64 * pl.waves), pl.lds, a.stream,
+    hipLaunchKernelGGL((conv_wave_kernel<XT, MT, T, PW, NFT, CAP, ALL>), grid, dim3(64 * pl.waves), pl.lds, a.stream,
                        static_cast<const XT *>(a.x), static_cast<XT *>(a.y), a.tile, a.alpha, P);
     return check_launch("tbn_conv2d_forward (one wave per pixel block)");
 }

@@ -67,7 +67,7 @@ def test_conv_wave_blocks_exact(tbn, N, C, H, W, O, ks, stride, pad, k, n_alpha,
 
 # float32: N, C, H, W, O, window, stride, pad, k
 SPECIAL = [(2, 64, 14, 14, 64, 3, 1, 1, 4), (1, 40, 9, 65, 66, 3, 1, 1, 2), (2, 48, 15, 17, 96, 3, 2, 1, 1), (1, 272, 9, 9, 128, 1, 1, 0, 1),
-           (1, 3500, 6, 6, 32, 3, 1, 1, 2)]   # the last one: more channels than tbn_conv_mfma.hip takes
+           (1, 4200, 6, 6, 32, 3, 1, 1, 2)]   # the last one: more channels than tbn_conv_mfma.hip takes
 
 
 @pytest.mark.parametrize("N,C,H,W,O,ks,stride,pad,k", SPECIAL)
@@ -84,3 +84,25 @@ def test_conv_wave_infinities_and_nan(tbn, N, C, H, W, O, ks, stride, pad, k):
     assert torch.isinf(ref).any() and torch.isnan(ref).any()
     assert torch.equal(torch.isnan(y), torch.isnan(ref))
     assert torch.equal(torch.isinf(y), torch.isinf(ref)) and torch.equal(y[torch.isinf(y)], ref[torch.isinf(ref)])
+
+
+@pytest.mark.parametrize("N,C,H,W,O,ks,stride,pad,k", [(1, 4200, 6, 6, 36, 3, 1, 1, 2), (1, 16, 2, 4096, 40, 1, 1, 0, 2),
+                                                      (1, 4100, 5, 9, 24, 3, 2, 1, 9)])
+def test_conv_small_activations_keep_all_their_bits(tbn, N, C, H, W, O, ks, stride, pad, k):
+    """Layers that tbn_conv_mfma.hip does not take, activations down to the smallest float32 numbers.  In float32 sums each of
+    the F additions is off by at most 2^-24 of the partial sum (at most the sum of the magnitudes) or, among subnormal
+    numbers, exact."""
+    g = torch.Generator().manual_seed(C)
+    F, p = C * ks * ks, O * C * ks * ks // k
+    x0 = torch.randn(N, C, H, W, generator=g, dtype=torch.float64)
+    tile = torch.randint(-2 ** 31, 2 ** 31, ((p + 31) // 32,), generator=g).int()
+    bits = np.unpackbits(tile.numpy().view(np.uint8), bitorder="little")[:p]
+    sign = torch.from_numpy(bits.astype(np.float64) * 2 - 1).repeat(k).view(O, C, ks, ks)
+    tile, alpha = tile.cuda(), torch.ones(1).cuda()
+    for e in (0, -105, -112, -118, -126, -134):
+        x = (x0 * 2.0 ** e).float()
+        y = tbn.tbn_conv2d_forward(x.cuda(), tile, alpha, O, ks, ks, k, stride=(stride, stride), pad=(pad, pad)).double().cpu()
+        want = torch.nn.functional.conv2d(x.double(), sign, stride=stride, padding=pad)
+        bound = F * 2.0 ** -24 * torch.nn.functional.conv2d(x.double().abs(), sign.abs(), stride=stride, padding=pad) + 2.0 ** -149
+        worst = float(((y - want).abs() / bound).max())
+        assert worst <= 1.0, (e, worst)
