@@ -53,10 +53,10 @@ constexpr int kChunkBytes = 256;   // bytes of a row per chunk: 64 floats (four 
 constexpr int kMaxNT = 4;          // column tiles of 32 per workgroup
 
 struct DirectLinearParams {
-    int64_t M, out;
-    int32_t in, U;
-    int32_t chunks;       // ceil(in / elements per chunk)
-    uint32_t last_word;   // of the tile
+    int64_t M, out, in;
+    int64_t chunks;       // ceil(in / elements per chunk)
+    int64_t last_word;    // of the tile
+    int32_t U;
     int32_t reps, n_alpha, relu;
     uint32_t groups;      // groups of NT * 32 distinct columns
     uint32_t row_tiles;   // tiles of 32 batch rows
@@ -153,12 +153,17 @@ struct Lds {
 // tile's first bits); y = alpha[c - 1] * first + alpha[c] * second.  The pass is a read of X: 8192 x 3000 in bfloat16 19.4 us
 // in the small-batch kernel's form (16 rows per workgroup, 64 bytes of a row per load instruction), 14.6 here; 12000 x 264
 // 9.2 against 4.7.
-template <typename XT, int NT, int KW, bool ENDS = false>
+// WIDE: rows or tiles whose offsets need 64 bits (2^25 elements in a row, 2^36 tile bits).
+template <typename XT, int NT, int KW, bool ENDS = false, bool WIDE = false>
 __global__ __launch_bounds__(64 * KW) __attribute__((amdgpu_waves_per_eu(2))) void linear_direct_kernel(const XT *__restrict__ x, XT *__restrict__ y,
                                                                const uint32_t *__restrict__ tile,
                                                                const float *__restrict__ alpha, DirectLinearParams P) {
     typedef Lds<NT, KW> L;
     typedef typename Piece<XT>::type piece_t;
+    typedef typename std::conditional<WIDE, int64_t, int32_t>::type idx_t;
+    typedef typename std::make_unsigned<idx_t>::type uidx_t;
+    const idx_t in = static_cast<idx_t>(P.in), chunks = static_cast<idx_t>(P.chunks);
+    const uidx_t last_word = static_cast<uidx_t>(P.last_word);
     constexpr bool kF32 = std::is_same<XT, float>::value;
     constexpr int kCE = kChunkBytes / static_cast<int>(sizeof(XT));   // elements of K per chunk
     constexpr int kEP = 16 / static_cast<int>(sizeof(XT));            // elements per piece
@@ -194,47 +199,47 @@ __global__ __launch_bounds__(64 * KW) __attribute__((amdgpu_waves_per_eu(2))) vo
     // a row.  Rows past M repeat the last one; they are never written.
     const unsigned char *x_blk = reinterpret_cast<const unsigned char *>(x + m0 * P.in);
     const int rows_last = static_cast<int>(P.M - 1 - m0 < 31 ? P.M - 1 - m0 : 31);
-    uint32_t ld_off[4];      // bytes from x_blk
+    uidx_t ld_off[4];        // bytes from x_blk
     // byte positions in the wave's region: 256 bytes per row, piece p of row r at place p ^ (r % 16); piece (i, h) is at
     // 2048 i + st_pos[(i + h) % 2]
     uint32_t st_pos[2];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         const int r = 8 * i + (lane >> 3);
-        ld_off[i] = static_cast<uint32_t>(r < rows_last ? r : rows_last) * static_cast<uint32_t>(P.in) * static_cast<uint32_t>(sizeof(XT));
+        ld_off[i] = static_cast<uidx_t>(r < rows_last ? r : rows_last) * static_cast<uidx_t>(in) * static_cast<uidx_t>(sizeof(XT));
     }
     st_pos[0] = static_cast<uint32_t>((lane >> 3) * 256 + (((lane & 7) ^ (lane >> 3)) << 4));
     st_pos[1] = st_pos[0] ^ 128u;
     const int e_lane = (lane & 7) * kEP;   // first element of piece h in a chunk: e_lane + h * kCE / 2
 
     u32x4_t xr[8];   // the chunk in flight: [i][h]
-    auto load_chunk = [&](int32_t c) {
-        if ((c + 1) * kCE <= P.in) {
+    auto load_chunk = [&](idx_t c) {
+        if ((c + 1) * kCE <= in) {
             const unsigned char *src = x_blk + int64_t(c) * kChunkBytes;
 #pragma unroll
             for (int i = 0; i < 4; ++i)
 #pragma unroll
                 for (int h = 0; h < 2; ++h)
                     xr[2 * i + h] = *reinterpret_cast<const piece_t *>(src + (ld_off[i] + 16 * (lane & 7)) + h * (kChunkBytes / 2));
-        } else if (P.in >= kEP) {   // the last chunk: pieces that would leave the row are read at its end
-            const int32_t lim = P.in - kEP;
+        } else if (in >= kEP) {   // the last chunk: pieces that would leave the row are read at its end
+            const idx_t lim = in - kEP;
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
-                const int32_t e = c * kCE + e_lane + h * (kCE / 2);
-                const uint32_t off = static_cast<uint32_t>(e < lim ? e : lim) * static_cast<uint32_t>(sizeof(XT));
+                const idx_t e = c * kCE + e_lane + h * (kCE / 2);
+                const uidx_t off = static_cast<uidx_t>(e < lim ? e : lim) * static_cast<uidx_t>(sizeof(XT));
 #pragma unroll
                 for (int i = 0; i < 4; ++i) xr[2 * i + h] = *reinterpret_cast<const piece_t *>(x_blk + (ld_off[i] + off));
             }
         } else {   // rows shorter than a piece
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                uint32_t off = ld_off[i];
+                uidx_t off = ld_off[i];
                 asm volatile("" : "+v"(off));   // the address is formed here, not kept in registers through the loops
                 const XT *row = reinterpret_cast<const XT *>(x_blk + off);
                 u32x4_t v = {0u, 0u, 0u, 0u};
 #pragma unroll
                 for (int j = 0; j < kEP - 1; ++j) {
-                    if (j >= P.in) break;
+                    if (j >= in) break;
                     if constexpr (kF32) v[j] = __float_as_uint(row[j]);
                     else v[j / 2] |= uint32_t(row[j]) << (16 * (j & 1));
                 }
@@ -245,7 +250,8 @@ __global__ __launch_bounds__(64 * KW) __attribute__((amdgpu_waves_per_eu(2))) vo
     };
 
     // tile words of this lane's column in every column tile: bit u * in + k, lane half lg covers kWords windows per chunk
-    uint32_t word0[NT], sh[NT];
+    uidx_t word0[NT];
+    uint32_t sh[NT];
     int32_t split = 0;   // ENDS: first element of the row that belongs to the tile that starts in it
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
@@ -253,29 +259,29 @@ __global__ __launch_bounds__(64 * KW) __attribute__((amdgpu_waves_per_eu(2))) vo
             const int32_t tc = static_cast<int32_t>(cg) * 16 + (ln & 15) + 1;
             tile_start_row(P, tc < P.k ? tc : 1, split);
             const int64_t bit = (ln < 16 ? P.p - split : int64_t(-split)) + lg * (kCE / 2);
-            word0[t] = static_cast<uint32_t>(bit >> 5);   // may be "negative": see load_words
+            word0[t] = static_cast<uidx_t>(bit >> 5);   // may be "negative": see load_words
             sh[t] = static_cast<uint32_t>(bit & 31);
         } else {
             const int32_t u = u0 + 32 * t + ln < P.U ? u0 + 32 * t + ln : P.U - 1;   // columns past U repeat the last one; never written
-            const uint64_t bit = uint64_t(u) * static_cast<uint32_t>(P.in) + static_cast<uint32_t>(lg * (kCE / 2));
-            word0[t] = static_cast<uint32_t>(bit >> 5);
+            const uint64_t bit = uint64_t(u) * static_cast<uint64_t>(in) + static_cast<uint32_t>(lg * (kCE / 2));
+            word0[t] = static_cast<uidx_t>(bit >> 5);
             sh[t] = static_cast<uint32_t>(bit & 31);
         }
     }
     uint32_t wr[NT][kWords + 1];
     // words past the tile's end belong to positions past the row's end (ENDS: past the first part), words before its start
     // (as unsigned numbers past it as well) to positions before the second part: any value will do
-    auto load_words = [&](int32_t c) {
+    auto load_words = [&](idx_t c) {
 #pragma unroll
         for (int t = 0; t < NT; ++t)
 #pragma unroll
             for (int w = 0; w <= kWords; ++w) {
-                const uint32_t i = word0[t] + static_cast<uint32_t>(c * (kCE / 32) + w);
-                wr[t][w] = tile[i < P.last_word ? i : P.last_word];
+                const uidx_t i = word0[t] + static_cast<uidx_t>(c * (kCE / 32) + w);
+                wr[t][w] = tile[i < last_word ? i : last_word];
             }
     };
 
-    if (wave < P.chunks) {
+    if (wave < chunks) {
         load_chunk(wave);
         load_words(wave);
     }
@@ -306,12 +312,12 @@ __global__ __launch_bounds__(64 * KW) __attribute__((amdgpu_waves_per_eu(2))) vo
         }
 
     // the chunk in flight into the region; returns its MFMA steps
-    auto stage = [&](int32_t c) __attribute__((always_inline)) {
+    auto stage = [&](idx_t c) __attribute__((always_inline)) {
         int steps = kSteps;
-        if ((c + 1) * kCE > P.in) {   // the last chunk of a row that does not fill it
-            const int tail = P.in - c * kCE;
+        if ((c + 1) * kCE > in) {   // the last chunk of a row that does not fill it
+            const int tail = static_cast<int>(in - c * kCE);
             if (tail < kCE / 2) steps = (tail + 7) / 8;   // step s takes elements 8s .. + 7 of both halves of the chunk
-            if (P.in >= kEP) {
+            if (in >= kEP) {
 #pragma unroll
                 for (int h = 0; h < 2; ++h) {
                     const int past = e_lane + h * (kCE / 2) - (tail - kEP);   // elements that the load was moved back by
@@ -336,11 +342,11 @@ __global__ __launch_bounds__(64 * KW) __attribute__((amdgpu_waves_per_eu(2))) vo
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     };
     // the +-1 operand from a byte of tile bits whose first element is e of the chunk
-    auto operand = [&](uint32_t byte, int32_t c, int e) __attribute__((always_inline)) {
+    auto operand = [&](uint32_t byte, idx_t c, int e) __attribute__((always_inline)) {
         Frag sg;
         sg.q = s_table[byte & 0xffu];
         if constexpr (ENDS) {
-            int32_t n = split - (c * kCE + lg * (kCE / 2) + e);   // of the eight elements, those before the start
+            int32_t n = split - static_cast<int32_t>(c * kCE + lg * (kCE / 2) + e);   // of the eight elements, those before the start
             n = n < 0 ? 0 : n > 8 ? 8 : n;
             const uint32_t before = (1u << n) - 1u;
             sg.q &= s_keep[ln < 16 ? before : 0xffu ^ before];
@@ -348,14 +354,14 @@ __global__ __launch_bounds__(64 * KW) __attribute__((amdgpu_waves_per_eu(2))) vo
         return sg;
     };
     bool lost = false;
-    for (int32_t c = wave; c < P.chunks; c += KW) {
+    for (idx_t c = wave; c < chunks; c += KW) {
         uint32_t wc[NT][kWords];
 #pragma unroll
         for (int t = 0; t < NT; ++t)
 #pragma unroll
             for (int w = 0; w < kWords; ++w) wc[t][w] = __funnelshift_r(wr[t][w], wr[t][w + 1], sh[t]);
         const int steps = stage(c);
-        if (c + KW < P.chunks) {
+        if (c + KW < chunks) {
             load_chunk(c + KW);
             load_words(c + KW);
         }
@@ -396,7 +402,8 @@ __global__ __launch_bounds__(64 * KW) __attribute__((amdgpu_waves_per_eu(2))) vo
         if (__builtin_expect(lost, 0)) {
 #pragma unroll 1
             for (int tt = 0; tt < NT; ++tt) {
-                uint32_t first = word0[0], shift = sh[0];
+                uidx_t first = word0[0];
+                uint32_t shift = sh[0];
 #pragma unroll
                 for (int t = 1; t < NT; ++t)
                     if (tt == t) { first = word0[t]; shift = sh[t]; }
@@ -404,13 +411,13 @@ __global__ __launch_bounds__(64 * KW) __attribute__((amdgpu_waves_per_eu(2))) vo
 #pragma unroll
                 for (int e = 0; e < 16; ++e) sum[e] = 0.f;
 #pragma unroll 1
-                for (int32_t c = wave; c < P.chunks; c += KW) {
+                for (idx_t c = wave; c < chunks; c += KW) {
                     load_chunk(c);
                     uint32_t w[2];
 #pragma unroll
                     for (int j = 0; j < 2; ++j) {
-                        const uint32_t i = first + static_cast<uint32_t>(c * (kCE / 32) + j);
-                        w[j] = tile[i < P.last_word ? i : P.last_word];
+                        const uidx_t i = first + static_cast<uidx_t>(c * (kCE / 32) + j);
+                        w[j] = tile[i < last_word ? i : last_word];
                     }
                     const uint32_t window = __funnelshift_r(w[0], w[1], shift);
                     const int steps = stage(c);
@@ -463,7 +470,7 @@ __global__ __launch_bounds__(64 * KW) __attribute__((amdgpu_waves_per_eu(2))) vo
             if (__builtin_expect(z[0] != z[0] || z[1] != z[1], 0)) {   // 0 x infinity in a masked operand, or a NaN: by elements
                 const XT *row = x + (m0 + r) * P.in;
                 z[0] = z[1] = 0.f;
-                for (int32_t j = 0; j < P.in; ++j) {
+                for (int32_t j = 0; j < in; ++j) {
                     const int64_t bit = (j < j_e ? P.p : 0) + j - j_e;
                     const float e = ElemIO<XT>::load(row + j), w = ((tile[bit >> 5] >> (bit & 31)) & 1u) ? e : -e;
                     if (j < j_e) z[0] += w; else z[1] += w;
@@ -526,12 +533,12 @@ dim3 grid_of(DirectLinearParams &P) {
     return dim3(P.grid_x, (n + P.grid_x - 1) / P.grid_x);
 }
 
-template <typename XT, int NT, int KW>
+template <typename XT, int NT, int KW, bool WIDE = false>
 tbn_status launch_one(const LinearArgs &a, DirectLinearParams P) {
     typedef Lds<NT, KW> L;
     // dynamic LDS above the default limit has to be allowed once per kernel (thread-safe static initialisation)
     static const hipError_t attr = L::kBytes > 65536
-        ? hipFuncSetAttribute(reinterpret_cast<const void *>(&linear_direct_kernel<XT, NT, KW>),
+        ? hipFuncSetAttribute(reinterpret_cast<const void *>(&linear_direct_kernel<XT, NT, KW, false, WIDE>),
                               hipFuncAttributeMaxDynamicSharedMemorySize, L::kBytes)
         : hipSuccess;
     if (attr != hipSuccess) {
@@ -539,7 +546,7 @@ tbn_status launch_one(const LinearArgs &a, DirectLinearParams P) {
         return TBN_ERR_DEVICE;
     }
     const dim3 grid = grid_of(P);
-    hipLaunchKernelGGL((linear_direct_kernel<XT, NT, KW>), grid, dim3(64 * KW), L::kBytes, a.stream,
+    hipLaunchKernelGGL((linear_direct_kernel<XT, NT, KW, false, WIDE>), grid, dim3(64 * KW), L::kBytes, a.stream,
                        static_cast<const XT *>(a.x), static_cast<XT *>(a.y), a.tile, a.alpha, P);
     return check_launch("tbn_linear_forward (direct kernel)");
 }
@@ -566,6 +573,7 @@ tbn_status launch_nt(const LinearArgs &a, const DirectLinearParams &P, int nt, i
 
 struct DirectPlan {
     int nt, kw;
+    bool wide;
     int64_t groups, row_tiles, chunks;
 };
 
@@ -583,8 +591,10 @@ DirectPlan plan(const LinearArgs &a) {
     pl.row_tiles = (a.M + 31) / 32;
     pl.chunks = (a.in + ce - 1) / ce;
     const int64_t W = pl.row_tiles * tiles;
+    // offsets inside 32 rows and tile words in 64 bits: one column tile and eight waves, the others share what their waves load
+    pl.wide = a.in >= (int64_t(1) << 25) || a.p >= (int64_t(1) << 36);
     int nt = kMaxNT;
-    if (W <= 1024) nt = 1;
+    if (W <= 1024 || pl.wide) nt = 1;
     else if (!f32 && W <= 4096) nt = 2;
     else if (!f32)
         for (int cand = kMaxNT - 1; cand >= 2; --cand)
@@ -592,7 +602,7 @@ DirectPlan plan(const LinearArgs &a) {
     pl.groups = (tiles + nt - 1) / nt;
     pl.nt = static_cast<int>((tiles + pl.groups - 1) / pl.groups);
     pl.kw = 8;
-    while (pl.kw > (f32 ? 4 : 1) && pl.row_tiles * pl.groups * pl.kw > 3072) pl.kw /= 2;
+    while (!pl.wide && pl.kw > (f32 ? 4 : 1) && pl.row_tiles * pl.groups * pl.kw > 3072) pl.kw /= 2;
     return pl;
 }
 
@@ -604,8 +614,7 @@ bool linear_direct_supported(const LinearArgs &a) {
     if (a.M < 1 || a.in < 1 || a.p % a.in != 0) return false;
     const int64_t U = a.p / a.in;
     if (U < 1 || U > a.out || a.out % U != 0 || a.out / U > (1 << 30)) return false;
-    // offsets inside 32 rows, columns and tile words are kept in 32 bits
-    if (a.in > (1 << 25) - 1 || U > (1 << 30) || a.p >= (int64_t(1) << 36)) return false;
+    if (U > (1 << 30)) return false;   // columns are kept in 32 bits
     if (a.n_alpha != 1 && a.n_alpha != a.out / U) return false;
     const DirectPlan pl = plan(a);
     return pl.row_tiles <= 0x7fffffffLL && pl.row_tiles * pl.groups <= 0x7fffffffLL;
@@ -615,6 +624,7 @@ bool linear_direct_supported(const LinearArgs &a) {
 // activations.  Graph replays, microseconds per call, the other kernel / this one; W is the number of 32 x 32 tiles of Z.
 bool linear_direct_preferred(const LinearArgs &a, DirectOver other) {
     if ((a.flags & ~uint32_t(TBN_FLAG_RELU)) || !linear_direct_supported(a)) return false;   // flags that steer to another kernel
+    if (plan(a).wide) return false;
     const bool f32 = a.dt == TBN_F32;
     const int64_t U = a.p / a.in, W = ((a.M + 31) / 32) * ((U + 31) / 32);
     if (other == DirectOver::Tile) {
@@ -673,10 +683,10 @@ tbn_status launch_linear_direct_ends(const LinearArgs &a) {
     if (a.k < 2) return TBN_OK;
     DirectLinearParams P = {};
     P.M = a.M; P.out = a.out;
-    P.in = static_cast<int32_t>(a.in);
+    P.in = a.in;
     P.p = a.p;
     P.k = a.k;
-    P.last_word = static_cast<uint32_t>((a.p + 31) / 32 - 1);
+    P.last_word = (a.p + 31) / 32 - 1;
     const int32_t ce = a.dt == TBN_F32 ? kChunkBytes / 4 : kChunkBytes / 2;
     P.chunks = (P.in + ce - 1) / ce;
     P.relu = (a.flags & TBN_FLAG_RELU) ? 1 : 0;
@@ -689,15 +699,16 @@ tbn_status launch_linear_direct(const LinearArgs &a) {
     const DirectPlan pl = plan(a);
     DirectLinearParams P;
     P.M = a.M; P.out = a.out;
-    P.in = static_cast<int32_t>(a.in);
+    P.in = a.in;
     P.U = static_cast<int32_t>(a.p / a.in);
-    P.last_word = static_cast<uint32_t>((a.p + 31) / 32 - 1);
-    P.chunks = static_cast<int32_t>(pl.chunks);
+    P.last_word = (a.p + 31) / 32 - 1;
+    P.chunks = pl.chunks;
     P.reps = static_cast<int32_t>(a.out / (a.p / a.in));
     P.n_alpha = a.n_alpha;
     P.relu = (a.flags & TBN_FLAG_RELU) ? 1 : 0;
     P.groups = static_cast<uint32_t>(pl.groups);
     P.row_tiles = static_cast<uint32_t>(pl.row_tiles);
+    if (pl.wide) return a.dt == TBN_F32 ? launch_one<float, 1, 8, true>(a, P) : launch_one<uint16_t, 1, 8, true>(a, P);
     return a.dt == TBN_F32 ? launch_nt<float>(a, P, pl.nt, pl.kw) : launch_nt<uint16_t>(a, P, pl.nt, pl.kw);
 }
 

@@ -197,3 +197,25 @@ def test_repair_pass_with_more_workgroups_than_a_grid_row_holds(tbn):
     for rows in (slice(0, 4000), slice(M - 20000, M)):
         want = tbn.tbn_linear_forward(x[rows], tile, alpha, cout, k, flags=tbn.TBN_FLAG_FORCE_GENERIC)
         assert torch.equal(y[rows], want)
+
+
+@pytest.mark.parametrize("dt", [torch.float32, torch.bfloat16])
+def test_rows_and_tiles_beyond_32_bit_offsets(tbn, dt):
+    """Rows of 2^25 and more elements, tiles of 2^36 and more bits; integers, so that the sums are exact."""
+    g = torch.Generator(device="cuda").manual_seed(4)
+    for M, cin, U, k in ((33, (1 << 25) + 3, 2, 2), (2, (1 << 25) + 3, 2048, 1)):
+        if dt == torch.bfloat16 and U > 2:
+            continue
+        cout, p = U * k, U * cin
+        assert tbn.tbn_linear_forward_kernel(dt, M, cin, cout, k) == "direct"
+        x = torch.empty(M, cin, device="cuda", dtype=dt).random_(0, 3, generator=g).sub_(1)
+        tile = torch.empty((p + 31) // 32, dtype=torch.int32, device="cuda").random_(-2 ** 31, 2 ** 31 - 1, generator=g)
+        y = tbn.tbn_linear_forward(x, tile, torch.ones(1, device="cuda"), cout, k).float()
+        for u in {0, 1, U // 2 + 1, U - 1} & set(range(U)):
+            first = u * cin
+            words = tile[first // 32: (first + cin + 31) // 32]
+            bits = ((words[:, None] >> torch.arange(32, device="cuda", dtype=torch.int32)) & 1).view(-1)[first % 32: first % 32 + cin]
+            sign = bits.double() * 2 - 1
+            for m in {0, 1, M - 1}:
+                want = (x[m].double() @ sign).to(dt).float()
+                assert torch.equal(y[m, u::U], want.repeat(k)), (m, u)
