@@ -155,7 +155,7 @@ tbn_status tbn_linear_forward(const void *x, void *y, tbn_dtype dt, int64_t M, i
  *   x, y : the pointers the forward call would get (any address space; only their alignment is looked at; NULL
  *          counts as aligned).
  * Returns a static string, one of "decode", "small-batch", "tile", "stream", "block", "general", "rows", "direct",
- * "generic"; "" on sizes tbn_linear_forward would reject.  The choice also depends on the current device's number
+ * "short-rows", "generic"; "" on sizes tbn_linear_forward would reject.  The choice also depends on the current device's number
  * of CUs (256 is assumed where there is no device).  A help for tests and for reading a profile; a caller never
  * needs it.
  */
@@ -204,6 +204,19 @@ tbn_status tbn_conv2d_forward(const void *x, void *y, tbn_dtype dt, int64_t N, i
                               int32_t stride_h, int32_t stride_w, int32_t pad_h, int32_t pad_w,
                               const uint32_t *tile, int32_t k, const float *alpha,
                               int32_t n_alpha, uint32_t flags, void *stream);
+
+/*
+ * Which kernel tbn_conv2d_forward would launch for these arguments, as tbn_linear_forward_kernel: host arithmetic only,
+ * nothing is launched, no pointer is dereferenced.
+ *
+ * Returns "direct", "block", "generic", or "wave" followed by the plan of the kernel with one wave per pixel block (filter
+ * tiles per wave x filters per tile, pixels per wave, pixels of a patch in LDS, channel slices, and "all-bits" for its
+ * instance that keeps the bits of small float32 activations); "" on sizes tbn_conv2d_forward would reject.  The string is
+ * valid until the calling thread's next call.
+ */
+const char *tbn_conv2d_forward_kernel(const void *x, const void *y, tbn_dtype dt, int64_t N, int64_t C, int64_t H, int64_t W,
+                                      int64_t O, int32_t kh, int32_t kw, int32_t stride_h, int32_t stride_w, int32_t pad_h,
+                                      int32_t pad_w, int32_t k, int32_t n_alpha, uint32_t flags);
 
 /*
  * Column-tiled variant of the fully-connected layer (Section "GPU Inference Kernel": the out x in weight
@@ -304,12 +317,15 @@ tbn_status tbn_linear_forward_binact(const uint32_t *xbits, void *y, tbn_dtype y
  *                           32x32x16 bf16 MFMAs (2 * 32 * 32 * 16 flop each); out is NULL or blocks * 256 floats.
  *   tbn_diag_mfma_fp4     : the same with 32x32x64 MFMAs on 4-bit float operands (2 * 32 * 32 * 64 flop each), the
  *                           instruction of tbn_linear_forward_binact.
+ *   tbn_diag_conv_plan_searches : how often the calling thread has searched for the plan of a convolution (a shape that it
+ *                           has used lately is not searched for again).
  * Errors: TBN_ERR_NULL, TBN_ERR_SHAPE, TBN_ERR_DEVICE.
  */
 tbn_status tbn_diag_empty_launch(void *stream);
 tbn_status tbn_diag_stream(const void *src, void *dst, size_t bytes, void *sink, void *stream);
 tbn_status tbn_diag_mfma(int32_t blocks, int32_t iters, float *out, void *stream);
 tbn_status tbn_diag_mfma_fp4(int32_t blocks, int32_t iters, float *out, void *stream);
+int64_t tbn_diag_conv_plan_searches(void);
 
 #ifdef __cplusplus
 }

@@ -4,6 +4,7 @@
 
 #include <cstdarg>
 #include <cstdio>
+#include <cstring>
 #include <numeric>
 
 namespace tbn {
@@ -169,6 +170,66 @@ static int workspace_splits(const LinearArgs &a) {
     if (a.flags & (TBN_FLAG_FORCE_GENERIC | TBN_FLAG_BLOCK_KERNEL | TBN_FLAG_STREAM_KERNEL | TBN_FLAG_TILE_KERNEL)) return 0;
     if (a.M <= 64) return 0;
     return linear_split_plan(a);
+}
+
+// Checks of a convolution's sizes, types and flags; the arguments of the launch.
+static tbn_status make_conv_args(const void *x, void *y, tbn_dtype dt, int64_t N, int64_t C, int64_t H, int64_t W, int64_t O,
+                                 int32_t kh, int32_t kw, int32_t stride_h, int32_t stride_w, int32_t pad_h, int32_t pad_w,
+                                 const uint32_t *tile, int32_t k, const float *alpha, int32_t n_alpha, uint32_t flags, void *stream,
+                                 ConvArgs *a) {
+    if (dt != TBN_F32 && dt != TBN_BF16) {
+        set_error("tbn_conv2d_forward: unknown dtype %d", (int)dt);
+        return TBN_ERR_UNSUPPORTED;
+    }
+    if (flags & ~(TBN_FLAG_RELU | TBN_FLAG_FORCE_GENERIC)) {
+        set_error("tbn_conv2d_forward: unknown flag bits 0x%x", flags);
+        return TBN_ERR_UNSUPPORTED;
+    }
+    if (N < 0 || C <= 0 || H <= 0 || W <= 0 || O <= 0 || kh <= 0 || kw <= 0 || stride_h <= 0 ||
+        stride_w <= 0 || pad_h < 0 || pad_w < 0) {
+        set_error("tbn_conv2d_forward: sizes and strides must be positive, padding non-negative");
+        return TBN_ERR_SHAPE;
+    }
+    if (H + 2 * (int64_t)pad_h < kh || W + 2 * (int64_t)pad_w < kw) {
+        set_error("tbn_conv2d_forward: kernel %dx%d larger than the padded input", kh, kw);
+        return TBN_ERR_SHAPE;
+    }
+    const int64_t lim = int64_t(1) << 40;
+    int64_t filt, n, xs, ys;
+    const int64_t Ho = (H + 2 * (int64_t)pad_h - kh) / stride_h + 1;
+    const int64_t Wo = (W + 2 * (int64_t)pad_w - kw) / stride_w + 1;
+    if (!mul_ok(C, (int64_t)kh * kw, &filt) || !mul_ok(filt, O, &n) || n > lim ||
+        !mul_ok(N * C, H * W, &xs) || xs > lim || !mul_ok(N * O, Ho * Wo, &ys) || ys > lim ||
+        H > (1 << 20) || W > (1 << 20) || C > (1 << 24) || O > (1 << 24) || N > (int64_t(1) << 31) ||
+        kh > 4096 || kw > 4096 || pad_h > 4096 || pad_w > 4096) {
+        set_error("tbn_conv2d_forward: sizes beyond the supported range");
+        return TBN_ERR_UNSUPPORTED;
+    }
+    const tbn_status st = check_tiling(n, k, n_alpha);
+    if (st != TBN_OK) return st;
+    *a = ConvArgs{x, y, (int)dt, N, C, H, W, O, Ho, Wo, kh, kw, stride_h, stride_w, pad_h, pad_w,
+                  tile, n / k, k, alpha, n_alpha, flags, static_cast<hipStream_t>(stream)};
+    return TBN_OK;
+}
+
+// The kernel family that serves a convolution (host arithmetic only).
+enum class ConvKernel { Direct, Wave, Mfma, Generic };
+
+static ConvKernel choose_conv(const ConvArgs &a) {
+    if (!(a.flags & TBN_FLAG_FORCE_GENERIC)) {
+        // up to 8 input channels (a network's first layer on colour images): the matrix-core kernel would stage chunks of
+        // 32 channels that are mostly zeros; the direct kernel is faster (3 -> 64 channels, 3x3, 32 x 32, 128 images:
+        // 23 us against 39; 224 x 224, 8 images: 60 against 111; from 12 channels on the matrix cores win: 36 against 48)
+        if (a.C <= 8 && conv_direct_supported(a)) return ConvKernel::Direct;
+        // 1x1 and 3x3: one wave per pixel block (equal or faster on every shape measured, 1.0 - 2.9 times, figures in
+        // tbn_conv_wave.hip); the block kernel keeps the other windows of nine taps and maps one pixel wide
+        if (conv_wave_supported(a)) return ConvKernel::Wave;
+        if (conv_mfma_supported(a)) return ConvKernel::Mfma;
+        // other windows (5x5, 7x7, ...) with a tile of whole filters: 16 distinct filters per workgroup on the vector ALUs
+        // (ResNet's 7x7, stride 2 first layer on 32 images: 2.0 ms with one thread per output element)
+        if (conv_direct_supported(a)) return ConvKernel::Direct;
+    }
+    return ConvKernel::Generic;
 }
 
 static size_t coltile_xf_bytes(tbn_dtype dt, int64_t M, int64_t q) {
@@ -444,55 +505,41 @@ tbn_status tbn_conv2d_forward(const void *x, void *y, tbn_dtype dt, int64_t N, i
         set_error("tbn_conv2d_forward: x, y, tile and alpha must not be NULL");
         return TBN_ERR_NULL;
     }
-    if (dt != TBN_F32 && dt != TBN_BF16) {
-        set_error("tbn_conv2d_forward: unknown dtype %d", (int)dt);
-        return TBN_ERR_UNSUPPORTED;
-    }
-    if (flags & ~(TBN_FLAG_RELU | TBN_FLAG_FORCE_GENERIC)) {
-        set_error("tbn_conv2d_forward: unknown flag bits 0x%x", flags);
-        return TBN_ERR_UNSUPPORTED;
-    }
-    if (N < 0 || C <= 0 || H <= 0 || W <= 0 || O <= 0 || kh <= 0 || kw <= 0 || stride_h <= 0 ||
-        stride_w <= 0 || pad_h < 0 || pad_w < 0) {
-        set_error("tbn_conv2d_forward: sizes and strides must be positive, padding non-negative");
-        return TBN_ERR_SHAPE;
-    }
-    if (H + 2 * (int64_t)pad_h < kh || W + 2 * (int64_t)pad_w < kw) {
-        set_error("tbn_conv2d_forward: kernel %dx%d larger than the padded input", kh, kw);
-        return TBN_ERR_SHAPE;
-    }
-    const int64_t lim = int64_t(1) << 40;
-    int64_t filt, n, xs, ys;
-    const int64_t Ho = (H + 2 * (int64_t)pad_h - kh) / stride_h + 1;
-    const int64_t Wo = (W + 2 * (int64_t)pad_w - kw) / stride_w + 1;
-    if (!mul_ok(C, (int64_t)kh * kw, &filt) || !mul_ok(filt, O, &n) || n > lim ||
-        !mul_ok(N * C, H * W, &xs) || xs > lim || !mul_ok(N * O, Ho * Wo, &ys) || ys > lim ||
-        H > (1 << 20) || W > (1 << 20) || C > (1 << 24) || O > (1 << 24) || N > (int64_t(1) << 31) ||
-        kh > 4096 || kw > 4096 || pad_h > 4096 || pad_w > 4096) {
-        set_error("tbn_conv2d_forward: sizes beyond the supported range");
-        return TBN_ERR_UNSUPPORTED;
-    }
-    tbn_status st = check_tiling(n, k, n_alpha);
+    ConvArgs a;
+    const tbn_status st = make_conv_args(x, y, dt, N, C, H, W, O, kh, kw, stride_h, stride_w, pad_h, pad_w, tile, k, alpha, n_alpha,
+                                         flags, stream, &a);
     if (st != TBN_OK) return st;
     if (N == 0) return TBN_OK;
-
-    ConvArgs a{x, y, (int)dt, N, C, H, W, O, Ho, Wo, kh, kw, stride_h, stride_w, pad_h, pad_w,
-               tile, n / k, k, alpha, n_alpha, flags, static_cast<hipStream_t>(stream)};
     drop_stale_error();
-    if (!(flags & TBN_FLAG_FORCE_GENERIC)) {
-        // up to 8 input channels (a network's first layer on colour images): the matrix-core kernel would stage chunks of
-        // 32 channels that are mostly zeros; the direct kernel is faster (3 -> 64 channels, 3x3, 32 x 32, 128 images:
-        // 23 us against 39; 224 x 224, 8 images: 60 against 111; from 12 channels on the matrix cores win: 36 against 48)
-        if (a.C <= 8 && conv_direct_supported(a)) return launch_conv_direct(a);
-        // 1x1 and 3x3: one wave per pixel block (equal or faster on every shape measured, 1.0 - 2.9 times, figures in
-        // tbn_conv_wave.hip); the block kernel keeps the other windows of nine taps and maps one pixel wide
-        if (conv_wave_supported(a)) return launch_conv_wave(a);
-        if (conv_mfma_supported(a)) return launch_conv_mfma(a);
-        // other windows (5x5, 7x7, ...) with a tile of whole filters: 16 distinct filters per workgroup on the vector ALUs
-        // (ResNet's 7x7, stride 2 first layer on 32 images: 2.0 ms with one thread per output element)
-        if (conv_direct_supported(a)) return launch_conv_direct(a);
+    switch (choose_conv(a)) {
+        case ConvKernel::Direct: return launch_conv_direct(a);
+        case ConvKernel::Wave: return launch_conv_wave(a);
+        case ConvKernel::Mfma: return launch_conv_mfma(a);
+        case ConvKernel::Generic: break;
     }
     return launch_conv_generic(a);
 }
+
+const char *tbn_conv2d_forward_kernel(const void *x, const void *y, tbn_dtype dt, int64_t N, int64_t C, int64_t H, int64_t W,
+                                      int64_t O, int32_t kh, int32_t kw, int32_t stride_h, int32_t stride_w, int32_t pad_h,
+                                      int32_t pad_w, int32_t k, int32_t n_alpha, uint32_t flags) {
+    static thread_local char text[96];
+    ConvArgs a;
+    char last[sizeof(g_err)];   // the query leaves tbn_last_error alone
+    std::memcpy(last, g_err, sizeof(g_err));
+    const bool ok = N > 0 && make_conv_args(x, const_cast<void *>(y), dt, N, C, H, W, O, kh, kw, stride_h, stride_w, pad_h, pad_w,
+                                            nullptr, k, nullptr, n_alpha, flags, nullptr, &a) == TBN_OK;
+    std::memcpy(g_err, last, sizeof(g_err));
+    if (!ok) return "";
+    switch (choose_conv(a)) {
+        case ConvKernel::Direct: return "direct";
+        case ConvKernel::Wave: conv_wave_describe(a, text, sizeof(text)); return text;
+        case ConvKernel::Mfma: return "block";
+        case ConvKernel::Generic: break;
+    }
+    return "generic";
+}
+
+int64_t tbn_diag_conv_plan_searches(void) { return conv_wave_searches(); }
 
 }  // extern "C"

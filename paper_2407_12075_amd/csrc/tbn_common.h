@@ -103,6 +103,8 @@ tbn_status launch_conv_mfma(const ConvArgs &a);
 tbn_status launch_conv_tile_ends(const ConvArgs &a);   // repair pass: the channels whose filter holds a tile start, two alphas
 bool conv_wave_supported(const ConvArgs &a);     // 1x1 and 3x3: one wave per block of output pixels and channel slice
 tbn_status launch_conv_wave(const ConvArgs &a);
+int64_t conv_wave_searches();   // plans the calling thread has searched for
+void conv_wave_describe(const ConvArgs &a, char *text, size_t size);
 bool conv_direct_supported(const ConvArgs &a);   // tile of whole filters, any window: vector-ALU kernel, 16 filters per workgroup
 tbn_status launch_conv_direct(const ConvArgs &a);
 

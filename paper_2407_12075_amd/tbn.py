@@ -99,6 +99,10 @@ def lib() -> ctypes.CDLL:
         L.tbn_diag_mfma.argtypes = [_c_i32, _c_i32, _c_vp, _c_vp]
         L.tbn_diag_mfma_fp4.restype = ctypes.c_int
         L.tbn_diag_mfma_fp4.argtypes = [_c_i32, _c_i32, _c_vp, _c_vp]
+        L.tbn_diag_conv_plan_searches.restype = _c_i64
+        L.tbn_diag_conv_plan_searches.argtypes = []
+        L.tbn_conv2d_forward_kernel.restype = ctypes.c_char_p
+        L.tbn_conv2d_forward_kernel.argtypes = [_c_vp, _c_vp, ctypes.c_int, *[_c_i64] * 5, *[_c_i32] * 8, _c_u32]
         global _host
         from . import _tbn_host
         _tbn_host.init(_raise, {name: ctypes.cast(getattr(L, name), _c_vp).value for name in (
@@ -393,6 +397,14 @@ def tbn_conv2d_forward(x: torch.Tensor, tile: torch.Tensor, alpha: torch.Tensor,
     if st != TBN_OK:
         _raise(st)
     return y
+
+
+def tbn_conv2d_forward_kernel(dtype: torch.dtype, N: int, C: int, H: int, W: int, out_channels: int, kh: int, kw: int, k: int,
+                              stride=(1, 1), pad=(0, 0), n_alpha: int = 1, flags: int = 0) -> str:
+    """The kernel tbn_conv2d_forward would launch for these sizes, and its plan (host arithmetic, nothing is launched)."""
+    dt = TBN_F32 if dtype == torch.float32 else TBN_BF16
+    return lib().tbn_conv2d_forward_kernel(None, None, dt, N, C, H, W, out_channels, kh, kw, stride[0], stride[1], pad[0], pad[1],
+                                           k, n_alpha, flags).decode()
 
 
 def tbn_sign_row_words(cin: int) -> int:

@@ -160,3 +160,44 @@ def test_kernel_choice_rejects_what_the_forward_call_rejects(lib):
     assert tbn.tbn_linear_forward_kernel(torch.float32, 0, 8, 8, 2) == ""     # empty batch: nothing is launched
     assert tbn.tbn_linear_forward_kernel(torch.float32, 4, 4, 4, 3) == ""     # n not divisible by k
     assert tbn.tbn_linear_forward_kernel(torch.float32, 4, 4, 4, 2, n_alpha=3) == ""
+
+
+def test_convolution_kernel_choice(lib):
+    import torch
+    from paper_2407_12075_amd import tbn
+    q = tbn.tbn_conv2d_forward_kernel
+    assert q(torch.float32, 128, 3, 32, 32, 64, 3, 3, 4, pad=(1, 1)) == "direct"            # up to 8 channels
+    assert q(torch.float32, 128, 256, 14, 14, 256, 3, 3, 8, pad=(1, 1)).startswith("wave ")
+    assert q(torch.bfloat16, 32, 64, 56, 56, 64, 1, 1, 4).startswith("wave ")
+    assert q(torch.float32, 4, 64, 14, 14, 64, 9, 1, 4, pad=(4, 0)) == "block"              # nine taps, not 3x3
+    assert q(torch.float32, 4, 64, 14, 14, 64, 5, 5, 4, pad=(2, 2)) == "direct"
+    assert q(torch.float32, 4, 64, 14, 14, 64, 3, 3, 4, flags=tbn.TBN_FLAG_FORCE_GENERIC) == "generic"
+    assert q(torch.float32, 4, 64, 14, 14, 64, 3, 3, 5) == ""                               # k does not divide n
+    assert q(torch.float32, 0, 64, 14, 14, 64, 3, 3, 4) == ""
+
+
+def test_convolution_plans_of_a_network_are_kept(lib):
+    """The 1x1 and 3x3 layers of a 50-layer residual network, run in a loop: every plan is searched for once."""
+    import torch
+    from paper_2407_12075_amd import tbn
+    layers, C = [], 64
+    for mid, blocks, size in ((64, 3, 56), (128, 4, 28), (256, 6, 14), (512, 3, 7)):
+        for b in range(blocks):
+            s = 2 if b == 0 and mid > 64 else 1
+            H = size * s
+            layers += [(C, H, mid, 1, 1), (mid, H, mid, 3, s), (mid, size, 4 * mid, 1, 1)]
+            if b == 0:
+                layers.append((C, H, 4 * mid, 1, s))
+            C = 4 * mid
+    assert len(layers) == 52
+
+    def one_pass():
+        before = lib.tbn_diag_conv_plan_searches()
+        for dt in (torch.float32, torch.bfloat16):
+            for (c, h, o, ks, s) in layers:
+                name = tbn.tbn_conv2d_forward_kernel(dt, 32, c, h, h, o, ks, ks, 4, stride=(s, s), pad=(ks // 2, ks // 2), n_alpha=4)
+                assert name.startswith("wave ")
+        return lib.tbn_diag_conv_plan_searches() - before
+
+    assert one_pass() <= 2 * len(set(layers))
+    assert one_pass() == 0
