@@ -2,7 +2,7 @@
 computation runs in the HIP kernels of the library.  PyTorch supplies device memory and the
 stream; tensors must live on the current CUDA (HIP) device and be contiguous.  The plain form of the
 everyday calls is made by the extension module ``_tbn_host`` (csrc/tbn_host.cpp), which answers None
-to every other form; the code of the wrappers then runs.
+to every other form, and need not be there; the code of the wrappers then runs.
 
 There is no CPU fallback: if ``libtbn.so`` is missing the import of a symbol raises.
 """
@@ -10,6 +10,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import warnings
 from typing import Optional, Tuple
 
 import torch
@@ -104,11 +105,15 @@ def lib() -> ctypes.CDLL:
         L.tbn_conv2d_forward_kernel.restype = ctypes.c_char_p
         L.tbn_conv2d_forward_kernel.argtypes = [_c_vp, _c_vp, ctypes.c_int, *[_c_i64] * 5, *[_c_i32] * 8, _c_u32]
         global _host
-        from . import _tbn_host
-        _tbn_host.init(_raise, {name: ctypes.cast(getattr(L, name), _c_vp).value for name in (
-            "tbn_pack_workspace_bytes", "tbn_pack_tile", "tbn_linear_forward", "tbn_conv2d_forward", "tbn_sign_pack",
-            "tbn_linear_coltiled_workspace_bytes", "tbn_linear_coltiled_forward", "tbn_linear_forward_binact")})
-        _lib, _host = L, _tbn_host
+        try:
+            from . import _tbn_host
+            _tbn_host.init(_raise, {name: ctypes.cast(getattr(L, name), _c_vp).value for name in (
+                "tbn_pack_workspace_bytes", "tbn_pack_tile", "tbn_linear_forward", "tbn_conv2d_forward", "tbn_sign_pack",
+                "tbn_linear_coltiled_workspace_bytes", "tbn_linear_coltiled_forward", "tbn_linear_forward_binact")})
+            _host = _tbn_host
+        except ImportError as e:   # not built, or built against another torch: the wrappers serve every call by themselves
+            warnings.warn(f"_tbn_host cannot be loaded ({e}): calls take about 6 us more host time each")
+        _lib = L
     return _lib
 
 

@@ -201,3 +201,28 @@ def test_convolution_plans_of_a_network_are_kept(lib):
 
     assert one_pass() <= 2 * len(set(layers))
     assert one_pass() == 0
+
+
+def test_binding_works_without_the_extension_module(lib, monkeypatch):
+    import sys
+    import paper_2407_12075_amd as package
+    import torch
+    from paper_2407_12075_amd import tbn
+    monkeypatch.setitem(sys.modules, "paper_2407_12075_amd._tbn_host", None)   # importing it raises ImportError
+    monkeypatch.delattr(package, "_tbn_host", raising=False)
+    monkeypatch.setattr(tbn, "_lib", None)
+    monkeypatch.setattr(tbn, "_host", None)
+    with pytest.warns(UserWarning, match="_tbn_host"):
+        assert tbn.lib() is not None
+    assert tbn._host is None
+    assert tbn.tbn_linear_forward_kernel(torch.bfloat16, 8192, 4096, 4096, 8) == "block"
+    with pytest.raises(ValueError):
+        tbn.tbn_pack_tile(torch.zeros(16), 2)
+
+
+def test_library_is_built_where_the_extension_module_cannot_be(tmp_path, monkeypatch, capsys):
+    from paper_2407_12075_amd import build
+    monkeypatch.setattr(build, "HOST", str(tmp_path / "_tbn_host.so"))
+    monkeypatch.setenv("PATH", str(tmp_path))   # no g++
+    build._compile_host()
+    assert not os.path.exists(build.HOST) and "not built" in capsys.readouterr().err
