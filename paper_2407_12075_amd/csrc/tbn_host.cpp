@@ -3,13 +3,14 @@
 // A call through ctypes costs the host 9 - 11 us (reading a dozen tensor attributes, allocating the output, looking up
 // the stream, marshalling), more than the small kernels take.  Here the same checks, allocations and library calls are made on
 // the C++ tensors.  Only the plain form of a call is taken: exact torch tensors that pass every check, integer arguments,
-// outputs and workspaces left to the call, the current stream, no dispatch mode.  Anything else returns None and nothing has
+// outputs and workspaces left to the call, the current stream, no dispatch or function mode.  Anything else returns None and nothing has
 // happened: the Python wrapper then runs its own code, which also words every error.
 // One token through a 4096 x 4096 bfloat16 layer, calls in a row: 11.3 us through ctypes, 4.2 here (the kernel takes 3.5).
 #include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
 #include <pybind11/pybind11.h>
 #include <ATen/ATen.h>
+#include <ATen/PythonTorchFunctionTLS.h>
 #include <c10/core/impl/LocalDispatchKeySet.h>
 #include <c10/core/impl/TorchDispatchModeTLS.h>
 #include <c10/hip/HIPStream.h>
@@ -56,7 +57,8 @@ bool activations(const at::Tensor &x, tbn_dtype &dt) {
 }
 
 bool ordinary_context() {
-    return !c10::impl::dispatch_mode_enabled() && !c10::impl::tls_local_dispatch_key_set().included_.has(c10::DispatchKey::FuncTorchDynamicLayerFrontMode);
+    return !c10::impl::dispatch_mode_enabled() && !at::impl::torch_function_mode_enabled() &&
+           !c10::impl::tls_local_dispatch_key_set().included_.has(c10::DispatchKey::FuncTorchDynamicLayerFrontMode);
 }
 
 bool integer(PyObject *o, int64_t lo, int64_t hi, int64_t &v) {

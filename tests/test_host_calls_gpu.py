@@ -81,6 +81,18 @@ def test_other_forms_are_left_to_the_wrapper(tbn):
 
     with Mode():
         assert h.linear_forward(x, tile, alpha, 64, 4, 0) is None
+    from torch.overrides import TorchFunctionMode
+    seen = []
+
+    class FunctionMode(TorchFunctionMode):
+        def __torch_function__(self, func, types, args=(), kwargs=None):
+            seen.append(func)
+            return func(*args, **(kwargs or {}))
+
+    with FunctionMode():
+        assert h.linear_forward(x, tile, alpha, 64, 4, 0) is None
+        tbn.tbn_linear_forward(x, tile, alpha, 64, 4)
+    assert torch.empty in seen   # the wrapper's own allocation of the output
     torch.cuda.synchronize()
 
 
