@@ -12,9 +12,11 @@
 //   * float32 activations are split exactly into three bf16 terms in registers;
 //   * the 8 partial 16 x 16 blocks are summed through LDS in a fixed order and all replicas are
 //     written by the whole workgroup with lanes running along the columns of Y.
-// Columns whose weight row contains a tile start (two alphas) are recomputed afterwards (tbn_linear_direct.hip).
+// Columns whose weight row contains a tile start (two alphas) are recomputed afterwards, by the repair form of the direct
+// kernel (tbn_linear_direct.hip) or, where its waves would wait for one chunk after the other, by this kernel in its FIXUP
+// form: the "columns" of a workgroup are then the up to k - 1 such rows, the sums before and from the tile start are kept in
+// two accumulators (operand elements of the other part are zeroed), and X is read once for all of them.
 #include "tbn_common.h"
-
 
 namespace tbn {
 
@@ -32,6 +34,7 @@ struct SkinnyParams {
     int64_t M, in, out, p, n_words, U;
     int32_t n_alpha;
     int aligned;
+    int32_t k;   // tile repeats (FIXUP form: tile starts 1 .. k - 1 are looked at)
 };
 
 union Frag {
@@ -100,14 +103,27 @@ template <> struct SkTraits<float> {
     }
 };
 
-template <typename XT, bool RELU>
+// Row of the weight that contains the start of tile number c (FIXUP form), j_e = the start's position in it
+// (0: the tile starts with the row, nothing to repair).
+__device__ __forceinline__ void tile_start_row(const SkinnyParams &P, int64_t c, int64_t &o_c, uint32_t &j_e) {
+    const uint64_t prod = static_cast<uint64_t>(c) * static_cast<uint64_t>(P.p);   // < 2^47
+    uint64_t q = static_cast<uint64_t>(static_cast<double>(prod) / static_cast<double>(P.in));
+    int64_t r = static_cast<int64_t>(prod - q * static_cast<uint64_t>(P.in));
+    if (r < 0) { r += P.in; --q; }
+    if (r >= P.in) { r -= P.in; ++q; }
+    o_c = static_cast<int64_t>(q);
+    j_e = static_cast<uint32_t>(r);
+}
+
+template <typename XT, bool RELU, bool FIXUP>
 __global__ __launch_bounds__(kThreads) void linear_skinny_kernel(const XT *__restrict__ x, XT *__restrict__ y,
                                                                  const uint32_t *__restrict__ tile,
                                                                  const float *__restrict__ alpha, SkinnyParams P) {
     using T = SkTraits<XT>;
     constexpr int NP = T::planes;
-    __shared__ float part[kWaves][16][17];         // partial blocks [wave][batch row][column], padded
-    __shared__ float zfin[16][17];
+    constexpr int NA = FIXUP ? 2 : 1;              // accumulators: FIXUP keeps the two alpha segments apart
+    __shared__ float part[NA][kWaves][16][17];     // partial blocks [wave][batch row][column], padded
+    __shared__ float zfin[NA][16][17];
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int ln = lane & 15, lg = lane >> 4;
@@ -121,7 +137,16 @@ __global__ __launch_bounds__(kThreads) void linear_skinny_kernel(const XT *__res
     const uint32_t p32 = static_cast<uint32_t>(P.p), in32 = static_cast<uint32_t>(P.in);
     // start bit of the lane's weight row in the tile
     uint32_t off;
-    {   // (u_l * in) mod p, the product is below 2^53
+    uint32_t j_e = 0;   // FIXUP: elements before j_e belong to the first alpha segment
+    if (FIXUP) {
+        // the lane's row is the one that holds the start of tile u0 + ln + 1; its first weight is
+        // tile bit p - j_e (lanes past k - 1, or whose tile starts with a row, compute a result nobody reads)
+        int64_t c = u0 + ln + 1;
+        c = c < P.k ? c : 1;
+        int64_t o_c;
+        tile_start_row(P, c, o_c, j_e);
+        off = j_e == 0 ? 0u : p32 - j_e;
+    } else {   // (u_l * in) mod p, the product is below 2^53
         const uint64_t prod = static_cast<uint64_t>(u_l) * in32;
         const uint64_t q = static_cast<uint64_t>(static_cast<double>(prod) / static_cast<double>(p32));
         int64_t r = static_cast<int64_t>(prod - q * p32);
@@ -144,15 +169,19 @@ __global__ __launch_bounds__(kThreads) void linear_skinny_kernel(const XT *__res
         return alpha[(P.n_alpha == 1) ? 0 : (P.aligned ? t : (o * P.in) / P.p)];
     };
     float al_first[4] = {0.f, 0.f, 0.f, 0.f};
+    if (!FIXUP) {
 #pragma unroll
-    for (int j = 0; j < 4; ++j) al_first[j] = alpha_of((tid >> 8) + j * kStep);
+        for (int j = 0; j < 4; ++j) al_first[j] = alpha_of((tid >> 8) + j * kStep);
+    }
 
     // operand constants kept in registers (two literals do not fit one instruction)
     uint32_t sign_mask = 0x80008000u, one_bits = 0x3f803f80u;
     asm volatile("" : "+v"(sign_mask), "+v"(one_bits));
     const uint32_t byte_sel = 0x01010101u * static_cast<uint32_t>(lg);   // byte lg of a window word
 
-    f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
+    f32x4_t acc[NA];
+#pragma unroll
+    for (int h = 0; h < NA; ++h) acc[h] = f32x4_t{0.f, 0.f, 0.f, 0.f};
     const int n_blocks = static_cast<int>((P.in + kKBlock - 1) / kKBlock);
 
     // K index of (block b, step s, lane group lg, element i) is 128*b + 32*s + 8*lg + i: per load
@@ -225,8 +254,27 @@ __global__ __launch_bounds__(kThreads) void linear_skinny_kernel(const XT *__res
             Frag bw, a[NP];
             expand_byte(bw, ~win[s], byte_sel, sign_mask, one_bits);
             T::planes_of(src[s], a);
+            if (FIXUP) {
+                // elements kb + 32 s + i with i < na lie before the tile start: keep them in the first
+                // operand, the others in the second (0.0 elsewhere)
+                const int32_t na = static_cast<int32_t>(j_e) - static_cast<int32_t>(kb + 32u * s);
+                Frag bw2;
 #pragma unroll
-            for (int pl = 0; pl < NP; ++pl) acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[pl].v, bw.v, acc, 0, 0, 0);
+                for (int v = 0; v < 4; ++v) {
+                    const uint32_t keep = (na > 2 * v ? 0x0000ffffu : 0u) | (na > 2 * v + 1 ? 0xffff0000u : 0u);
+                    bw2.u[v] = bw.u[v] & ~keep;
+                    bw.u[v] &= keep;
+                }
+#pragma unroll
+                for (int pl = 0; pl < NP; ++pl) {
+                    acc[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[pl].v, bw.v, acc[0], 0, 0, 0);
+                    acc[NA - 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[pl].v, bw2.v, acc[NA - 1], 0, 0, 0);
+                }
+            } else {
+#pragma unroll
+                for (int pl = 0; pl < NP; ++pl)
+                    acc[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[pl].v, bw.v, acc[0], 0, 0, 0);
+            }
         }
     };
 
@@ -247,20 +295,50 @@ __global__ __launch_bounds__(kThreads) void linear_skinny_kernel(const XT *__res
 
     // accumulator layout: lane holds column ln, batch rows 4*lg + i
 #pragma unroll
-    for (int i = 0; i < 4; ++i) part[wave][4 * lg + i][ln] = acc[i];
+    for (int h = 0; h < NA; ++h)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) part[h][wave][4 * lg + i][ln] = acc[h][i];
     __syncthreads();
     if (tid < 256) {
         const int mm = tid >> 4, uu = tid & 15;
-        float s = 0.f;
 #pragma unroll
-        for (int w = 0; w < kWaves; ++w) s += part[w][mm][uu];
-        zfin[mm][uu] = s;
+        for (int h = 0; h < NA; ++h) {
+            float s = 0.f;
+#pragma unroll
+            for (int w = 0; w < kWaves; ++w) s += part[h][w][mm][uu];
+            zfin[h][mm][uu] = s;
+        }
     }
     __syncthreads();
 
+    if (FIXUP) {   // one column per (tile start, batch row): y = alpha[c-1] * (sum before) + alpha[c] * (sum from)
+        const int64_t c = u0 + u + 1;
+        if (tid < 256 && c < P.k && m0 + m < P.M) {
+            int64_t o_c;
+            uint32_t je;
+            tile_start_row(P, c, o_c, je);
+            if (je != 0 && o_c < P.out) {
+                float z[2] = {zfin[0][m][u], zfin[NA - 1][m][u]};
+                if (__builtin_expect(z[0] != z[0] || z[1] != z[1], 0)) {   // 0 x infinity in a masked operand, or a NaN: by elements
+                    const XT *row = x + (m0 + m) * P.in;
+                    z[0] = z[1] = 0.f;
+                    for (int64_t j = 0; j < P.in; ++j) {
+                        const int64_t bit = (j < je ? P.p : 0) + j - je;
+                        const float e = ElemIO<XT>::load(row + j), w = ((tile[bit >> 5] >> (bit & 31)) & 1u) ? e : -e;
+                        if (j < je) z[0] += w; else z[1] += w;
+                    }
+                }
+                float v = alpha[c - 1] * z[0] + alpha[c] * z[1];
+                if (RELU) v = fmaxf(v, 0.f);
+                ElemIO<XT>::store(y + (m0 + m) * P.out + o_c, v);
+            }
+        }
+        return;
+    }
+
     // epilogue: thread -> (replica t, batch row m, column u); u runs fastest over the lanes
     if (u0 + u < P.U && m0 + m < P.M) {
-        const float z = zfin[m][u];
+        const float z = zfin[0][m][u];
         XT *yrow = y + (m0 + m) * P.out;
         for (int64_t t0 = tid >> 8; t0 < reps; t0 += 4 * kStep) {
             float al[4];   // fetched up front: one memory round trip per four replicas
@@ -280,17 +358,17 @@ __global__ __launch_bounds__(kThreads) void linear_skinny_kernel(const XT *__res
     }
 }
 
-template <typename XT, bool RELU> void launch_sk(const LinearArgs &a, const SkinnyParams &P, dim3 grid) {
-    hipLaunchKernelGGL((linear_skinny_kernel<XT, RELU>), grid, dim3(kThreads), 0, a.stream,
+template <typename XT, bool RELU, bool FIXUP> void launch_sk(const LinearArgs &a, const SkinnyParams &P, dim3 grid) {
+    hipLaunchKernelGGL((linear_skinny_kernel<XT, RELU, FIXUP>), grid, dim3(kThreads), 0, a.stream,
                        static_cast<const XT *>(a.x), static_cast<XT *>(a.y), a.tile, a.alpha, P);
 }
 
-void launch_sk_any(const LinearArgs &a, const SkinnyParams &P, dim3 grid) {
+template <bool FIXUP> void launch_sk_any(const LinearArgs &a, const SkinnyParams &P, dim3 grid) {
     const bool relu = (a.flags & TBN_FLAG_RELU) != 0;
     if (a.dt == TBN_F32) {
-        if (relu) launch_sk<float, true>(a, P, grid); else launch_sk<float, false>(a, P, grid);
+        if (relu) launch_sk<float, true, FIXUP>(a, P, grid); else launch_sk<float, false, FIXUP>(a, P, grid);
     } else {
-        if (relu) launch_sk<uint16_t, true>(a, P, grid); else launch_sk<uint16_t, false>(a, P, grid);
+        if (relu) launch_sk<uint16_t, true, FIXUP>(a, P, grid); else launch_sk<uint16_t, false, FIXUP>(a, P, grid);
     }
 }
 
@@ -309,6 +387,7 @@ SkinnyParams make_params(const LinearArgs &a) {
     P.U = unique_rows(a.out, a.in, a.p);
     P.n_alpha = a.n_alpha;
     P.aligned = (a.p % a.in == 0) ? 1 : 0;
+    P.k = a.k;
     return P;
 }
 
@@ -330,8 +409,26 @@ bool linear_skinny_supported(const LinearArgs &a) {
     return ((U + 15) / 16) * ((a.M + 15) / 16) <= (a.dt == TBN_F32 ? 2048 : 512);
 }
 
+// Which repair pass takes the columns whose weight row holds a tile start.  Both read X once per 16 tile starts; the FIXUP
+// form keeps 256 (float32) or 512 elements of a row in flight per wave, the direct kernel's 64 or 128, which its larger row
+// tiles make up for once there are more than a workgroup of FIXUP's per CU, or rows so short that a wave has one chunk.
+// Microseconds by which the direct kernel's pass is slower, means over some 3800 shapes: float32, up to 256 workgroups, rows
+// of 256 - 512 / 512 - 800 / 800 - 1400 / 1400 - 2000 / 2000 - 3600 elements: -0.1 / 0.3 / 0.6 / 1.5 / 2.4; more workgroups:
+// -3.6 / -4.8 / -4.7 / -5.5 / -8; bfloat16, up to 8 rows: -0.3 / -0.2 / 0 / 0.3 / 0.5, from 9: -0.7 / -1 / -0.9 / -0.6 / -0.3.
+static bool fixup_preferred(const LinearArgs &a) {
+    if (!shape_ok(a) || a.n_alpha != a.k) return false;
+    if (a.dt == TBN_BF16) return a.M <= 8 && a.in > 1400;
+    return a.in >= 512 && ((a.M + 15) / 16) * ((int64_t(a.k) - 1 + 15) / 16) <= 256;
+}
+
 // Recomputes the columns whose weight row holds a tile start (two alphas), at any batch size.
 tbn_status launch_linear_tile_ends(const LinearArgs &a) {
+    if (a.k < 2 || a.M == 0) return TBN_OK;
+    if (fixup_preferred(a)) {
+        const SkinnyParams P = make_params(a);
+        launch_sk_any<true>(a, P, dim3(static_cast<unsigned>((int64_t(a.k) - 1 + 15) / 16), static_cast<unsigned>((a.M + 15) / 16)));
+        return check_launch("tbn_linear_forward (tile-start repair kernel)");
+    }
     return linear_direct_ends_supported(a) ? launch_linear_direct_ends(a) : launch_linear_rows_fixup(a);
 }
 
@@ -342,7 +439,7 @@ tbn_status launch_linear_skinny(const LinearArgs &a) {
         set_error("tbn_linear_forward: too many distinct rows for one launch");
         return TBN_ERR_UNSUPPORTED;
     }
-    launch_sk_any(a, P, dim3(static_cast<unsigned>(gx), static_cast<unsigned>(gy)));
+    launch_sk_any<false>(a, P, dim3(static_cast<unsigned>(gx), static_cast<unsigned>(gy)));
     tbn_status st = check_launch("tbn_linear_forward (small-batch kernel)");
     if (st != TBN_OK) return st;
     // columns whose weight row straddles a tile end need two alphas

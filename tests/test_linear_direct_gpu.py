@@ -127,7 +127,7 @@ def test_small_activations_keep_all_their_bits(tbn, M, cin, cout, k, ends):
 
 
 # tile starts inside rows, an alpha per tile: M, in, out, k
-ENDS = [(33, 264, 520, 11), (1000, 3000, 3072, 9), (64, 1000, 312, 16), (17, 1016, 123, 24), (40, 136, 45, 6), (700, 520, 1000, 64)]
+ENDS = [(33, 264, 520, 11), (1000, 3000, 3072, 9), (8, 1448, 330, 16), (9, 1448, 330, 16), (3, 512, 300, 16), (300, 776, 250, 20), (4100, 520, 250, 16), (64, 1000, 312, 16), (17, 1016, 123, 24), (40, 136, 45, 6), (700, 520, 1000, 64)]
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
@@ -155,14 +155,14 @@ def test_tile_starts_inside_rows_exact(tbn, M, cin, cout, k, dtype):
 
 
 @pytest.mark.parametrize("dt", [torch.float32, torch.bfloat16])
-def test_tile_starts_inside_rows_infinities_and_nan(tbn, dt):
+@pytest.mark.parametrize("M,cin,cout,k", [(70, 264, 520, 11), (8, 1448, 330, 16), (55, 776, 250, 20)])
+def test_tile_starts_inside_rows_infinities_and_nan(tbn, M, cin, cout, k, dt):
     """An infinity on one side of a tile start leaves the other side's sum alone."""
-    M, cin, cout, k = 70, 264, 520, 11
     g = torch.Generator().manual_seed(3)
     tile, alpha = tbn.tbn_pack_tile(torch.randn(cin * cout, generator=g).cuda(), k, k)
     x = torch.randn(M, cin, generator=g)
-    x[5, 7], x[6, cin - 1], x[33, 100], x[40, 9] = float("inf"), float("-inf"), float("inf"), float("nan")
-    x[50, 0], x[50, cin - 1] = float("inf"), float("inf")
+    x[5, 7], x[6, cin - 1], x[M // 2, 100], x[1, 9] = float("inf"), float("-inf"), float("inf"), float("nan")
+    x[M - 1, 0], x[M - 1, cin - 1] = float("inf"), float("inf")
     x = x.to(dt).cuda()
     starts = torch.arange(1, k, device="cuda") * (cin * cout // k)
     cols = (starts // cin)[starts % cin != 0]
