@@ -490,6 +490,63 @@ __global__ __launch_bounds__((64 * waves_of(NFT)), (waves_of(NFT) == 8 ? 4 : 2))
         const int yo = q / cols, xo = q - yo * cols;
         out_pix[j] = yo * static_cast<int>(P.Wo) + xo;
     }
+    // A NaN in a sum may come from an infinity: minus its own leading term in the split of a float32, or times a masked
+    // weight (FIX).  Such sums are formed again by elements, so that the staging need not look for infinities.
+    bool bad = false;
+#pragma unroll
+    for (int ft = 0; ft < NFT; ++ft)
+#pragma unroll
+        for (int j = 0; j < kTilesPerWave; ++j)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) bad = bad || (out_live[j] && acc[ft][j][i] != acc[ft][j][i]);
+    if ((NP == 3 || FIX) && __builtin_expect(__any(bad), 0)) {
+#pragma unroll 1
+        for (int s = 0; s < NFT * kTilesPerWave * 4; ++s) {
+            const int fs = s / (kTilesPerWave * 4), js = (s / 4) % kTilesPerWave, is = s % 4;
+            float z = 0.f;
+            int pix = 0;
+            bool live = false;
+#pragma unroll
+            for (int ft = 0; ft < NFT; ++ft)
+#pragma unroll
+                for (int j = 0; j < kTilesPerWave; ++j)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        if (ft == fs && j == js && i == is) { z = acc[ft][j][i]; pix = out_pix[j]; live = out_live[j]; }
+            int64_t u = u0 + fs * 16 + 4 * lg + is;   // filter, or half of a pair
+            int64_t first = 0, last = P.F, start;     // its weights, and the tile bit of weight 0
+            if constexpr (FIX) {
+                const int64_t c = u / 2 + 1, f = c * P.p, o = f / P.F, keep = f - o * P.F;
+                live = live && c < P.n_alpha && o < P.O;
+                if (u & 1) first = keep; else last = keep;
+                start = u & 1 ? -keep : P.p - keep;
+            } else {
+                live = live && u < P.R;
+                start = live ? u * P.F % P.p : 0;
+            }
+            if (live && z != z) {
+                const int yo = pix / static_cast<int>(P.Wo), xo = pix - yo * static_cast<int>(P.Wo);
+                z = 0.f;
+                for (int64_t w = first; w < last; ++w) {
+                    const int64_t ch = w / T;
+                    const int tap = static_cast<int>(w - ch * T);
+                    const int64_t iy = int64_t(row0 + yo) * P.sh - P.ph + tap / P.kw, ix = int64_t(col0 + xo) * P.sw - P.pw + tap % P.kw;
+                    if (iy < 0 || iy >= P.H || ix < 0 || ix >= P.W) continue;
+                    int64_t bit = start + w;
+                    if (bit >= P.p) bit -= P.p;
+                    const float e = ElemIO<XT>::load(x_img + ch * plane_hw + iy * P.W + ix);
+                    z += ((tile[bit >> 5] >> (bit & 31)) & 1u) ? e : -e;
+                }
+            }
+#pragma unroll
+            for (int ft = 0; ft < NFT; ++ft)
+#pragma unroll
+                for (int j = 0; j < kTilesPerWave; ++j)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        if (ft == fs && j == js && i == is) acc[ft][j][i] = z;
+        }
+    }
     if constexpr (FIX) {
         // registers i = 0, 1 and i = 2, 3 of a filter tile are the two halves of a pair
 #pragma unroll

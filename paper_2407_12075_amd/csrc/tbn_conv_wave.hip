@@ -253,28 +253,16 @@ __global__ __launch_bounds__(64 * kMaxWaves, (wave_bound(sizeof(XT) == 4, MT, T,
                 } else {   // exact three-term split: the top 8 significand bits, the next 8, the rest
                     unsigned char *dst = region + loff[it][0] + g * kGroup;
                     u32x4_t v0, v1, v2;
-                    float top = 0.f;
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
                         const float a = __uint_as_float(s[2 * e]), b = __uint_as_float(s[2 * e + 1]);
                         const float a1 = a - __uint_as_float(s[2 * e] & 0xffff0000u), b1 = b - __uint_as_float(s[2 * e + 1] & 0xffff0000u);
                         const float a2 = a1 - __uint_as_float(__float_as_uint(a1) & 0xffff0000u);
                         const float b2 = b1 - __uint_as_float(__float_as_uint(b1) & 0xffff0000u);
-                        top = fmaxf(top, fmaxf(fabsf(a), fabsf(b)));
                         if (ALL) low_bits |= __float_as_uint(a2) | __float_as_uint(b2);
                         v0[e] = pack_hi16(s[2 * e], s[2 * e + 1]);
                         v1[e] = pack_hi16(__float_as_uint(a1), __float_as_uint(b1));
                         v2[e] = pack_hi16(__float_as_uint(a2), __float_as_uint(b2));
-                    }
-                    if (__builtin_expect(__any(top == __builtin_inff()), 0)) {   // all in the first term (infinity minus itself is a NaN)
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) {
-                            uint32_t keep = 0xffffffffu;
-                            if (fabsf(__uint_as_float(s[2 * e])) == __builtin_inff()) keep &= 0xffff0000u;
-                            if (fabsf(__uint_as_float(s[2 * e + 1])) == __builtin_inff()) keep &= 0x0000ffffu;
-                            v1[e] &= keep;
-                            v2[e] &= keep;
-                        }
                     }
                     *reinterpret_cast<u32x4_t *>(dst) = v0;
                     *reinterpret_cast<u32x4_t *>(dst + kPlane) = v1;
@@ -497,28 +485,44 @@ __global__ __launch_bounds__(64 * kMaxWaves, (wave_bound(sizeof(XT) == 4, MT, T,
             for (int s = 1; s < KS; ++s)
 #pragma unroll
                 for (int e = 0; e < PG; ++e) v[e] += red[s * (MT * PW) + f * PW + px + e];
-            if (ALL && __builtin_expect(small, 0)) {   // those bits, one output at a time
-#pragma unroll 1
-                for (int e = 0; e < PG; ++e) {
-                    const int oy = P.d_cols.div(px + e), ox = px + e - oy * P.cols;
-                    if (px + e >= PX || ox >= cols) continue;
-                    const int iy0 = (row0 + oy) * P.sh - P.ph, ix0 = (col0 + ox) * P.sw - P.pw;
-                    int64_t bit = u * P.F % P.p;
-                    float sum = 0.f;
-                    for (int c = 0; c < P.C; ++c)
-                        for (int tap = 0; tap < T; ++tap) {
-                            const int iy = iy0 + tap / 3, ix = ix0 + tap % 3;
-                            if (iy >= 0 && iy < P.H && ix >= 0 && ix < P.W) {
-                                const float a = *reinterpret_cast<const float *>(x_img + c * hwb + (int64_t(iy) * P.W + ix) * 4);
-                                const float a1 = a - __uint_as_float(__float_as_uint(a) & 0xffff0000u);
-                                const float a2 = a1 - __uint_as_float(__float_as_uint(a1) & 0xffff0000u);
-                                const float r = fabsf(a) < 1.f ? a2 - __uint_as_float(__float_as_uint(a2) & 0xffff0000u) : 0.f;
-                                sum += ((tile[bit >> 5] >> (bit & 31)) & 1u) ? r : -r;
-                            }
-                            if (++bit == P.p) bit = 0;
-                        }
+            // A NaN may come from an infinity minus its own leading term: such sums are formed again by elements, so that the
+            // staging need not look for infinities.  ALL: the bits left out of small activations, likewise.
+            if constexpr (NP == 3) {
+                bool again = ALL && small;
 #pragma unroll
-                    for (int i = 0; i < PG; ++i) v[i] += i == e ? sum : 0.f;
+                for (int e = 0; e < PG; ++e) again = again || v[e] != v[e];
+                if (__builtin_expect(__any(again), 0)) {
+                    int fo = f, po = px;
+                    asm volatile("" : "+v"(fo), "+v"(po));   // nothing of this is formed ahead of the loops
+#pragma unroll 1
+                    for (int e = 0; e < PG; ++e) {
+                        float z = v[0];
+#pragma unroll
+                        for (int i = 1; i < PG; ++i) z = i == e ? v[i] : z;
+                        const bool full = z != z;
+                        const int oy = P.d_cols.div(po + e), ox = po + e - oy * P.cols;
+                        if (po + e >= PX || ox >= cols || !(full || (ALL && small))) continue;
+                        const int iy0 = (row0 + oy) * P.sh - P.ph, ix0 = (col0 + ox) * P.sw - P.pw;
+                        int64_t bit = (u0 + ft * MT + fo) * P.F % P.p;
+                        float sum = 0.f;
+                        for (int c = 0; c < P.C; ++c)
+                            for (int tap = 0; tap < T; ++tap) {
+                                const int iy = iy0 + tap / 3, ix = ix0 + tap % 3;
+                                if (iy >= 0 && iy < P.H && ix >= 0 && ix < P.W) {
+                                    float a = *reinterpret_cast<const float *>(x_img + c * hwb + (int64_t(iy) * P.W + ix) * 4);
+                                    if (!full) {
+                                        const float a1 = a - __uint_as_float(__float_as_uint(a) & 0xffff0000u);
+                                        const float a2 = a1 - __uint_as_float(__float_as_uint(a1) & 0xffff0000u);
+                                        a = fabsf(a) < 1.f ? a2 - __uint_as_float(__float_as_uint(a2) & 0xffff0000u) : 0.f;
+                                    }
+                                    sum += ((tile[bit >> 5] >> (bit & 31)) & 1u) ? a : -a;
+                                }
+                                if (++bit == P.p) bit = 0;
+                            }
+#pragma unroll
+                        for (int i = 0; i < PG; ++i)
+                            if (i == e) v[i] = full ? sum : v[i] + sum;
+                    }
                 }
             }
             const int yo = whole_rows ? 0 : P.d_cols.div(px), xo = px - yo * P.cols;

@@ -70,6 +70,24 @@ SPECIAL = [(2, 64, 14, 14, 64, 3, 1, 1, 4), (1, 40, 9, 65, 66, 3, 1, 1, 2), (2, 
            (1, 4200, 6, 6, 32, 3, 1, 1, 2)]   # the last one: more channels than tbn_conv_mfma.hip takes
 
 
+@pytest.mark.parametrize("dt", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("N,C,H,W,O,kh,kw,k", [(1, 32, 10, 12, 40, 3, 3, 9), (2, 64, 9, 12, 45, 1, 1, 8), (2, 32, 14, 9, 34, 9, 1, 8),
+                                              (3, 64, 20, 20, 64, 9, 1, 4), (1, 64, 9, 30, 33, 1, 9, 4)])
+def test_conv_block_kernel_infinities_and_nan(tbn, N, C, H, W, O, kh, kw, k, dt):
+    """The block kernel (windows of nine taps in a row) and the pass over channels whose filter contains a tile start."""
+    g = torch.Generator().manual_seed(C + O)
+    x = torch.randn(N, C, H, W, generator=g)
+    x[0, 3, 0, 1], x[0, C - 1, H - 1, W - 1], x[N - 1, 9, 4, 4] = float("inf"), float("-inf"), float("nan")
+    x = x.to(dt).cuda()
+    tile, alpha = tbn.tbn_pack_tile(torch.randn(O * C * kh * kw, generator=g).cuda(), k, k)
+    pad = ((kh - 1) // 2, (kw - 1) // 2)
+    y = tbn.tbn_conv2d_forward(x, tile, alpha, O, kh, kw, k, pad=pad).float()
+    ref = tbn.tbn_conv2d_forward(x, tile, alpha, O, kh, kw, k, pad=pad, flags=tbn.TBN_FLAG_FORCE_GENERIC).float()
+    assert torch.isinf(ref).any() and torch.isnan(ref).any()
+    assert torch.equal(torch.isnan(y), torch.isnan(ref))
+    assert torch.equal(torch.isinf(y), torch.isinf(ref)) and torch.equal(y[torch.isinf(y)], ref[torch.isinf(ref)])
+
+
 @pytest.mark.parametrize("N,C,H,W,O,ks,stride,pad,k", SPECIAL)
 def test_conv_wave_infinities_and_nan(tbn, N, C, H, W, O, ks, stride, pad, k):
     """An infinity or a NaN reaches the outputs whose window holds it, as in the one-thread-per-output kernel."""
