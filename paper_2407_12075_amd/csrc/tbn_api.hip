@@ -221,9 +221,9 @@ static ConvKernel choose_conv(const ConvArgs &a) {
         // 32 channels that are mostly zeros; the direct kernel is faster (3 -> 64 channels, 3x3, 32 x 32, 128 images:
         // 23 us against 39; 224 x 224, 8 images: 60 against 111; from 12 channels on the matrix cores win: 36 against 48)
         if (a.C <= 8 && conv_direct_supported(a)) return ConvKernel::Direct;
-        // 1x1 and 3x3: one wave per pixel block (equal or faster on every shape measured, 1.0 - 2.9 times, figures in
-        // tbn_conv_wave.hip); the block kernel keeps the other windows of nine taps and maps one pixel wide
-        if (conv_wave_supported(a)) return ConvKernel::Wave;
+        // 1x1 and 3x3: one wave per pixel block; the block kernel keeps the small grids it is faster on (the rule and its
+        // figures are in tbn_conv_wave.hip), the other windows of nine taps and maps one pixel wide
+        if (conv_wave_preferred(a)) return ConvKernel::Wave;
         if (conv_mfma_supported(a)) return ConvKernel::Mfma;
         // other windows (5x5, 7x7, ...) with a tile of whole filters: 16 distinct filters per workgroup on the vector ALUs
         // (ResNet's 7x7, stride 2 first layer on 32 images: 2.0 ms with one thread per output element)

@@ -101,7 +101,7 @@ tbn_status launch_conv_generic_tile_ends(const ConvArgs &a);   // only the chann
 bool conv_mfma_supported(const ConvArgs &a);
 tbn_status launch_conv_mfma(const ConvArgs &a);
 tbn_status launch_conv_tile_ends(const ConvArgs &a);   // repair pass: the channels whose filter holds a tile start, two alphas
-bool conv_wave_supported(const ConvArgs &a);     // 1x1 and 3x3: one wave per block of output pixels and channel slice
+bool conv_wave_preferred(const ConvArgs &a);     // 1x1 and 3x3: one wave per block of output pixels and channel slice
 tbn_status launch_conv_wave(const ConvArgs &a);
 int64_t conv_wave_searches();   // plans the calling thread has searched for
 void conv_wave_describe(const ConvArgs &a, char *text, size_t size);

@@ -570,6 +570,7 @@ struct WavePlan {
     size_t lds;
     int64_t total_waves;
     bool all_bits;
+    bool preferred;   // over tbn_conv_mfma.hip
 };
 
 WavePlan plan_wave_for(const ConvArgs &a, int nft) {
@@ -672,18 +673,55 @@ WavePlan plan_wave_for(const ConvArgs &a, int nft) {
     return pl;
 }
 
+// A 1x1 layer that neither strides nor pads takes the planes as single rows: full pixel blocks whatever the width, and
+// blocks that start at multiples of 64 pixels (bfloat16, k = 2, by image rows / as one row / in tbn_conv_mfma.hip: 65 x 256 x
+// 55 x 55 -> 64 59.2 / 42.1 / 42.3 us, 14 x 512 x 53 x 53 -> 128 36.0 / 26.9 / 23.7).
+ConvArgs as_rows(ConvArgs a) {
+    if (a.kh == 1 && a.kw == 1 && a.sh == 1 && a.sw == 1 && a.ph == 0 && a.pw == 0 && a.H * a.W < (1 << 24)) {
+        a.W = a.Wo = a.H * a.W;
+        a.H = a.Ho = 1;
+    }
+    return a;
+}
+
+// Where tbn_conv_mfma.hip is the faster kernel: small grids whose epilogue is long, since the 64 threads of a channel slice
+// write all replicas of their filters where its workgroups have 256 or 512 (float32, 2 x 16 x 93 x 93 -> 512, 1x1, stride 2,
+// k = 8: 24.1 us here, 9.6 there).  Below 1024 waves (one per SIMD) both are estimated, in microseconds: here a constant, the
+// chunks per slice (16 channels, 32 where a tile has 16 filters), the 16-byte stores per thread and the waves / 1024; there a
+// constant, the chunks of 32 channels, the replicas and the pixel blocks / 256.  Least squares over 9169 random layers
+// of common sizes, 10 - 15 % off on the average, so the other kernel has to be estimated 9 % faster.  Of 16550 layers (also
+// larger ones) 1543 were more than 4 % slower here than there with this kernel always; by this rule 663 are, and 67 are
+// slower there than here (margin 3 %: 550 and 207).
+bool prefer_wave(const ConvArgs &a, const WavePlan &pl) {
+    struct Model { double wave[4], block[4]; };
+    static const Model models[2][2] = {   // [bfloat16][3x3]
+        {{{3.27, 1.53, 0.23, 1.30}, {3.45, 0.61, 0.36, 2.35}}, {{2.89, 4.08, 0.23, 1.84}, {4.97, 1.35, 0.37, 3.26}}},
+        {{{3.82, 1.18, 0.25, 0.87}, {3.46, 0.47, 0.43, 2.08}}, {{2.93, 2.39, 0.27, 1.72}, {5.14, 0.90, 0.41, 2.86}}}};
+    if (pl.total_waves >= 1024) return true;
+    const Model &m = models[a.dt == TBN_F32 ? 0 : 1][a.kh == 3 ? 1 : 0];
+    const double waves = static_cast<double>(pl.total_waves), slices = 1 << pl.ks_log2;
+    const int64_t R = unique_rows(a.O, a.C * a.kh * a.kw, a.p);
+    const double reps = static_cast<double>(a.O) / static_cast<double>(R);
+    const double stores = static_cast<double>(std::min<int64_t>(R, pl.mt * pl.nft)) * reps * pl.pw / (a.dt == TBN_F32 ? 4 : 8) / (64 * slices);
+    const double here = m.wave[0] + m.wave[1] * pl.n_chunks / slices + m.wave[2] * stores + m.wave[3] * waves / 1024;
+    const double there = m.block[0] + m.block[1] * static_cast<double>((a.C + 31) / 32) + m.block[2] * reps + m.block[3] * waves / slices / 256;
+    return 0.91 * here <= there;
+}
+
 // Filters per wave: as many tiles of 32 as there are (at most four: the staged input then feeds four times the MFMAs), but
 // fewer where the grid would leave SIMDs empty.
-WavePlan search_wave(const ConvArgs &a) {
+WavePlan search_wave(const ConvArgs &layer) {
+    const ConvArgs a = as_rows(layer);
     if (a.kh < 1 || a.kh != a.kw || a.p < 1) return WavePlan{};
     const int64_t R = unique_rows(a.O, a.C * a.kh * a.kw, a.p);
     WavePlan pl{};
     // Float32 layers that are too large for tbn_conv_mfma.hip (more channels than its LDS holds filters for, maps wider than
     // its blocks) were float32 FMAs before and keep every bit of their activations; the others never had those below 2^-133.
-    const bool all_bits = a.dt == TBN_F32 && !conv_mfma_supported(a);
+    const bool other = conv_mfma_supported(layer), all_bits = a.dt == TBN_F32 && !other;
     for (int nft = R <= 32 ? 1 : R <= 64 || (a.dt == TBN_F32 && a.kh == 3) ? 2 : 4; nft >= 1; nft /= 2) {
         pl = plan_wave_for(a, nft);
         pl.all_bits = all_bits;
+        pl.preferred = pl.ok && (!other || prefer_wave(a, pl));
         if (pl.ok && (a.kh == 1 ? pl.total_waves >> pl.ks_log2 >= 2048 : pl.total_waves >= 1024)) break;   // (1x1: rather more filter blocks than channel slices)
     }
     return pl;
@@ -751,18 +789,19 @@ tbn_status launch_wave_shape(const ConvArgs &a, const WaveConvParams &P, const W
 
 }  // namespace
 
-bool conv_wave_supported(const ConvArgs &a) { return plan_wave(a).ok; }
+bool conv_wave_preferred(const ConvArgs &a) { return plan_wave(a).preferred; }
 
 int64_t conv_wave_searches() { return n_searches; }
 
 void conv_wave_describe(const ConvArgs &a, char *text, size_t size) {
     const WavePlan pl = plan_wave(a);
-    std::snprintf(text, size, "wave filters=%dx%d pixels=%d patch=%d slices=%d%s", pl.nft, pl.mt, pl.pw, pl.cap, 1 << pl.ks_log2,
-                  pl.all_bits ? " all-bits" : "");
+    std::snprintf(text, size, "wave filters=%dx%d pixels=%d patch=%d slices=%d waves=%lld%s", pl.nft, pl.mt, pl.pw, pl.cap,
+                  1 << pl.ks_log2, static_cast<long long>(pl.total_waves), pl.all_bits ? " all-bits" : "");
 }
 
-tbn_status launch_conv_wave(const ConvArgs &a) {
-    const WavePlan pl = plan_wave(a);
+tbn_status launch_conv_wave(const ConvArgs &layer) {
+    const WavePlan pl = plan_wave(layer);
+    const ConvArgs a = as_rows(layer);
     if (!pl.ok) {
         set_error("tbn_conv2d_forward: shape not supported by the kernel with one wave per pixel block");
         return TBN_ERR_UNSUPPORTED;
@@ -802,7 +841,7 @@ tbn_status launch_conv_wave(const ConvArgs &a) {
         st = pl.nft == 1 ? launch_wave_shape<uint16_t, 32, 1>(a, P, pl, grid)
              : pl.nft == 2 ? launch_wave_shape<uint16_t, 32, 2>(a, P, pl, grid) : launch_wave_shape<uint16_t, 32, 4>(a, P, pl, grid);
     if (st != TBN_OK || a.n_alpha == 1 || P.aligned) return st;
-    return launch_conv_tile_ends(a);   // channels whose filter contains a tile start: two alphas
+    return launch_conv_tile_ends(layer);   // channels whose filter contains a tile start: two alphas
 }
 
 }  // namespace tbn
