@@ -65,6 +65,70 @@ def test_conv_wave_blocks_exact(tbn, N, C, H, W, O, ks, stride, pad, k, n_alpha,
     assert bad.size == 0, f"{len(bad)} of {got.size} outputs differ, first at {tuple(bad[0])}: {got[tuple(bad[0])]} against {ref[tuple(bad[0])]}"
 
 
+# Every instance of the kernel: dtype, N, C, H, W, O, window, stride, k, n_alpha, the plan (filter tiles per wave x filters per
+# tile, pixels per wave, pixels of a patch in LDS; "all-bits": the instance for layers the block kernel does not take)
+PLANS = [
+    ("bf16", 1, 41, 4, 4, 18, 1, 2, 2, 2, "1x16 pixels=64 patch=129"),
+    ("bf16", 1, 64, 4, 4, 17, 1, 2, 1, 1, "1x32 pixels=64 patch=129"),
+    ("bf16", 64, 17, 16, 65, 140, 1, 1, 2, 2, "2x32 pixels=64 patch=129"),
+    ("bf16", 96, 16, 46, 46, 130, 1, 2, 1, 1, "4x32 pixels=64 patch=129"),
+    ("bf16", 1, 16, 4, 4, 18, 3, 2, 2, 1, "1x16 pixels=64 patch=128"),
+    ("bf16", 1, 17, 4, 4, 17, 3, 2, 1, 1, "1x32 pixels=64 patch=128"),
+    ("bf16", 1, 16, 9, 9, 9, 3, 2, 1, 1, "1x32 pixels=64 patch=256"),
+    ("bf16", 1, 16, 15, 15, 17, 3, 2, 1, 1, "1x32 pixels=32 patch=256"),
+    ("bf16", 64, 127, 4, 4, 140, 3, 2, 2, 2, "2x32 pixels=64 patch=128"),
+    ("bf16", 64, 128, 9, 9, 70, 3, 2, 1, 1, "2x32 pixels=64 patch=256"),
+    ("bf16", 64, 128, 15, 15, 34, 3, 2, 1, 1, "2x32 pixels=32 patch=256"),
+    ("bf16", 64, 128, 4, 4, 260, 3, 2, 2, 2, "4x32 pixels=64 patch=128"),
+    ("bf16", 64, 127, 9, 9, 130, 3, 2, 1, 1, "4x32 pixels=64 patch=256"),
+    ("bf16", 64, 64, 15, 15, 130, 3, 2, 1, 1, "4x32 pixels=32 patch=256"),
+    ("bf16", 128, 128, 4, 4, 99, 3, 2, 16, 1, "4x32 pixels=64 patch=128"),      # tile ends inside filters
+    ("f32", 1, 64, 4, 4, 18, 1, 2, 2, 2, "1x32 pixels=64 patch=65"),
+    ("f32", 64, 17, 16, 65, 140, 1, 1, 2, 2, "2x32 pixels=64 patch=65"),
+    ("f32", 96, 16, 46, 46, 130, 1, 2, 1, 1, "4x32 pixels=64 patch=65"),
+    ("f32", 1, 64, 4, 4, 18, 3, 2, 2, 2, "1x32 pixels=64 patch=100"),
+    ("f32", 1, 64, 9, 9, 9, 3, 2, 1, 1, "1x32 pixels=64 patch=128"),
+    ("f32", 2, 16, 3, 200, 9, 3, 2, 1, 1, "1x32 pixels=64 patch=192"),
+    ("f32", 64, 17, 14, 14, 9, 3, 2, 1, 1, "1x32 pixels=32 patch=192"),
+    ("f32", 64, 127, 4, 4, 140, 3, 2, 2, 2, "2x32 pixels=64 patch=100"),
+    ("f32", 32, 64, 5, 130, 34, 3, 2, 1, 1, "2x32 pixels=64 patch=128"),
+    ("f32", 64, 16, 5, 130, 70, 3, 2, 1, 1, "2x32 pixels=64 patch=192"),
+    ("f32", 64, 128, 14, 14, 34, 3, 2, 1, 1, "2x32 pixels=32 patch=192"),
+    ("f32", 64, 128, 4, 4, 70, 3, 2, 3, 1, "2x32 pixels=64 patch=100"),       # tile ends inside filters
+    ("f32", 1, 4200, 4, 4, 18, 3, 2, 2, 2, "1x32 pixels=64 patch=100 all-bits"),
+    ("f32", 1, 4200, 9, 9, 9, 3, 2, 1, 1, "1x32 pixels=64 patch=128 all-bits"),
+    ("f32", 1, 16, 2, 4096, 40, 1, 1, 2, 2, "1x32 pixels=64 patch=65 all-bits"),
+]
+
+
+def _plan_matches(name, plan):
+    fields = dict(f.split("=") for f in name.split()[1:] if "=" in f)
+    want = plan.split()
+    return name.startswith("wave ") and fields["filters"] == want[0] and all(f"{k}={fields[k]}" in want for k in ("pixels", "patch")) and \
+        name.endswith("all-bits") == plan.endswith("all-bits")
+
+
+@pytest.mark.parametrize("dtype,N,C,H,W,O,ks,stride,k,n_alpha,plan", PLANS)
+def test_conv_wave_every_instance_exact(tbn, dtype, N, C, H, W, O, ks, stride, k, n_alpha, plan):
+    """Exact arithmetic, against one thread per output.  Float32: integers of 20 bits, which take all three terms of the split, so
+    few of them that no sum leaves 24 bits; bfloat16: integers of 8 bits."""
+    dt = torch.float32 if dtype == "f32" else torch.bfloat16
+    name = tbn.tbn_conv2d_forward_kernel(dt, N, C, H, W, O, ks, ks, k, (stride, stride), (ks // 2, ks // 2), n_alpha)
+    assert _plan_matches(name, plan), name
+    g = torch.Generator(device="cuda").manual_seed(O * C)
+    F, p = C * ks * ks, O * C * ks * ks // k
+    top = 2 ** 19 if dtype == "f32" else 255
+    x = torch.randint(-top, top + 1, (N, C, H, W), generator=g, device="cuda").float()
+    x *= torch.rand(x.shape, generator=g, device="cuda") < (6.0 / F if dtype == "f32" else 0.5)
+    tile = torch.randint(-2 ** 31, 2 ** 31, ((p + 31) // 32,), generator=g, device="cuda", dtype=torch.int64).int()
+    alpha = torch.exp2((torch.arange(n_alpha, device="cuda") % 5 - 2).float())
+    args = (x.to(dt), tile, alpha, O, ks, ks, k)
+    y = tbn.tbn_conv2d_forward(*args, stride=(stride, stride), pad=(ks // 2, ks // 2))
+    ref = tbn.tbn_conv2d_forward(*args, stride=(stride, stride), pad=(ks // 2, ks // 2), flags=tbn.TBN_FLAG_FORCE_GENERIC)
+    assert float(ref.float().abs().max()) < 2 ** 26 and ref.any()
+    assert torch.equal(y, ref)
+
+
 # float32: N, C, H, W, O, window, stride, pad, k
 SPECIAL = [(2, 64, 14, 14, 64, 3, 1, 1, 4), (1, 40, 9, 65, 66, 3, 1, 1, 2), (2, 48, 15, 17, 96, 3, 2, 1, 1), (1, 272, 9, 9, 128, 1, 1, 0, 1),
            (1, 4200, 6, 6, 32, 3, 1, 1, 2)]   # the last one: more channels than tbn_conv_mfma.hip takes
