@@ -483,9 +483,14 @@ __global__ __launch_bounds__(64 * KW) __attribute__((amdgpu_waves_per_eu(2))) vo
         return;
     }
     // y[m, u + t*U] = alpha[t] * Z[m, u]: a thread adds and writes kEP adjacent columns of a row, neighbouring threads
-    // neighbouring columns
-    constexpr int kGroupsPerRow = NT * 32 / kEP;
-    for (int unit = tid; unit < 32 * kGroupsPerRow; unit += 64 * KW) {
+    // neighbouring columns.  bfloat16 leaves threads without such columns (384 of 512 with one column tile): from four replicas
+    // on they share them and each adds the sums anew (17 x 80 -> 2157, k = 16: 9.4 / 5.6 us; with one replica that costs 0.1 us, and
+    // float32, where half the threads have columns, lost 30 % by it).
+    constexpr int kGroupsPerRow = NT * 32 / kEP, kUnits = 32 * kGroupsPerRow;
+    constexpr int kShare = !kF32 && 64 * KW > kUnits ? 64 * KW / kUnits : 1;
+    const int share = kShare > 1 && P.reps >= 4 ? kShare : 1;
+    for (int i = tid; i < kUnits * share; i += 64 * KW) {
+        const int part = kShare > 1 ? i / kUnits : 0, unit = i - part * kUnits;
         const int r = unit / kGroupsPerRow, g = unit - r * kGroupsPerRow;
         const int64_t m = m0 + r;
         const int32_t u = u0 + g * kEP;
@@ -499,9 +504,9 @@ __global__ __launch_bounds__(64 * KW) __attribute__((amdgpu_waves_per_eu(2))) vo
                 const f32x4_t v = *reinterpret_cast<const f32x4_t *>(s_raw + 4096 + w * L::kRegion + t * 4096 + r * 128 + (((g4 + j) ^ (r & 7)) << 4));
                 z[j] = w == 0 ? v : z[j] + v;
             }
-        XT *dst = y + m * P.out + u;
+        XT *dst = y + m * P.out + u + part * P.U;
         const bool whole = u + kEP <= P.U;
-        for (int32_t rep = 0; rep < P.reps; ++rep, dst += P.U) {
+        for (int32_t rep = part; rep < P.reps; rep += share, dst += share * P.U) {
             const float al = alpha[P.n_alpha == 1 ? 0 : rep];
             float v[kEP];
 #pragma unroll
