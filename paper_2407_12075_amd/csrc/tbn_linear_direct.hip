@@ -81,13 +81,12 @@ __device__ __forceinline__ uint32_t pack2(float a, float b) {
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(f, bf16x2_t));   // round to nearest even in hardware
 }
 
-// Truncation split of eight floats into three bf16x8 operands (8 + 8 + 8 significand bits: exact).  An infinity is all in
-// the first term (infinity minus itself would put a NaN in the others); a NaN stays one in the second.  A bfloat16 has no
-// bits below 2^-133: what an activation has there (the low 16 bits of the third term, activations below 2^-110 only) is left
-// out and `lost` set.
+// Truncation split of eight floats into three bf16x8 operands (8 + 8 + 8 significand bits: exact).  A NaN stays one in the
+// second term, and an infinity, minus itself, puts one there: sums that come out as a NaN are formed again by elements in the
+// epilogue.  A bfloat16 has no bits below 2^-133: what an activation has there (the low 16 bits of the third term,
+// activations below 2^-110 only) is left out and `lost` set.
 __device__ __forceinline__ void split8(const float (&x)[8], Frag (&t)[3], bool &lost) {
     uint32_t h[3][8], low = 0u;
-    float top = 0.f;
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
         const uint32_t t0 = __float_as_uint(x[i]) & 0xffff0000u;
@@ -95,15 +94,9 @@ __device__ __forceinline__ void split8(const float (&x)[8], Frag (&t)[3], bool &
         const uint32_t t1 = __float_as_uint(r1) & 0xffff0000u;
         const float r2 = r1 - __uint_as_float(t1);
         h[0][i] = t0; h[1][i] = t1; h[2][i] = __float_as_uint(r2);
-        top = fmaxf(top, fabsf(x[i]));
         low |= h[2][i];
     }
-    if (__builtin_expect(__any(top == __builtin_inff() || (low << 16) != 0u), 0)) {
-        lost = true;
-#pragma unroll
-        for (int i = 0; i < 8; ++i)
-            if (fabsf(x[i]) == __builtin_inff()) h[1][i] = h[2][i] = 0u;
-    }
+    lost = lost || __any((low << 16) != 0u);
 #pragma unroll
     for (int j = 0; j < 3; ++j)
 #pragma unroll
@@ -483,14 +476,17 @@ __global__ __launch_bounds__(64 * KW) __attribute__((amdgpu_waves_per_eu(2))) vo
         return;
     }
     // y[m, u + t*U] = alpha[t] * Z[m, u]: a thread adds and writes kEP adjacent columns of a row, neighbouring threads
-    // neighbouring columns.  bfloat16 leaves threads without such columns (384 of 512 with one column tile): from four replicas
-    // on they share them and each adds the sums anew (17 x 80 -> 2157, k = 16: 9.4 / 5.6 us; with one replica that costs 0.1 us, and
-    // float32, where half the threads have columns, lost 30 % by it).
+    // neighbouring columns.  bfloat16 leaves threads without such columns (384 of 512 with one column tile): they share the
+    // replicas and each adds the sums anew (one column tile and eight waves, 2 / 4 / 8 / 16 replicas: 1.00 / 1.03 / 1.10 / 1.21
+    // times faster, columns in no multiple of 8 1.03 / 1.12 / 1.28 / 1.47 times; 17 x 80 -> 2157, k = 16: 9.4 / 5.6 us).  In
+    // float32, where half the threads have columns, one replica lost 2 % by it and 16 gained 5 %: left alone.
     constexpr int kGroupsPerRow = NT * 32 / kEP, kUnits = 32 * kGroupsPerRow;
     constexpr int kShare = !kF32 && 64 * KW > kUnits ? 64 * KW / kUnits : 1;
-    const int share = kShare > 1 && P.reps >= 4 ? kShare : 1;
+    static_assert(kUnits % 64 == 0, "a wave has one part");
+    const int share = kShare > 1 && P.reps >= 2 ? kShare : 1;
     for (int i = tid; i < kUnits * share; i += 64 * KW) {
-        const int part = kShare > 1 ? i / kUnits : 0, unit = i - part * kUnits;
+        // (the same for a whole wave: alpha comes by scalar loads, a vector load would wait for the stores before it)
+        const int part = kShare > 1 ? __builtin_amdgcn_readfirstlane(i / kUnits) : 0, unit = i - part * kUnits;
         const int r = unit / kGroupsPerRow, g = unit - r * kGroupsPerRow;
         const int64_t m = m0 + r;
         const int32_t u = u0 + g * kEP;
@@ -504,6 +500,32 @@ __global__ __launch_bounds__(64 * KW) __attribute__((amdgpu_waves_per_eu(2))) vo
                 const f32x4_t v = *reinterpret_cast<const f32x4_t *>(s_raw + 4096 + w * L::kRegion + t * 4096 + r * 128 + (((g4 + j) ^ (r & 7)) << 4));
                 z[j] = w == 0 ? v : z[j] + v;
             }
+        if constexpr (kF32) {   // a NaN in a sum may come from an infinity, minus itself in the split: by elements
+            bool again = false;
+#pragma unroll
+            for (int e = 0; e < kEP; ++e) again = again || (u + e < P.U && z[e / 4][e % 4] != z[e / 4][e % 4]);
+            if (__builtin_expect(__any(again), 0)) {
+                int32_t col = u;
+                asm volatile("" : "+v"(col));   // nothing of this is formed ahead
+#pragma unroll 1
+                for (int e = 0; e < kEP; ++e) {
+                    float s = z[0][0];
+#pragma unroll
+                    for (int i = 1; i < kEP; ++i) s = i == e ? z[i / 4][i % 4] : s;
+                    if (col + e >= P.U || s == s) continue;
+                    const XT *row = x + m * P.in;
+                    const int64_t first = int64_t(col + e) * in;
+                    s = 0.f;
+                    for (idx_t j = 0; j < in; ++j) {
+                        const int64_t bit = first + j;
+                        s += ((tile[bit >> 5] >> (bit & 31)) & 1u) ? static_cast<float>(row[j]) : -static_cast<float>(row[j]);
+                    }
+#pragma unroll
+                    for (int i = 0; i < kEP; ++i)
+                        if (i == e) z[i / 4][i % 4] = s;
+                }
+            }
+        }
         XT *dst = y + m * P.out + u + part * P.U;
         const bool whole = u + kEP <= P.U;
         for (int32_t rep = part; rep < P.reps; rep += share, dst += share * P.U) {
