@@ -658,18 +658,22 @@ bool linear_direct_preferred(const LinearArgs &a, DirectOver other) {
         // the tile kernel splits K among waves in whole slices: rows that do not divide leave it one wave per tile (bfloat16
         // 1297 x 3840 -> 64: 23.0 / 8.8; 500 x 512 -> 256: 6.1 / 4.6; 9926 x 512 -> 32: 7.5 / 7.9; float32 817 x 640 -> 476:
         // 15.5 / 8.4); float32 and few tiles, where it takes four column tiles per wave (200 x 4096 -> 512: 23.5 / 15.5;
-        // 600 x 4096 -> 512: 25.1 / 29.4)
-        if (f32 && W <= 256) return true;
-        return linear_tile_k_slices(a) == 1 && W <= 1024 && a.in > kChunkBytes / (f32 ? 4 : 2) && (f32 || a.M <= 4096);
+        // 600 x 4096 -> 512: 25.1 / 29.4), unless there is only one (2867 x 3072 -> 32: 10.6 / 12.4; 3867 x 5632 -> 24: 17.7 /
+        // 21.2)
+        const bool one_slice = linear_tile_k_slices(a) == 1;
+        if (f32 && W <= 256 && (U > 32 || one_slice)) return true;
+        return one_slice && W <= 1024 && a.in > kChunkBytes / (f32 ? 4 : 2) && (f32 || a.M <= 4096);
     }
     if (other == DirectOver::SmallBatch) {
         // more than one workgroup of the small-batch kernel per CU (bfloat16 530 x 2600 -> 190: 12.3 / 8.1; float32
-        // 1000 x 776 -> 250: 20.3 / 6.7); below that rows of whole lines (bfloat16 in = 384 / 768 / 1280 / 5120 at 64 x 512
-        // columns: 4.6 / 4.1, 6.4 / 4.5, 7.6 / 5.3, 13.4 / 9.6, but 8.7 / 8.1 at 4096, left where it was, and in = 888,
-        // 1168: 5.6 / 6.9, 7.1 / 9.7; float32 in = 512 / 1024 / 1536: 5.6 / 5.0, 8.0 / 6.5, 7.7 / 8.1)
+        // 1000 x 776 -> 250: 20.3 / 6.7); below that rows of whole lines (bfloat16 in = 384 / 768 / 1280 at 64 x 512 columns:
+        // 4.6 / 4.1, 6.4 / 4.5, 7.6 / 5.3, but in = 888, 1168: 5.6 / 6.9, 7.1 / 9.7; float32 in = 512 / 1024 / 1536: 5.6 / 5.0,
+        // 8.0 / 6.5, 7.7 / 8.1).  bfloat16 rows of about 4096: a wave of the small-batch kernel has all its blocks of 128 in
+        // flight there and needs a second round from some 4600 on, a wave here takes one chunk after the other (in = 3840 / 3968 /
+        // 4096 / 4224 / 5120 / 6144: 7.9 / 8.4, 7.6 / 8.2, 8.7 / 8.3, 7.9 / 8.4, 13.4 / 9.7, 13.5 / 10.7).
         if (W <= 1024 && ((U + 15) / 16) * ((a.M + 15) / 16) > 256) return true;
         if (U % 8 != 0 || a.in < 384) return false;
-        return f32 ? a.in % 64 == 0 && a.in <= 1280 : a.in % 128 == 0 && a.in % 4096 != 0;
+        return f32 ? a.in % 64 == 0 && a.in <= 1280 : a.in % 128 == 0 && (a.in <= 3584 || a.in >= 4608);
     }
     // short rows in few blocks of the block or the streaming kernel (bfloat16 8961 x 256 -> 96: 8.1 / 5.7; 1289 x 256 -> 848:
     // 6.4 / 5.3; 1810 x 512 -> 528: 8.8 / 5.7; 6395 x 512 -> 168: 9.2 / 6.7; with activations at an odd element, 1226 x 256 ->
@@ -678,8 +682,16 @@ bool linear_direct_preferred(const LinearArgs &a, DirectOver other) {
     // the general kernel's 128 x 128 blocks: few of them (bfloat16 200 x 520 -> 640: 11.1 / 4.6; 12000 x 520 -> 152: 13.0 /
     // 10.6; 2500 x 2504 -> 640: 20.0 / 20.2; 2500 x 1000 -> 1400: 15.9 / 19.4; float32 300 x 200 -> 250: 21.6 / 4.4; 6000 x
     // 2504 -> 640: 75 / 66; 12000 x 520 -> 640: 51 / 50), and columns that it stores one by one (bfloat16 8364 x 376 -> 1076:
-    // 54 / 24; 5338 x 1024 -> 2564: 74 / 60)
-    if (U % 8 != 0) return W <= 16384;
+    // 54 / 24; 5338 x 1024 -> 2564: 74 / 60).  In bfloat16 long rows outweigh that where its blocks fill the CUs (4040 x 7344 ->
+    // 948: 64 / 108): times in microseconds by least squares over 471 shapes with more than 2e6 tile rows W * in; of 36 shapes
+    // that were more than 4 % slower here 8 are left, and 2 of 4218 went the other way.
+    if (U % 8 != 0) {
+        const double rows = 1e-6 * static_cast<double>(W) * static_cast<double>(a.in);
+        if (f32 || rows <= 2) return W <= 16384;
+        const int64_t rounds = (((a.M + 127) / 128) * ((U + 127) / 128) + 255) / 256;
+        const double outputs = 1e-6 * static_cast<double>(a.M) * static_cast<double>(a.out);
+        return W <= 16384 && 8.7 + 3.18 * rows + 0.41 * outputs <= 6.9 + 7.1e-3 * static_cast<double>(rounds) * static_cast<double>(a.in) + 1.93 * outputs;
+    }
     if (f32) return W <= 4096;
     return W <= 1024 || (W <= 2048 && a.in <= 2048);
 }

@@ -308,7 +308,8 @@ tbn_status launch_one(const LinearArgs &a, const ShortParams &P, int lds) {
     return check_launch("tbn_linear_forward (short rows)");
 }
 
-// (the read behind the last row's last chunk ends 112 bytes after its padding)
+// (the read behind the last chunk of a row, whose data is never used: lane half 1 of the last row reads up to 80 bytes past
+// its chunks, 64 past the 16 of its padding)
 int64_t lds_bytes(int64_t in) { return kRows * (((in + 63) / 64) * 128 + 16) + 128; }
 
 // Column ranges per row block: a workgroup costs about 4 us to start and load its rows and 10.6 us per pass over K = 512
@@ -341,7 +342,8 @@ bool linear_short_supported(const LinearArgs &a) {
 // One replica: 8192 x 128 / 256 / 320 / 512 / 576 -> 4096 columns 30 / 20, 37 / 24, 41 / 27, 50 / 40 - 45, 56 / 43;
 // 12638 x 72 -> 824 15.6 / 9.7; 6853 x 448 -> 2616 (share 0.54) 29.4 / 28.2; 2049 x 512 -> 3912 (0.51) 17.4 / 18.4.  Two
 // replicas: 12000 x 200 -> 1400 29.2 / 24.7; 7815 x 576 -> 2584 (0.62) 44 / 40; 13011 x 504 -> 1344 (0.52) 35.6 / 37.0.  With
-// more the stores bind either kernel (8192 x 256 -> 4096, four replicas: 62 / 53 - 64).
+// more the stores bind either kernel: four, 8192 x 128 / 256 / 512 -> 4096 53.4 / 52.4, 62 / 53, 66 / 64; eight, 8192 x 256 ->
+// 4096 109 / 128.  The line is drawn below four, where the one shape that gains 15 % stays with the general kernel.
 bool linear_short_preferred(const LinearArgs &a) {
     if ((a.flags & ~uint32_t(TBN_FLAG_RELU)) || !linear_short_supported(a)) return false;   // flags that steer to another kernel
     const int64_t U = a.p / a.in, reps = a.out / U;
