@@ -5,8 +5,7 @@
 // written as alpha(o) * Z[u] (Eq. 4-5 on the flattened (O, C, kh, kw) weight; the paper's replicated-channel example in
 // Section "CNN Architectures").
 //
-// What bounds these layers is neither the matrix pipe nor memory but the work around them: in the kernel that had all
-// of them before, a workgroup zeroed its patch, transposed the filter bits in LDS (2.8 us), staged the input with 4-byte
+// What bounds these layers is neither the matrix pipe nor memory but the work around them: in the block kernel a workgroup zeroed its patch, transposed the filter bits in LDS (2.8 us), staged the input with 4-byte
 // LDS stores (two elements each, colliding on the banks) behind a barrier per 32 channels, and every wave expanded the
 // filter operands anew for its own 16 pixels.  Here
 //   * a wave owns 64 (or 32) pixels x up to four tiles of MT filters over its own channels: an expanded filter operand
@@ -26,11 +25,12 @@
 //     load between the stores waits for every store before it (1 - 2 us each time).
 //
 // Measured (us per call, this kernel against tbn_conv_mfma.hip; 3x3, N x C x map -> O):
-//   float32   32 x 64 x 56^2 -> 64, k = 4: 23.1 / 37.2    128 x 256 x 14^2 -> 256, k = 8: 23.7 / 27.8
-//             8 x 64 x 112^2 -> 64, k = 4: 23.2 / 36.8    16 x 16 x 100^2 -> 32, k = 4: 16.3 / 46.1
-//             128 x 256 x 14^2 -> 256, k = 3 (256 filters): 148 / 180
-//   bfloat16  32 x 64 x 56^2 -> 64, k = 4: 13.2 / 31.3    128 x 256 x 14^2 -> 256, k = 8: 17.8 / 24.4
-//   1x1       32 x 64 x 56^2 -> 256, k = 4 / 2, float32 / bfloat16: 27.4 / 30.7, 30.2 / 39.0
+//   float32   32 x 64 x 56^2 -> 64, k = 4: 23.0 / 36.9    128 x 256 x 14^2 -> 256, k = 8: 24.6 / 28.1
+//             8 x 64 x 112^2 -> 64, k = 4: 23.3 / 37.0    16 x 16 x 100^2 -> 32, k = 4: 15.0 / 44.6
+//             128 x 256 x 14^2 -> 256, k = 3 (256 filters, one alpha): 101 / 127
+//   bfloat16  32 x 64 x 56^2 -> 64, k = 4: 13.5 / 31.3    128 x 256 x 14^2 -> 256, k = 8: 15.8 / 22.7
+//   1x1       32 x 64 x 56^2 -> 256, k = 4 / 2, float32 / bfloat16: 27.5 / 30.2, 29.6 / 39.1
+// Layers it is slower on go to that kernel (prefer_wave).
 // Stamps (bfloat16 56^2, all waves resident at once): set-up 1.0 us, first loads to LDS 3.7, product 1.3, sums 0.5, stores
 // 2.0: the kernel is bound by its chain of memory latencies (25.7 MB are 5 us at copy rate), float32 at 256 channels by
 // the matrix pipe as well (three planes: 5.8 us).
@@ -53,7 +53,8 @@ typedef uint16_t u16x2_t __attribute__((ext_vector_type(2)));
 
 constexpr int kMaxWaves = 8;
 
-// n / d for 0 <= n < 2^31 by a multiplication (the set-up of a wave divides a dozen times; as instructions of a general
+// n / d for 0 <= n < 2^31 by a multiplication (Granlund and Montgomery, "Division by invariant integers using multiplication",
+// 1994; the set-up of a wave divides a dozen times; as instructions of a general
 // division that was 1 us before the first load)
 struct FastDiv {
     uint32_t mul, shift, d;

@@ -15,15 +15,16 @@
 //     leaves its row and no load is conditional.
 //   * The +-1 operand: 32 or 64 tile bits per lane, column and chunk at any bit position (two or three words and a
 //     funnel shift; the shift never changes), a byte of them through a 256-entry table in LDS.
-//   * float32 activations are split exactly into three bfloat16 terms, every product is exact and the sums are float32.
+//   * float32 activations are split into three bfloat16 terms, every product is exact and the sums are float32; what the terms
+//     leave out of activations below 2^-110 is added in a second walk, which costs 1 % where there is nothing to add.
 //   * The waves leave their sums in LDS as rows of 32 columns; all threads of the workgroup add them in wave order (the
 //     result does not depend on timing) and store four (float32) or eight (bfloat16) columns of a row at once.
 //
 // Microseconds per call (graph replays), before (a batch row and 16 columns per thread on the vector ALUs) / now:
 // float32 8192 x 196 -> 384, k = 4: 32.9 / 7.8; 12608 x 197 -> 96, k = 4: 27.6 / 5.7; 8192 x 1199 -> 1024, k = 2:
 // 330 / 41; bfloat16 8192 x 2050 -> 1026, k = 2: 490 / 44; 16 x 4095 -> 4096, k = 8: 275 / 13; 8192 x 4096 -> 4096,
-// k = 8 with activations at an odd element: 1077 / 72.  Its relative error in float32 against 64-bit sums at the first of
-// these: 2.5e-7 / 5.6e-8.
+// k = 8 with activations at an odd element: 1077 / 72.  Its relative error in float32 against 64-bit sums: 2.5e-7 / 5.6e-8
+// at the first of these, 5.6e-8 at in = 1199; the leading terms have one float32 sum per wave, so that it grows with the steps.
 #include "tbn_common.h"
 
 #include <type_traits>
