@@ -155,7 +155,7 @@ tbn_status tbn_linear_forward(const void *x, void *y, tbn_dtype dt, int64_t M, i
  *   x, y : the pointers the forward call would get (any address space; only their alignment is looked at; NULL
  *          counts as aligned).
  * Returns a static string, one of "decode", "small-batch", "tile", "stream", "block", "general", "rows", "direct",
- * "short-rows", "generic"; "" on sizes tbn_linear_forward would reject.  The choice also depends on the current device's number
+ * "short-rows", "window", "generic"; "" on sizes tbn_linear_forward would reject.  The choice also depends on the current device's number
  * of CUs (256 is assumed where there is no device).  A help for tests and for reading a profile; a caller never
  * needs it.
  */

@@ -58,7 +58,7 @@ static tbn_status check_tiling(int64_t n, int32_t k, int32_t n_alpha) {
 
 // The kernel family that serves a fully-connected call (host arithmetic only: shapes, alignment of the pointers, the
 // number of CUs of the current device).
-enum class LinearKernel { Decode, Tile, Skinny, Stream, Block, Mfma, Rows, Direct, Short, Generic };
+enum class LinearKernel { Decode, Tile, Skinny, Stream, Block, Mfma, Rows, Direct, Short, Window, Generic };
 
 static LinearKernel choose_linear(const LinearArgs &a) {
     if (!(a.flags & TBN_FLAG_FORCE_GENERIC)) {
@@ -94,7 +94,10 @@ static LinearKernel choose_linear(const LinearArgs &a) {
             // 1024 distinct columns 57 us against 84, 8192 x 4096 -> 8192 distinct columns 1379 against 1672)
             if (a.dt == TBN_F32 && linear_tile_supported(a)) return LinearKernel::Tile;
         }
-        if (linear_mfma_supported(a)) return linear_direct_preferred(a, DirectOver::General) ? LinearKernel::Direct : LinearKernel::Mfma;
+        if (linear_mfma_supported(a)) {
+            if (linear_direct_preferred(a, DirectOver::General)) return LinearKernel::Direct;
+            return linear_window_preferred(a) ? LinearKernel::Window : LinearKernel::Mfma;
+        }
         if (linear_rows_supported(a)) return LinearKernel::Rows;
         // tile of whole rows, row lengths and alignments that none of the kernels above takes
         if (linear_direct_supported(a)) return LinearKernel::Direct;
@@ -113,6 +116,7 @@ static const char *linear_kernel_name(LinearKernel kn) {
         case LinearKernel::Rows: return "rows";
         case LinearKernel::Direct: return "direct";
         case LinearKernel::Short: return "short-rows";
+        case LinearKernel::Window: return "window";
         case LinearKernel::Generic: return "generic";
     }
     return "generic";
@@ -130,6 +134,7 @@ static tbn_status dispatch_linear(const LinearArgs &a) {
         case LinearKernel::Rows: return launch_linear_rows(a);
         case LinearKernel::Direct: return launch_linear_direct(a);
         case LinearKernel::Short: return launch_linear_short(a);
+        case LinearKernel::Window: return launch_linear_window(a);
         case LinearKernel::Generic: break;
     }
     return launch_linear_generic(a);

@@ -42,6 +42,12 @@
 //     sums, the store waves take them over).  8192 x 4096 -> 16384, k = 2 / 4 / 8 / 16: 410 / 211 / 117 / 86 us
 //     against 410 / 216 / 127 / 97 with the stores after each loop; 32768 x 4096 -> 4096, k = 8: 137 against 152.
 //     What stays exposed is the stores of a workgroup's last block.
+//   * Rows of any length in multiples of 8 and tiles that end inside rows (WIN = true): the tile bits of a chunk begin at any
+//     position, so the words that hold them come to LDS as they are and are shifted into the layout above by waves that do
+//     not multiply; the zeros behind a row's end come from a piece of zeros in memory; alphas may differ from column to
+//     column.  The MFMA waves' loop is the same.  8192 x 3000 -> 3072, k = 9 (1024 distinct columns, two blocks per CU): 55 us
+//     against 61 in the general kernel, whose MFMA waves load and fetch windows for themselves; what is left to the aligned
+//     form (8192 x 3072: 47) is the loads of rows that start inside lines, and 7 % for fetching the words.
 //   * Split K (SPLIT = true, for grids that would leave most CUs idle and callers that bring a workspace):
 //     the K loop of a block is dealt to S workgroups; each writes its float32 partial sums of the 128 x 128
 //     block to the workspace, [split][M][U], and a second kernel adds the S partial sums of every output in
@@ -79,6 +85,11 @@ constexpr int kTableOff = 0;             // 256 entries of 16 bytes
 constexpr int kRingOff = 4096;
 constexpr int kTileOff = kRingOff + kNB * kSlotBytes;
 constexpr int kLdsBytes = kTileOff + kTileSlots * kTileSlotBytes;
+// WIN: the words of three chunks as they come from memory, in the layout of the tile chunks; the alphas
+constexpr int kRawSlots = 3;
+constexpr int kRawOff = kLdsBytes;
+constexpr int kAlphaOff = kRawOff + kRawSlots * kTileSlotBytes;
+constexpr int kMaxWinAlphas = (160 * 1024 - kAlphaOff) / 4;
 constexpr int kXchgOff = kRingOff;       // after the main loop the ring holds the partial sums handed over (4 x 16 KiB)
 static_assert(kLdsBytes <= 160 * 1024, "LDS budget of a gfx950 workgroup");
 
@@ -93,6 +104,9 @@ struct BlockParams {
     int32_t splits;       // workgroups that share the K loop of a block (1: none)
     uint32_t vrows;       // tiles_m * splits: (row block, split) pairs
     float *partial;       // split K: [split][M][U] float32 partial sums
+    // WIN
+    int32_t p;            // tile bits
+    int32_t alpha_step;   // tile copies per replica: alpha of column u + t*U is that of column u, t * alpha_step on
 };
 
 // s_waitcnt immediate that waits for the vector-memory counter only (gfx9 encoding: vmcnt in bits
@@ -136,6 +150,22 @@ __device__ __forceinline__ uint32_t pack2(float a, float b) {
 
 template <int V> using Int = std::integral_constant<int, V>;
 
+__device__ __forceinline__ void lds_read4(uint32_t &dst, uint32_t addr) {
+    asm volatile("ds_read_b32 %0, %1" : "=v"(dst) : "v"(addr));
+}
+__device__ __forceinline__ void tie(uint32_t &r) { asm volatile("" : "+v"(r)); }
+
+// x / p and x % p for 0 <= x < 2^43 and 1 <= p < 2^31
+__device__ __forceinline__ uint32_t divide(uint64_t x, uint32_t p, uint32_t &rest) {
+    uint64_t q = static_cast<uint64_t>(static_cast<double>(x) / static_cast<double>(p));
+    int64_t r = static_cast<int64_t>(x - q * p);
+    if (r < 0) { --q; r += p; }
+    if (r >= static_cast<int64_t>(p)) { ++q; r -= p; }
+    rest = static_cast<uint32_t>(r);
+    return static_cast<uint32_t>(q);
+}
+__device__ __align__(16) const uint32_t kZeroPiece[4] = {0u, 0u, 0u, 0u};   // what lies behind the end of a row
+
 // 16-byte store to a scalar base plus a 32-bit lane offset (NT: non-temporal)
 template <bool NT>
 __device__ __forceinline__ void global_store16(unsigned char *base, uint32_t off, const u32x4_t &v) {
@@ -168,7 +198,10 @@ __device__ __forceinline__ void block_coords(const BlockParams &P, uint32_t bid,
 // waves 4 and 5 load, waves 6 and 7 write the replicas of the block before.  The
 // first rounds of the next block start in the ring slot behind the current block's last round, and the hand-over uses
 // the slots of the last two rounds.
-template <bool RELU, bool SPLIT, bool PERSIST>
+// WIN (any row length in multiples of 8, tile starts anywhere): the loads of the last rounds take zeros for what lies behind
+// a row's end; the load waves fetch the tile bits of a chunk into registers two rounds ahead, shift them into place and
+// write them to the chunk's slot, so that the MFMA waves see aligned chunks; alphas come from LDS, column by column.
+template <bool RELU, bool SPLIT, bool PERSIST, bool WIN>
 __global__ __launch_bounds__(512, 1) void linear_block_bf16_kernel(const uint16_t *__restrict__ x,
                                                                                      uint16_t *__restrict__ y,
                                                                                      const uint32_t *__restrict__ tile,
@@ -217,7 +250,7 @@ __global__ __launch_bounds__(512, 1) void linear_block_bf16_kernel(const uint16_
     const unsigned char *x_blk[NQ] = {};
     const unsigned char *tile_bytes = nullptr;
     uint32_t a_off[NQ][8];
-    uint32_t t_off[NQ];
+    uint32_t t_off[NQ];   // WIN: tile position of the lane's piece in the next chunk to fetch
     auto set_block = [&](uint32_t b) __attribute__((always_inline)) {
         uint32_t tile_m, tile_n;
         block_coords(P, b, tile_m, tile_n);
@@ -247,13 +280,20 @@ __global__ __launch_bounds__(512, 1) void linear_block_bf16_kernel(const uint16_
             const int S = 64 * lq + lane, rho = S & 127, l = rho & 31;
             int32_t u = n0 + (rho & 64) + 16 * (l >> 3) + 8 * ((l >> 2) & 1) + 4 * ((rho >> 5) & 1) + (l & 3);
             u = u < P.U ? u : P.U - 1;   // columns past U repeat the last one; they are never written
-            t_off[q] = static_cast<uint32_t>(u) * (static_cast<uint32_t>(P.in) >> 3) + static_cast<uint32_t>((S >> 7) * 16);
+            if constexpr (WIN) {
+                divide(uint64_t(static_cast<uint32_t>(u)) * static_cast<uint32_t>(P.in), static_cast<uint32_t>(P.p), t_off[q]);
+                t_off[q] += static_cast<uint32_t>((S >> 7) * 128);
+                if (t_off[q] >= static_cast<uint32_t>(P.p)) t_off[q] -= static_cast<uint32_t>(P.p);
+            } else {
+                t_off[q] = static_cast<uint32_t>(u) * (static_cast<uint32_t>(P.in) >> 3) + static_cast<uint32_t>((S >> 7) * 16);
+            }
         }
     };
     set_block(bid);
     // issue order per round, which the wait counts rely on: eight activation wave-loads per quarter, then (even
     // rounds) a quarter's share of the tile chunk of this round and the next
-    auto issue_x = [&](auto q_c, auto j_c, int32_t round_, int32_t phase) {
+    // tail: part of the round lies behind the rows' ends (WIN)
+    auto issue_x = [&](auto q_c, auto j_c, auto tail_c, int32_t round_, int32_t phase) __attribute__((always_inline)) {
         constexpr int Q = decltype(q_c)::value, J = decltype(j_c)::value;
         const int lq = first_q + Q;
         unsigned char *const ring_q = lds_raw + kRingOff + (lq >> 1) * 16384 + (lq & 1) * 8192;
@@ -261,7 +301,73 @@ __global__ __launch_bounds__(512, 1) void linear_block_bf16_kernel(const uint16_
         asm volatile("" : "+s"(src));   // one scalar base, the lane offset stays a 32-bit register
         uint32_t off = a_off[Q][J];
         asm volatile("" : "+v"(off));
-        wave_load<(J & 3)>(src, off, ring_q + ((round_ + phase) & (kNB - 1)) * kSlotBytes + (J >> 2) * 4096);
+        unsigned char *dst = ring_q + ((round_ + phase) & (kNB - 1)) * kSlotBytes + (J >> 2) * 4096;
+        if constexpr (decltype(tail_c)::value) {   // in % 8 == 0: a piece lies inside the row or outside
+            const int piece = (lane & 7) ^ ((4 * J + (lane >> 4)) & 7);
+            const bool inside = round_ * 128 + 64 * (lq >> 1) + 8 * piece < P.in;
+            const unsigned char *from = inside ? src + off : reinterpret_cast<const unsigned char *>(kZeroPiece) - (J & 3) * 1024;
+            __builtin_amdgcn_global_load_lds(from, dst, 16, (J & 3) * 1024, 0);
+        } else {
+            wave_load<(J & 3)>(src, off, dst);
+        }
+    };
+    // WIN: the chunk of the tile that round_ (even) and the next take.  fetch_tile brings the four words that a piece's 128 bits
+    // begin in to LDS as they are (by registers the compiler would wait for every load in flight), put_tile, later, shifts
+    // them into place; its fifth word is the first of the row's next piece, so that the chunk behind has to be there too.
+    auto fetch_tile = [&](int32_t round_) __attribute__((always_inline)) {
+        const uint32_t last = ((static_cast<uint32_t>(P.p) + 31u) >> 5) - 4u;
+        unsigned char *const raw = lds_raw + kRawOff + ((round_ >> 1) % kRawSlots) * kTileSlotBytes;
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) {
+            const uint32_t w = t_off[q] >> 5;
+            __builtin_amdgcn_global_load_lds(tile + (w < last ? w : last), raw + (first_q + q) * 1024, 16, 0, 0);
+            t_off[q] += 256u;
+            if (t_off[q] >= static_cast<uint32_t>(P.p)) t_off[q] -= static_cast<uint32_t>(P.p);
+        }
+    };
+    uint32_t t_put[NQ];   // the position of the lane's piece in the next chunk to put in place
+    auto start_tile = [&]() __attribute__((always_inline)) {   // of a block's first chunk
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) t_put[q] = t_off[q];
+    };
+    auto put_tile = [&](int32_t round_) __attribute__((always_inline)) {
+        const uint32_t bits = static_cast<uint32_t>(P.p);
+        const uint32_t raw = static_cast<uint32_t>(kRawOff + ((round_ >> 1) % kRawSlots) * kTileSlotBytes);
+        const uint32_t raw_next = static_cast<uint32_t>(kRawOff + (((round_ >> 1) + 1) % kRawSlots) * kTileSlotBytes);
+        u32x4_t lo[NQ];
+        uint32_t hi[NQ];
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) {
+            const uint32_t S = static_cast<uint32_t>(64 * (first_q + q) + lane);
+            lds_read16<0>(lo[q], raw + S * 16u);
+            lds_read4(hi[q], (S < 128u ? raw : raw_next) + (S ^ 128u) * 16u);
+        }
+        lds_wait<0>();
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) {
+            tie(lo[q]);
+            tie(hi[q]);
+            const uint32_t pos = t_put[q], word[5] = {lo[q][0], lo[q][1], lo[q][2], lo[q][3], hi[q]};
+            u32x4_t v;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) v[i] = __builtin_amdgcn_alignbit(word[i + 1], word[i], pos & 31u);
+            if (pos + 288u > bits) {   // the tile's end lies in this piece or the next: from memory, going on at the tile's first bit
+                const uint32_t last = (bits - 1u) >> 5;
+#pragma unroll 1
+                for (int i = 0; i < 4; ++i) {
+                    uint32_t b = pos + 32u * static_cast<uint32_t>(i);
+                    b = b >= bits ? b - bits : b;
+                    const uint32_t k = b >> 5, left = bits - b;
+                    uint32_t r = __builtin_amdgcn_alignbit(tile[k < last ? k + 1 : last], tile[k], b & 31u);
+                    if (left < 32u) r = (r & ((1u << left) - 1u)) | (tile[0] << left);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) v[e] = e == i ? r : v[e];
+                }
+            }
+            lds_write16<0>(static_cast<uint32_t>(kTileOff + (first_q + q) * 1024 + lane * 16 + ((round_ >> 1) % kTileSlots) * kTileSlotBytes), v);
+            t_put[q] = pos + 256u;
+            if (t_put[q] >= bits) t_put[q] -= bits;
+        }
     };
     auto issue_tile = [&](auto q_c, int32_t round_) {   // round_ is even
         constexpr int Q = decltype(q_c)::value;
@@ -271,9 +377,20 @@ __global__ __launch_bounds__(512, 1) void linear_block_bf16_kernel(const uint16_
         asm volatile("" : "+v"(off));
         __builtin_amdgcn_global_load_lds(src + off, lds_raw + kTileOff + (first_q + Q) * 1024 + ((round_ >> 1) % kTileSlots) * kTileSlotBytes, 16, 0, 0);
     };
-    auto issue_quarter = [&](auto q_c, int32_t round_, int32_t phase) {
-        issue_x(q_c, Int<0>{}, round_, phase); issue_x(q_c, Int<1>{}, round_, phase); issue_x(q_c, Int<2>{}, round_, phase); issue_x(q_c, Int<3>{}, round_, phase);
-        issue_x(q_c, Int<4>{}, round_, phase); issue_x(q_c, Int<5>{}, round_, phase); issue_x(q_c, Int<6>{}, round_, phase); issue_x(q_c, Int<7>{}, round_, phase);
+    auto issue_quarter = [&](auto q_c, int32_t round_, int32_t phase) __attribute__((always_inline)) {
+        auto pieces = [&](auto tail_c) __attribute__((always_inline)) {
+            issue_x(q_c, Int<0>{}, tail_c, round_, phase); issue_x(q_c, Int<1>{}, tail_c, round_, phase);
+            issue_x(q_c, Int<2>{}, tail_c, round_, phase); issue_x(q_c, Int<3>{}, tail_c, round_, phase);
+            issue_x(q_c, Int<4>{}, tail_c, round_, phase); issue_x(q_c, Int<5>{}, tail_c, round_, phase);
+            issue_x(q_c, Int<6>{}, tail_c, round_, phase); issue_x(q_c, Int<7>{}, tail_c, round_, phase);
+        };
+        if constexpr (WIN) {
+            if (round_ * 128 + 128 > P.in) {
+                pieces(std::true_type{});
+                return;
+            }
+        }
+        pieces(std::false_type{});
     };
     auto issue_round = [&](int32_t round_, int32_t phase = 0) {
         issue_quarter(Int<0>{}, round_, phase);
@@ -283,7 +400,38 @@ __global__ __launch_bounds__(512, 1) void linear_block_bf16_kernel(const uint16_
             if constexpr (NQ == 2) issue_tile(Int<1>{}, round_);
         }
     };
-    constexpr int kOdd = 8 * NQ, kEven = 9 * NQ;   // loads of an odd and of an even round per load wave
+    // loads of an odd and of an even round per load wave
+    constexpr int kOdd = 8 * NQ, kEven = 9 * NQ;
+    // WIN: alpha of a lane's eight columns from col on, replica 0
+    auto alpha_index = [&](int32_t col, uint32_t (&idx)[8]) __attribute__((always_inline)) -> bool {   // all the same in the wave?
+        uint32_t rest, i = 0;
+        if (P.n_alpha > 1) i = divide(uint64_t(static_cast<uint32_t>(col)) * static_cast<uint32_t>(P.in), static_cast<uint32_t>(P.p), rest);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            idx[e] = i;
+            if (P.n_alpha > 1) {
+                rest += static_cast<uint32_t>(P.in);
+                if (rest >= static_cast<uint32_t>(P.p)) { rest -= static_cast<uint32_t>(P.p); ++i; }
+            }
+        }
+        return __all(idx[0] == static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(idx[0]))) && idx[0] == idx[7]);
+    };
+    // (columns past U and replicas past `out` may name an alpha that does not exist: the last one is read for them)
+    auto alphas_of = [&](const uint32_t (&idx)[8], int32_t t, float (&al)[8]) __attribute__((always_inline)) {
+        uint32_t raw[8];
+        const uint32_t step = static_cast<uint32_t>(t) * static_cast<uint32_t>(P.alpha_step), last = static_cast<uint32_t>(P.n_alpha) - 1u;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const uint32_t i = idx[e] + step;
+            lds_read4(raw[e], static_cast<uint32_t>(kAlphaOff) + (i < last ? i : last) * 4u);
+        }
+        lds_wait<0>();
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            tie(raw[e]);
+            al[e] = __uint_as_float(raw[e]);
+        }
+    };
 
     // a lane's place in the stores of a replica: eight lanes per row of Y, eight adjacent columns each
     const int g8 = lane & 7, rr = lane >> 3;
@@ -301,12 +449,18 @@ __global__ __launch_bounds__(512, 1) void linear_block_bf16_kernel(const uint16_
     // waves of their own because the vector-memory counter counts loads and stores alike and in issue order: a
     // wave that did both would wait for its stores whenever it waits for a round of loads.
     if (PERSIST && wave >= 6) {
-        float alpha_lanes;
-        {
+        float alpha_lanes = 0.f;
+        if constexpr (!WIN) {
             const int t = P.n_alpha == 1 ? 0 : (lane < P.reps ? lane : P.reps - 1);
             const uint32_t off = static_cast<uint32_t>(t) * 4u;
             asm volatile("global_load_dword %0, %1, %2\n\ts_waitcnt vmcnt(0)" : "=v"(alpha_lanes) : "v"(off), "s"(alpha) : "memory");
         }
+        // WIN: of the eight columns of a lane in either quarter, replica 0; where all columns of a quarter have the same one (and
+        // there are at most 64 replicas), its value for replica t in lane t (a read of LDS per unit cost 4 %)
+        uint32_t alpha_at[2][8];
+        bool alpha_same[2] = {false, false};
+        float alpha_q[2] = {0.f, 0.f};
+        int32_t st_col0 = 0;
         float zr[2][2][4][8];   // [quarter][32-row half][row rr + 8*i][column 8*g8 + e]
         unsigned char *st_base = nullptr;   // &Y[first row of quarter 0][first column of quarter 0], replica 0
         int64_t st_rows = 0;          // rows of the quarters that exist (may be <= 0)
@@ -317,7 +471,24 @@ __global__ __launch_bounds__(512, 1) void linear_block_bf16_kernel(const uint16_
             const int32_t sub = uidx & 3, half = sub & 1, q = sub >> 1;
             int32_t t = (uidx >> 2) + st_rot;
             t = t >= P.reps ? t - P.reps : t;
-            const float al = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, alpha_lanes), t));
+            float al[8];
+            bool exists = true;
+            if constexpr (WIN) {
+                if (q == 0 ? alpha_same[0] : alpha_same[1]) {
+                    const float one = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, q == 0 ? alpha_q[0] : alpha_q[1]), t));
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) al[e] = one;
+                } else if (q == 0) {
+                    alphas_of(alpha_at[0], t, al);
+                } else {
+                    alphas_of(alpha_at[1], t, al);
+                }
+                exists = st_col0 + 64 * q + 8 * g8 + t * P.U < P.out;
+            } else {
+                const float one = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, alpha_lanes), t));
+#pragma unroll
+                for (int e = 0; e < 8; ++e) al[e] = one;
+            }
             unsigned char *dst = st_base + static_cast<uint32_t>(t) * rep_bytes + static_cast<uint32_t>(half) * 4u * out_bytes8 + static_cast<uint32_t>(q) * 128u;
             const int64_t rows_left = st_rows - 32 * half;
             auto emit = [&](auto q_c, auto half_c) __attribute__((always_inline)) {
@@ -327,11 +498,11 @@ __global__ __launch_bounds__(512, 1) void linear_block_bf16_kernel(const uint16_
                     float v[8];
 #pragma unroll
                     for (int e = 0; e < 8; ++e) {
-                        v[e] = al * zr[Q][H][i][e];
+                        v[e] = al[e] * zr[Q][H][i][e];
                         if (RELU) v[e] = fmaxf(v[e], 0.f);
                     }
                     const u32x4_t pk = {pack2(v[0], v[1]), pack2(v[2], v[3]), pack2(v[4], v[5]), pack2(v[6], v[7])};
-                    if (st_col_ok[Q] && rr + 8 * i < rows_left) global_store16<true>(dst, z_lane + static_cast<uint32_t>(i) * out_bytes8, pk);
+                    if (st_col_ok[Q] && exists && rr + 8 * i < rows_left) global_store16<true>(dst, z_lane + static_cast<uint32_t>(i) * out_bytes8, pk);
                 }
             };
             if (sub == 0) emit(Int<0>{}, Int<0>{});
@@ -340,22 +511,41 @@ __global__ __launch_bounds__(512, 1) void linear_block_bf16_kernel(const uint16_
             else emit(Int<1>{}, Int<1>{});
         };
         int32_t ph = 0;
+        if constexpr (WIN) {
+            __builtin_amdgcn_s_barrier();   // the words of the first chunks are there
+            start_tile();
+            put_tile(0);
+            lds_wait<0>();
+        }
         for (;;) {
             const int64_t cur_m0 = m0;
             const int32_t cur_n0 = n0;
+            const uint32_t next = bid + gridDim.x;
+            const bool more = next < n_blocks;
             __builtin_amdgcn_s_barrier();   // the block's first barrier
+            if constexpr (WIN) put_tile(2);
             for (int32_t g = 0; g < n_rounds; ++g) {
+                if constexpr (WIN) lds_wait<0>();
                 __builtin_amdgcn_s_barrier();
+                if constexpr (WIN) {   // the words were there by this barrier; the next one publishes what they become
+                    if ((g & 1) && g + 3 < n_rounds) {
+                        put_tile(g + 3);
+                    } else if (g + 1 == n_rounds && more) {
+                        bid = next;
+                        set_block(bid);
+                        start_tile();
+                        put_tile(0);
+                    }
+                }
                 st_credit += st_total;
                 for (; st_credit >= n_rounds && st_next < st_total; st_credit -= n_rounds) store_unit(st_next++);
             }
             while (st_next < st_total) store_unit(st_next++);
-            const uint32_t next = bid + gridDim.x;
-            const bool more = next < n_blocks;
-            if (more) {
+            if (!WIN && more) {
                 bid = next;
                 set_block(bid);
             }
+            if constexpr (WIN) lds_wait<0>();
             __builtin_amdgcn_s_barrier();   // the two barriers of the hand-over
             __builtin_amdgcn_s_barrier();
             __builtin_amdgcn_s_barrier();   // the sums of the finished block are in the hand-over area
@@ -398,6 +588,16 @@ __global__ __launch_bounds__(512, 1) void linear_block_bf16_kernel(const uint16_
                 st_col_ok[1] = cur_n0 + 64 + 8 * g8 < P.U;
                 st_rot = static_cast<int32_t>(static_cast<uint32_t>(cur_m0 >> 7) % static_cast<uint32_t>(P.reps));
                 st_next = 0;
+                if constexpr (WIN) {
+                    st_col0 = cur_n0;
+#pragma unroll
+                    for (int q = 0; q < 2; ++q) {
+                        alpha_same[q] = alpha_index(cur_n0 + 64 * q + 8 * g8, alpha_at[q]) && P.reps <= 64;
+                        float al[8];
+                        alphas_of(alpha_at[q], lane, al);
+                        alpha_q[q] = al[0];
+                    }
+                }
                 st_total = 4 * P.reps;
                 st_credit = 0;
                 ph = (ph + n_rounds) & 3;
@@ -412,7 +612,107 @@ __global__ __launch_bounds__(512, 1) void linear_block_bf16_kernel(const uint16_
     // =================================================================================================
     // load waves
     // =================================================================================================
-    if (wave >= 4) {
+    if constexpr (WIN) {
+        if (wave >= 4) {
+        // The rounds of the loops below, two at a time (even, odd).  The words of a chunk are fetched behind the activations of
+        // the even round before and put in place two rounds later (PERSIST: by the store waves; two load waves
+        // that did it were late for the barriers: 8192 x 3000 -> 1024 distinct columns 56 us against 54); the barrier after that
+        // publishes them.  Chunks past the end of a row are fetched and never used.
+        auto issue_round_x = [&](int32_t round_, int32_t phase) __attribute__((always_inline)) {
+            issue_quarter(Int<0>{}, round_, phase);
+            if constexpr (NQ == 2) issue_quarter(Int<1>{}, round_, phase);
+        };
+        if constexpr (PERSIST) {
+            fetch_tile(0);
+            fetch_tile(2);
+            fetch_tile(4);
+            issue_round_x(0, 0);
+            issue_round_x(1, 0);
+            __builtin_amdgcn_s_waitcnt(vmcnt_imm(2 * kOdd));
+            __builtin_amdgcn_s_barrier();   // the words are there
+            __builtin_amdgcn_s_waitcnt(vmcnt_imm(kOdd));   // round 0
+            int32_t ph = 0;
+            for (;;) {
+                __builtin_amdgcn_s_barrier();   // meets the MFMA waves' "round 0 readable; the hand-over area is free"
+                issue_round_x(2, ph);
+                fetch_tile(6);
+                const int32_t ph_next = (ph + n_rounds) & 3;
+                const uint32_t next = bid + gridDim.x;
+                const bool more = next < n_blocks;
+                for (int32_t g = 0; g < n_rounds; g += 2) {
+                    if (g + 2 < n_rounds || more) __builtin_amdgcn_s_waitcnt(vmcnt_imm(kEven));
+                    else __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+                    __builtin_amdgcn_s_barrier();
+                    if (g + 3 < n_rounds) issue_round_x(g + 3, ph);
+                    else if (more) issue_round_x(1, ph_next);   // (set_block and round 0 of the next block: below)
+                    if (g + 3 < n_rounds) __builtin_amdgcn_s_waitcnt(vmcnt_imm(kOdd));
+                    else __builtin_amdgcn_s_waitcnt(vmcnt_imm(2 * kOdd));   // the words of the next block's first two chunks, older than its rounds 0 and 1
+                    __builtin_amdgcn_s_barrier();
+                    if (g + 4 < n_rounds) {
+                        issue_round_x(g + 4, ph);
+                        fetch_tile(g + 8);
+                    } else if (more) {
+                        if (g + 4 == n_rounds) {
+                            bid = next;
+                            set_block(bid);
+                            fetch_tile(0);
+                            fetch_tile(2);
+                            issue_round_x(0, ph_next);
+                        } else {
+                            fetch_tile(4);
+                        }
+                    }
+                }
+                __builtin_amdgcn_s_barrier();   // the two barriers of the hand-over
+                __builtin_amdgcn_s_barrier();
+                __builtin_amdgcn_s_barrier();   // the store waves take the sums of the finished block
+                if (!more) return;
+                ph = ph_next;
+                __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));   // rounds 0 and 1 of the next block, the words of its third chunk
+            }
+        } else {
+            start_tile();
+            fetch_tile(0);
+            fetch_tile(2);
+            fetch_tile(4);
+            issue_round_x(0, 0);
+            issue_round_x(1, 0);
+            if (n_rounds > 2) {
+                issue_round_x(2, 0);
+                __builtin_amdgcn_s_waitcnt(vmcnt_imm(3 * kOdd));
+            } else {
+                __builtin_amdgcn_s_waitcnt(vmcnt_imm(2 * kOdd));
+            }
+            __builtin_amdgcn_s_barrier();   // the words are there
+            put_tile(0);
+            if (n_rounds > 2) put_tile(2);
+            fetch_tile(6);
+            if (n_rounds > 2) __builtin_amdgcn_s_waitcnt(vmcnt_imm(kOdd + kEven));
+            else __builtin_amdgcn_s_waitcnt(vmcnt_imm(kEven));
+            lds_wait<0>();
+            __builtin_amdgcn_s_barrier();   // meets the MFMA waves' "table written, round 0 readable"
+            for (int32_t g = 0; g < n_rounds; g += 2) {
+                if (g + 2 < n_rounds) __builtin_amdgcn_s_waitcnt(vmcnt_imm(kEven));
+                else __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+                lds_wait<0>();
+                __builtin_amdgcn_s_barrier();
+                if (g + 3 < n_rounds) {
+                    issue_round_x(g + 3, 0);
+                    __builtin_amdgcn_s_waitcnt(vmcnt_imm(kOdd));
+                }
+                __builtin_amdgcn_s_barrier();
+                if (g + 4 < n_rounds) {
+                    issue_round_x(g + 4, 0);
+                    fetch_tile(g + 8);
+                    put_tile(g + 4);
+                }
+            }
+            __builtin_amdgcn_s_barrier();   // the two barriers of the hand-over
+            __builtin_amdgcn_s_barrier();
+            return;
+        }
+        }
+    } else if (wave >= 4) {
         if constexpr (PERSIST) {
             // One workgroup walks blocks.  The last three rounds of a block load nothing for it, and the two ring slots behind its last round
             // are free by then: the activations of the next block's rounds 0 and 1 are issued there, one round each,
@@ -496,8 +796,13 @@ __global__ __launch_bounds__(512, 1) void linear_block_bf16_kernel(const uint16_
     // =================================================================================================
     // alpha of replica t in lane t (at most 64 replicas), fetched by hand so that the compiler places no wait
     // for it inside the rounds
-    float alpha_lanes;
-    {
+    float alpha_lanes = 0.f;
+    if constexpr (WIN) {
+        for (int32_t i = tid; i < P.n_alpha; i += 256) {
+            const uint32_t v = __float_as_uint(alpha[i]);
+            asm volatile("ds_write_b32 %0, %1" : : "v"(static_cast<uint32_t>(kAlphaOff) + static_cast<uint32_t>(i) * 4u), "v"(v) : "memory");
+        }
+    } else {
         const int t = P.n_alpha == 1 ? 0 : (lane < P.reps ? lane : P.reps - 1);
         const uint32_t off = static_cast<uint32_t>(t) * 4u;
         asm volatile("global_load_dword %0, %1, %2" : "=v"(alpha_lanes) : "v"(off), "s"(alpha));
@@ -619,6 +924,7 @@ __global__ __launch_bounds__(512, 1) void linear_block_bf16_kernel(const uint16_
     };
 
     lds_wait<0>();   // the table
+    if constexpr (WIN) __builtin_amdgcn_s_barrier();   // the load and store waves': the words of the first chunks are there
     for (;;) {   // one block per pass (a single pass unless PERSIST)
 #pragma unroll
     for (int i = 0; i < 4; ++i)
@@ -801,14 +1107,25 @@ __global__ __launch_bounds__(512, 1) void linear_block_bf16_kernel(const uint16_
             continue;
         }
         unsigned char *z_rep = reinterpret_cast<unsigned char *>(y) + (row0 * P.out + n0 + 64 * wn) * 2;
+        uint32_t alpha_at[8];
+        if constexpr (WIN) alpha_index(n0 + 64 * wn + 8 * g8, alpha_at);
         for (int32_t t = 0; t < P.reps; ++t, z_rep += rep_bytes) {
-            const float al = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, alpha_lanes), t));
+            float al[8];
+            bool exists = col_ok;
+            if constexpr (WIN) {
+                alphas_of(alpha_at, t, al);
+                exists = col_ok && n0 + 64 * wn + 8 * g8 + t * P.U < P.out;
+            } else {
+                const float one = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, alpha_lanes), t));
+#pragma unroll
+                for (int e = 0; e < 8; ++e) al[e] = one;
+            }
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 float v[8];
 #pragma unroll
                 for (int e = 0; e < 8; ++e) {
-                    v[e] = al * zr[i][e];
+                    v[e] = al[e] * zr[i][e];
                     if (RELU) v[e] = fmaxf(v[e], 0.f);
                 }
                 const u32x4_t pk = {pack2(v[0], v[1]), pack2(v[2], v[3]), pack2(v[4], v[5]), pack2(v[6], v[7])};
@@ -817,7 +1134,7 @@ __global__ __launch_bounds__(512, 1) void linear_block_bf16_kernel(const uint16_
                 asm volatile("" : "+s"(dst));
                 uint32_t off = z_lane + static_cast<uint32_t>(i) * out_bytes8;
                 asm volatile("" : "+v"(off));   // scalar base + 32-bit lane offset
-                if (col_ok && rr + 8 * i < rows_left) *(global_u32x4_t *)(dst + off) = pk;
+                if (exists && rr + 8 * i < rows_left) *(global_u32x4_t *)(dst + off) = pk;
             }
         }
     }
@@ -942,7 +1259,7 @@ tbn_status launch_linear_split(const LinearArgs &a, int splits, void *workspace)
     P.partial = static_cast<float *>(workspace);
     const int64_t wgs = int64_t(P.vrows) * P.tiles_n;
     typedef void (*kernel_t)(const uint16_t *, uint16_t *, const uint32_t *, const float *, BlockParams);
-    static const kernel_t kernel = &linear_block_bf16_kernel<false, true, false>;
+    static const kernel_t kernel = &linear_block_bf16_kernel<false, true, false, false>;
     static const tbn_status attr = set_lds_limit_once(reinterpret_cast<const void *>(kernel), kLdsBytes);
     if (attr != TBN_OK) {
         set_error("tbn_linear_forward_ws: cannot reserve %d bytes of LDS for the block kernel", kLdsBytes);
@@ -961,6 +1278,85 @@ tbn_status launch_linear_split(const LinearArgs &a, int splits, void *workspace)
     return check_launch("tbn_linear_forward_ws (sum of the split-K partial sums)");
 }
 
+// The windowed form: any row length in multiples of 8 and tile starts anywhere, a row holding at most one of them.
+static bool linear_window_supported(const LinearArgs &a) {
+    if (a.dt != TBN_BF16 || a.in % 8 != 0 || a.in < 8) return false;
+    if (a.p < a.in || a.p < 512 || a.p >= (int64_t(1) << 31) - 512) return false;   // positions in 32 bits, at most one tile end in two pieces
+    if (a.in > (1 << 20) || a.out > (1 << 22) || a.out % 8 != 0) return false;
+    if (unique_rows(a.out, a.in, a.p) % 8 != 0 || a.n_alpha > kMaxWinAlphas) return false;
+    if (a.M < 1 || a.M > (int64_t(1) << 36)) return false;
+    if ((reinterpret_cast<uintptr_t>(a.x) | reinterpret_cast<uintptr_t>(a.y)) & 15u) return false;
+    if (reinterpret_cast<uintptr_t>(a.tile) & 3u) return false;
+    // the repair pass of the columns with two alphas must be able to run (its fallback counts groups of 16 rows in 16 bits)
+    if (a.n_alpha > 1 && a.p % a.in != 0 && a.M > int64_t(65535) * 16) return false;
+    return ((a.M + kBM - 1) / kBM) * ((unique_rows(a.out, a.in, a.p) + kBN - 1) / kBN) <= 0x7fffffffLL;
+}
+
+// Where the windowed form beats the general matrix-core kernel (graph replays of 8109 random layers that the latter had, both
+// kernels; microseconds, general / this).  With at most one block per CU nearly always (4777 of 5028 shapes, 12 % on the
+// average, 35 of them more than 4 % slower: 1090 x 744 -> 1600, k = 12: 23.3 / 15.7; 2048 x 3000 -> 1024 distinct columns 24.8 /
+// 21.8; 3746 x 952 -> 584 15.1 / 13.0), but not on rows of one pair of rounds that is mostly padding.  On larger grids the
+// general kernel has two workgroups per CU and smaller losses in the last, incomplete wave of blocks (288 blocks: 25 / 60);
+// rows that do not start on lines cost it more: there two models by least squares over 2659 shapes (R rounds, W = blocks per
+// CU rounded up, 8 - 11 % off), and this form has to be estimated 3 % faster: 684 shapes, 7.8 % on the average, 22 of
+// them more than 4 % slower (8192 x 3000 -> 1024 distinct columns: 60.6 / 55.0).  Rows of whole lines on such grids stay with
+// the general kernel (8192 x 3008 -> 1024: 51 / 53).
+bool linear_window_preferred(const LinearArgs &a) {
+    if ((a.flags & ~uint32_t(TBN_FLAG_RELU)) || !linear_window_supported(a)) return false;   // flags that steer to another kernel
+    const int64_t U = unique_rows(a.out, a.in, a.p), cus = device_cus();
+    const int64_t blocks = ((a.M + kBM - 1) / kBM) * ((U + kBN - 1) / kBN);
+    if (blocks <= cus) return a.in >= 200;
+    if (a.in % 64 == 0) return false;
+    const double R = 2.0 * static_cast<double>((a.in + 255) / 256), W = static_cast<double>((blocks + cus - 1) / cus);
+    const double outputs = 1e-6 * static_cast<double>(a.M) * static_cast<double>(a.out);
+    const double per_cu = static_cast<double>(blocks) / static_cast<double>(cus), pairs = static_cast<double>((blocks + 2 * cus - 1) / (2 * cus));
+    const double general = 5.71 + R * (0.2685 * per_cu + 0.687 * W + 0.1293 * pairs) + 0.231 * outputs;
+    const double here = 7.30 + 0.7866 * W * R + 1.7866 * W + 0.2972 * outputs;
+    return here < 0.97 * general;
+}
+
+tbn_status launch_linear_window(const LinearArgs &a) {
+    BlockParams P;
+    const int64_t U = unique_rows(a.out, a.in, a.p);
+    P.M = a.M;
+    P.in = static_cast<int32_t>(a.in);
+    P.out = static_cast<int32_t>(a.out);
+    P.U = static_cast<int32_t>(U);
+    P.reps = static_cast<int32_t>((a.out + U - 1) / U);
+    P.n_alpha = a.n_alpha;
+    P.tiles_m = static_cast<uint32_t>((a.M + kBM - 1) / kBM);
+    P.tiles_n = (P.U + kBN - 1) / kBN;
+    P.n_rounds = 2 * static_cast<int32_t>((a.in + 255) / 256);
+    P.splits = 1;
+    P.vrows = P.tiles_m;
+    P.partial = nullptr;
+    P.p = static_cast<int32_t>(a.p);
+    P.alpha_step = a.n_alpha > 1 && P.reps > 1 ? static_cast<int32_t>(U * a.in / a.p) : 0;   // (more than one replica: U is the period)
+    const int lds = kAlphaOff + 4 * a.n_alpha;
+    const bool relu = (a.flags & TBN_FLAG_RELU) != 0;
+    int cus = device_cus() & ~7;
+    if (cus < 8) cus = 8;
+    const int64_t blocks = int64_t(P.tiles_m) * P.tiles_n;
+    const bool persist = blocks > cus && P.n_rounds >= 4;
+    typedef void (*kernel_t)(const uint16_t *, uint16_t *, const uint32_t *, const float *, BlockParams);
+    static const kernel_t kernels[4] = {&linear_block_bf16_kernel<false, false, false, true>, &linear_block_bf16_kernel<true, false, false, true>,
+                                        &linear_block_bf16_kernel<false, false, true, true>, &linear_block_bf16_kernel<true, false, true, true>};
+    static const tbn_status attr[4] = {set_lds_limit_once(reinterpret_cast<const void *>(kernels[0]), 160 * 1024),
+                                       set_lds_limit_once(reinterpret_cast<const void *>(kernels[1]), 160 * 1024),
+                                       set_lds_limit_once(reinterpret_cast<const void *>(kernels[2]), 160 * 1024),
+                                       set_lds_limit_once(reinterpret_cast<const void *>(kernels[3]), 160 * 1024)};
+    const int which = (relu ? 1 : 0) + (persist ? 2 : 0);
+    if (attr[which] != TBN_OK) {
+        set_error("tbn_linear_forward: cannot reserve %d bytes of LDS for the block kernel", lds);
+        return TBN_ERR_DEVICE;
+    }
+    hipLaunchKernelGGL(kernels[which], dim3(static_cast<unsigned>(persist ? cus : blocks)), dim3(512), lds, a.stream,
+                       static_cast<const uint16_t *>(a.x), static_cast<uint16_t *>(a.y), a.tile, a.alpha, P);
+    const tbn_status st = check_launch("tbn_linear_forward (matrix-core kernel with load waves, windows)");
+    if (st != TBN_OK || a.n_alpha == 1 || a.p % a.in == 0) return st;
+    return launch_linear_tile_ends(a);   // columns whose weight row holds a tile start: two alphas
+}
+
 tbn_status launch_linear_block(const LinearArgs &a) {
     BlockParams P;
     fill_params(a, P);
@@ -973,8 +1369,8 @@ tbn_status launch_linear_block(const LinearArgs &a) {
     const bool persist = int64_t(P.tiles_m) * P.tiles_n > cus && P.n_rounds >= 4;
     // (its store waves write with non-temporal stores whatever the shape: next to a running K loop, plain stores push
     // the activations that the other column blocks of the same rows still need out of the XCD's L2)
-    static const kernel_t kernels[4] = {&linear_block_bf16_kernel<false, false, false>, &linear_block_bf16_kernel<true, false, false>,
-                                        &linear_block_bf16_kernel<false, false, true>, &linear_block_bf16_kernel<true, false, true>};
+    static const kernel_t kernels[4] = {&linear_block_bf16_kernel<false, false, false, false>, &linear_block_bf16_kernel<true, false, false, false>,
+                                        &linear_block_bf16_kernel<false, false, true, false>, &linear_block_bf16_kernel<true, false, true, false>};
     // dynamic LDS above the default limit has to be allowed once per kernel (thread-safe static initialisation)
     static const tbn_status attr[4] = {set_lds_limit_once(reinterpret_cast<const void *>(kernels[0]), kLdsBytes),
                                        set_lds_limit_once(reinterpret_cast<const void *>(kernels[1]), kLdsBytes),
