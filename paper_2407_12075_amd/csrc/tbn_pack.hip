@@ -6,9 +6,14 @@
 // with its neighbours' and each weight is read exactly once.  Column sums s_i (Eq. 2) are kept
 // in double precision in row order, which makes the sign (Eq. 3) independent of the launch
 // shape and identical to a sequential double-precision sum.  |a| is summed per row in double
-// precision: a wave reduces its share of row r and writes one partial per (wave, r) to the
+// precision: a block reduces its share of row r and writes one partial per (block, r) to the
 // workspace; a second small kernel adds the partials in a fixed order and divides (Eq. 6 / 8).
-// No floating-point atomics are used, so results are reproducible bit for bit.
+// No floating-point atomics are used, so results are reproducible bit for bit.  A tile of one block
+// needs neither workspace nor second kernel (6000 weights, k = 3: 7.1 -> 6.0 us per call).
+//
+// One kernel for every size, its last block adding the partials, was slower: with a ticket per call 512 blocks wait 15 us
+// for each other's operations on one address (30 ns each), with a ticket per 32 blocks the chain of four or five
+// device-scope operations takes as long as the second kernel (1,600,000 weights, k = 8: 10.2 -> 11.3 us).
 //
 // The same kernels build the tile of the column-tiled layout (GPU Inference Kernel section): there the k
 // summands of tile position i = o * blk + j are the entries (o, r * blk + j) of an out x in matrix with
@@ -22,7 +27,9 @@ namespace tbn {
 
 constexpr int kPackThreads = 256;
 constexpr int kPackWaves = kPackThreads / kWave;
-constexpr int kPackQ = 4;  // loads per row per thread
+constexpr int kPackQ = 4;  // loads per row per thread, one row at a time; small tiles: one load, kRowsAhead rows at a time
+constexpr int kRowsAhead = 4;
+constexpr int kMaxRows = 64;   // summands per position whose block sums fit the LDS array; beyond, one partial per wave
 
 template <int VEC> struct PackVec;
 template <> struct PackVec<4> { using type = float4; };
@@ -34,75 +41,94 @@ __device__ __forceinline__ double wave_sum_f64(double v) {
     return v;
 }
 
-// positions handled by one block: kPackThreads * VEC * kPackQ, a multiple of 64
-template <int VEC, bool SEPARATE_A>
+__device__ __forceinline__ double alpha_denominator(int32_t n_alpha, int64_t p, int32_t k) {
+    return n_alpha == 1 ? static_cast<double>(p) * static_cast<double>(k) : static_cast<double>(p);
+}
+
+// Q: loads per row per thread; R: rows requested together.  Positions handled by one block: kPackThreads * VEC * Q, a multiple of 64
+template <int VEC, bool SEPARATE_A, int Q, int R>
 __global__ __launch_bounds__(kPackThreads) void pack_kernel(const float *__restrict__ w,
                                                             const float *__restrict__ a, int64_t p, int32_t k,
                                                             int64_t blk, int64_t ld,
-                                                            uint32_t *__restrict__ tile_out, int64_t n_words,
-                                                            double *__restrict__ partial) {
+                                                            uint32_t *__restrict__ tile_out,
+                                                            double *__restrict__ partial, int32_t n_alpha,
+                                                            float *__restrict__ alpha_out) {
+    __shared__ double row_sum[kPackWaves][kMaxRows];
+    const int64_t n_words = (p + 31) / 32;
     constexpr int64_t kChunk = int64_t(kPackThreads) * VEC;   // positions covered by one load round
     const int tid = threadIdx.x;
     const int lane = tid & (kWave - 1);
     const int wave = tid / kWave;
-    const int64_t block_base = int64_t(blockIdx.x) * kChunk * kPackQ;
+    const int64_t block_base = int64_t(blockIdx.x) * kChunk * Q;
 
-    double s[kPackQ][VEC];
+    double s[Q][VEC];
 #pragma unroll
-    for (int q = 0; q < kPackQ; ++q)
+    for (int q = 0; q < Q; ++q)
 #pragma unroll
         for (int v = 0; v < VEC; ++v) s[q][v] = 0.0;
 
-    int64_t pos[kPackQ];   // offset of summand 0 of the thread's positions
-    bool live[kPackQ];
+    int64_t pos[Q];   // offset of summand 0 of the thread's positions
+    bool live[Q];
 #pragma unroll
-    for (int q = 0; q < kPackQ; ++q) {
+    for (int q = 0; q < Q; ++q) {
         const int64_t i = block_base + q * kChunk + int64_t(tid) * VEC;
         live[q] = i < p;  // VEC == 4 is only used when p % 4 == 0: a vector is all in or all out
         pos[q] = (blk == p || !live[q]) ? i : (i / blk) * ld + i % blk;   // blk % 4 == 0 with VEC == 4: no vector spans two rows
     }
 
+    const bool by_block = k <= kMaxRows;
     double *my_partial = partial + (int64_t(blockIdx.x) * kPackWaves + wave) * k;
 
-    for (int32_t r = 0; r < k; ++r) {
-        const float *wr = w + int64_t(r) * blk;
-        const float *ar = SEPARATE_A ? a + int64_t(r) * blk : wr;
-        float wv[kPackQ][VEC];
-        float av[kPackQ][VEC];
+    for (int32_t r0 = 0; r0 < k; r0 += R) {
+        float wv[R][Q][VEC];
+        float av[R][Q][VEC];
 #pragma unroll
-        for (int q = 0; q < kPackQ; ++q) {
-            if (live[q]) {
-                if constexpr (VEC == 4) {
-                    const float4 t = *reinterpret_cast<const float4 *>(wr + pos[q]);
-                    wv[q][0] = t.x; wv[q][1] = t.y; wv[q][2] = t.z; wv[q][3] = t.w;
-                    if constexpr (SEPARATE_A) {
-                        const float4 u = *reinterpret_cast<const float4 *>(ar + pos[q]);
-                        av[q][0] = u.x; av[q][1] = u.y; av[q][2] = u.z; av[q][3] = u.w;
+        for (int j = 0; j < R; ++j) {
+            const int32_t r = R == 1 || r0 + j < k ? r0 + j : k - 1;   // past the last row: that one again, not added
+            const float *wr = w + int64_t(r) * blk;
+            const float *ar = SEPARATE_A ? a + int64_t(r) * blk : wr;
+#pragma unroll
+            for (int q = 0; q < Q; ++q) {
+                if (live[q]) {
+                    if constexpr (VEC == 4) {
+                        const float4 t = *reinterpret_cast<const float4 *>(wr + pos[q]);
+                        wv[j][q][0] = t.x; wv[j][q][1] = t.y; wv[j][q][2] = t.z; wv[j][q][3] = t.w;
+                        if constexpr (SEPARATE_A) {
+                            const float4 u = *reinterpret_cast<const float4 *>(ar + pos[q]);
+                            av[j][q][0] = u.x; av[j][q][1] = u.y; av[j][q][2] = u.z; av[j][q][3] = u.w;
+                        }
+                    } else {
+                        wv[j][q][0] = wr[pos[q]];
+                        if constexpr (SEPARATE_A) av[j][q][0] = ar[pos[q]];
                     }
                 } else {
-                    wv[q][0] = wr[pos[q]];
-                    if constexpr (SEPARATE_A) av[q][0] = ar[pos[q]];
-                }
-            } else {
 #pragma unroll
-                for (int v = 0; v < VEC; ++v) { wv[q][v] = 0.f; av[q][v] = 0.f; }
+                    for (int v = 0; v < VEC; ++v) { wv[j][q][v] = 0.f; av[j][q][v] = 0.f; }
+                }
             }
         }
-        double l1 = 0.0;
 #pragma unroll
-        for (int q = 0; q < kPackQ; ++q)
+        for (int j = 0; j < R; ++j) {
+            if (R > 1 && r0 + j >= k) break;
+            double l1 = 0.0;
 #pragma unroll
-            for (int v = 0; v < VEC; ++v) {
-                s[q][v] += static_cast<double>(wv[q][v]);
-                l1 += static_cast<double>(fabsf(SEPARATE_A ? av[q][v] : wv[q][v]));
+            for (int q = 0; q < Q; ++q)
+#pragma unroll
+                for (int v = 0; v < VEC; ++v) {
+                    s[q][v] += static_cast<double>(wv[j][q][v]);
+                    l1 += static_cast<double>(fabsf(SEPARATE_A ? av[j][q][v] : wv[j][q][v]));
+                }
+            l1 = wave_sum_f64(l1);
+            if (lane == 0) {
+                if (by_block) row_sum[wave][r0 + j] = l1;
+                else my_partial[r0 + j] = l1;
             }
-        l1 = wave_sum_f64(l1);
-        if (lane == 0) my_partial[r] = l1;
+        }
     }
 
     // Eq. 3 and bit packing, LSB first
 #pragma unroll
-    for (int q = 0; q < kPackQ; ++q) {
+    for (int q = 0; q < Q; ++q) {
         if constexpr (VEC == 4) {
             uint32_t nib = 0;
 #pragma unroll
@@ -120,43 +146,57 @@ __global__ __launch_bounds__(kPackThreads) void pack_kernel(const float *__restr
             if (lane == 1 && wi + 1 < n_words) tile_out[wi + 1] = static_cast<uint32_t>(mask >> 32);
         }
     }
+
+    if (!by_block) return;
+    __syncthreads();
+    double sum = 0.0;
+    if (tid < k) {
+#pragma unroll
+        for (int wv = 0; wv < kPackWaves; ++wv) sum += row_sum[wv][tid];
+    }
+    if (gridDim.x > 1) {
+        if (tid < k) partial[int64_t(blockIdx.x) * k + tid] = sum;
+    } else if (wave == 0) {   // (k <= 64)
+        const double all = n_alpha == 1 ? wave_sum_f64(sum) : sum;
+        if (tid < n_alpha) alpha_out[tid] = static_cast<float>(all / alpha_denominator(n_alpha, p, k));
+    }
 }
 
-// alpha[r] = (sum over all (block, wave) partials of row r) / p, or one alpha = total / n.
-// One block per output scalar; fixed strided order + fixed tree -> reproducible.
-__global__ __launch_bounds__(256) void pack_alpha_kernel(const double *__restrict__ partial, int64_t n_part,
-                                                         int32_t k, int32_t n_alpha, int64_t p,
-                                                         float *__restrict__ alpha_out) {
-    __shared__ double red[256 / kWave];
+// alpha[r] = (sum over the n_part partials of row r) / p, or one alpha = total / n: then all partials, which lie side by side,
+// are one row.  One block per output scalar; fixed strided order + fixed tree -> reproducible.  (With one alpha, 256 threads
+// going through the rows one after the other took as long as the tile kernel: 4096 x 4096, k = 8 17.9 us in all instead of 14.6;
+// 64 million weights, k = 16: 76 instead of 42.)
+constexpr int kAlphaThreads = 1024;   // 256 for few partials
+__global__ __launch_bounds__(kAlphaThreads) void pack_alpha_kernel(const double *__restrict__ partial, int64_t n_part,
+                                                                   int32_t k, int32_t n_alpha, int64_t p,
+                                                                   float *__restrict__ alpha_out) {
+    __shared__ double red[kAlphaThreads / kWave];
     const int tid = threadIdx.x;
-    const int32_t r_begin = (n_alpha == 1) ? 0 : blockIdx.x;
-    const int32_t r_end = (n_alpha == 1) ? k : blockIdx.x + 1;
+    const int64_t stride = n_alpha == 1 ? 1 : k, n = n_alpha == 1 ? n_part * k : n_part;
+    const double *src = partial + blockIdx.x;
     double acc = 0.0;
-    for (int32_t r = r_begin; r < r_end; ++r) {
-        int64_t i = tid;
-        for (; i + 7 * 256 < n_part; i += 8 * 256) {   // eight independent loads in flight
-            double t[8];
+    const int64_t T = blockDim.x;
+    int64_t i = tid;
+    for (; i + 3 * T < n; i += 4 * T) {   // four independent loads in flight
+        double t[4];
 #pragma unroll
-            for (int j = 0; j < 8; ++j) t[j] = partial[(i + j * 256) * k + r];
+        for (int j = 0; j < 4; ++j) t[j] = src[(i + j * T) * stride];
 #pragma unroll
-            for (int j = 0; j < 8; ++j) acc += t[j];
-        }
-        for (; i < n_part; i += 256) acc += partial[i * k + r];
+        for (int j = 0; j < 4; ++j) acc += t[j];
     }
+    for (; i < n; i += T) acc += src[i * stride];
     acc = wave_sum_f64(acc);
     if ((tid & (kWave - 1)) == 0) red[tid / kWave] = acc;
     __syncthreads();
     if (tid == 0) {
         double total = 0.0;
-#pragma unroll
-        for (int wv = 0; wv < 256 / kWave; ++wv) total += red[wv];
-        const double denom = (n_alpha == 1) ? static_cast<double>(p) * static_cast<double>(k) : static_cast<double>(p);
-        alpha_out[blockIdx.x] = static_cast<float>(total / denom);
+        for (int wv = 0; wv < static_cast<int>(T / kWave); ++wv) total += red[wv];
+        alpha_out[blockIdx.x] = static_cast<float>(total / alpha_denominator(n_alpha, p, k));
     }
 }
 
-static int64_t pack_blocks(int64_t p, int vec) {
-    const int64_t per_block = int64_t(kPackThreads) * vec * kPackQ;
+static int64_t pack_blocks(int64_t p, int vec, int q = kPackQ) {
+    const int64_t per_block = int64_t(kPackThreads) * vec * q;
     return (p + per_block - 1) / per_block;
 }
 
@@ -171,28 +211,35 @@ tbn_status launch_pack(const float *w, const float *a, int64_t n, int32_t k, int
                        uint32_t *tile_out, float *alpha_out, void *workspace, hipStream_t stream,
                        int64_t blk, int64_t ld) {
     const int64_t p = n / k;
-    const int64_t n_words = (p + 31) / 32;
     if (blk <= 0) { blk = p; ld = 0; }   // flat layout
     const bool vec4 = (p % 4 == 0) && (blk % 4 == 0) && (ld % 4 == 0) && ((reinterpret_cast<uintptr_t>(w) & 15u) == 0) &&
                       (!a || (reinterpret_cast<uintptr_t>(a) & 15u) == 0);
-    const int64_t blocks = pack_blocks(p, vec4 ? 4 : 1);
+    // Below 192 blocks of four loads per row a thread takes one load of four rows at a time: as many bytes in flight, four times
+    // the blocks (graph replays: 49 blocks, k = 8 9.6 -> 7.2 us; 13 blocks, k = 16 14.8 -> 9.8; 98 blocks, k = 8 9.9 -> 7.9; but 245
+    // blocks, k = 4 7.3 -> 7.9).  With a partial per block (64 rows or fewer) these still fit the workspace.
+    const bool by_block = k <= kMaxRows, small = by_block && pack_blocks(p, vec4 ? 4 : 1) > 1 && pack_blocks(p, vec4 ? 4 : 1) <= 192;
+    const int64_t blocks = pack_blocks(p, vec4 ? 4 : 1, small ? 1 : kPackQ);
     if (blocks > 0x7fffffffLL) {
         set_error("tbn_pack_tile: tile of %lld bits is beyond the supported range", (long long)p);
         return TBN_ERR_UNSUPPORTED;
     }
     double *partial = static_cast<double *>(workspace);
-    const dim3 grid(static_cast<unsigned>(blocks)), block(kPackThreads);
+    auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(blocks)), dim3(kPackThreads), 0, stream, w, a, p, k, blk, ld, tile_out,
+                           partial, n_alpha, alpha_out);
+    };
     if (vec4) {
-        if (a) hipLaunchKernelGGL((pack_kernel<4, true>), grid, block, 0, stream, w, a, p, k, blk, ld, tile_out, n_words, partial);
-        else   hipLaunchKernelGGL((pack_kernel<4, false>), grid, block, 0, stream, w, a, p, k, blk, ld, tile_out, n_words, partial);
+        if (a) small ? launch(&pack_kernel<4, true, 1, kRowsAhead>) : launch(&pack_kernel<4, true, kPackQ, 1>);
+        else   small ? launch(&pack_kernel<4, false, 1, kRowsAhead>) : launch(&pack_kernel<4, false, kPackQ, 1>);
     } else {
-        if (a) hipLaunchKernelGGL((pack_kernel<1, true>), grid, block, 0, stream, w, a, p, k, blk, ld, tile_out, n_words, partial);
-        else   hipLaunchKernelGGL((pack_kernel<1, false>), grid, block, 0, stream, w, a, p, k, blk, ld, tile_out, n_words, partial);
+        if (a) small ? launch(&pack_kernel<1, true, 1, kRowsAhead>) : launch(&pack_kernel<1, true, kPackQ, 1>);
+        else   small ? launch(&pack_kernel<1, false, 1, kRowsAhead>) : launch(&pack_kernel<1, false, kPackQ, 1>);
     }
     tbn_status st = check_launch("tbn_pack_tile (tile kernel)");
-    if (st != TBN_OK) return st;
-    hipLaunchKernelGGL(pack_alpha_kernel, dim3(static_cast<unsigned>(n_alpha)), dim3(256), 0, stream, partial,
-                       blocks * kPackWaves, k, n_alpha, p, alpha_out);
+    if (st != TBN_OK || (by_block && blocks == 1)) return st;   // (one block has written the scalars)
+    const int64_t n_part = by_block ? blocks : blocks * kPackWaves;
+    hipLaunchKernelGGL(pack_alpha_kernel, dim3(static_cast<unsigned>(n_alpha)), dim3((n_alpha == 1 ? n_part * k : n_part) > 1024 ? kAlphaThreads : 256), 0,
+                       stream, partial, n_part, k, n_alpha, p, alpha_out);
     return check_launch("tbn_pack_tile (alpha kernel)");
 }
 
