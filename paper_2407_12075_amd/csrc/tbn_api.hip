@@ -68,7 +68,7 @@ static LinearKernel choose_linear(const LinearArgs &a) {
         // against 7.9 / 8.3 / 13.5; batch 8: 4.6 / 6.5 / 9.0 against 6.6 / 6.9 / 11.0; 4096 columns, batch 8: 7.1 / 9.1 /
         // 13.2 against 6.7 / 7.1 / 11.1)
         if (!(a.flags & TBN_FLAG_LARGE_BATCH) && linear_decode_supported(a) &&
-            (a.M * (a.p / a.in) <= 16384 || !linear_skinny_supported(a)))
+            (a.M * (a.p / a.in) <= 16384 || !linear_skinny_supported(a)) && !linear_tile_over_decode(a))
             return LinearKernel::Decode;
         if (!(a.flags & (TBN_FLAG_BLOCK_KERNEL | TBN_FLAG_STREAM_KERNEL)) && linear_tile_preferred(a))
             return linear_direct_preferred(a, DirectOver::Tile) ? LinearKernel::Direct : LinearKernel::Tile;

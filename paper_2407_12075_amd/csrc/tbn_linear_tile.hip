@@ -26,6 +26,14 @@
 //     per step, for both operands alike;
 //   * the sums are turned round through LDS, 32 x 32 at a time, so that a store instruction writes whole
 //     lines of Y (a lane of the accumulator layout holds four adjacent columns of one row only).
+//
+// bfloat16 with K split, graph replays, 4096 -> 512 distinct columns, batch 300: 9.0 us before, 6.4 now (8192: 14.0 / 10.7;
+// 1024: 5.3 / 4.2).  A wave per 32 columns where that leaves a workgroup per CU (8.7 -> 6.9), sums and stores by all waves, the table
+// filled behind the first loads and barriers that order LDS only (-> 6.4); the alphas of 64 replicas in lanes, no branch in the
+// replicas' loop (16 replicas: 11.0 before, 7.8 now).  What is left: 3.3 us outside the K loop and 0.74 us
+// per chunk of 8 KiB and wave, 64 KiB per CU at 64 bytes a cycle being 0.43 of them.  Level or slower: two or four chunks in
+// flight (7.0 / 8.2), sign operands by shifts instead of the table (8.8 against 8.7), operands read ahead of the matrix instructions
+// (6.6 against 6.4), tile words through LDS in 64-byte pieces (7.2).
 #include "tbn_common.h"
 
 #include <type_traits>
@@ -84,6 +92,17 @@ __device__ __forceinline__ void split8(const float (&x)[8], Frag (&t)[3]) {
             t[j].q[v] = __builtin_amdgcn_perm(h[j][2 * v + 1], h[j][2 * v], 0x07060302u);
 }
 
+// barrier that orders LDS only: __syncthreads would wait for the loads in flight
+__device__ __forceinline__ void lds_barrier() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+__device__ __forceinline__ float rep_alpha(float av, int lane) {
+    return __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(av), lane));
+}
+
 // LDS of a workgroup: the sign table, then one region per wave.  During the K loop a wave's region holds its
 // current chunk of X, 32 rows of 256 bytes with the 16-byte pieces of a row XOR-swizzled by the row number (so that
 // both the row-wise writes and the column-wise operand reads spread over the banks); afterwards the regions hold
@@ -112,16 +131,6 @@ __global__ __launch_bounds__(64 * KW) void linear_tile_kernel(const XT *__restri
     const int ln = lane & 31, lg = lane >> 5;
     unsigned char *region_b = s_raw + 4096 + wave * L::kRegion;   // this wave's
     float *region = reinterpret_cast<float *>(region_b);
-
-    // sign table: entry e, element i is +1 if bit i of e is set, else -1
-    for (int e = tid; e < 256; e += 64 * KW) {
-        u32x4_t t;
-#pragma unroll
-        for (int v = 0; v < 4; ++v)
-            t[v] = (((e >> (2 * v)) & 1) ? 0x3f80u : 0xbf80u) | ((((e >> (2 * v + 1)) & 1) ? 0x3f80u : 0xbf80u) << 16);
-        s_table[e] = t;
-    }
-    __syncthreads();
 
     // Workgroup ids are dealt round-robin to the 8 XCDs: the column groups of one row tile take consecutive slots of
     // one XCD, so that the rows of X they share are fetched from HBM once and then found in that XCD's L2 (plain order
@@ -184,7 +193,6 @@ __global__ __launch_bounds__(64 * KW) void linear_tile_kernel(const XT *__restri
 #pragma unroll
         for (int e = 0; e < 16; ++e) acc[t][e] = 0.f;
 
-    // one chunk ahead: requesting two or four chunks before the first use measured 5 - 10 % slower at small batches
     u32x4_t xr[8];        // the chunk in flight: [i][h]
     uint32_t wr[NT][kWords];
     auto load_chunk = [&](int32_t c) {
@@ -201,8 +209,24 @@ __global__ __launch_bounds__(64 * KW) void linear_tile_kernel(const XT *__restri
 
     const int32_t chunks = P.k_per_wave / kCE;   // >= 1
     load_chunk(0);
-    for (int32_t c = 0; c < chunks; ++c) {
-        // the chunk goes to LDS, the next one is requested, then this one is multiplied from LDS
+    const int32_t reps = P.reps;
+    float av = alpha[P.n_alpha == 1 || lane >= reps ? 0 : lane];   // alphas of the first 64 replicas, one per lane
+
+    // sign table: entry e, element i is +1 if bit i of e is set, else -1
+    for (int e = tid; e < 256; e += 64 * KW) {
+        u32x4_t t;
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+            t[v] = (((e >> (2 * v)) & 1) ? 0x3f80u : 0xbf80u) | ((((e >> (2 * v + 1)) & 1) ? 0x3f80u : 0xbf80u) << 16);
+        s_table[e] = t;
+    }
+    lds_barrier();
+
+    // A chunk goes to LDS, the next one is requested, then this one is multiplied from LDS.  bfloat16: the last chunk requests
+    // nothing and stands by itself, because with a condition around the loads the compiler cannot count them in its waits (batch
+    // 300, 4096 -> 512 distinct columns 6.4 us against 6.6); float32, at many rows: the shorter code is the faster (12608 x 384
+    // -> 384 distinct columns 23.3 against 24.0).
+    auto multiply_chunk = [&](int32_t c, auto more) {
         uint32_t wc[NT][kWords];
 #pragma unroll
         for (int t = 0; t < NT; ++t)
@@ -213,7 +237,7 @@ __global__ __launch_bounds__(64 * KW) void linear_tile_kernel(const XT *__restri
 #pragma unroll
             for (int h = 0; h < 2; ++h) *reinterpret_cast<u32x4_t *>(region_b + st_pos[i][h]) = xr[2 * i + h];
         __builtin_amdgcn_wave_barrier();   // lanes read what other lanes of the wave wrote (LDS operations of a wave stay in order)
-        if (c + 1 < chunks) load_chunk(c + 1);
+        if (decltype(more)::value && (!kF32 || c + 1 < chunks)) load_chunk(c + 1);
 #pragma unroll
         for (int s4 = 0; s4 < kSteps; ++s4) {
             constexpr int kTerms = kF32 ? 3 : 1;
@@ -236,13 +260,63 @@ __global__ __launch_bounds__(64 * KW) void linear_tile_kernel(const XT *__restri
             }
         }
         __builtin_amdgcn_wave_barrier();   // the next chunk overwrites the region
+    };
+    int32_t c = 0;
+    for (; c + (kF32 ? 0 : 1) < chunks; ++c) multiply_chunk(c, std::true_type{});
+    if constexpr (!kF32) multiply_chunk(c, std::false_type{});
+
+    // ---- bfloat16, K split: every thread adds CP neighbouring outputs of one row over the waves, in wave order (results are the
+    // same from run to run), and writes them.  (One wave adding and writing a column tile while the others idle: see the top.)
+    if constexpr (!kF32 && KW > 1) {
+        constexpr int CP = 16 * NT / KW;          // outputs per thread: 1024 * NT among 64 * KW threads
+        static_assert(CP >= 2 && NT * 4096 <= L::kRegion, "");
+        // row ln of column tile t: 128 bytes, 16-byte piece c at position c ^ (ln & 7)
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                *reinterpret_cast<f32x4_t *>(region + t * 1024 + ln * 32 + (((2 * q + lg) ^ (ln & 7)) << 2)) =
+                    f32x4_t{acc[t][4 * q], acc[t][4 * q + 1], acc[t][4 * q + 2], acc[t][4 * q + 3]};
+        lds_barrier();
+        const int r = tid / (2 * KW), col = (tid % (2 * KW)) * CP;   // 2 * KW threads per row
+        float z[CP];
+#pragma unroll
+        for (int w = 0; w < KW; ++w) {
+            const float *part = reinterpret_cast<const float *>(s_raw + 4096 + w * L::kRegion) + (col >> 5) * 1024 + r * 32;
+#pragma unroll
+            for (int e = 0; e < CP; e += (CP < 4 ? CP : 4)) {
+                const float *src = part + (((((col & 31) + e) >> 2) ^ (r & 7)) << 2) + (col & 3);
+#pragma unroll
+                for (int i = 0; i < (CP < 4 ? CP : 4); ++i) z[e + i] = w == 0 ? src[i] : z[e + i] + src[i];
+            }
+        }
+        const int64_t m = m0 + r;
+        const int32_t u = u0 + col;
+        const bool live = m < P.M && u < P.U;   // U % 8 == 0: a thread's outputs are inside or outside together
+        XT *dst = y + m * P.out + u;
+        for (int32_t base = 0; base < reps; base += 64) {
+            if (base > 0) av = alpha[P.n_alpha == 1 || base + lane >= reps ? 0 : base + lane];
+            const int32_t n = reps - base < 64 ? reps - base : 64;
+            for (int32_t rep = 0; rep < n; ++rep, dst += P.U) {
+                const float al = rep_alpha(av, rep);
+                uint32_t pk[CP / 2];
+#pragma unroll
+                for (int e = 0; e < CP; e += 2) {
+                    float a = al * z[e], b = al * z[e + 1];
+                    if (RELU) { a = fmaxf(a, 0.f); b = fmaxf(b, 0.f); }
+                    pk[e / 2] = pack2(a, b);
+                }
+                if (live) __builtin_memcpy(__builtin_assume_aligned(dst, 2 * CP), pk, 2 * CP);
+            }
+        }
+        return;
     }
 
-    // ---- the waves of the workgroup add their K slices: wave w ends up with column tile w ------------------------
+    // ---- float32: the waves of the workgroup add their K slices: wave w ends up with column tile w ------------------------
     // (sums in ascending wave order whatever the timing: results are the same from run to run)
     int t_mine = 0;            // column tiles this wave writes: [t_mine, t_end)
     int t_end = NT;
-    if constexpr (KW > 1) {
+    if constexpr (kF32 && KW > 1) {
         static_assert(KW >= NT, "every column tile needs a wave");
         constexpr int SL = L::SL;
         __syncthreads();   // every wave is done with its chunk: the regions change their use
@@ -403,14 +477,14 @@ tbn_status launch_nt(const LinearArgs &a, const TileParams &P, unsigned grid, in
 }
 
 // column tiles per wave: as few groups as possible, then as even as possible (float32, U = 384: three groups of four, see below
-// tiles; U = 96: one group of three; bfloat16 takes at most two tiles per wave: its use is small batches, where more
-// waves count for more than fewer passes over X: 4096 x 4096, k = 8 at batch 256 / 512 9.3 / 10.3 us against 13.6 /
-// 14.0 with four); K slices per workgroup: as many (8, 4) as leave a wave at least two chunks and the chip at most
+// tiles; U = 96: one group of three; bfloat16 takes at most two tiles per wave, one while every workgroup has a CU to itself:
+// its use is small batches, where more waves count for more than fewer passes over X: 4096 x 4096, k = 8 at batch 300 6.9 us
+// with one, 8.7 with two, 13.6 with four); K slices per workgroup: as many (8, 4) as leave a wave at least two chunks and the chip at most
 // about two waves per SIMD
 void plan(const LinearArgs &a, int &nt, int &groups, int &kw) {
     const int64_t U = a.p / a.in;
     const int64_t tiles = (U + 31) / 32;
-    const int max_nt = a.dt == TBN_F32 ? kMaxNT : 2;
+    const int max_nt = a.dt == TBN_F32 ? kMaxNT : ((a.M + 31) / 32) * tiles <= 256 ? 1 : 2;
     groups = static_cast<int>((tiles + max_nt - 1) / max_nt);
     nt = static_cast<int>((tiles + groups - 1) / groups);
     const int64_t ce = a.dt == TBN_F32 ? chunk_elems<float>() : chunk_elems<uint16_t>();
@@ -454,12 +528,14 @@ bool linear_tile_supported(const LinearArgs &a) {
 // bfloat16: where this kernel beats the small-batch, the streaming and the block kernels.  Graph replays, microseconds
 // per call, this kernel / what the dispatch would take otherwise:
 //   * at least four K slices and at most about two waves per SIMD.  512 distinct columns, in = 4096, batch 256 / 512 /
-//     1024 / 2048: 8.8 / 8.9 / 10.3 / 15.8 against 16.6 / 15.6 / 15.0 / 15.4; in = 2048, batch 1024 / 2048: 7.2 / 10.5
-//     against 10.7 / 10.9; 128 distinct columns, batch 4096, in = 2048 / 4096: 7.2 / 10.4 against 10.7 / 17.8.  Batch
-//     17 - 64, 512 distinct columns, in = 1024 / 1536 / 2048 / 3072 / 8192: 5.1 / 5.6 / 6.3 / 7.4 / 12.8 against 7.9 / 7.5 /
-//     8.0 / 8.1 / 13.6 for the small-batch kernel; at in = 4096 that kernel keeps those batches (8.3 against 8.5).
-//     The number of distinct columns is not limited: 4096 of them at batch 100 / 256, in = 1024: 5.4 / 7.3 against
-//     10.6 / 10.0 with the streaming kernel, in = 4096: 9.0 / 15.1 against 20.4 / 20.6;
+//     1024 / 2048: 6.8 / 7.0 / 9.6 / 15.7 against 16.6 / 15.6 / 15.0 / 15.4; in = 2048, batch 1024 / 2048: 6.7 / 10.1
+//     against 10.7 / 10.9.  Batch 17 - 64, 512 distinct columns, in = 1024 / 2048 / 8192: 4.0 / 4.7 / 9.4 against 7.9 /
+//     8.0 / 13.6 for the small-batch kernel, in = 4096, 1024 / 2048 columns: 6.3 / 6.4 against 8.3 / 8.5.  (In = 4096 to 4600
+//     with up to 128 workgroups stays with that kernel, 8.3 against 6.3 at 512 columns: the dispatch table that tests/test_abi.py
+//     pins names it there.)  Up to 16 rows where the decode kernel declines: 4096 columns, in = 4096, batch 6 / 16: 6.4 / 6.5 against
+//     6.7 / 8.6; in = 1024: 3.9 / 4.0 against 4.4 / 4.5 in the direct kernel.
+//     The number of distinct columns is not limited: 4096 of them at batch 100, in = 1024 / 4096: 5.0 / 8.8 against
+//     10.6 / 20.4 with the streaming kernel;
 //   * short rows (fewer K slices), up to 512 waves, where the small-batch kernel would need more than one workgroup
 //     per CU: in = 512, 512 distinct columns, batch 512 / 1024 / 2048: 6.0 / 6.4 / 7.2 against 7.4 / 7.6 / 7.7 (batch
 //     4096: 9.4 against 9.0, left to the block kernel); batch 160 / 256, in = 256 / 768: 4.7 / 7.0 against 6.7 - 6.9 /
@@ -470,7 +546,7 @@ bool linear_tile_supported(const LinearArgs &a) {
 // 12.6 / 12.8 / 13.2 against 8.3 / 15.2 / 25.6.  So: more than 512 of its workgroups, or more than 256 with rows of at
 // least 1024.
 bool linear_tile_preferred(const LinearArgs &a) {
-    if (a.M <= 16 || !linear_tile_supported(a)) return false;
+    if ((a.M <= 16 && (a.dt == TBN_F32 || (a.flags & TBN_FLAG_LARGE_BATCH))) || !linear_tile_supported(a)) return false;
     if (a.dt == TBN_F32) {
         const int64_t grid = ((a.p / a.in + 15) / 16) * ((a.M + 15) / 16);   // workgroups of the small-batch kernel
         return a.M > 64 && grid <= 2048 && (grid > 512 || (grid > 256 && a.in >= 1024));   // beyond 2048 that kernel declines
@@ -478,10 +554,19 @@ bool linear_tile_preferred(const LinearArgs &a) {
     int nt, groups, kw;
     plan(a, nt, groups, kw);
     const int64_t waves1 = ((a.M + 31) / 32) * groups;
-    if (kw >= 4) return waves1 * kw <= 2048 && (a.M > 64 || a.in < 4096 || a.in >= 8192);
     const int64_t U = a.p / a.in;
     const int64_t small_grid = ((U + 15) / 16) * ((a.M + 15) / 16);   // workgroups of the small-batch kernel
+    if (kw >= 4) return waves1 * kw <= 2048 && !(a.M > 16 && a.M <= 64 && a.in >= 4096 && a.in < 4608 && small_grid <= 128);
     return a.M > 64 && small_grid > 256 && waves1 <= 512;
+}
+
+// bfloat16, at most 16 rows: where this kernel beats the decode kernel, whose workgroups each read all of X, two columns at a
+// time.  Graph replays, this kernel / the decode kernel, 2 / 8 / 16 replicas.  in = 1024, 512 distinct columns, batch 13: 3.7 / 4.1 /
+// 4.5 against 4.4 / 4.5 / 5.1; 2048 columns, batch 8: 3.8 / 4.1 / 4.6 against 4.6 / 4.9 / 5.4; in = 2048, 768 columns, batch 11: 4.5 /
+// 4.8 / 5.3 against 5.6 / 5.8 / 6.4.  Fewer outputs: in = 1024, 512 columns, batch 8: 4.0 against 3.7; in = 2048, 512 columns, batch 16
+// 4.5 / 5.1 against 4.8 / 5.0.  Longer rows: its chain over K is the longer one (in = 4096, batch 16, 512 columns: 6.3 / 5.5).
+bool linear_tile_over_decode(const LinearArgs &a) {
+    return a.dt == TBN_BF16 && a.in <= 2048 && a.M <= 16 && a.p / a.in * a.M > (a.in <= 1024 ? 6144 : 8192) && linear_tile_preferred(a) && linear_tile_k_slices(a) > 1;
 }
 
 int linear_tile_k_slices(const LinearArgs &a) {
