@@ -479,8 +479,9 @@ tbn_status launch_nt(const LinearArgs &a, const TileParams &P, unsigned grid, in
 // column tiles per wave: as few groups as possible, then as even as possible (float32, U = 384: three groups of four, see below
 // tiles; U = 96: one group of three; bfloat16 takes at most two tiles per wave, one while every workgroup has a CU to itself:
 // its use is small batches, where more waves count for more than fewer passes over X: 4096 x 4096, k = 8 at batch 300 6.9 us
-// with one, 8.7 with two, 13.6 with four); K slices per workgroup: as many (8, 4) as leave a wave at least two chunks and the chip at most
-// about two waves per SIMD
+// with one, 8.7 with two, 13.6 with four; two workgroups of one tile on a CU are slower than one of two: batch 1024 11.7 /
+// 9.4); K slices per workgroup: as many (8, 4) as leave a wave at least two chunks and the chip at most about two waves per
+// SIMD
 void plan(const LinearArgs &a, int &nt, int &groups, int &kw) {
     const int64_t U = a.p / a.in;
     const int64_t tiles = (U + 31) / 32;
