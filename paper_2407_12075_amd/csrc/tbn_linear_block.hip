@@ -85,7 +85,17 @@ constexpr int kTableOff = 0;             // 256 entries of 16 bytes
 constexpr int kRingOff = 4096;
 constexpr int kTileOff = kRingOff + kNB * kSlotBytes;
 constexpr int kLdsBytes = kTileOff + kTileSlots * kTileSlotBytes;
-// WIN: the words of three chunks as they come from memory, in the layout of the tile chunks; the alphas
+// WIN: the words of three chunks as they come from memory, in the layout of the tile chunks; the alphas.  Chunk c (rounds 2c and
+// 2c + 1) has raw slot c % 3 and is read by put_tile of chunks c and c - 1 (the fifth words), pieces that another load wave
+// brought among them.  So between the last read of a slot and the next fetch into it lies a barrier:
+//   one block per workgroup   put_tile(0) (slots 0, 1)           | "round 0 readable"        | fetch of chunk 3 (slot 0)
+//                             put_tile(2) (slots 1, 2)           | the same and round 0's    | fetch of chunk 4 (slot 1)
+//                             chunk c, behind round 2c - 3's     | round 2c - 2's            | fetch of chunk c + 3
+//   PERSIST                   chunk 0, behind the last round's   | the block's first         | fetch of chunk 3
+//                             chunk 1, behind the block's first  | round 0's                 | fetch of chunk 4
+//                             chunk c, behind round 2c - 3's     | round 2c - 2's            | fetch of chunk c + 3
+//                             last chunk                         | round n - 4's             | the next block's fetches of chunks 0 and 1
+// (tests/test_window_schedule.py walks the statements of these waves and checks this for every access.)
 constexpr int kRawSlots = 3;
 constexpr int kRawOff = kLdsBytes;
 constexpr int kAlphaOff = kRawOff + kRawSlots * kTileSlotBytes;
@@ -686,11 +696,11 @@ __global__ __launch_bounds__(512, 1) void linear_block_bf16_kernel(const uint16_
             __builtin_amdgcn_s_barrier();   // the words are there
             put_tile(0);
             if (n_rounds > 2) put_tile(2);
-            fetch_tile(6);
-            if (n_rounds > 2) __builtin_amdgcn_s_waitcnt(vmcnt_imm(kOdd + kEven));
-            else __builtin_amdgcn_s_waitcnt(vmcnt_imm(kEven));
+            if (n_rounds > 2) __builtin_amdgcn_s_waitcnt(vmcnt_imm(2 * kOdd));   // round 0
+            else __builtin_amdgcn_s_waitcnt(vmcnt_imm(kOdd));
             lds_wait<0>();
             __builtin_amdgcn_s_barrier();   // meets the MFMA waves' "table written, round 0 readable"
+            fetch_tile(6);   // into the slot of chunk 0, which every load wave has put in place by that barrier
             for (int32_t g = 0; g < n_rounds; g += 2) {
                 if (g + 2 < n_rounds) __builtin_amdgcn_s_waitcnt(vmcnt_imm(kEven));
                 else __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
