@@ -67,10 +67,11 @@ static LinearKernel choose_linear(const LinearArgs &a) {
         // is the faster one (graph replays, 2048 distinct columns, batch 16, in = 1024 / 4096 / 8192: 9.0 / 11.4 / 16.1 us
         // against 7.9 / 8.3 / 13.5; batch 8: 4.6 / 6.5 / 9.0 against 6.6 / 6.9 / 11.0; 4096 columns, batch 8: 7.1 / 9.1 /
         // 13.2 against 6.7 / 7.1 / 11.1)
+        const bool tile = !(a.flags & (TBN_FLAG_BLOCK_KERNEL | TBN_FLAG_STREAM_KERNEL));   // these keep the tile kernel out
         if (!(a.flags & TBN_FLAG_LARGE_BATCH) && linear_decode_supported(a) &&
-            (a.M * (a.p / a.in) <= 16384 || !linear_skinny_supported(a)) && !linear_tile_over_decode(a))
+            (a.M * (a.p / a.in) <= 16384 || !linear_skinny_supported(a)) && !(tile && linear_tile_over_decode(a)))
             return LinearKernel::Decode;
-        if (!(a.flags & (TBN_FLAG_BLOCK_KERNEL | TBN_FLAG_STREAM_KERNEL)) && linear_tile_preferred(a))
+        if (tile && linear_tile_preferred(a))
             return linear_direct_preferred(a, DirectOver::Tile) ? LinearKernel::Direct : LinearKernel::Tile;
         // bfloat16, rows of at most 576 elements and many distinct columns: the rows of a block stay in LDS
         if (linear_short_preferred(a)) return LinearKernel::Short;

@@ -154,6 +154,16 @@ def test_kernel_choice(lib, dtype, M, cin, out, k, flags, x_ptr, expected):
     assert tbn.tbn_linear_forward_kernel(dt, M, cin, out, k, 1, flags, x_ptr=x_ptr) == expected
 
 
+@pytest.mark.parametrize("M,cin,cout,k", [(4, 1024, 6656, 2), (16, 2048, 2048, 2), (13, 1024, 1664, 2)])
+def test_flags_of_the_larger_kernels_leave_a_few_rows_to_the_decode_kernel(lib, M, cin, cout, k):
+    """Without them the kernel with one wave per 32 rows takes these calls; they keep that one out, not the decode kernel."""
+    import torch
+    from paper_2407_12075_amd import tbn
+    q = lambda flags: tbn.tbn_linear_forward_kernel(torch.bfloat16, M, cin, cout, k, 1, flags)
+    assert q(0) == "tile"
+    assert q(tbn.TBN_FLAG_BLOCK_KERNEL) == q(tbn.TBN_FLAG_STREAM_KERNEL) == "decode"
+
+
 def test_kernel_choice_rejects_what_the_forward_call_rejects(lib):
     import torch
     from paper_2407_12075_amd import tbn
