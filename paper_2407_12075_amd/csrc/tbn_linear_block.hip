@@ -1302,27 +1302,43 @@ static bool linear_window_supported(const LinearArgs &a) {
     return ((a.M + kBM - 1) / kBM) * ((unique_rows(a.out, a.in, a.p) + kBN - 1) / kBN) <= 0x7fffffffLL;
 }
 
-// Where the windowed form beats the general matrix-core kernel (graph replays of 8109 random layers that the latter had, both
-// kernels; microseconds, general / this).  With at most one block per CU nearly always (4777 of 5028 shapes, 12 % on the
-// average, 35 of them more than 4 % slower: 1090 x 744 -> 1600, k = 12: 23.3 / 15.7; 2048 x 3000 -> 1024 distinct columns 24.8 /
-// 21.8; 3746 x 952 -> 584 15.1 / 13.0), but not on rows of one pair of rounds that is mostly padding.  On larger grids the
-// general kernel has two workgroups per CU and smaller losses in the last, incomplete wave of blocks (288 blocks: 25 / 60);
-// rows that do not start on lines cost it more: there two models by least squares over 2659 shapes (R rounds, W = blocks per
-// CU rounded up, 8 - 11 % off), and this form has to be estimated 3 % faster: 684 shapes, 7.8 % on the average, 22 of
-// them more than 4 % slower (8192 x 3000 -> 1024 distinct columns: 60.6 / 55.0).  Rows of whole lines on such grids stay with
-// the general kernel (8192 x 3008 -> 1024: 51 / 53).
+// Where the windowed form beats the general matrix-core kernel (graph replays of both kernels over 10700 random layers that the latter
+// took, profiles/dispatch_over_random_shapes.md; microseconds, general / this).
+//   * With at most one block per CU nearly always (1090 x 744 -> 1600, k = 12: 23.0 / 15.6; 2048 x 3000 -> 1024 distinct columns
+//     36.2 / 29.7 with the repair pass; 3746 x 952 -> 584 15.2 / 13.0), but not on rows of one pair of rounds that is mostly padding.
+//   * Every tile start among a block's 128 rows stops a load wave for a chain of reads (put_tile), so not where a block has many:
+//     128 in / p of them.  One alpha: from three on (3141 x 3608 -> 80, k = 11, 17.6 of them: 23.9 / 33.0; three to four: level, a quarter of
+//     the layers more than 4 % slower), on two pairs of rounds from one on (level, a quarter slower).  An alpha per tile copy costs
+//     the general kernel more: from five on, with rows of more than 1024 and at most two replicas (427 layers 5 % slower here; those that
+//     stay 17 % faster).
+//   * On larger grids the general kernel has two workgroups per CU and smaller losses in the last, incomplete wave of blocks (288
+//     blocks: 25 / 60); rows that do not start on lines cost it more: there two models by least squares (R rounds, W =
+//     blocks per CU rounded up; 10 and 11 % off on the 2787 drawn layers that the last sentence leaves them), and this form has to be estimated 3 % faster, 5 % with rows of at most 2048, which must
+//     not be a tenth padding either (15 layers of 1300 - 1700: 6 % slower): 8192 x 3000 -> 1024 distinct columns 60.6 / 55.0.  Rows of whole lines
+//     stay with the general kernel (8192 x 3008 -> 1024: 51 / 53; 369 drawn ones: 11 % slower here), and so do five replicas and more,
+//     or three where activations and outputs overflow the last-level cache, whose non-temporal stores the models do not see
+//     (21113 x 3512 -> 3552, 12 replicas: 101 / 162; 17647 x 4000 -> 4880, ten: 153 / 210).
 bool linear_window_preferred(const LinearArgs &a) {
     if ((a.flags & ~uint32_t(TBN_FLAG_RELU)) || !linear_window_supported(a)) return false;   // flags that steer to another kernel
-    const int64_t U = unique_rows(a.out, a.in, a.p), cus = device_cus();
+    const int64_t U = unique_rows(a.out, a.in, a.p), reps = (a.out + U - 1) / U, cus = device_cus();
     const int64_t blocks = ((a.M + kBM - 1) / kBM) * ((U + kBN - 1) / kBN);
-    if (blocks <= cus) return a.in >= 200;
-    if (a.in % 64 == 0) return false;
+    const auto starts = [&](int64_t n) { return a.p % a.in != 0 && kBN * a.in >= n * a.p; };   // at least n tile starts inside a block's rows
+    if (blocks <= cus) {
+        if (a.in < 200) return false;
+        if (a.n_alpha == 1) return !starts(3) && !(starts(1) && a.in > 256 && a.in <= 512);
+        return !(starts(5) && a.in > 1024 && reps <= 2);
+    }
+    if (a.in % 64 == 0 || starts(3)) return false;
+    const bool overflow = a.M * (a.in + a.out) > 85000000;   // 170 MB in bfloat16
+    if (reps >= 5 || (reps >= 3 && overflow)) return false;
+    const bool short_rows = a.in <= 2048;
     const double R = 2.0 * static_cast<double>((a.in + 255) / 256), W = static_cast<double>((blocks + cus - 1) / cus);
+    if (short_rows && R * 128.0 > 1.1 * static_cast<double>(a.in)) return false;
     const double outputs = 1e-6 * static_cast<double>(a.M) * static_cast<double>(a.out);
     const double per_cu = static_cast<double>(blocks) / static_cast<double>(cus), pairs = static_cast<double>((blocks + 2 * cus - 1) / (2 * cus));
     const double general = 5.71 + R * (0.2685 * per_cu + 0.687 * W + 0.1293 * pairs) + 0.231 * outputs;
     const double here = 7.30 + 0.7866 * W * R + 1.7866 * W + 0.2972 * outputs;
-    return here < 0.97 * general;
+    return here < (short_rows ? 0.95 : 0.97) * general;
 }
 
 tbn_status launch_linear_window(const LinearArgs &a) {

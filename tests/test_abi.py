@@ -164,6 +164,32 @@ def test_flags_of_the_larger_kernels_leave_a_few_rows_to_the_decode_kernel(lib, 
     assert q(tbn.TBN_FLAG_BLOCK_KERNEL) == q(tbn.TBN_FLAG_STREAM_KERNEL) == "decode"
 
 
+# bfloat16, rows in multiples of 8 that the general and the windowed kernel both take: M, in, out, k, n_alpha, expected
+WINDOW_CHOICE = [
+    (3141, 3608, 80, 11, 1, "general"),       # 17.6 tile starts among a block's rows
+    (12804, 1560, 128, 3, 1, "general"),      # three
+    (1300, 3000, 384, 9, 1, "general"),       # three, as ninths of more rows
+    (1300, 3000, 408, 9, 1, "window"),        # 2.8
+    (2288, 384, 408, 9, 1, "general"),        # two pairs of rounds: from one start on
+    (1200, 264, 3064, 11, 1, "window"),
+    (3851, 2072, 152, 7, 7, "general"),       # an alpha per tile copy: 5.9
+    (3851, 2080, 152, 5, 5, "window"),        # 4.2
+    (16000, 1000, 1088, 1000, 1000, "window"),   # rows of at most 1024
+    (21113, 3512, 3552, 12, 1, "general"),    # larger grids: twelve replicas
+    (17120, 3000, 3072, 3, 3, "general"),     # three, activations and outputs beyond 170 MB
+    (8192, 3000, 3072, 9, 9, "window"),
+    (9827, 1312, 1952, 1, 1, "general"),      # rows with a sixth of padding
+    (12000, 2984, 2944, 4, 4, "window"),
+]
+
+
+@pytest.mark.parametrize("M,cin,cout,k,n_alpha,expected", WINDOW_CHOICE)
+def test_windowed_kernel_leaves_what_the_general_kernel_does_faster(lib, M, cin, cout, k, n_alpha, expected):
+    import torch
+    from paper_2407_12075_amd import tbn
+    assert tbn.tbn_linear_forward_kernel(torch.bfloat16, M, cin, cout, k, n_alpha) == expected
+
+
 def test_kernel_choice_rejects_what_the_forward_call_rejects(lib):
     import torch
     from paper_2407_12075_amd import tbn
