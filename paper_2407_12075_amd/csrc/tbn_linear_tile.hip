@@ -224,8 +224,10 @@ __global__ __launch_bounds__(64 * KW) void linear_tile_kernel(const XT *__restri
 
     // A chunk goes to LDS, the next one is requested, then this one is multiplied from LDS.  bfloat16: the last chunk requests
     // nothing and stands by itself, because with a condition around the loads the compiler cannot count them in its waits (batch
-    // 300, 4096 -> 512 distinct columns 6.4 us against 6.6); float32, at many rows: the shorter code is the faster (12608 x 384
-    // -> 384 distinct columns 23.3 against 24.0).
+    // 300, 4096 -> 512 distinct columns 6.4 us against 6.6); it then has to be kept from moving them down, which four waves pay for
+    // with every chunk (312 x 8704 -> 976 distinct columns: 15.5 us with the condition, 17.5 with the loads moved down, 14.1 now; 177 x
+    // 5632 -> 1664: 11.8 / 13.0 / 10.6; eight waves are level: 300 x 8192 -> 512 14.3 / 10.5 / 10.6).  float32, at many rows: the
+    // shorter code is the faster (12608 x 384 -> 384 distinct columns 23.3 against 24.0).
     auto multiply_chunk = [&](int32_t c, auto more) {
         uint32_t wc[NT][kWords];
 #pragma unroll
@@ -238,6 +240,8 @@ __global__ __launch_bounds__(64 * KW) void linear_tile_kernel(const XT *__restri
             for (int h = 0; h < 2; ++h) *reinterpret_cast<u32x4_t *>(region_b + st_pos[i][h]) = xr[2 * i + h];
         __builtin_amdgcn_wave_barrier();   // lanes read what other lanes of the wave wrote (LDS operations of a wave stay in order)
         if (decltype(more)::value && (!kF32 || c + 1 < chunks)) load_chunk(c + 1);
+        // bfloat16: left to itself the compiler moves these loads behind most of the products below, which they are to run under
+        if constexpr (!kF32) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int s4 = 0; s4 < kSteps; ++s4) {
             constexpr int kTerms = kF32 ? 3 : 1;

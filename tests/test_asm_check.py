@@ -86,3 +86,25 @@ kernel_a:
     .end_amdhsa_kernel
 """
     assert any("touches registers" in f for f in _check(text))
+
+
+def test_tile_kernel_requests_a_chunk_before_the_products_of_the_one_before():
+    """The bfloat16 kernel with one wave per 32 rows has one chunk in flight: its loads have to stand before the loop's matrix
+    instructions, where the compiler does not leave them by itself."""
+    text = asm_check.compile_to_asm(os.path.join(hip_build.CSRC, "tbn_linear_tile.hip"))
+    loops = 0
+    for name, lines in asm_check._split_kernels(text).items():
+        if "linear_tile_kernelIt" not in name:
+            continue
+        block = []
+        for line in lines + [".LBB_end:"]:
+            if not line.startswith(".L"):
+                block.append(line)
+                continue
+            loads = [i for i, l in enumerate(block) if l.startswith("global_load_dwordx")]
+            products = [i for i, l in enumerate(block) if l.startswith("v_mfma")]
+            if loads and products:
+                loops += 1
+                assert loads[-1] < products[0], f"{name}: loads behind the first of {len(products)} matrix instructions"
+            block = []
+    assert loops == 12   # with and without ReLU, one and two column tiles, one, four and eight slices of K
