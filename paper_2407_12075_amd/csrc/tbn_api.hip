@@ -62,15 +62,14 @@ enum class LinearKernel { Decode, Tile, Skinny, Stream, Block, Mfma, Rows, Direc
 
 static LinearKernel choose_linear(const LinearArgs &a) {
     if (!(a.flags & TBN_FLAG_FORCE_GENERIC)) {
-        // at most 16 batch rows: the decode kernel (a workgroup per two distinct columns reads all of X); with many
-        // distinct columns and 8 - 16 rows the small-batch kernel, whose workgroups share X sixteen columns at a time,
-        // is the faster one (graph replays, 2048 distinct columns, batch 16, in = 1024 / 4096 / 8192: 9.0 / 11.4 / 16.1 us
-        // against 7.9 / 8.3 / 13.5; batch 8: 4.6 / 6.5 / 9.0 against 6.6 / 6.9 / 11.0; 4096 columns, batch 8: 7.1 / 9.1 /
-        // 13.2 against 6.7 / 7.1 / 11.1)
+        // at most 16 batch rows: the decode kernel (a workgroup per two distinct columns reads all of X).  With many distinct columns the
+        // kernels whose workgroups share X among more columns are faster: bfloat16 with K in four slices or more the one with one wave per 32
+        // rows (rules and figures in tbn_linear_tile.hip), otherwise and in float32, at 8 - 16 rows, the small-batch kernel or the direct one
+        // (graph replays, 2048 distinct columns, batch 16, float32, in = 1024 / 4096 / 8192: 9.1 / 16.5 / 26.1 us in the decode kernel, 5.9 / 12.2 /
+        // 21.5 here; bfloat16, in = 1280 / 4224: 8.8 / 12.4 and 4.6 / 7.5; batch 8: 4096 columns, float32, 5.3 / 10.7 / 17.7 and 5.9 / 10.0 / 16.5)
         const bool tile = !(a.flags & (TBN_FLAG_BLOCK_KERNEL | TBN_FLAG_STREAM_KERNEL));   // these keep the tile kernel out
-        if (!(a.flags & TBN_FLAG_LARGE_BATCH) && linear_decode_supported(a) &&
-            (a.M * (a.p / a.in) <= 16384 || !linear_skinny_supported(a)) && !(tile && linear_tile_over_decode(a)))
-            return LinearKernel::Decode;
+        if (!(a.flags & TBN_FLAG_LARGE_BATCH) && linear_decode_supported(a) && (a.M * (a.p / a.in) <= 16384 || !linear_skinny_supported(a)))
+            return tile && linear_tile_over_decode(a) ? LinearKernel::Tile : LinearKernel::Decode;
         if (tile && linear_tile_preferred(a))
             return linear_direct_preferred(a, DirectOver::Tile) ? LinearKernel::Direct : LinearKernel::Tile;
         // bfloat16, rows of at most 576 elements and many distinct columns: the rows of a block stay in LDS

@@ -539,6 +539,9 @@ bool linear_tile_supported(const LinearArgs &a) {
 //     with up to 128 workgroups stays with that kernel, 8.3 against 6.3 at 512 columns: the dispatch table that tests/test_abi.py
 //     pins names it there.)  Up to 16 rows where the decode kernel declines: 4096 columns, in = 4096, batch 6 / 16: 6.4 / 6.5 against
 //     6.7 / 8.6; in = 1024: 3.9 / 4.0 against 4.4 / 4.5 in the direct kernel.
+//     More replicas than 32 to 96, the more the longer the rows, leave it behind the direct kernel where that is the other choice: up to 16
+//     rows, in to 2048, 33 - 48 / 49 - 64 / 65 - 100 replicas 0.98 / 0.94 / 0.90 of that kernel's speed on the mean, in to 3584 1.03 / 0.98 / 0.95, beyond
+//     4096 1.11 / 1.07 / 1.02 and from 101 on 0.94; 17 - 64 rows, in beyond 4096: 1.12 to 100, 0.97 from there (688 drawn layers).
 //     The number of distinct columns is not limited: 4096 of them at batch 100, in = 1024 / 4096: 5.0 / 8.8 against
 //     10.6 / 20.4 with the streaming kernel;
 //   * short rows (fewer K slices), up to 512 waves, where the small-batch kernel would need more than one workgroup
@@ -561,17 +564,28 @@ bool linear_tile_preferred(const LinearArgs &a) {
     const int64_t waves1 = ((a.M + 31) / 32) * groups;
     const int64_t U = a.p / a.in;
     const int64_t small_grid = ((U + 15) / 16) * ((a.M + 15) / 16);   // workgroups of the small-batch kernel
-    if (kw >= 4) return waves1 * kw <= 2048 && !(a.M > 16 && a.M <= 64 && a.in >= 4096 && a.in < 4608 && small_grid <= 128);
+    if (kw >= 4) {
+        const int64_t limit = a.in <= 2048 ? 32 : a.in >= 6144 ? 96 : a.in / 64;   // replicas
+        const bool few = a.M <= 16 || (a.M <= 64 && a.in >= 4096 && a.in < 8192);
+        if (few && a.out / U > limit && linear_direct_preferred(a, DirectOver::SmallBatch)) return false;
+        return waves1 * kw <= 2048 && !(a.M > 16 && a.M <= 64 && a.in >= 4096 && a.in < 4608 && small_grid <= 128);
+    }
     return a.M > 64 && small_grid > 256 && waves1 <= 512;
 }
 
 // bfloat16, at most 16 rows: where this kernel beats the decode kernel, whose workgroups each read all of X, two columns at a
-// time.  Graph replays, this kernel / the decode kernel, 2 / 8 / 16 replicas.  in = 1024, 512 distinct columns, batch 13: 3.7 / 4.1 /
-// 4.5 against 4.4 / 4.5 / 5.1; 2048 columns, batch 8: 3.8 / 4.1 / 4.6 against 4.6 / 4.9 / 5.4; in = 2048, 768 columns, batch 11: 4.5 /
-// 4.8 / 5.3 against 5.6 / 5.8 / 6.4.  Fewer outputs: in = 1024, 512 columns, batch 8: 4.0 against 3.7; in = 2048, 512 columns, batch 16
-// 4.5 / 5.1 against 4.8 / 5.0.  Longer rows: its chain over K is the longer one (in = 4096, batch 16, 512 columns: 6.3 / 5.5).
+// time.  Graph replays, this kernel / the decode kernel, 2 / 8 / 16 replicas.  in = 1024, 512 distinct columns, batch 13: 3.5 / 3.9 /
+// 4.4 against 4.2 / 4.4 / 5.0; 2048 columns, batch 5 and 8: 3.5 / 3.9 / 4.4 against 4.4 / 4.6 / 4.9 and 4.5 / 4.8 / 5.3; in = 2048, 6144 columns,
+// batch 2: 4.6 / 4.9 / 5.3 against 7.3 / 7.4 / 7.6; 768 columns, batch 11: 4.4 / 4.7 / 5.1 against 5.6 / 5.8 / 6.3.  Fewer outputs: in = 1024,
+// 512 columns, batch 8: 3.5 / 3.9 / 4.4 against 3.6 / 3.7 / 3.8.  Longer rows: its chain over K is the longer one (in = 4096, batch 16, 512
+// columns: 5.9 / 6.3 / 6.7 against 5.3 / 5.4 / 6.0).  Many replicas, of which a thread here stores 4 - 16 bytes at a time: 49 to 64 of them still 1.17
+// times as fast on the mean of 8 layers, 101 to 200 0.94 of 17 (batch 4, in = 1024, 4096 columns, 200: 17.7 against 16.8).
 bool linear_tile_over_decode(const LinearArgs &a) {
-    return a.dt == TBN_BF16 && a.in <= 2048 && a.M <= 16 && a.p / a.in * a.M > (a.in <= 1024 ? 6144 : 8192) && linear_tile_preferred(a) && linear_tile_k_slices(a) > 1;
+    if (a.dt != TBN_BF16 || a.in > 2048 || a.M > 16 || !linear_tile_supported(a)) return false;
+    int nt, groups, kw;
+    plan(a, nt, groups, kw);
+    const int64_t U = a.p / a.in;
+    return kw >= 4 && int64_t(groups) * kw <= 2048 && U * a.M > (a.in <= 1024 ? 6144 : 8192) && a.out / U <= 64;
 }
 
 int linear_tile_k_slices(const LinearArgs &a) {

@@ -164,6 +164,21 @@ def test_flags_of_the_larger_kernels_leave_a_few_rows_to_the_decode_kernel(lib, 
     assert q(tbn.TBN_FLAG_BLOCK_KERNEL) == q(tbn.TBN_FLAG_STREAM_KERNEL) == "decode"
 
 
+@pytest.mark.parametrize("M,cin,U,k,expected", [
+    (16, 1536, 1192, 32, "tile"), (16, 1536, 1192, 33, "direct"),      # the direct kernel is the other choice
+    (14, 3072, 2048, 48, "tile"), (14, 3072, 2048, 49, "direct"),
+    (14, 8192, 2048, 96, "tile"), (14, 8192, 2048, 97, "direct"),
+    (50, 6656, 2048, 96, "tile"), (50, 6656, 2048, 97, "direct"),
+    (7, 4096, 2400, 100, "tile"),                                        # the small-batch kernel is
+    (16, 1536, 1024, 64, "tile"), (16, 1536, 1024, 65, "decode"),
+    (33, 1024, 1024, 70, "tile"),                                        # more rows: no limit
+])
+def test_many_replicas_of_a_few_rows(lib, M, cin, U, k, expected):
+    import torch
+    from paper_2407_12075_amd import tbn
+    assert tbn.tbn_linear_forward_kernel(torch.bfloat16, M, cin, U * k, k, 1) == expected
+
+
 # bfloat16, rows in multiples of 8 that the general and the windowed kernel both take: M, in, out, k, n_alpha, expected
 WINDOW_CHOICE = [
     (3141, 3608, 80, 11, 1, "general"),       # 17.6 tile starts among a block's rows
