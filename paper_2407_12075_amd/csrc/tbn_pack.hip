@@ -22,6 +22,7 @@
 #include "tbn_common.h"
 
 #include <mutex>
+#include <type_traits>
 
 namespace tbn {
 
@@ -45,15 +46,16 @@ __device__ __forceinline__ double alpha_denominator(int32_t n_alpha, int64_t p, 
     return n_alpha == 1 ? static_cast<double>(p) * static_cast<double>(k) : static_cast<double>(p);
 }
 
-// Q: loads per row per thread; R: rows requested together.  Positions handled by one block: kPackThreads * VEC * Q, a multiple of 64
-template <int VEC, bool SEPARATE_A, int Q, int R>
+// Q: loads per row per thread; R: rows requested together; BY_BLOCK: a partial per block and row (k <= kMaxRows), else per wave.
+// Positions handled by one block: kPackThreads * VEC * Q, a multiple of 64
+template <int VEC, bool SEPARATE_A, int Q, int R, bool BY_BLOCK>
 __global__ __launch_bounds__(kPackThreads) void pack_kernel(const float *__restrict__ w,
                                                             const float *__restrict__ a, int64_t p, int32_t k,
                                                             int64_t blk, int64_t ld,
                                                             uint32_t *__restrict__ tile_out,
                                                             double *__restrict__ partial, int32_t n_alpha,
                                                             float *__restrict__ alpha_out) {
-    __shared__ double row_sum[kPackWaves][kMaxRows];
+    __shared__ double row_sum[kPackWaves][BY_BLOCK ? kMaxRows : 1];
     const int64_t n_words = (p + 31) / 32;
     constexpr int64_t kChunk = int64_t(kPackThreads) * VEC;   // positions covered by one load round
     const int tid = threadIdx.x;
@@ -76,7 +78,6 @@ __global__ __launch_bounds__(kPackThreads) void pack_kernel(const float *__restr
         pos[q] = (blk == p || !live[q]) ? i : (i / blk) * ld + i % blk;   // blk % 4 == 0 with VEC == 4: no vector spans two rows
     }
 
-    const bool by_block = k <= kMaxRows;
     double *my_partial = partial + (int64_t(blockIdx.x) * kPackWaves + wave) * k;
 
     for (int32_t r0 = 0; r0 < k; r0 += R) {
@@ -120,7 +121,7 @@ __global__ __launch_bounds__(kPackThreads) void pack_kernel(const float *__restr
                 }
             l1 = wave_sum_f64(l1);
             if (lane == 0) {
-                if (by_block) row_sum[wave][r0 + j] = l1;
+                if constexpr (BY_BLOCK) row_sum[wave][r0 + j] = l1;
                 else my_partial[r0 + j] = l1;
             }
         }
@@ -147,18 +148,19 @@ __global__ __launch_bounds__(kPackThreads) void pack_kernel(const float *__restr
         }
     }
 
-    if (!by_block) return;
-    __syncthreads();
-    double sum = 0.0;
-    if (tid < k) {
+    if constexpr (BY_BLOCK) {
+        __syncthreads();
+        double sum = 0.0;
+        if (tid < k) {
 #pragma unroll
-        for (int wv = 0; wv < kPackWaves; ++wv) sum += row_sum[wv][tid];
-    }
-    if (gridDim.x > 1) {
-        if (tid < k) partial[int64_t(blockIdx.x) * k + tid] = sum;
-    } else if (wave == 0) {   // (k <= 64)
-        const double all = n_alpha == 1 ? wave_sum_f64(sum) : sum;
-        if (tid < n_alpha) alpha_out[tid] = static_cast<float>(all / alpha_denominator(n_alpha, p, k));
+            for (int wv = 0; wv < kPackWaves; ++wv) sum += row_sum[wv][tid];
+        }
+        if (gridDim.x > 1) {
+            if (tid < k) partial[int64_t(blockIdx.x) * k + tid] = sum;
+        } else if (wave == 0) {   // (k <= 64)
+            const double all = n_alpha == 1 ? wave_sum_f64(sum) : sum;
+            if (tid < n_alpha) alpha_out[tid] = static_cast<float>(all / alpha_denominator(n_alpha, p, k));
+        }
     }
 }
 
@@ -228,12 +230,19 @@ tbn_status launch_pack(const float *w, const float *a, int64_t n, int32_t k, int
         hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(blocks)), dim3(kPackThreads), 0, stream, w, a, p, k, blk, ld, tile_out,
                            partial, n_alpha, alpha_out);
     };
+    auto pick = [&](auto vec, auto separate) {
+        constexpr int V = decltype(vec)::value;
+        constexpr bool A = decltype(separate)::value;
+        if (small) launch(&pack_kernel<V, A, 1, kRowsAhead, true>);
+        else if (by_block) launch(&pack_kernel<V, A, kPackQ, 1, true>);
+        else launch(&pack_kernel<V, A, kPackQ, 1, false>);
+    };
     if (vec4) {
-        if (a) small ? launch(&pack_kernel<4, true, 1, kRowsAhead>) : launch(&pack_kernel<4, true, kPackQ, 1>);
-        else   small ? launch(&pack_kernel<4, false, 1, kRowsAhead>) : launch(&pack_kernel<4, false, kPackQ, 1>);
+        if (a) pick(std::integral_constant<int, 4>{}, std::true_type{});
+        else   pick(std::integral_constant<int, 4>{}, std::false_type{});
     } else {
-        if (a) small ? launch(&pack_kernel<1, true, 1, kRowsAhead>) : launch(&pack_kernel<1, true, kPackQ, 1>);
-        else   small ? launch(&pack_kernel<1, false, 1, kRowsAhead>) : launch(&pack_kernel<1, false, kPackQ, 1>);
+        if (a) pick(std::integral_constant<int, 1>{}, std::true_type{});
+        else   pick(std::integral_constant<int, 1>{}, std::false_type{});
     }
     tbn_status st = check_launch("tbn_pack_tile (tile kernel)");
     if (st != TBN_OK || (by_block && blocks == 1)) return st;   // (one block has written the scalars)
