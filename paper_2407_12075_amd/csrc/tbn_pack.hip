@@ -216,10 +216,16 @@ tbn_status launch_pack(const float *w, const float *a, int64_t n, int32_t k, int
     if (blk <= 0) { blk = p; ld = 0; }   // flat layout
     const bool vec4 = (p % 4 == 0) && (blk % 4 == 0) && (ld % 4 == 0) && ((reinterpret_cast<uintptr_t>(w) & 15u) == 0) &&
                       (!a || (reinterpret_cast<uintptr_t>(a) & 15u) == 0);
-    // Below 192 blocks of four loads per row a thread takes one load of four rows at a time: as many bytes in flight, four times
+    // Up to 192 blocks of four loads per row a thread takes one load of four rows at a time: as many bytes in flight, four times
     // the blocks (graph replays: 49 blocks, k = 8 9.6 -> 7.2 us; 13 blocks, k = 16 14.8 -> 9.8; 98 blocks, k = 8 9.9 -> 7.9; but 245
-    // blocks, k = 4 7.3 -> 7.9).  With a partial per block (64 rows or fewer) these still fit the workspace.
-    const bool by_block = k <= kMaxRows, small = by_block && pack_blocks(p, vec4 ? 4 : 1) > 1 && pack_blocks(p, vec4 ? 4 : 1) <= 192;
+    // blocks, k = 4 7.3 -> 7.9).  With fewer than four rows some of these loads are idle, and with scalar loads the second kernel has four
+    // times the partials of fewer weights to add: there up to 128 blocks below eight rows (141 - 190 blocks, k = 3 / 5: 5.8 -> 6.1, 7.1 -> 7.5; 128 blocks:
+    // 5.7 -> 5.5, 6.8 -> 6.5), never with one row, and with one row and vector loads up to 96 (183: 5.3 -> 5.5; 72: 5.0).  One row and scalar
+    // loads: with 2 - 128 blocks what a partial per block waits for costs more than it saves (12 - 50 blocks 4.4 -> 4.9; 170: level).
+    // With a partial per block (64 rows or fewer) the small form's partials still fit the workspace.
+    const int64_t large_blocks = pack_blocks(p, vec4 ? 4 : 1), most = vec4 ? (k == 1 ? 96 : 192) : k >= 8 ? 192 : k >= 2 ? 128 : 0;
+    const bool by_block = k <= kMaxRows && !(k == 1 && !vec4 && large_blocks > 1 && large_blocks <= 128);
+    const bool small = by_block && large_blocks > 1 && large_blocks <= most;
     const int64_t blocks = pack_blocks(p, vec4 ? 4 : 1, small ? 1 : kPackQ);
     if (blocks > 0x7fffffffLL) {
         set_error("tbn_pack_tile: tile of %lld bits is beyond the supported range", (long long)p);
