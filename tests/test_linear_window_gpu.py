@@ -1,6 +1,10 @@
 """The windowed form of the bfloat16 block kernel (row lengths in multiples of 8, tile starts inside rows) at the edges of its
 blocks, rounds and tile pieces: exact arithmetic (activations in {-1, 0, +1}, alphas powers of two), so it has to equal the
 oracle and the kernel with one thread per output bit for bit."""
+import collections
+import math
+import random
+
 import numpy as np
 import pytest
 import torch
@@ -22,6 +26,14 @@ CASES = [
     (12000, 2984, 2944, 4, 4),      # more blocks than CUs: stores under the next block
     (8192, 3000, 3072, 9, 9),       # two blocks per CU
     (8192, 3000, 3072, 9, 1),
+    # workgroups with three blocks at every ring phase and slot: 14, 16, 18, 20, 22 and 26 rounds (24 above), the last row block
+    # of a few rows, tile starts in the first and in the last chunk of a row
+    (4867, 1656, 2320, 9, 9),
+    (22019, 1872, 392, 9, 9),
+    (17412, 2088, 424, 9, 9),
+    (13314, 2376, 536, 11, 11),
+    (9730, 2600, 776, 13, 13),
+    (11144, 3120, 648, 13, 13),
 ]
 
 
@@ -49,6 +61,38 @@ def test_window_exact(M, cin, cout, k, n_alpha):
     got = y[torch.from_numpy(rows).cuda()].float().cpu().numpy()
     bad = np.argwhere(got != ref)
     assert bad.size == 0, f"{len(bad)} of {got.size} outputs differ, first at {tuple(bad[0])}"
+
+
+@pytest.mark.parametrize("seed", [1, 2])
+def test_drawn_layers_in_both_forms(seed):
+    """Rows in multiples of 8, on grids of at most a block per CU and on larger ones (the form whose workgroups walk blocks)."""
+    from paper_2407_12075_amd import tbn
+    rng = random.Random(seed)
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    drawn = collections.Counter()
+    while min(drawn[False], drawn[True]) < 20:
+        large = drawn[True] < 20 and rng.random() < 0.5
+        M = rng.randint(4000, 20000) if large else rng.randint(100, 5000)
+        cin, cout, k = 8 * rng.randint(25, 420), 8 * rng.randint(8, 300), rng.choice([1, 2, 3, 4, 5, 6, 7, 9, 10, 12])
+        if cin * cout % k or M * cin * cout > 3e10:
+            continue
+        p, n_alpha, flags = cin * cout // k, rng.choice([1, k]), rng.choice([0, tbn.TBN_FLAG_RELU])
+        blocks = -(-M // 128) * -(-min(cout, p // math.gcd(p, cin)) // 128)
+        if (blocks > cus) != large or tbn.tbn_linear_forward_kernel(torch.bfloat16, M, cin, cout, k, n_alpha, flags) != "window":
+            continue
+        drawn[large] += 1
+        what = f"M={M} in={cin} out={cout} k={k} n_alpha={n_alpha} flags={flags} blocks={blocks}"
+        print(what, flush=True)
+        g = torch.Generator(device="cuda").manual_seed(M + cin)
+        tile = torch.randint(-2 ** 31, 2 ** 31 - 1, ((p + 31) // 32,), device="cuda", dtype=torch.int32, generator=g)
+        alpha = torch.tensor([2.0 ** (i % 3 - 1) for i in range(n_alpha)], device="cuda")
+        # (as above: every partial sum that is rounded stays exact in bfloat16)
+        keep = torch.rand(M, cin, device="cuda", generator=g) < 60 / cin
+        x = ((torch.randint(-1, 2, (M, cin), device="cuda", generator=g)) * keep).bfloat16()
+        y = tbn.tbn_linear_forward(x, tile, alpha, cout, k, flags=flags)
+        gen = tbn.tbn_linear_forward(x, tile, alpha, cout, k, flags=flags | tbn.TBN_FLAG_FORCE_GENERIC)
+        assert torch.equal(y, gen), what
+    print(f"seed {seed}: {drawn[False]} layers with a block per workgroup, {drawn[True]} with several", flush=True)
 
 
 def test_window_infinity_and_rows_behind_others():
