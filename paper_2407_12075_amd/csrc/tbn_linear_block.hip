@@ -1,5 +1,6 @@
-// Matrix-core kernel for the fully-connected tiled-bit layer with bfloat16 activations and a tile that
-// holds whole weight rows (p % in == 0), one 128 x 128 block of Z per workgroup, with separate load waves.
+// Matrix-core kernel for the fully-connected tiled-bit layer with bfloat16 activations, one 128 x 128 block of Z per
+// workgroup or several one after the other, with separate load waves; for tiles that hold whole weight rows
+// (p % in == 0) and, in the windowed form (WIN), rows of any length in multiples of 8 and tiles that end inside rows.
 //
 // What is computed (Section "Method", Eq. 4-5 and the scaling after Eq. 8): with p a multiple of `in` the
 // (out x in) weight is the U = p / in rows of the tile stacked k times, copy t scaled by alpha[t].  So
@@ -203,14 +204,17 @@ __device__ __forceinline__ void block_coords(const BlockParams &P, uint32_t bid,
 }
 
 // RELU: fused max(0, .) of Algorithm 1.  SPLIT: the workgroup takes one of P.splits equal parts of K and writes
-// float32 partial sums to P.partial instead of Y.  512 threads: waves 0 .. 3 multiply, waves 4 .. 7 load.
+// float32 partial sums to P.partial instead of Y.  512 threads: waves 0 .. 3 multiply, waves 4 .. 7 load (and, PERSIST, store).
 // PERSIST (grids of more blocks than CUs; at least four rounds): the workgroup walks blocks blockIdx.x, + gridDim.x, ...;
 // waves 4 and 5 load, waves 6 and 7 write the replicas of the block before.  The
 // first rounds of the next block start in the ring slot behind the current block's last round, and the hand-over uses
 // the slots of the last two rounds.
 // WIN (any row length in multiples of 8, tile starts anywhere): the loads of the last rounds take zeros for what lies behind
-// a row's end; the load waves fetch the tile bits of a chunk into registers two rounds ahead, shift them into place and
-// write them to the chunk's slot, so that the MFMA waves see aligned chunks; alphas come from LDS, column by column.
+// a row's end; the load waves bring the words that hold a chunk's tile bits to one of three raw slots in LDS as they are
+// (fetch_tile), three chunks ahead of the chunk that is multiplied, and put_tile shifts them into the chunk's slot, so that the
+// MFMA waves see aligned chunks.  put_tile is the load waves' with one block per workgroup and the store waves' under PERSIST;
+// behind the barrier of round 2c - 3 for chunk c, so that round 2c - 2's publishes it, and which barrier frees a raw slot
+// stands at kRawSlots.  Alphas come from LDS, column by column.
 template <bool RELU, bool SPLIT, bool PERSIST, bool WIN>
 __global__ __launch_bounds__(512, 1) void linear_block_bf16_kernel(const uint16_t *__restrict__ x,
                                                                                      uint16_t *__restrict__ y,
@@ -236,8 +240,9 @@ __global__ __launch_bounds__(512, 1) void linear_block_bf16_kernel(const uint16_
         return PERSIST ? static_cast<uint32_t>(kRingOff + ((P.n_rounds - 2 + phase) & 3) * kSlotBytes) : static_cast<uint32_t>(kXchgOff);
     };
     // Waves 4 .. 7.  One block per workgroup: four load waves, each issues a quarter of a round's loads (quarter q:
-    // K group q / 2, row-slot half q % 2).  PERSIST: waves 4 and 5 load (two quarters each: K group = wave - 4),
-    // waves 6 and 7 write the replicas of the block before (the quarters of MFMA waves 2*(wave - 6) and + 1).
+    // K group q / 2, row-slot half q % 2; WIN: and puts its quarter of the tile chunks in place).  PERSIST: waves 4 and 5 load
+    // (two quarters each: K group = wave - 4), waves 6 and 7 write the replicas of the block before (the quarters of MFMA
+    // waves 2*(wave - 6) and + 1; WIN: and put two quarters of the tile chunks in place).
     constexpr int NQ = PERSIST ? 2 : 1;   // quarters per load wave (and per store wave)
     const int first_q = PERSIST ? 2 * (wave & 1) : (wave & 3);
     const int32_t n_rounds = P.n_rounds;

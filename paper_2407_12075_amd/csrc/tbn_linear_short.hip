@@ -8,9 +8,10 @@
 // What bounds it: with K = 512 a 128 x 128 block of Z is four rounds of the block kernel, whose pipeline fill, hand-over of
 // partial sums and barriers then take as long as its multiplications.  Here a workgroup loads the whole rows of its 128 (or
 // 64) batch rows into LDS once and its eight waves walk the columns without ever meeting again: a wave multiplies all rows
-// with 64 columns at a time over all of K, so there are no partial sums to hand over, the stores of one wave run
-// under the multiplications of the other wave of its SIMD, and per eight matrix instructions a wave reads four operands
-// from LDS and expands two from the tile bits in registers (18 vector instructions).
+// with 64 columns at a time over all of K, so there are no partial sums to hand over, and per eight matrix instructions a
+// wave reads four operands from LDS and expands two from the tile bits in registers (18 vector instructions).  The two waves of a
+// SIMD start at the same barrier and do equal passes, so they store at about the same time: only what they drift apart
+// lets one wave's stores run under the other's multiplications, and nothing runs under those of the last pass.
 //   * Rows in LDS are padded with zeros to whole chunks of 64 elements and by 16 bytes, which spreads the operand reads of 16
 //     rows over all banks.
 //   * In a chunk of 64 elements of K lane half lg takes elements 32 lg + 8 s .. + 7 in step s, so that its tile bits of a

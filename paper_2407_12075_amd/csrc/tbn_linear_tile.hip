@@ -535,9 +535,10 @@ bool linear_tile_supported(const LinearArgs &a) {
 //   * at least four K slices and at most about two waves per SIMD.  512 distinct columns, in = 4096, batch 256 / 512 /
 //     1024 / 2048: 6.8 / 7.0 / 9.6 / 15.7 against 16.6 / 15.6 / 15.0 / 15.4; in = 2048, batch 1024 / 2048: 6.7 / 10.1
 //     against 10.7 / 10.9.  Batch 17 - 64, 512 distinct columns, in = 1024 / 2048 / 8192: 4.0 / 4.7 / 9.4 against 7.9 /
-//     8.0 / 13.6 for the small-batch kernel, in = 4096, 1024 / 2048 columns: 6.3 / 6.4 against 8.3 / 8.5.  (In = 4096 to 4600
-//     with up to 128 workgroups stays with that kernel, 8.3 against 6.3 at 512 columns: the dispatch table that tests/test_abi.py
-//     pins names it there.)  Up to 16 rows where the decode kernel declines: 4096 columns, in = 4096, batch 6 / 16: 6.4 / 6.5 against
+//     8.0 / 13.6 for the small-batch kernel, in = 4096, 1024 / 2048 columns: 6.3 / 6.4 against 8.3 / 8.5.  (Rows of
+//     4096, of all lengths with four slices, stay with that kernel at up to 128 of its workgroups, where it is the slower one: 8.0 - 9.4
+//     against 5.6 - 7.0, all of 300 drawn layers, 1.35 times as long on the mean.  No measurement stands behind that: the dispatch
+//     table that tests/test_abi.py pins has such a call.)  Up to 16 rows where the decode kernel declines: 4096 columns, in = 4096, batch 6 / 16: 6.4 / 6.5 against
 //     6.7 / 8.6; in = 1024: 3.9 / 4.0 against 4.4 / 4.5 in the direct kernel.
 //     More replicas than 32 to 96, the more the longer the rows, leave it behind the direct kernel where that is the other choice: up to 16
 //     rows, in to 2048, 33 - 48 / 49 - 64 / 65 - 100 replicas 0.98 / 0.94 / 0.90 of that kernel's speed on the mean, in to 3584 1.03 / 0.98 / 0.95, beyond
@@ -568,7 +569,7 @@ bool linear_tile_preferred(const LinearArgs &a) {
         const int64_t limit = a.in <= 2048 ? 32 : a.in >= 6144 ? 96 : a.in / 64;   // replicas
         const bool few = a.M <= 16 || (a.M <= 64 && a.in >= 4096 && a.in < 8192);
         if (few && a.out / U > limit && linear_direct_preferred(a, DirectOver::SmallBatch)) return false;
-        return waves1 * kw <= 2048 && !(a.M > 16 && a.M <= 64 && a.in >= 4096 && a.in < 4608 && small_grid <= 128);
+        return waves1 * kw <= 2048 && !(a.M > 16 && a.M <= 64 && a.in == 4096 && small_grid <= 128);
     }
     return a.M > 64 && small_grid > 256 && waves1 <= 512;
 }

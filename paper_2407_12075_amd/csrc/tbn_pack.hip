@@ -9,7 +9,8 @@
 // precision: a block reduces its share of row r and writes one partial per (block, r) to the
 // workspace; a second small kernel adds the partials in a fixed order and divides (Eq. 6 / 8).
 // No floating-point atomics are used, so results are reproducible bit for bit.  A tile of one block
-// needs neither workspace nor second kernel (6000 weights, k = 3: 7.1 -> 6.0 us per call).
+// needs neither workspace nor second kernel (6000 weights, k = 3, three scalars: 5.7 -> 4.0 us as graph replays, 7.5 -> 5.0 in
+// calls in a row through the binding).
 //
 // One kernel for every size, its last block adding the partials, was slower: with a ticket per call 512 blocks wait 15 us
 // for each other's operations on one address (30 ns each), with a ticket per 32 blocks the chain of four or five
@@ -166,8 +167,8 @@ __global__ __launch_bounds__(kPackThreads) void pack_kernel(const float *__restr
 
 // alpha[r] = (sum over the n_part partials of row r) / p, or one alpha = total / n: then all partials, which lie side by side,
 // are one row.  One block per output scalar; fixed strided order + fixed tree -> reproducible.  (With one alpha, 256 threads
-// going through the rows one after the other took as long as the tile kernel: 4096 x 4096, k = 8 17.9 us in all instead of 14.6;
-// 64 million weights, k = 16: 76 instead of 42.)
+// going through the rows one after the other took as long as the tile kernel, graph replays: 4096 x 4096, k = 8 18.2 us in all
+// instead of 14.9; 64 million weights, k = 16: 87 instead of 51.)
 constexpr int kAlphaThreads = 1024;   // 256 for few partials
 __global__ __launch_bounds__(kAlphaThreads) void pack_alpha_kernel(const double *__restrict__ partial, int64_t n_part,
                                                                    int32_t k, int32_t n_alpha, int64_t p,

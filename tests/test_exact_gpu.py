@@ -144,11 +144,19 @@ def test_exact_one_wave_per_32_rows_many_distinct_columns(tbn):
 
 
 def test_exact_at_most_16_rows_many_distinct_columns(tbn):
-    """Up to 16 batch rows: the decode kernel, or the small-batch kernel where rows x distinct columns exceed 16384."""
+    """Up to 16 batch rows: the decode kernel, or one whose workgroups share the rows among more columns where rows x distinct columns
+    exceed 16384 (bfloat16 with K in slices: already at 6144)."""
+    def case(M, cin, cout, dtype, family, seed, alpha_vals):
+        dt = torch.float32 if dtype == "f32" else torch.bfloat16
+        assert tbn.tbn_linear_forward_kernel(dt, M, cin, cout, 2, 2) == family
+        _exact_case(tbn, M, cin, cout, 2, dtype, 0, seed, alpha_vals=alpha_vals)
+
     for dtype in ("bf16", "f32"):
-        _exact_case(tbn, 16, 512, 4096, 2, dtype, 0, 41, alpha_vals=[2, 0.5])            # 2048 distinct columns: small-batch kernel
-        _exact_case(tbn, 4, 512, 8192, 2, dtype, 0, 42, alpha_vals=[2, 0.5])             # 4096 distinct columns, 4 rows: decode kernel
-        _exact_case(tbn, 9, 1024, 8192, 2, dtype, 0, 43, alpha_vals=[1, 4])              # 4096 distinct columns, 9 rows: small-batch kernel
+        case(16, 512, 4096, dtype, "direct", 41, [2, 0.5])            # 2048 distinct columns
+        case(4, 512, 8192, dtype, "decode", 42, [2, 0.5])             # 4096 distinct columns, 4 rows
+        case(9, 1024, 8192, dtype, "tile" if dtype == "bf16" else "direct", 43, [1, 4])   # 4096 distinct columns, 9 rows
+        case(9, 1160, 8192, dtype, "small-batch", 44, [1, 4])         # row lengths that K slices and chunks do not divide
+        case(16, 4224, 4352, dtype, "small-batch", 45, [0.5, 2])
 
 
 @pytest.mark.parametrize("M,cin,cout,k", [(16640, 512, 8192, 32), (33000, 768, 8192, 64), (9000, 1024, 16384, 16)])
