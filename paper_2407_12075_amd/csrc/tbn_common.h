@@ -83,8 +83,8 @@ tbn_status launch_linear_window(const LinearArgs &a);
 int linear_split_plan(const LinearArgs &a);         // split K over workgroups for small grids: number of splits, 0 = none
 size_t linear_split_workspace_bytes(const LinearArgs &a, int splits);
 tbn_status launch_linear_split(const LinearArgs &a, int splits, void *workspace);   // workspace: 16-byte aligned, the bytes above
-bool linear_tile_supported(const LinearArgs &a);   // tile of whole rows, at most 512 distinct rows: one wave per 32 batch rows
-bool linear_tile_preferred(const LinearArgs &a);   // bfloat16 at a few hundred batch rows: faster than the other kernels
+bool linear_tile_supported(const LinearArgs &a);   // tile of whole rows: one wave per 32 batch rows
+bool linear_tile_preferred(const LinearArgs &a);   // where it is faster than the other kernels (the decode kernel apart)
 bool linear_tile_over_decode(const LinearArgs &a);   // at most 16 rows, over the decode kernel
 tbn_status launch_linear_tile(const LinearArgs &a);
 tbn_status launch_linear_mfma(const LinearArgs &a);
