@@ -1308,7 +1308,7 @@ static bool linear_window_supported(const LinearArgs &a) {
 }
 
 // Where the windowed form beats the general matrix-core kernel (graph replays of both kernels over 10700 random layers that the latter
-// took, profiles/dispatch_over_random_shapes.md; microseconds, general / this).
+// took; microseconds, general / this).
 //   * With at most one block per CU nearly always (1090 x 744 -> 1600, k = 12: 23.0 / 15.6; 2048 x 3000 -> 1024 distinct columns
 //     36.2 / 29.7 with the repair pass; 3746 x 952 -> 584 15.2 / 13.0), but not on rows of one pair of rounds that is mostly padding.
 //   * Every tile start among a block's 128 rows stops a load wave for a chain of reads (put_tile), so not where a block has many:
@@ -1317,12 +1317,13 @@ static bool linear_window_supported(const LinearArgs &a) {
 //     the general kernel more: from five on, with rows of more than 1024 and at most two replicas (427 layers 5 % slower here; those that
 //     stay 17 % faster).
 //   * On larger grids the general kernel has two workgroups per CU and smaller losses in the last, incomplete wave of blocks (288
-//     blocks: 25 / 60); rows that do not start on lines cost it more: there two models by least squares (R rounds, W =
-//     blocks per CU rounded up; 10 and 11 % off on the 2787 drawn layers that the last sentence leaves them), and this form has to be estimated 3 % faster, 5 % with rows of at most 2048, which must
-//     not be a tenth padding either (15 layers of 1300 - 1700: 6 % slower): 8192 x 3000 -> 1024 distinct columns 60.6 / 55.0.  Rows of whole lines
-//     stay with the general kernel (8192 x 3008 -> 1024: 51 / 53; 369 drawn ones: 11 % slower here), and so do five replicas and more,
-//     or three where activations and outputs overflow the last-level cache, whose non-temporal stores the models do not see
-//     (21113 x 3512 -> 3552, 12 replicas: 101 / 162; 17647 x 4000 -> 4880, ten: 153 / 210).
+//     blocks: 25 / 60); rows that do not start on lines cost it more: there two models by least squares (R rounds, W = blocks per CU
+//     rounded up; 10 and 11 % off on the 2787 drawn layers that the last sentence leaves them), and this form has to be
+//     estimated 3 % faster (8192 x 3000 -> 1024 distinct columns: 60.6 / 55.0), 5 % with rows of at most 2048, which must not be a
+//     tenth padding either (15 layers of 1300 - 1700: 6 % slower).  Rows of whole lines stay with the general kernel (8192 x 3008 ->
+//     1024: 51 / 53; 369 drawn ones: 11 % slower here), and so do five replicas and more, or three where activations and
+//     outputs overflow the last-level cache: the models do not see the cost of the non-temporal stores (21113 x 3512 -> 3552, 12
+//     replicas: 101 / 162; 17647 x 4000 -> 4880, ten: 153 / 210).
 bool linear_window_preferred(const LinearArgs &a) {
     if ((a.flags & ~uint32_t(TBN_FLAG_RELU)) || !linear_window_supported(a)) return false;   // flags that steer to another kernel
     const int64_t U = unique_rows(a.out, a.in, a.p), reps = (a.out + U - 1) / U, cus = device_cus();
