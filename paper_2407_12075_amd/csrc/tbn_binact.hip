@@ -3,7 +3,7 @@
 // rule Eq. 3 applies to a weight sum -- +1 where it is greater than zero -- and the layer operation stated after
 // Eq. 8 is applied to those signs unchanged).  Activations travel as rows of sign bits, 32 per word.
 //
-// Three kernels:
+// Kernels:
 //   * sign_pack: real activations -> rows of sign bits (one pass over X, 16 bytes per lane where rows are whole
 //     words, a wave ballot otherwise).
 //   * binact_mfma (tile of whole weight rows, in % 256 == 0): Z = S T^T on the matrix cores in the 4-bit float
@@ -20,6 +20,8 @@
 //     assignment is.  The distinct columns are computed once and every replica is written as alpha[t] * Z in whole
 //     128-byte lines after a turn through LDS (Section "CNN Architectures": only one of the tile computations needs
 //     to be executed).
+//   * binact_staged: the same product for small and middle layers, in blocks of 64 x 64 whose four waves share K and whose bits
+//     pass through LDS (the reasons stand at the kernel, the line between the two at binact_staged_preferred).
 //   * binact_generic: every other legal shape, one thread per output, XOR and population count on whole words
 //     where a word lies inside one tile copy, bit by bit where it crosses a tile end.
 #include "tbn_common.h"
@@ -532,6 +534,351 @@ __global__ __launch_bounds__(256, 2) void binact_mfma_kernel(const uint32_t *__r
     }
 }
 
+// ---- matrix-core forward of small and middle layers: sign bits through LDS, K dealt to the waves ------------
+// What bounds it: latency.  One block per CU at most (or two), so a layer takes what one workgroup takes from its first load
+// to its last store.  binact_mfma_kernel's 128 x 128 block is 256 matrix instructions per wave behind loads that touch 32
+// lines each; here a block is 64 x 64, its four waves share K (64 instructions each at in = 4096), and the bits come as
+// whole lines, once per workgroup, 32 KiB at a time through registers into one of two LDS slots, so that a stage's loads run
+// under the products of the one before.  Stamps of 1024 x 4096 -> 4096, k = 8, sign bits out: 1.1 us to the first stage, 2.1 of products, 0.5 to
+// exchange the sums, 1.5 for the words; kernel 13.1 us before and 6.3 now, one row 9.3 / 5.8.  Tried: blocks of 128 x 128 with K dealt to two
+// pairs of waves (13.6 us at any number of rows), products and expansions ordered instruction by instruction through inline
+// assembly (6.2; at 8192 rows 16.7 against 16.3), LDS writes and loads dealt one behind each product (8.5).
+
+struct BinactStagedParams {
+    int64_t M;
+    int32_t out, U;
+    int32_t reps;       // out / U
+    int32_t n_alpha;
+    int32_t tiles_n;    // column blocks
+    uint32_t tiles_m;   // row blocks
+    int32_t n_super;    // in / 256
+    int32_t row_bytes;  // in / 8
+};
+
+// A block of 64 batch rows x 64 distinct columns per workgroup; every wave takes all of it (2 x 2 MFMA tiles) over the
+// super-steps (256 elements of K) congruent to its number (mod 4), and the four sums meet in LDS.
+constexpr int kGroups = 4;                          // groups of waves that share K
+constexpr int kStBM = 64, kStBN = 64;
+constexpr int kStPieces = 4 * kGroups;                   // 16-byte pieces of a row per stage: two super-steps of every group
+constexpr int kStStage = (kStBM + kStBN) * kStPieces * 16;   // 32 KiB
+constexpr int kStStride = kStBN + 4;                // floats per row of a group's sums
+constexpr int kStPlane = kStBM * kStStride;         // floats
+constexpr int kStLds = kGroups * kStPlane * 4 > 2 * kStStage ? kGroups * kStPlane * 4 : 2 * kStStage;
+
+template <typename YT, bool RELU, bool SIGN>
+__global__ __launch_bounds__(256, 2) void binact_staged_kernel(const uint32_t *__restrict__ xbits, YT *__restrict__ y,
+                                                                            const uint32_t *__restrict__ tile,
+                                                                            const float *__restrict__ alpha, BinactStagedParams P) {
+    constexpr int TM = 2, TN = 2, BM = kStBM, BN = kStBN, NP = kStPieces, NF = TM + TN;
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int ln = lane & 31, lh = lane >> 5;
+    const int grp = wave;                                  // K group
+    const uint32_t bid = blockIdx.x;
+    // Workgroup ids are dealt round-robin to the 8 XCDs: the column blocks of one row block take consecutive slots of
+    // one XCD, so that the rows of sign bits they share come from that XCD's L2 (the remaining row blocks: plain order).
+    uint32_t tile_m, tile_n;
+    {
+        const uint32_t tiles_n = static_cast<uint32_t>(P.tiles_n), xcd = bid & 7, slot = bid >> 3;
+        const uint32_t full = (P.tiles_m / 8) * tiles_n;   // slots per XCD in the regular part
+        if (slot < full) {
+            const uint32_t q = slot / tiles_n;
+            tile_n = slot - q * tiles_n;
+            tile_m = q * 8 + xcd;
+        } else {
+            const uint32_t rest = bid - full * 8;
+            const uint32_t q = rest / tiles_n;
+            tile_n = rest - q * tiles_n;
+            tile_m = (P.tiles_m / 8) * 8 + q;
+        }
+    }
+    const int64_t m0 = int64_t(tile_m) * BM;
+    const int32_t n0 = static_cast<int32_t>(tile_n) * BN;
+
+    // ---- the sign bits of a stage: eight 16-byte pieces per thread, whole lines of a row ------------------------
+    // LDS rows 0 .. BM - 1 are the batch rows, the BN behind them the tile rows; row BM + 32 t + l holds distinct column
+    // 32 t + 16*((l >> 2) & 1) + 4*(l >> 3) + (l & 3): the instruction leaves row 8*(r / 4) + 4*lh + r % 4 of its result in
+    // register r, so that register r of a lane is column 32 t + 16*lh + r, sixteen adjacent columns.  Rows past M and columns
+    // past U repeat the last one.  Piece c of row r lies in slot c ^ swizzle(r) of the row: operand reads free of conflicts.
+    constexpr int kPasses = (BM + BN) * NP / 256;          // 8
+    static_assert(kPasses == 8 && BM * NP % 256 == 0, "a pass lies in the batch rows or in the tile rows");
+    auto swizzle = [](int r) { return r & 15; };
+    const unsigned char *src[2] = {reinterpret_cast<const unsigned char *>(xbits) + m0 * P.row_bytes,
+                                   reinterpret_cast<const unsigned char *>(tile) + int64_t(n0) * P.row_bytes};
+    uint32_t from[kPasses], to[kPasses];
+    const int piece = tid % NP;
+#pragma unroll
+    for (int i = 0; i < kPasses; ++i) {
+        const int r = i * (256 / NP) + tid / NP;
+        const bool act = i < BM * NP / 256;
+        const int l = r & 31, c = ((r - BM) & ~31) + 16 * ((l >> 2) & 1) + 4 * (l >> 3) + (l & 3);
+        const int64_t left = act ? P.M - 1 - m0 : int64_t(P.U - 1 - n0);
+        const int want = act ? r : c;
+        from[i] = static_cast<uint32_t>(want < left ? want : static_cast<int>(left)) * static_cast<uint32_t>(P.row_bytes);
+        to[i] = static_cast<uint32_t>(r * NP + (piece ^ swizzle(r))) * 16u;
+    }
+    const int32_t last_piece = P.row_bytes - 16;
+    u32x4_t held[kPasses];   // the stage after the one in LDS
+    auto fetch_all = [&](int32_t stage) __attribute__((always_inline)) {   // behind a row's end: its last piece, never used
+        const int32_t at = stage * (NP * 16) + piece * 16;
+        const uint32_t off = static_cast<uint32_t>(at < last_piece ? at : last_piece);
+#pragma unroll
+        for (int i = 0; i < kPasses; ++i)
+            held[i] = *reinterpret_cast<const u32x4_t *>(src[i < BM * NP / 256 ? 0 : 1] + (from[i] + off));
+    };
+    auto put = [&](int i, uint32_t at) __attribute__((always_inline)) { *reinterpret_cast<u32x4_t *>(lds + at + to[i]) = held[i]; };
+    auto lds_barrier = [] __attribute__((always_inline)) {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+    };
+
+    // Operands of a super-step: piece 2 * (kGroups * j + grp) + lh of rows 32 t + ln, word i for instruction i.
+    uint32_t op_row[NF];
+    int op_swz[NF];
+#pragma unroll
+    for (int f = 0; f < NF; ++f) {
+        const int r = f < TM ? 32 * f + ln : BM + 32 * (f - TM) + ln;
+        op_row[f] = static_cast<uint32_t>(r * NP * 16);
+        op_swz[f] = swizzle(r);
+    }
+    auto read = [&](u32x4_t (&r)[NF], uint32_t at, int j) __attribute__((always_inline)) {
+        const int c = 2 * (kGroups * j + grp) + lh;
+#pragma unroll
+        for (int f = 0; f < NF; ++f)
+            r[f] = *reinterpret_cast<const u32x4_t *>(lds + at + op_row[f] + static_cast<uint32_t>(c ^ op_swz[f]) * 16u);
+    };
+    // 32 sign bits -> 32 four-bit floats: bit 4n + j becomes the sign of value n of register j (0x2 is +1.0, 0xA is -1.0).
+    // A set bit gives -1 in both operands alike, so their products are those of the signs.
+    uint32_t sign_bits = 0x88888888u, one_bits = 0x22222222u;
+    asm volatile("" : "+v"(sign_bits), "+v"(one_bits));   // registers: an and-or takes no constants of this size
+    auto expand = [&](i32x8_t &f, uint32_t word) __attribute__((always_inline)) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) f[j] = static_cast<int>(((word << (3 - j)) & sign_bits) | one_bits);
+    };
+
+    f32x16_t acc[TM][TN];
+#pragma unroll
+    for (int a = 0; a < TM; ++a)
+#pragma unroll
+        for (int b = 0; b < TN; ++b)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) acc[a][b][i] = 0.f;
+
+    const int32_t n_stages = (P.n_super + 2 * kGroups - 1) / (2 * kGroups);
+    fetch_all(0);
+#pragma unroll
+    for (int i = 0; i < kPasses; ++i) put(i, 0);
+    if (n_stages > 1) fetch_all(1);
+    lds_barrier();
+    u32x4_t raw[2][NF];
+    read(raw[0], 0, 0);
+    i32x8_t F[2][NF] = {};   // the upper four words of an operand are not read in this format
+#pragma unroll
+    for (int f = 0; f < NF; ++f) expand(F[0][f], raw[0][f][0]);
+    constexpr int kOne = 0;   // both scale operands zero: the compiler takes the form of the instruction without block scales
+    // One super-step: four groups of four instructions; in front of an instruction one operand of the next group is expanded.
+    auto multiply = [&](const u32x4_t (&r)[NF], const u32x4_t (&r_next)[NF]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int s = i & 1, n = s ^ 1;
+#pragma unroll
+            for (int q = 0; q < NF; ++q) {
+                expand(F[n][q], i < 3 ? r[q][i + 1] : r_next[q][0]);
+                __builtin_amdgcn_sched_barrier(0);
+                const int tm = q >> 1, tn = q & 1;
+                acc[tm][tn] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(F[s][TM + tn], F[s][tm], acc[tm][tn], 4, 4, 0, kOne, 0, kOne);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+    };
+    // Two LDS slots: stage s + 1 goes to LDS while the first half of stage s is multiplied; the barrier between the halves
+    // publishes it and frees the slot of stage s (every wave's reads of it have arrived by then).
+    uint32_t slot = 0;
+    for (int32_t st = 0; st < n_stages; ++st) {
+        const int32_t first = st * (2 * kGroups) + grp;
+        const uint32_t other = slot ^ static_cast<uint32_t>(kStStage);
+        read(raw[1], slot, 1);
+        if (st + 1 < n_stages) {
+#pragma unroll
+            for (int i = 0; i < kPasses; ++i) put(i, other);
+            if (st + 2 < n_stages) fetch_all(st + 2);
+        }
+        if (first < P.n_super) multiply(raw[0], raw[1]);
+        lds_barrier();
+        if (st + 1 < n_stages) read(raw[0], other, 0);
+        if (first + kGroups < P.n_super) multiply(raw[1], raw[0]);
+        slot = other;
+    }
+
+    // ---- the groups' sums meet in LDS (nothing reads the stages behind the last barrier); every replica is written --------
+    float *planes = reinterpret_cast<float *>(lds);
+    constexpr int STR = kStStride;
+    {
+        float *zt = planes + grp * kStPlane;
+#pragma unroll
+        for (int tm = 0; tm < TM; ++tm)
+#pragma unroll
+            for (int tn = 0; tn < TN; ++tn)
+#pragma unroll
+                for (int a = 0; a < 4; ++a) {
+                    const f32x4_t v = {acc[tm][tn][4 * a], acc[tm][tn][4 * a + 1], acc[tm][tn][4 * a + 2], acc[tm][tn][4 * a + 3]};
+                    *reinterpret_cast<f32x4_t *>(zt + (32 * tm + ln) * STR + 32 * tn + 16 * lh + 4 * a) = v;
+                }
+    }
+    // alpha of replica t in lane t (replicas past the 64th are fetched one by one below)
+    float alpha_lanes = alpha[P.n_alpha == 1 ? 0 : (lane < P.reps ? lane : P.reps - 1)];
+    asm volatile("" : "+v"(alpha_lanes));   // loaded by every lane here, not by those with columns below
+    lds_barrier();
+    // a wave takes a quarter of the rows
+    if constexpr (SIGN) {
+        // alpha[t] * z is positive where z and alpha[t] have the same sign: a lane adds up one column of a row, and the votes
+        // "z > 0" and "z < 0" of the wave are the words of 64 columns.  A pass takes as many rows as make 32 words; lane l
+        // stores word l % 32 of the pass for replicas l / 32, l / 32 + 2, ..., the "positive" or the "negative" word by the
+        // sign of that replica's alpha (zero or not a number: no bit).
+        uint32_t *yb = reinterpret_cast<uint32_t *>(y);
+        const int64_t out_words = P.out >> 5;
+        constexpr int WPR = BN / 32, RPP = 32 / WPR;          // words of a row, rows per pass
+        const int slot_w = lane & 31, t_first = lane >> 5;
+        const int32_t colw = n0 + 32 * (slot_w % WPR);
+        const int32_t words_per_replica = P.U >> 5;
+        // the alphas of this lane's first eight replicas (up to 16 replicas in all) are fetched once
+        float al_own[8];
+#pragma unroll
+        for (int c = 0; c < 8; ++c) {
+            const int32_t t = t_first + 2 * c;
+            al_own[c] = alpha[P.n_alpha == 1 ? 0 : (t < P.reps ? t : P.reps - 1)];
+        }
+#pragma unroll 1
+        for (int q = 0; q < BM / 4 / RPP; ++q) {
+            const int row0 = wave * (BM / 4) + q * RPP;
+            uint64_t wp = 0, wn = 0;   // the words of 64 columns that this lane stores one of
+            float part[RPP][BN / 64][kGroups];   // every read is issued before the first sum
+#pragma unroll
+            for (int r = 0; r < RPP; ++r)
+#pragma unroll
+                for (int h = 0; h < BN / 64; ++h)
+#pragma unroll
+                    for (int g = 0; g < kGroups; ++g) part[r][h][g] = planes[g * kStPlane + (row0 + r) * STR + 64 * h + lane];
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int r = 0; r < RPP; ++r) {
+#pragma unroll
+                for (int h = 0; h < BN / 64; ++h) {
+                    float sum = part[r][h][0];
+#pragma unroll
+                    for (int g = 1; g < kGroups; ++g) sum += part[r][h][g];
+                    const uint64_t pos = __ballot(sum > 0.f), neg = __ballot(sum < 0.f);
+                    const bool mine = (slot_w >> 1) == r * (WPR / 2) + h;
+                    wp = mine ? pos : wp;
+                    wn = mine ? neg : wn;
+                }
+            }
+            const int up = 32 * (slot_w & 1);
+            const uint32_t sp = static_cast<uint32_t>(wp >> up), sn = static_cast<uint32_t>(wn >> up);
+            const int64_t m = m0 + row0 + slot_w / WPR;
+            if (m < P.M && colw < P.U) {
+                uint32_t *dst = yb + m * out_words + (colw >> 5);
+#pragma unroll
+                for (int c = 0; c < 8; ++c) {
+                    const int32_t t = t_first + 2 * c;
+                    if (t < P.reps) dst[int64_t(t) * words_per_replica] = al_own[c] > 0.f ? sp : (al_own[c] < 0.f ? sn : 0u);
+                }
+                for (int32_t t = t_first + 16; t < P.reps; t += 2) {
+                    const float al = alpha[P.n_alpha == 1 ? 0 : t];
+                    dst[int64_t(t) * words_per_replica] = al > 0.f ? sp : (al < 0.f ? sn : 0u);
+                }
+            }
+        }
+        return;
+    }
+    // a lane takes eight adjacent columns of one row
+    constexpr int LPR = BN / 8, RPP = 64 / LPR, PASSES = BM / 4 / RPP;   // lanes per row, rows per pass
+    const int c8 = lane % LPR, rsub = lane / LPR;
+    const int row_first = wave * (BM / 4) + rsub;
+    auto sums = [&](int row, f32x4_t &z0, f32x4_t &z1) __attribute__((always_inline)) {
+        const float *z = planes + row * STR + 8 * c8;
+        z0 = *reinterpret_cast<const f32x4_t *>(z);
+        z1 = *reinterpret_cast<const f32x4_t *>(z + 4);
+#pragma unroll
+        for (int g = 1; g < kGroups; ++g) {
+            z0 += *reinterpret_cast<const f32x4_t *>(z + g * kStPlane);
+            z1 += *reinterpret_cast<const f32x4_t *>(z + g * kStPlane + 4);
+        }
+    };
+    const int32_t col = n0 + 8 * c8;
+    if (col < P.U) {
+#pragma unroll 1
+        for (int q = 0; q < PASSES; ++q) {
+            const int row = row_first + q * RPP;
+            const int64_t m = m0 + row;
+            if (m >= P.M) continue;
+            f32x4_t z0, z1;
+            sums(row, z0, z1);
+            YT *yrow = y + m * P.out + col;
+            auto emit = [&](int32_t t, float al) __attribute__((always_inline)) {
+                float v[8];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    v[i] = al * z0[i];
+                    v[4 + i] = al * z1[i];
+                }
+                if (RELU) {
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) v[i] = fmaxf(v[i], 0.f);
+                }
+                if constexpr (sizeof(YT) == 4) {
+                    f32x4_t o0 = {v[0], v[1], v[2], v[3]}, o1 = {v[4], v[5], v[6], v[7]};
+                    *reinterpret_cast<f32x4_t *>(yrow + int64_t(t) * P.U) = o0;
+                    *reinterpret_cast<f32x4_t *>(yrow + int64_t(t) * P.U + 4) = o1;
+                } else {
+                    u32x4_t o;
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) o[i] = pack_bf16x2(v[2 * i], v[2 * i + 1]);
+                    *reinterpret_cast<u32x4_t *>(yrow + int64_t(t) * P.U) = o;
+                }
+            };
+            const int32_t reps_in_lanes = P.reps < 64 ? P.reps : 64;
+            for (int32_t t = 0; t < reps_in_lanes; ++t)
+                emit(t, __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, alpha_lanes), t)));
+            for (int32_t t = 64; t < P.reps; ++t) emit(t, alpha[P.n_alpha == 1 ? 0 : t]);
+        }
+    }
+}
+
+template <typename YT, bool RELU, bool SIGN = false>
+static tbn_status launch_staged_t(const BinactArgs &a, const BinactStagedParams &P) {
+    static const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&binact_staged_kernel<YT, RELU, SIGN>),
+                                                    hipFuncAttributeMaxDynamicSharedMemorySize, kStLds);
+    if (e != hipSuccess) {
+        set_error("tbn_linear_forward_binact: the matrix-core kernel was refused %d bytes of LDS", kStLds);
+        (void)hipGetLastError();
+        return TBN_ERR_DEVICE;
+    }
+    hipLaunchKernelGGL((binact_staged_kernel<YT, RELU, SIGN>), dim3(P.tiles_m * static_cast<uint32_t>(P.tiles_n)), dim3(256),
+                       kStLds, a.stream, a.xbits, static_cast<YT *>(a.y), a.tile, a.alpha, P);
+    return check_launch("tbn_linear_forward_binact (matrix-core kernel)");
+}
+
+static tbn_status launch_binact_staged(const BinactArgs &a) {
+    const int64_t U = a.p / a.in;
+    BinactStagedParams P;
+    P.M = a.M;
+    P.out = static_cast<int32_t>(a.out);
+    P.U = static_cast<int32_t>(U);
+    P.reps = static_cast<int32_t>(a.out / U);
+    P.n_alpha = a.n_alpha;
+    P.tiles_n = static_cast<int32_t>((U + kStBN - 1) / kStBN);
+    P.tiles_m = static_cast<uint32_t>((a.M + kStBM - 1) / kStBM);
+    P.n_super = static_cast<int32_t>(a.in / 256);
+    P.row_bytes = static_cast<int32_t>(a.in / 8);
+    const bool relu = (a.flags & TBN_FLAG_RELU) != 0;
+    if (a.flags & TBN_FLAG_SIGN_OUT) return launch_staged_t<float, false, true>(a, P);
+    if (a.dt == TBN_F32) return relu ? launch_staged_t<float, true>(a, P) : launch_staged_t<float, false>(a, P);
+    return relu ? launch_staged_t<uint16_t, true>(a, P) : launch_staged_t<uint16_t, false>(a, P);
+}
+
 bool binact_mfma_supported(const BinactArgs &a) {
     if (a.p % a.in != 0 || a.in % 256 != 0) return false;
     const int64_t U = a.p / a.in;
@@ -541,6 +888,20 @@ bool binact_mfma_supported(const BinactArgs &a) {
     if ((reinterpret_cast<uintptr_t>(a.xbits) | reinterpret_cast<uintptr_t>(a.tile) | reinterpret_cast<uintptr_t>(a.y)) & 15u) return false;
     const int64_t blocks = ((a.M + 127) / 128) * ((U + 127) / 128);
     return blocks <= 0x7fffffffLL;
+}
+
+// Where the staged kernel's blocks of 64 x 64 beat the 128 x 128 of binact_mfma_kernel (400 drawn layers of 1 - 8192 rows, 256 -
+// 4096 elements and columns, k = 2, 4, 8, as graph replays): a workgroup takes a quarter of the time, so while there is a CU for
+// each of them the larger blocks leave CUs idle (geometric mean 1.41 times as fast at up to 256 blocks, 1024 x 4096 -> 4096, k = 8,
+// bfloat16 out 14.6 us against 7.1, sign bits 13.1 / 6.3).  With two per CU they still win with sign bits out (4096 rows 13.6 / 9.0; 385
+// - 512 blocks 1.16 - 1.36 in the mean) and, up to 384, with real outputs of at least three super-steps; beyond, the operands that
+// are expanded twice as often per product cost more than the filling gains (8192 x 1024 -> 1024, k = 2: 8.0 / 9.5).  Real outputs of up to 64 short
+// rows: 14 x 256 -> 1536, k = 4: 4.1 / 4.6.
+bool binact_staged_preferred(const BinactArgs &a) {
+    const int64_t U = a.p / a.in, blocks = ((a.M + kStBM - 1) / kStBM) * ((U + kStBN - 1) / kStBN);
+    if (a.flags & TBN_FLAG_SIGN_OUT) return blocks <= 512;
+    if (a.in < 768) return a.M > 64 && blocks <= 256;
+    return blocks <= 384;
 }
 
 // the permission for more than 64 KiB of LDS, once per process
@@ -676,7 +1037,7 @@ tbn_status launch_linear_binact(const uint32_t *xbits, void *y, int dt, int64_t 
                                 uint32_t flags, hipStream_t stream) {
     const BinactArgs a{xbits, y, dt, M, in, out, tile, p, k, alpha, n_alpha, flags, stream};
     if (!(flags & TBN_FLAG_FORCE_GENERIC)) {
-        if (binact_mfma_supported(a)) return launch_binact_mfma(a);
+        if (binact_mfma_supported(a)) return binact_staged_preferred(a) ? launch_binact_staged(a) : launch_binact_mfma(a);
         // (at small batches with short rows one thread per output is level or ahead: 64 rows of 1000 bits 12.7 us
         // against 22.4)
         if ((a.M > 64 || a.in >= 2048) && binact_direct_supported(a)) return launch_binact_direct(a);

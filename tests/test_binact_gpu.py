@@ -130,6 +130,26 @@ def test_forward_matrix_core_kernel_exact(tbn, M, cin, out, k, n_alpha, dtype):
     _check(tbn, M, cin, out, k, n_alpha, dtype)
 
 
+# blocks of 64 x 64 and stages of eight super-steps: one and several stages, whole and cut ones, waves without a share, ragged
+# rows and columns (lanes without columns still bring replicas' alphas), more replicas than lanes
+STAGED = [(1, 768, 128, 2, 2), (63, 1792, 96, 1, 1), (65, 2048, 768, 8, 8), (130, 2304, 256, 8, 8), (64, 4352, 320, 2, 1), (3, 6400, 1056, 11, 11), (70, 768, 2240, 70, 70)]
+
+
+@pytest.mark.parametrize("M,cin,out,k,n_alpha", STAGED)
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_forward_staged_kernel_exact(tbn, M, cin, out, k, n_alpha, dtype):
+    _check(tbn, M, cin, out, k, n_alpha, dtype)
+
+
+@pytest.mark.parametrize("M,cin,out,k,n_alpha", STAGED + [(4200, 768, 1064, 1, 1), (4200, 1280, 1088, 1, 1)])
+def test_blocks_and_general_kernel_agree_bit_for_bit(tbn, M, cin, out, k, n_alpha):
+    xbits, tile, alpha = _layer(M, cin, out, k, n_alpha, 6)
+    alpha = alpha * np.where(np.arange(n_alpha) % 3 == 1, -1, 1).astype(np.float32)
+    a = (bits_dev(xbits), cin, dev(tile.view(np.int32)), dev(alpha), out, k)
+    for flags in (0, 1) + ((0x4000,) if out // k % 32 == 0 else ()):
+        assert torch.equal(tbn.tbn_linear_forward_binact(*a, flags=flags), tbn.tbn_linear_forward_binact(*a, flags=flags | 0x100)), flags
+
+
 @pytest.mark.parametrize("M,cin,out,k,n_alpha", [MFMA[3], MFMA[4]])
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_forward_matrix_core_kernel_relu(tbn, M, cin, out, k, n_alpha, dtype):
