@@ -15,12 +15,16 @@
 //   * Rows in LDS are padded with zeros to whole chunks of 64 elements and by 16 bytes, which spreads the operand reads of 16
 //     rows over all banks.
 //   * In a chunk of 64 elements of K lane half lg takes elements 32 lg + 8 s .. + 7 in step s, so that its tile bits of a
-//     column are one 32-bit window (any bit position: two words and a funnel shift), fetched a chunk ahead.
+//     column are one 32-bit window (any bit position: two words and a funnel shift).  The words come four at a time, two chunks
+//     per load: a load of the words touches a line per column whatever its width, 64 cycles of the CU's load path, and word
+//     by word the 16 loads of a wave's first chunks took 3 us and those of a pass as long as its multiplications.
 //   * The +-1 operand is the row operand of v_mfma_f32_32x32x16_bf16 with its lanes numbered so that a lane ends up with eight
 //     adjacent columns of one row of Y; two register sets trade halves (v_permlane16_swap) so that a store instruction
 //     writes 64 bytes of 16 rows, without another pass through LDS.
-// 8192 x 512 -> 4096, k = 1 (the product of a column-tiled layer of 4096 x 4096, k = 8): 48 - 51 us in the block kernel, 38 - 42
-// here: 4 us to start and load the rows, 27 of multiplications (1.3 PFLOP/s), the rest stores that nothing runs under.
+// 8192 x 512 -> 4096, k = 1 (the product of a column-tiled layer of 4096 x 4096, k = 8): 48 - 51 us in the block kernel, 39 here with
+// word loads, 34 now: 3 us to start and load the rows, 25 of multiplications (a pass keeps the matrix pipe 94 % busy, at 1.5 - 1.7 GHz:
+// the power limit), the rest stores that nothing runs under.  8192 x 128 / 256 / 320 / 576 -> 4096: 21.6 / 24.9 / 27.5 / 42.3 before,
+// 18.7 / 23.6 / 25.5 / 39.9 now; 2000 x 384 -> 4096 15.7 / 13.7; with two replicas of 4096 columns of 256 elements 33.1 / 34.0.
 // Tried: 64 rows per workgroup (55 us: twice the vector instructions per matrix instruction), non-temporal stores and wave
 // priorities (no difference).
 #include "tbn_common.h"
@@ -36,6 +40,7 @@ typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
 typedef float f32x2_t __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
+typedef u32x4_t u32x4_a4_t __attribute__((aligned(4)));   // at any word of the tile
 typedef uint16_t u16x2_t __attribute__((ext_vector_type(2)));
 
 constexpr int kThreads = 512, kWaves = 8;
@@ -102,11 +107,60 @@ __global__ __launch_bounds__(kThreads, 2) void linear_short_kernel(const uint16_
     const int rows = static_cast<int>(P.M - m0 < kRows ? P.M - m0 : kRows);
     const uint32_t stride = static_cast<uint32_t>(P.chunks) * 128u + 16u;   // bytes per row in LDS
 
+    const int32_t g_end = static_cast<int32_t>(sp + 1) * P.groups_per_split < P.groups ? static_cast<int32_t>(sp + 1) * P.groups_per_split : P.groups;
+    // tile words of chunk c for a lane's two columns: operand lane l of column tile tn supplies column
+    // 16*(l/8) + 8*((l/4)%2) + 4*tn + l%4 of the 64
+    struct Cols { uint32_t word[2], sh[2]; };
+    auto columns = [&](int32_t g) {
+        Cols k;
+#pragma unroll
+        for (int tn = 0; tn < 2; ++tn) {
+            int32_t u = g * kCols + 16 * (ln >> 3) + 8 * ((ln >> 2) & 1) + 4 * tn + (ln & 3);
+            u = u < P.U ? u : P.U - 1;   // columns past U repeat the last one; never written
+            const uint64_t bit = uint64_t(u) * static_cast<uint32_t>(P.in) + static_cast<uint32_t>(32 * lg);
+            k.word[tn] = static_cast<uint32_t>(bit >> 5);
+            k.sh[tn] = static_cast<uint32_t>(bit & 31);
+        }
+        return k;
+    };
+    // the four words from 2 c on: chunks c and c + 1 (even c).  Past the row's end any value will do, past the tile's nothing may
+    // be read: a lane there takes the last four words and moves them down.
+    auto load_words = [&](const Cols &k, int32_t c, u32x4_t (&w)[2]) {
+#pragma unroll
+        for (int tn = 0; tn < 2; ++tn) {
+            const uint32_t i = k.word[tn] + static_cast<uint32_t>(2 * c), end = P.last_word - 3u;
+            w[tn] = *reinterpret_cast<const u32x4_a4_t *>(tile + (i < end ? i : end));
+        }
+        if (__any(k.word[0] + static_cast<uint32_t>(2 * c) > P.last_word - 3u || k.word[1] + static_cast<uint32_t>(2 * c) > P.last_word - 3u)) {
+#pragma unroll
+            for (int tn = 0; tn < 2; ++tn) {
+                const uint32_t i = k.word[tn] + static_cast<uint32_t>(2 * c), end = P.last_word - 3u, past = i > end ? i - end : 0u;
+                if (past & 1u) w[tn] = u32x4_t{w[tn][1], w[tn][2], w[tn][3], w[tn][3]};
+                if (past & 2u) w[tn] = u32x4_t{w[tn][2], w[tn][3], w[tn][3], w[tn][3]};
+            }
+        }
+    };
+    // inverted windows of chunks 0 .. kAhead - 1 of the next pass, formed before the stores of this one are issued: a load
+    // behind the stores can only be waited for together with them (one counter, in issue order)
+    constexpr int kAhead = 4;
+    uint32_t first[kAhead][2];
+    u32x4_t ring[kAhead / 2][2];   // [pair of chunks][column]
+    Cols cols;
+    auto form = [&](const Cols &k, int d, uint32_t (&win)[2]) {   // chunk d of the four in the ring
+#pragma unroll
+        for (int tn = 0; tn < 2; ++tn) win[tn] = ~__funnelshift_r(ring[d >> 1][tn][2 * (d & 1)], ring[d >> 1][tn][2 * (d & 1) + 1], k.sh[tn]);
+    };
+    // (the first pass's words are requested in front of the rows: behind the barrier they keep the waves waiting)
+    int32_t g = static_cast<int32_t>(sp) * P.groups_per_split + wave;
+    cols = columns(g);
+#pragma unroll
+    for (int h = 0; h < kAhead / 2; ++h) load_words(cols, 2 * h, ring[h]);
+
     // ---- the rows: eight threads per 128 bytes of a row; rows past M repeat the last one (never written) --------------
     {
         const unsigned char *src = reinterpret_cast<const unsigned char *>(x + m0 * P.in);
         constexpr int kPasses = kRows / (kThreads / 8);   // rows per thread
-        constexpr int kDepth = 4;                           // chunks of 128 bytes requested together
+        constexpr int kDepth = 8;                           // chunks of 128 bytes requested together
         uint32_t from[kPasses], to[kPasses];
 #pragma unroll
         for (int i = 0; i < kPasses; ++i) {
@@ -119,6 +173,7 @@ __global__ __launch_bounds__(kThreads, 2) void linear_short_kernel(const uint16_
             u32x4_t v[kDepth][kPasses];
 #pragma unroll
             for (int d = 0; d < kDepth; ++d) {
+                if (c0 + d >= P.chunks) break;
                 const int32_t at = (c0 + d) * 128 + (tid & 7) * 16;
 #pragma unroll
                 for (int i = 0; i < kPasses; ++i)
@@ -136,49 +191,11 @@ __global__ __launch_bounds__(kThreads, 2) void linear_short_kernel(const uint16_
     }
     __syncthreads();
 
-    const int32_t g_end = static_cast<int32_t>(sp + 1) * P.groups_per_split < P.groups ? static_cast<int32_t>(sp + 1) * P.groups_per_split : P.groups;
     uint32_t signs = 0x80008000u, ones = 0x3f803f80u;
     asm volatile("" : "+s"(signs), "+s"(ones));   // scalar registers: an and-or takes no constants of this size
     const unsigned char *a_ptr = s_x + static_cast<uint32_t>(ln) * stride + static_cast<uint32_t>(lg) * 64u;
-    // tile words of chunk c for a lane's two columns: operand lane l of column tile tn supplies column
-    // 16*(l/8) + 8*((l/4)%2) + 4*tn + l%4 of the 64
-    struct Cols { uint32_t word[2], sh[2]; };
-    auto columns = [&](int32_t g) {
-        Cols k;
 #pragma unroll
-        for (int tn = 0; tn < 2; ++tn) {
-            int32_t u = g * kCols + 16 * (ln >> 3) + 8 * ((ln >> 2) & 1) + 4 * tn + (ln & 3);
-            u = u < P.U ? u : P.U - 1;   // columns past U repeat the last one; never written
-            const uint64_t bit = uint64_t(u) * static_cast<uint32_t>(P.in) + static_cast<uint32_t>(32 * lg);
-            k.word[tn] = static_cast<uint32_t>(bit >> 5);
-            k.sh[tn] = static_cast<uint32_t>(bit & 31);
-        }
-        return k;
-    };
-    auto load_words = [&](const Cols &k, int32_t c, uint32_t (&w)[2][2]) {   // past the row's end any value will do
-#pragma unroll
-        for (int tn = 0; tn < 2; ++tn)
-#pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                const uint32_t i = k.word[tn] + static_cast<uint32_t>(2 * c + j);
-                w[tn][j] = tile[i < P.last_word ? i : P.last_word];
-            }
-    };
-    // inverted windows of chunks 0 .. kAhead - 1 of the next pass, formed before the stores of this one are issued: a load
-    // behind the stores can only be waited for together with them (one counter, in issue order)
-    constexpr int kAhead = 4;
-    uint32_t first[kAhead][2], ring[kAhead][2][2];
-    Cols cols;
-    auto form = [&](const Cols &k, const uint32_t (&w)[2][2], uint32_t (&win)[2]) {
-#pragma unroll
-        for (int tn = 0; tn < 2; ++tn) win[tn] = ~__funnelshift_r(w[tn][0], w[tn][1], k.sh[tn]);
-    };
-    int32_t g = static_cast<int32_t>(sp) * P.groups_per_split + wave;
-    cols = columns(g);
-#pragma unroll
-    for (int d = 0; d < kAhead; ++d) load_words(cols, d, ring[d]);
-#pragma unroll
-    for (int d = 0; d < kAhead; ++d) form(cols, ring[d], first[d]);
+    for (int d = 0; d < kAhead; ++d) form(cols, d, first[d]);
     for (; g < g_end; g += kWaves) {
         f32x16_t acc[TM][2];
 #pragma unroll
@@ -226,8 +243,8 @@ __global__ __launch_bounds__(kThreads, 2) void linear_short_kernel(const uint16_
         auto chunk = [&](int32_t c, auto d_c, const uint32_t (&ready)[2], bool formed) {
             constexpr int D = decltype(d_c)::value;
             if (formed) { next[0] = ready[0]; next[1] = ready[1]; }
-            else form(cols, ring[(D + 1) % kAhead], next);
-            if (c + kAhead < P.chunks) load_words(cols, c + kAhead, ring[D]);
+            else form(cols, (D + 1) % kAhead, next);
+            if (D % 2 == 0 && c + kAhead < P.chunks) load_words(cols, c + kAhead, ring[D / 2]);   // both chunks of the pair have been formed
             multiply(win, next);
             win[0] = next[0]; win[1] = next[1];
         };
@@ -245,10 +262,10 @@ __global__ __launch_bounds__(kThreads, 2) void linear_short_kernel(const uint16_
         if (g + kWaves < g_end) {
             cols = columns(g + kWaves);
 #pragma unroll
-            for (int d = 0; d < kAhead; ++d) load_words(cols, d, ring[d]);
+            for (int h = 0; h < kAhead / 2; ++h) load_words(cols, 2 * h, ring[h]);
 #pragma unroll
             for (int d = 0; d < kAhead; ++d) {
-                form(cols, ring[d], first[d]);
+                form(cols, d, first[d]);
                 asm volatile("" : "+v"(first[d][0]), "+v"(first[d][1]) : : "memory");   // not moved behind the stores
             }
         }
@@ -330,7 +347,7 @@ int64_t column_splits(int64_t row_blocks, int64_t passes, int64_t in, int64_t re
 
 // Shapes this kernel takes: whole rows of the tile, 16-byte loads and stores, 128 rows in LDS.
 bool linear_short_supported(const LinearArgs &a) {
-    if (a.dt != TBN_BF16 || a.in % 8 != 0 || a.p % a.in != 0 || a.in > 576 || lds_bytes(a.in) > kLdsMax) return false;
+    if (a.dt != TBN_BF16 || a.in % 8 != 0 || a.p % a.in != 0 || a.in > 576 || a.p < 128 || lds_bytes(a.in) > kLdsMax) return false;
     const int64_t U = a.p / a.in;
     if (U > a.out || a.out % U != 0 || U % 8 != 0 || a.out > (1 << 22) || a.p >= (int64_t(1) << 36)) return false;
     if ((reinterpret_cast<uintptr_t>(a.x) | reinterpret_cast<uintptr_t>(a.y)) & 15u) return false;
