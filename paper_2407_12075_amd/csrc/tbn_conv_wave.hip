@@ -276,7 +276,9 @@ __global__ __launch_bounds__(64 * kMaxWaves, (wave_bound(sizeof(XT) == 4, MT, T,
     constexpr int kBits = 8 * T;                     // bits a lane supplies per chunk
     const int32_t p32 = static_cast<int32_t>(P.p);
     int32_t pos[NFT];
-    uint32_t raw[NFT][T == 1 ? 2 : 4];
+    typedef uint32_t words_t __attribute__((ext_vector_type(T == 1 ? 2 : 4)));
+    typedef words_t words_a4_t __attribute__((aligned(4)));
+    words_t raw[NFT];
 #pragma unroll
     for (int ft = 0; ft < NFT; ++ft) {
         int64_t u = u0 + ft * MT + ln;
@@ -284,15 +286,18 @@ __global__ __launch_bounds__(64 * kMaxWaves, (wave_bound(sizeof(XT) == 4, MT, T,
         const int64_t f = u * P.F + (ks * CK + 8 * q) * T;
         pos[ft] = static_cast<int32_t>(P.aligned ? f : f % P.p);   // whole filters: u < R = p / F (channels past C belong to zero activations)
     }
+    // One load per window: the lanes' windows lie in lines of their own, and a load takes the CU's load path as many cycles as it
+    // touches lines, whatever its width.  Against four loads of a word (3x3, bfloat16): 27 x 512 x 35^2 -> 256, k = 2 122 us before,
+    // 103 now; 5 x 512 x 8 x 7 -> 256, k = 4 12.2 / 10.3; 128 x 256 x 14^2 -> 256, k = 8, float32 27.4 / 26.6.
+    // Nothing is read past the tile: a lane whose window ends there takes the last words and moves them down before it uses them.
+    // (1x1: two words, where the moving costs what a load does.)
+    const int32_t last_words = P.n_words - 4;
     auto load_bits = [&]() {
 #pragma unroll
         for (int ft = 0; ft < NFT; ++ft) {
             const int32_t w = pos[ft] >> 5;
-#pragma unroll
-            for (int i = 0; i < (T == 1 ? 2 : 4); ++i) {
-                const int32_t wi = w + i;
-                raw[ft][i] = tile[wi < P.n_words ? wi : P.n_words - 1];
-            }
+            if constexpr (T == 1) raw[ft] = words_t{tile[w < P.n_words ? w : P.n_words - 1], tile[w + 1 < P.n_words ? w + 1 : P.n_words - 1]};
+            else raw[ft] = *reinterpret_cast<const words_a4_t *>(tile + (w < last_words ? w : last_words));
         }
     };
 
@@ -327,6 +332,13 @@ __global__ __launch_bounds__(64 * kMaxWaves, (wave_bound(sizeof(XT) == 4, MT, T,
 #pragma unroll
         for (int ft = 0; ft < NFT; ++ft) {
             const uint32_t sft = static_cast<uint32_t>(pos[ft] & 31);
+            if constexpr (T != 1) {
+                const int32_t past = (pos[ft] >> 5) - last_words;
+                if (__any(past > 0)) {
+                    if (past > 0 && (past & 1)) raw[ft] = words_t{raw[ft][1], raw[ft][2], raw[ft][3], raw[ft][3]};
+                    if (past > 0 && (past & 2)) raw[ft] = words_t{raw[ft][2], raw[ft][3], raw[ft][3], raw[ft][3]};
+                }
+            }
             uint32_t w[T == 1 ? 1 : 3];
 #pragma unroll
             for (int i = 0; i < (T == 1 ? 1 : 3); ++i) w[i] = __builtin_amdgcn_alignbit(raw[ft][i + 1], raw[ft][i], sft);
