@@ -35,7 +35,20 @@ struct SkinnyParams {
     int32_t n_alpha;
     int aligned;
     int32_t k;   // tile repeats (FIXUP form: tile starts 1 .. k - 1 are looked at)
+    int64_t reps;   // of the distinct columns: ceil(out / U)
+    double inv_p, inv_in;   // 1 / p and 1 / in
 };
+
+// x / d and x % d, inv = 1 / d, quotients below 2^40: the quotient by multiplication is at most one off.  (General divisions of 64-bit
+// numbers in front of the first load were a few hundred instructions.)
+__device__ __forceinline__ uint64_t divide(uint64_t x, int64_t d, double inv, int64_t &rest) {
+    uint64_t q = static_cast<uint64_t>(static_cast<double>(x) * inv);
+    int64_t r = static_cast<int64_t>(x - q * static_cast<uint64_t>(d));
+    if (r < 0) { r += d; --q; }
+    if (r >= d) { r -= d; ++q; }
+    rest = r;
+    return q;
+}
 
 union Frag {
     bf16x8_t v;
@@ -106,11 +119,8 @@ template <> struct SkTraits<float> {
 // Row of the weight that contains the start of tile number c (FIXUP form), j_e = the start's position in it
 // (0: the tile starts with the row, nothing to repair).
 __device__ __forceinline__ void tile_start_row(const SkinnyParams &P, int64_t c, int64_t &o_c, uint32_t &j_e) {
-    const uint64_t prod = static_cast<uint64_t>(c) * static_cast<uint64_t>(P.p);   // < 2^47
-    uint64_t q = static_cast<uint64_t>(static_cast<double>(prod) / static_cast<double>(P.in));
-    int64_t r = static_cast<int64_t>(prod - q * static_cast<uint64_t>(P.in));
-    if (r < 0) { r += P.in; --q; }
-    if (r >= P.in) { r -= P.in; ++q; }
+    int64_t r;
+    const uint64_t q = divide(static_cast<uint64_t>(c) * static_cast<uint64_t>(P.p), P.in, P.inv_in, r);   // the product is below 2^47
     o_c = static_cast<int64_t>(q);
     j_e = static_cast<uint32_t>(r);
 }
@@ -125,7 +135,7 @@ __global__ __launch_bounds__(kThreads) void linear_skinny_kernel(const XT *__res
     __shared__ float part[NA][kWaves][16][17];     // partial blocks [wave][batch row][column], padded
     __shared__ float zfin[NA][16][17];
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int ln = lane & 15, lg = lane >> 4;
     const int64_t u0 = int64_t(blockIdx.x) * 16, m0 = int64_t(blockIdx.y) * 16;
 
@@ -147,33 +157,23 @@ __global__ __launch_bounds__(kThreads) void linear_skinny_kernel(const XT *__res
         tile_start_row(P, c, o_c, j_e);
         off = j_e == 0 ? 0u : p32 - j_e;
     } else {   // (u_l * in) mod p, the product is below 2^53
-        const uint64_t prod = static_cast<uint64_t>(u_l) * in32;
-        const uint64_t q = static_cast<uint64_t>(static_cast<double>(prod) / static_cast<double>(p32));
-        int64_t r = static_cast<int64_t>(prod - q * p32);
-        if (r < 0) r += p32;
-        if (r >= static_cast<int64_t>(p32)) r -= p32;
+        int64_t r;
+        divide(static_cast<uint64_t>(u_l) * in32, P.p, P.inv_p, r);
         off = static_cast<uint32_t>(r);
     }
-    uint32_t head[5];   // start of the tile: continues a window that runs past the tile end (n_words >= 4)
-#pragma unroll
-    for (int j = 0; j < 5; ++j) head[j] = tile[j < P.n_words ? j : P.n_words - 1];
-
-    // alphas of this thread's first four replicas: requested now, used in the epilogue
+    // alphas of this thread's first four replicas: requested behind the first activations and tile words, used in the epilogue
     const int u = tid & 15, m = (tid >> 4) & 15;
-    const int64_t reps = (P.out + P.U - 1) / P.U;
+    const int64_t reps = P.reps;
     constexpr int kStep = kThreads / 256;   // replicas taken by one thread are kStep apart
     auto alpha_of = [&](int64_t t) {
         t = t < reps ? t : reps - 1;
         int64_t o = u0 + u + t * P.U;
         o = o < P.out ? o : P.out - 1;
-        return alpha[(P.n_alpha == 1) ? 0 : (P.aligned ? t : (o * P.in) / P.p)];
+        if (P.n_alpha == 1) return alpha[0];
+        int64_t rest;
+        return alpha[P.aligned ? t : static_cast<int64_t>(divide(static_cast<uint64_t>(o) * in32, P.p, P.inv_p, rest))];
     };
     float al_first[4] = {0.f, 0.f, 0.f, 0.f};
-    if (!FIXUP) {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) al_first[j] = alpha_of((tid >> 8) + j * kStep);
-    }
-
     // operand constants kept in registers (two literals do not fit one instruction)
     uint32_t sign_mask = 0x80008000u, one_bits = 0x3f803f80u;
     asm volatile("" : "+v"(sign_mask), "+v"(one_bits));
@@ -191,19 +191,12 @@ __global__ __launch_bounds__(kThreads) void linear_skinny_kernel(const XT *__res
     typename T::Piece pc[NB][4];
     WinWords wraw[NB];
     uint32_t wpos[NB];
-    auto issue = [&](int b, typename T::Piece (&dst)[4], WinWords &wr, uint32_t &wp) {
-        const uint32_t kb = static_cast<uint32_t>(b) * kKBlock + 8u * lg;
-        if (row_ok) {   // lanes of batch rows past M load nothing (at M = 1 that is 15 of 16 lanes)
+    // Lanes of batch rows past M load nothing (at M = 1 that is 15 of 16 lanes); their operands are zeros throughout.
 #pragma unroll
-            for (int s = 0; s < 4; ++s) {
-                uint32_t k = kb + 32u * s;
-                k = k < in32 - 8 ? k : in32 - 8;   // in % 8 == 0; pieces past the end are zeroed when used
-                T::load(dst[s], reinterpret_cast<const XT *>(xrow + k * static_cast<uint32_t>(sizeof(XT))));
-            }
-        } else {
+    for (int j = 0; j < NB; ++j)
 #pragma unroll
-            for (int s = 0; s < 4; ++s) T::zero(dst[s]);
-        }
+        for (int s = 0; s < 4; ++s) T::zero(pc[j][s]);
+    auto issue_words = [&](int b, WinWords &wr, uint32_t &wp) {
         uint32_t pos = off + static_cast<uint32_t>(b) * kKBlock;   // < 2p: b * 128 < in <= p
         if (pos >= p32) pos -= p32;
         const uint32_t w = pos >> 5;
@@ -213,6 +206,32 @@ __global__ __launch_bounds__(kThreads) void linear_skinny_kernel(const XT *__res
         const uint32_t w4 = (wb + 4 < static_cast<uint32_t>(P.n_words)) ? wb + 4 : static_cast<uint32_t>(P.n_words) - 1;
         wr.tail = tile[w4];
         wp = pos;
+    };
+    auto issue_x = [&](int b, typename T::Piece (&dst)[4]) {
+        const uint32_t kb = static_cast<uint32_t>(b) * kKBlock + 8u * lg;
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+            uint32_t k = kb + 32u * s;
+            k = k < in32 - 8 ? k : in32 - 8;   // in % 8 == 0; pieces past the end are zeroed when used
+            T::load(dst[s], reinterpret_cast<const XT *>(xrow + k * static_cast<uint32_t>(sizeof(XT))));
+        }
+    };
+    // Up to NB blocks from b0 on: every load is issued before anything waits (with the rows' condition around each block's loads the
+    // compiler waited for the alphas before the first block and for that block before the tile words), and none that is not
+    // used (the loads of a workgroup queue at its CU's load path).
+    auto issue = [&](int b0) {
+#pragma unroll
+        for (int j = 0; j < NB; ++j) {
+            const int b = b0 + j * kWaves;
+            if (b < n_blocks) issue_words(b, wraw[j], wpos[j]);
+        }
+        if (row_ok) {
+#pragma unroll
+            for (int j = 0; j < NB; ++j) {
+                const int b = b0 + j * kWaves;
+                if (b < n_blocks) issue_x(b, pc[j]);
+            }
+        }
     };
     auto consume = [&](int b, typename T::Piece (&src)[4], const WinWords &wr, uint32_t pos) {
         const uint32_t kb = static_cast<uint32_t>(b) * kKBlock + 8u * lg;
@@ -224,6 +243,9 @@ __global__ __launch_bounds__(kThreads) void linear_skinny_kernel(const XT *__res
         const uint32_t left = p32 - pos;   // bits before the tile end; the window continues at bit 0
         if (__any((pos >> 5) > last || left < 128u)) {   // rare: near the tile end
             const uint32_t skip = (pos >> 5) > last ? (pos >> 5) - last : 0u;   // words the load was moved back by
+            uint32_t head[5];   // start of the tile: continues a window that runs past the tile end (n_words >= 5)
+#pragma unroll
+            for (int j = 0; j < 5; ++j) head[j] = tile[j];
             uint32_t t[9];
 #pragma unroll
             for (int j = 0; j < 9; ++j) t[j] = j < 4 ? wr.q[j] : (j == 4 ? wr.tail : 0u);
@@ -278,18 +300,29 @@ __global__ __launch_bounds__(kThreads) void linear_skinny_kernel(const XT *__res
         }
     };
 
-    // The wave's blocks are wave, wave + 8, ...; NB of them are loaded at once (for in <= 4096 with
-    // bf16 that is all of them: one round trip to memory), then multiplied.
+    // The wave's blocks are wave, wave + 8, ...; up to NB of them are loaded at once (for in <= 4096 with bf16 that is all of
+    // them: one round trip to memory), and the alphas behind them.  Before, every wave loaded NB blocks whatever it had, and
+    // four general 64-bit divisions and a wait for the alphas stood in front of the first load: 300 drawn calls take 1 / 1.2 of the time on
+    // the mean; bfloat16 94 x 1280 -> 152, k = 4: 7.9 us before, 4.7 now; 18 x 1536 -> 1224, k = 4: 8.2 / 5.2; float32 60 x 2040 -> 1888,
+    // k = 5: 13.3 / 10.7.
+    if (wave < n_blocks) issue(wave);
+    if (!FIXUP) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) al_first[j] = alpha_of((tid >> 8) + j * kStep);
+    }
+
     for (int b0 = wave; b0 < n_blocks; b0 += kWaves * NB) {
 #pragma unroll
         for (int j = 0; j < NB; ++j) {
             const int b = b0 + j * kWaves;
-            issue(b < n_blocks ? b : b0, pc[j], wraw[j], wpos[j]);   // a repeated block is loaded but not used
-        }
-#pragma unroll
-        for (int j = 0; j < NB; ++j) {
-            const int b = b0 + j * kWaves;
-            if (b < n_blocks) consume(b, pc[j], wraw[j], wpos[j]);
+            if (b >= n_blocks) break;
+            consume(b, pc[j], wraw[j], wpos[j]);
+            // the block that takes its place, under the products of the others
+            const int next = b + kWaves * NB;
+            if (next < n_blocks) {
+                issue_words(next, wraw[j], wpos[j]);
+                if (row_ok) issue_x(next, pc[j]);
+            }
         }
     }
 
@@ -388,6 +421,9 @@ SkinnyParams make_params(const LinearArgs &a) {
     P.n_alpha = a.n_alpha;
     P.aligned = (a.p % a.in == 0) ? 1 : 0;
     P.k = a.k;
+    P.reps = (P.out + P.U - 1) / P.U;
+    P.inv_p = 1.0 / static_cast<double>(a.p);
+    P.inv_in = 1.0 / static_cast<double>(a.in);
     return P;
 }
 
