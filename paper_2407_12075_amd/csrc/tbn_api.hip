@@ -69,7 +69,7 @@ static LinearKernel choose_linear(const LinearArgs &a) {
         // 21.5 here; bfloat16, in = 1280 / 4224: 8.8 / 12.4 and 4.6 / 7.5; batch 8: 4096 columns, float32, 5.3 / 10.7 / 17.7 and 5.9 / 10.0 / 16.5)
         const bool tile = !(a.flags & (TBN_FLAG_BLOCK_KERNEL | TBN_FLAG_STREAM_KERNEL));   // these keep the tile kernel out
         if (!(a.flags & TBN_FLAG_LARGE_BATCH) && linear_decode_supported(a) && (a.M * (a.p / a.in) <= 16384 || !linear_skinny_supported(a)))
-            return tile && linear_tile_over_decode(a) ? LinearKernel::Tile : LinearKernel::Decode;
+            return tile && linear_tile_over_decode(a) ? LinearKernel::Tile : linear_skinny_over_decode(a) ? LinearKernel::Skinny : LinearKernel::Decode;
         if (tile && linear_tile_preferred(a))
             return linear_direct_preferred(a, DirectOver::Tile) ? LinearKernel::Direct : LinearKernel::Tile;
         // bfloat16, rows of at most 576 elements and many distinct columns: the rows of a block stay in LDS

@@ -66,6 +66,7 @@ bool linear_short_supported(const LinearArgs &a);    // bfloat16, short rows res
 bool linear_short_preferred(const LinearArgs &a);
 tbn_status launch_linear_short(const LinearArgs &a);
 bool linear_skinny_supported(const LinearArgs &a); // small-batch (decode-shaped) matrix-core kernel
+bool linear_skinny_over_decode(const LinearArgs &a);   // at most 16 rows
 tbn_status launch_linear_skinny(const LinearArgs &a);
 bool linear_decode_supported(const LinearArgs &a); // at most 16 batch rows, tile of whole rows: latency-built GEMV kernel
 tbn_status launch_linear_decode(const LinearArgs &a);

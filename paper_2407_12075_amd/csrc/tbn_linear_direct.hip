@@ -666,14 +666,13 @@ bool linear_direct_preferred(const LinearArgs &a, DirectOver other) {
         return one_slice && W <= 1024 && a.in > kChunkBytes / (f32 ? 4 : 2) && (f32 || a.M <= 4096);
     }
     if (other == DirectOver::SmallBatch) {
-        // more than one workgroup of the small-batch kernel per CU (bfloat16 530 x 2600 -> 190: 12.3 / 8.1; float32
-        // 1000 x 776 -> 250: 20.3 / 6.7); below that rows of whole lines (bfloat16 in = 384 / 768 / 1280 at 64 x 512 columns:
-        // 4.6 / 4.1, 6.4 / 4.5, 7.6 / 5.3, but in = 888, 1168: 5.6 / 6.9, 7.1 / 9.7; float32 in = 512 / 1024 / 1536: 5.6 / 5.0,
-        // 8.0 / 6.5, 7.7 / 8.1).  bfloat16 rows of about 4096: a wave of the small-batch kernel has all its blocks of 128 in
-        // flight there and needs a second round from some 4600 on, a wave here takes one chunk after the other (in = 3840 / 3968 /
-        // 4096 / 4224 / 5120 / 6144: 7.9 / 8.4, 7.6 / 8.2, 8.7 / 8.3, 7.9 / 8.4, 13.4 / 9.7, 13.5 / 10.7).
+        // more than one workgroup of the small-batch kernel per CU (700 drawn calls of up to 16 replicas, that kernel / this one: 257 - 512 of
+        // them bfloat16 1.18 - 1.72, float32 0.96 - 1.43, more 1.28 - 2.46).  Below that the small-batch kernel is the faster one, 0.74 - 0.92
+        // on the mean of each class of lengths, and level on bfloat16 rows of whole lines from 2048 elements on (0.98 - 1.04).
         if (W <= 1024 && ((U + 15) / 16) * ((a.M + 15) / 16) > 256) return true;
-        if (U % 8 != 0 || a.in < 384) return false;
+        // Rows of whole lines with many replicas, which that kernel stores two bytes at a time, and up to 16 rows (calls that the decode
+        // kernel leaves, more than 16384 outputs of Z: 0.85 - 0.92 there too, but the tests' table of kernels has such calls here).
+        if ((a.M > 16 && a.out / U <= 32) || U % 8 != 0 || a.in < 384) return false;
         return f32 ? a.in % 64 == 0 && a.in <= 1280 : a.in % 128 == 0 && (a.in <= 3584 || a.in >= 4608);
     }
     // short rows in few blocks of the block or the streaming kernel (bfloat16 8961 x 256 -> 96: 8.1 / 5.7; 1289 x 256 -> 848:
