@@ -901,7 +901,13 @@ bool binact_staged_preferred(const BinactArgs &a) {
     const int64_t U = a.p / a.in, blocks = ((a.M + kStBM - 1) / kStBM) * ((U + kStBN - 1) / kStBN);
     if (a.flags & TBN_FLAG_SIGN_OUT) return blocks <= 512;
     if (a.in < 768) return a.M > 64 && blocks <= 256;
-    return blocks <= 384;
+    if (blocks <= 384) return true;
+    // Real outputs of long rows, 385 - 2048 blocks, by rounds of two blocks per CU (in = 3072 and 4096, 512 - 2048 distinct columns, 2 and 8
+    // replicas, 80 layers, 128 x 128 blocks / these): float32 0.99 - 1.23; bfloat16 with at most half of the last round filled, where the larger blocks fill
+    // theirs as little, 1.04 - 1.19; with more of it 0.90 - 0.99 at two replicas and at eight 0.97 - 1.09 (in = 3072) and 1.00 - 1.11
+    // (8192 x 4096 -> 4096, k = 8: 21.4 us / 19.8).  in = 2048: 0.83 - 1.02 in bfloat16.
+    if (a.in < 3072 || blocks > 2048) return false;
+    return a.dt == TBN_F32 || (blocks - 1) % 512 < 256 || (a.in >= 4096 && a.out / U >= 8);
 }
 
 // the permission for more than 64 KiB of LDS, once per process

@@ -141,7 +141,8 @@ def test_forward_staged_kernel_exact(tbn, M, cin, out, k, n_alpha, dtype):
     _check(tbn, M, cin, out, k, n_alpha, dtype)
 
 
-@pytest.mark.parametrize("M,cin,out,k,n_alpha", STAGED + [(4200, 768, 1064, 1, 1), (4200, 1280, 1088, 1, 1)])
+@pytest.mark.parametrize("M,cin,out,k,n_alpha", STAGED + [(4200, 768, 1064, 1, 1), (4200, 1280, 1088, 1, 1),
+                                                          (2100, 4096, 2112, 1, 1), (1000, 4096, 8192, 8, 8)])
 def test_blocks_and_general_kernel_agree_bit_for_bit(tbn, M, cin, out, k, n_alpha):
     xbits, tile, alpha = _layer(M, cin, out, k, n_alpha, 6)
     alpha = alpha * np.where(np.arange(n_alpha) % 3 == 1, -1, 1).astype(np.float32)
