@@ -16,8 +16,8 @@ CASES = [
     ("bf16", 5, 2048, 3072, 2, 1, "small-batch"),      # five rows, 16
     ("bf16", 33, 4104, 200, 5, 5, "small-batch"),      # 33: a second round for one wave; tile starts inside rows or not
     ("bf16", 40, 8200, 72, 3, 3, "small-batch"),       # a third
-    ("f32", 10, 1024, 640, 16, 16, "small-batch"),
-    ("f32", 8, 768, 2080, 4, 4, "small-batch"),
+    ("f32", 10, 1024, 640, 16, 16, "decode"),
+    ("f32", 8, 768, 2080, 4, 4, "decode"),
     ("f32", 17, 2056, 80, 5, 1, "small-batch"),        # 17 blocks: a second round for one wave
     ("f32", 21, 6200, 48, 3, 3, "small-batch"),
     ("bf16", 9, 1544, 64, 4, 4, "decode"),             # beyond the lines
@@ -40,3 +40,30 @@ def test_small_batch_exact(dtype, M, cin, cout, k, n_alpha, kernel):
     x = torch.from_numpy(rng.integers(-1, 2, size=(M, cin)).astype(np.float32)).cuda().to(dt)
     args = (x, torch.from_numpy(tile.view(np.int32)).cuda(), torch.from_numpy(alpha).cuda(), cout, k)
     assert torch.equal(tbn.tbn_linear_forward(*args), tbn.tbn_linear_forward(*args, flags=tbn.TBN_FLAG_FORCE_GENERIC))
+
+
+# float32 calls next to the bfloat16 ones that the small-batch kernel takes: its sums of three terms turn an infinity into a NaN
+# and drop what lies below 2^-133, the decode and the direct kernel do neither
+@pytest.mark.parametrize("relu", [False, True])
+@pytest.mark.parametrize("M,cin,cout,k,kernel", [
+    (5, 512, 3328, 4, "decode"), (8, 768, 2080, 4, "decode"), (12, 512, 2048, 4, "decode"), (16, 1024, 1024, 8, "decode"),
+    (16, 1152, 4096, 4, "decode"), (17, 512, 512, 4, "direct"), (32, 1280, 1024, 4, "direct"), (64, 512, 1024, 4, "direct"),
+    (128, 640, 512, 4, "direct"), (200, 1024, 1024, 8, "direct")])
+def test_float32_infinities_nan_and_smallest_numbers(M, cin, cout, k, kernel, relu):
+    from paper_2407_12075_amd import tbn
+    rng = np.random.default_rng(M + cin)
+    x = rng.integers(-999, 1000, size=(M, cin)).astype(np.float32)   # whole numbers: sums are exact in any order
+    x[1::5] *= np.float32(2.0 ** -149)
+    x[2::5, 7] = np.inf
+    x[3::5, cin - 1] = -np.inf
+    x[3::5, 100] = np.inf
+    x[4::5, cin // 2] = np.nan
+    tile = torch.from_numpy(rng.integers(0, 2 ** 32, size=cin * cout // k // 32, dtype=np.uint64).astype(np.uint32).view(np.int32)).cuda()
+    alpha = torch.tensor([2.0 ** (i % 5 - 2) for i in range(k)], device="cuda")
+    args = (torch.from_numpy(x).cuda(), tile, alpha, cout, k)
+    y = tbn.tbn_linear_forward(*args, flags=int(relu))
+    want = tbn.tbn_linear_forward(*args, flags=int(relu) | tbn.TBN_FLAG_FORCE_GENERIC)
+    assert torch.isinf(want[2]).any() and (want[1] != 0).any()
+    assert torch.equal(torch.isnan(y), torch.isnan(want)) and torch.equal(torch.nan_to_num(y, 3.0, posinf=torch.inf, neginf=-torch.inf),
+                                                                         torch.nan_to_num(want, 3.0, posinf=torch.inf, neginf=-torch.inf))
+    assert tbn.tbn_linear_forward_kernel(torch.float32, M, cin, cout, k, k) == kernel
