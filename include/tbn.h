@@ -306,6 +306,13 @@ tbn_status tbn_linear_forward_binact(const uint32_t *xbits, void *y, tbn_dtype y
                                      int32_t n_alpha, uint32_t flags, void *stream);
 
 /*
+ * Which kernel tbn_linear_forward_binact would launch for these arguments, as tbn_linear_forward_kernel (a tile address of 16-byte
+ * alignment assumed): "staged", "matrix-core", "direct" or "generic"; "" on sizes tbn_linear_forward_binact would reject.
+ */
+const char *tbn_linear_forward_binact_kernel(const uint32_t *xbits, const void *y, tbn_dtype y_dt, int64_t M, int64_t in,
+                                             int64_t out, int32_t k, int32_t n_alpha, uint32_t flags);
+
+/*
  * Measurement aids.  No part of the method (the paper reports no kernel timings; its Section "GPU Inference Kernel"
  * measures memory only): they give the benchmark its denominators, measured the same way as the layer kernels.
  *

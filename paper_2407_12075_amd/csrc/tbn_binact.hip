@@ -1010,6 +1010,18 @@ tbn_status launch_binact_direct(const BinactArgs &a) {
     return check_launch("tbn_linear_forward_binact (direct kernel)");
 }
 
+enum class BinactKernel { Staged, MatrixCore, Direct, Generic };
+
+BinactKernel choose_binact(const BinactArgs &a) {
+    if (!(a.flags & TBN_FLAG_FORCE_GENERIC)) {
+        if (binact_mfma_supported(a)) return binact_staged_preferred(a) ? BinactKernel::Staged : BinactKernel::MatrixCore;
+        // (at small batches with short rows one thread per output is level or ahead: 64 rows of 1000 bits 12.7 us
+        // against 22.4)
+        if ((a.M > 64 || a.in >= 2048) && binact_direct_supported(a)) return BinactKernel::Direct;
+    }
+    return BinactKernel::Generic;
+}
+
 }  // namespace
 
 tbn_status launch_sign_pack(const void *x, int dt, int64_t M, int64_t in, uint32_t *xbits, hipStream_t stream) {
@@ -1042,13 +1054,24 @@ tbn_status launch_linear_binact(const uint32_t *xbits, void *y, int dt, int64_t 
                                 const uint32_t *tile, int64_t p, int32_t k, const float *alpha, int32_t n_alpha,
                                 uint32_t flags, hipStream_t stream) {
     const BinactArgs a{xbits, y, dt, M, in, out, tile, p, k, alpha, n_alpha, flags, stream};
-    if (!(flags & TBN_FLAG_FORCE_GENERIC)) {
-        if (binact_mfma_supported(a)) return binact_staged_preferred(a) ? launch_binact_staged(a) : launch_binact_mfma(a);
-        // (at small batches with short rows one thread per output is level or ahead: 64 rows of 1000 bits 12.7 us
-        // against 22.4)
-        if ((a.M > 64 || a.in >= 2048) && binact_direct_supported(a)) return launch_binact_direct(a);
+    switch (choose_binact(a)) {
+        case BinactKernel::Staged: return launch_binact_staged(a);
+        case BinactKernel::MatrixCore: return launch_binact_mfma(a);
+        case BinactKernel::Direct: return launch_binact_direct(a);
+        case BinactKernel::Generic: break;
     }
     return launch_binact_generic(a);
+}
+
+const char *linear_binact_kernel_name(const uint32_t *xbits, const void *y, int dt, int64_t M, int64_t in, int64_t out, int64_t p,
+                                      int32_t k, int32_t n_alpha, uint32_t flags) {
+    switch (choose_binact(BinactArgs{xbits, const_cast<void *>(y), dt, M, in, out, nullptr, p, k, nullptr, n_alpha, flags, nullptr})) {
+        case BinactKernel::Staged: return "staged";
+        case BinactKernel::MatrixCore: return "matrix-core";
+        case BinactKernel::Direct: return "direct";
+        case BinactKernel::Generic: break;
+    }
+    return "generic";
 }
 
 }  // namespace tbn

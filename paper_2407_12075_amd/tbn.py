@@ -102,6 +102,8 @@ def lib() -> ctypes.CDLL:
         L.tbn_diag_mfma_fp4.argtypes = [_c_i32, _c_i32, _c_vp, _c_vp]
         L.tbn_diag_conv_plan_searches.restype = _c_i64
         L.tbn_diag_conv_plan_searches.argtypes = []
+        L.tbn_linear_forward_binact_kernel.restype = ctypes.c_char_p
+        L.tbn_linear_forward_binact_kernel.argtypes = [_c_vp, _c_vp, ctypes.c_int, _c_i64, _c_i64, _c_i64, _c_i32, _c_i32, _c_u32]
         L.tbn_conv2d_forward_kernel.restype = ctypes.c_char_p
         L.tbn_conv2d_forward_kernel.argtypes = [_c_vp, _c_vp, ctypes.c_int, *[_c_i64] * 5, *[_c_i32] * 8, _c_u32]
         global _host
@@ -463,6 +465,13 @@ def tbn_linear_forward_binact(xbits: torch.Tensor, cin: int, tile: torch.Tensor,
     if st != TBN_OK:
         _raise(st)
     return y
+
+
+def tbn_linear_forward_binact_kernel(dtype: torch.dtype, M: int, cin: int, out_features: int, k: int, n_alpha: int = 1,
+                                     flags: int = 0) -> str:
+    """Name of the kernel tbn_linear_forward_binact would launch for these sizes and aligned tensors ("" on sizes it rejects)."""
+    dt = TBN_F32 if dtype == torch.float32 else TBN_BF16
+    return lib().tbn_linear_forward_binact_kernel(None, None, dt, M, cin, out_features, k, n_alpha, flags).decode()
 
 
 def tbn_diag_empty_launch(stream=None) -> None:

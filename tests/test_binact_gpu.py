@@ -110,6 +110,7 @@ def _check(tbn, M, cin, out, k, n_alpha, dtype, flags=0, seed=0, dirty_padding=F
         assert np.abs(got - ref).max() <= tol * scale
 
 
+# Most of these are small enough for the staged kernel; those that the 128 x 128 kernel serves stand at LARGE below.
 MFMA = [
     # M, in, out, k, n_alpha      (tile of whole rows, in % 256 == 0, U % 8 == 0)
     (64, 256, 64, 1, 1),          # one super-step
@@ -138,6 +139,7 @@ STAGED = [(1, 768, 128, 2, 2), (63, 1792, 96, 1, 1), (65, 2048, 768, 8, 8), (130
 @pytest.mark.parametrize("M,cin,out,k,n_alpha", STAGED)
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_forward_staged_kernel_exact(tbn, M, cin, out, k, n_alpha, dtype):
+    assert tbn.tbn_linear_forward_binact_kernel(torch.float32 if dtype == "f32" else torch.bfloat16, M, cin, out, k, n_alpha) == "staged"
     _check(tbn, M, cin, out, k, n_alpha, dtype)
 
 
@@ -147,8 +149,40 @@ def test_blocks_and_general_kernel_agree_bit_for_bit(tbn, M, cin, out, k, n_alph
     xbits, tile, alpha = _layer(M, cin, out, k, n_alpha, 6)
     alpha = alpha * np.where(np.arange(n_alpha) % 3 == 1, -1, 1).astype(np.float32)
     a = (bits_dev(xbits), cin, dev(tile.view(np.int32)), dev(alpha), out, k)
+    large = (M, cin, out, k) in [(4200, 768, 1064, 1), (4200, 1280, 1088, 1)]   # 66 x 17 blocks
     for flags in (0, 1) + ((0x4000,) if out // k % 32 == 0 else ()):
+        name = tbn.tbn_linear_forward_binact_kernel(torch.float32, M, cin, out, k, n_alpha, flags)
+        assert name == ("matrix-core" if large or (flags == 0x4000 and M == 2100) else "staged")
         assert torch.equal(tbn.tbn_linear_forward_binact(*a, flags=flags), tbn.tbn_linear_forward_binact(*a, flags=flags | 0x100)), flags
+
+
+# Past the lines of the staged kernel, and calls that it takes for their rounds of workgroups: M, in, out, k, flags, dtype, kernel.
+# Exact against the kernel with one thread per output, alphas of both signs, zero among them.
+LARGE = [
+    (4200, 768, 8 * 544, 8, 0x4000, "f32", "matrix-core"),        # sign bits: 66 x 9 blocks of 64 x 64, an alpha per lane and a second
+    (3000, 512, 20 * 704, 20, 0x4000, "f32", "matrix-core"),      # more than 16 replicas
+    (8192, 4096, 4096, 8, 0x4000, "f32", "matrix-core"),
+    (4200, 1024, 8 * 544, 8, 1, "bf16", "matrix-core"),           # ReLU, eight replicas
+    (4200, 1024, 8 * 544, 8, 0, "bf16", "matrix-core"),
+    (2900, 2560, 3 * 584, 3, 1, "f32", "matrix-core"),
+    (40, 512, 5 * 264, 5, 1, "bf16", "matrix-core"),              # few short rows
+    (1000, 4096, 16 * 1600, 16, 1, "bf16", "staged"),             # 16 x 25 blocks: the last round less than half filled
+    (2048, 4096, 8 * 1024, 8, 0, "bf16", "staged"),               # 512: eight replicas
+    (2048, 4096, 2 * 1024, 2, 0, "bf16", "matrix-core"),          # two
+    (2048, 4096, 2 * 1024, 2, 1, "f32", "staged"),
+    (8400, 4096, 2 * 1024, 2, 0, "f32", "matrix-core"),           # 2112
+]
+
+
+@pytest.mark.parametrize("M,cin,out,k,flags,dtype,kernel", LARGE)
+def test_large_layers_agree_with_the_general_kernel(tbn, M, cin, out, k, flags, dtype, kernel):
+    dt = torch.float32 if dtype == "f32" else torch.bfloat16
+    assert tbn.tbn_linear_forward_binact_kernel(dt, M, cin, out, k, k, flags) == kernel
+    g = torch.Generator(device="cuda").manual_seed(M + cin + k)
+    words = lambda *shape: torch.randint(-2 ** 31, 2 ** 31, shape, generator=g, device="cuda", dtype=torch.int64).int()
+    alpha = torch.rand(k, generator=g, device="cuda") * torch.tensor([(1.0, -1.0, 1.0, -1.0, 0.0)[t % 5] for t in range(k)], device="cuda")
+    a = (words(M, cin // 32), cin, words(cin * out // k // 32), alpha, out, k, dt)
+    assert torch.equal(tbn.tbn_linear_forward_binact(*a, flags=flags), tbn.tbn_linear_forward_binact(*a, flags=flags | 0x100))
 
 
 @pytest.mark.parametrize("M,cin,out,k,n_alpha", [MFMA[3], MFMA[4]])
