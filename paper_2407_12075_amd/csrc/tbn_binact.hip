@@ -902,12 +902,15 @@ bool binact_staged_preferred(const BinactArgs &a) {
     if (a.flags & TBN_FLAG_SIGN_OUT) return blocks <= 512;
     if (a.in < 768) return a.M > 64 && blocks <= 256;
     if (blocks <= 384) return true;
-    // Real outputs of long rows, 385 - 2048 blocks, by rounds of two blocks per CU (in = 3072 and 4096, 512 - 2048 distinct columns, 2 and 8
-    // replicas, 80 layers, 128 x 128 blocks / these): float32 0.99 - 1.23; bfloat16 with at most half of the last round filled, where the larger blocks fill
-    // theirs as little, 1.04 - 1.19; with more of it 0.90 - 0.99 at two replicas and at eight 0.97 - 1.09 (in = 3072) and 1.00 - 1.11
-    // (8192 x 4096 -> 4096, k = 8: 21.4 us / 19.8).  in = 2048: 0.83 - 1.02 in bfloat16.
-    if (a.in < 3072 || blocks > 2048) return false;
-    return a.dt == TBN_F32 || (blocks - 1) % 512 < 256 || (a.in >= 4096 && a.out / U >= 8);
+    // Real outputs of long rows, 385 - 2048 blocks, by rounds of two blocks per CU (2 x 420 layers of 2048 - 16384 elements and 1 - 16
+    // replicas, graph replays, 128 x 128 blocks / these, range and mean): from 4096 elements on float32 0.97 - 1.63, 1.22; bfloat16 with at
+    // most half of the last round filled, where the larger blocks fill theirs as little, 0.97 - 1.59, 1.23, with more of it at eight replicas
+    // 0.96 - 1.82, 1.27 (8192 x 4096 -> 4096, k = 8: 21.4 us / 19.8; fewer replicas 0.96 - 1.71, not taken).  3072 - 3840 elements: at eight
+    // replicas and more 0.94 - 1.38, 1.10 over the layers taken; at fewer 0.76 - 1.38, mostly lost (1947 x 3328 -> 3392, k = 1, bfloat16: 16.8 us / 22.2).
+    // Shorter: 0.74 - 1.38.  Of the 256 layers of both draws that these lines take six are more than 3 % slower, by 6 % at most.
+    const int64_t reps = a.out / U;
+    if (a.in < (reps >= 8 ? 3072 : 4096) || blocks > 2048) return false;
+    return a.dt == TBN_F32 || (blocks - 1) % 512 < 256 || (a.in >= 4096 && reps >= 8);
 }
 
 // the permission for more than 64 KiB of LDS, once per process

@@ -179,6 +179,24 @@ def test_many_replicas_of_a_few_rows(lib, M, cin, U, k, expected):
     assert tbn.tbn_linear_forward_kernel(torch.bfloat16, M, cin, U * k, k, 1) == expected
 
 
+# layers on sign bits with real outputs: the 64 x 64 blocks of the staged kernel end at 384 of them, with long rows at 2048
+@pytest.mark.parametrize("dtype,M,cin,out,k,expected", [
+    ("bf16", 8192, 4096, 4096, 8, "staged"), ("f32", 2048, 4096, 2048, 2, "staged"),
+    ("bf16", 384, 3328, 4096, 1, "staged"),           # 384
+    ("bf16", 1947, 3328, 3392, 1, "matrix-core"),     # 1643, one replica
+    ("f32", 3406, 3840, 2048, 1, "matrix-core"),
+    ("bf16", 2292, 3584, 12288, 4, "matrix-core"),
+    ("f32", 2048, 3072, 7 * 1024, 7, "matrix-core"), ("f32", 2048, 3072, 8 * 1024, 8, "staged"),
+    ("f32", 2048, 2816, 8 * 1024, 8, "matrix-core"),
+    ("bf16", 1000, 3584, 8 * 1600, 8, "matrix-core"), ("bf16", 2300, 3584, 8 * 1024, 8, "staged"),   # a last round of 400 and of 64 in 512
+])
+def test_kernel_choice_of_layers_on_sign_bits(lib, dtype, M, cin, out, k, expected):
+    import torch
+    from paper_2407_12075_amd import tbn
+    dt = torch.float32 if dtype == "f32" else torch.bfloat16
+    assert tbn.tbn_linear_forward_binact_kernel(dt, M, cin, out, k, 1) == expected
+
+
 # bfloat16, rows in multiples of 8 that the general and the windowed kernel both take: M, in, out, k, n_alpha, expected
 WINDOW_CHOICE = [
     (3141, 3608, 80, 11, 1, "general"),       # 17.6 tile starts among a block's rows

@@ -166,8 +166,9 @@ LARGE = [
     (4200, 1024, 8 * 544, 8, 0, "bf16", "matrix-core"),
     (2900, 2560, 3 * 584, 3, 1, "f32", "matrix-core"),
     (40, 512, 5 * 264, 5, 1, "bf16", "matrix-core"),              # few short rows
-    (1000, 4096, 16 * 1600, 16, 1, "bf16", "staged"),             # 16 x 25 blocks: the last round less than half filled
-    (2048, 4096, 8 * 1024, 8, 0, "bf16", "staged"),               # 512: eight replicas
+    (1000, 4096, 16 * 1600, 16, 1, "bf16", "staged"),             # 16 x 25 blocks, sixteen replicas
+    (2048, 4096, 8 * 1024, 8, 0, "bf16", "staged"),               # 512: eight
+    (2300, 4096, 2 * 1024, 2, 0, "bf16", "staged"),               # 576: a last round of 64
     (2048, 4096, 2 * 1024, 2, 0, "bf16", "matrix-core"),          # two
     (2048, 4096, 2 * 1024, 2, 1, "f32", "staged"),
     (8400, 4096, 2 * 1024, 2, 0, "f32", "matrix-core"),           # 2112
