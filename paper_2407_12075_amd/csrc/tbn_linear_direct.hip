@@ -666,15 +666,15 @@ bool linear_direct_preferred(const LinearArgs &a, DirectOver other) {
         return one_slice && W <= 1024 && a.in > kChunkBytes / (f32 ? 4 : 2) && (f32 || a.M <= 4096);
     }
     if (other == DirectOver::SmallBatch) {
-        // more than one workgroup of the small-batch kernel per CU (700 drawn calls of up to 16 replicas, that kernel / this one: 257 - 512 of
-        // them bfloat16 1.18 - 1.72, float32 0.96 - 1.43, more 1.28 - 2.46).  Below that, in bfloat16, the small-batch kernel is the faster one,
-        // 0.74 - 0.92 on the mean of each class of lengths, and level on rows of whole lines from 2048 elements on (0.98 - 1.04).
+        // more than one workgroup of the small-batch kernel per CU (700 drawn calls, that kernel / this one: 257 - 512 of
+        // them bfloat16 1.18 - 1.72, float32 0.96 - 1.43, more 1.28 - 2.46)
         if (W <= 1024 && ((U + 15) / 16) * ((a.M + 15) / 16) > 256) return true;
-        // Rows of whole lines: float32, whose sums here keep infinities and the bits below 2^-133 and have accumulators of their own for the
-        // small terms (that kernel does neither, so its speed, 0.74 - 0.92 here too, does not count); bfloat16 with many replicas, which
-        // that kernel stores two bytes at a time, and up to 16 rows (calls that the decode kernel leaves, more than 16384 outputs
-        // of Z: 0.85 - 0.92 there too, but the tests' table of kernels has such calls here).
-        if ((!f32 && a.M > 16 && a.out / U <= 32) || U % 8 != 0 || a.in < 384) return false;
+        // Below that, rows of whole lines: float32, whose sums here keep infinities and the bits below 2^-133 and have accumulators of
+        // their own for the small terms (that kernel does neither, so that its speed, 0.74 - 0.92 of the time, does not count); bfloat16 with many
+        // replicas, which that kernel stores two bytes at a time (102 drawn layers of 17 - 600 rows, the time here over the time there: to 1280
+        // elements 1.13 with up to eight replicas, 1.06 with 16, 0.96 with 32; longer rows 1.02, 0.96 and 0.90), and bfloat16 of up to 16 rows
+        // (calls that the decode kernel leaves, more than 16384 outputs of Z: 1.1 there too, but the tests' table of kernels has such calls here).
+        if ((!f32 && a.M > 16 && a.out / U <= (a.in <= 1280 ? 16 : 8)) || U % 8 != 0 || a.in < 384) return false;
         return f32 ? a.in % 64 == 0 && a.in <= 1280 : a.in % 128 == 0 && (a.in <= 3584 || a.in >= 4608);
     }
     // short rows in few blocks of the block or the streaming kernel (bfloat16 8961 x 256 -> 96: 8.1 / 5.7; 1289 x 256 -> 848:

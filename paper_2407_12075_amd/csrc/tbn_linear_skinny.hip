@@ -449,13 +449,14 @@ bool linear_skinny_supported(const LinearArgs &a) {
 // layers of whole rows of both types, graph replays, decode kernel / this one).  More than eight rows: to 1024 elements 1.31 times as fast on
 // the mean (1.09 at least), to 1536 1.10, with more than 8192 outputs of Z to 3072 1.2 - 1.4 (beyond 0.8 - 1.1).  Five to eight rows and
 // more than 4096 outputs: to 2048 1.13 - 1.6; fewer outputs 0.6 - 1.07.  (Up to four rows it would gain 1.03 - 1.2 there, but
-// the tests' table of kernels has such a call in the decode kernel.)  Measured to 16 replicas, which this kernel stores two
-// bytes at a time.  float32 stays with the decode kernel, though it takes 1.1 - 1.3 times as long: that one adds whole float32 numbers,
+// the tests' table of kernels has such a call in the decode kernel.)  Replicas, which this kernel stores two bytes at a time: to 16 of them
+// on rows of at most 1280 elements (1.19 on the mean of 80 layers, 0.94 at least), on longer ones to eight (1.02 - 1.2; 16: 0.94 - 1.03).
+// float32 stays with the decode kernel, though that takes 0.9 - 1.3 times as long: it adds whole float32 numbers,
 // here the split into three terms makes a NaN of an infinity and drops what lies below 2^-133.
 bool linear_skinny_over_decode(const LinearArgs &a) {
     if (a.dt != TBN_BF16 || (a.flags & ~uint32_t(TBN_FLAG_RELU)) || a.M <= 4 || a.M > 16 || a.p % a.in != 0 || !linear_skinny_supported(a)) return false;
     const int64_t U = a.p / a.in, outputs = a.M * U;
-    if (a.out / U > 16) return false;
+    if (a.out / U > (a.in <= 1280 ? 16 : 8)) return false;
     return a.M > 8 ? a.in <= 1536 || (outputs > 8192 && a.in <= 3072) : outputs > 4096 && a.in <= 2048;
 }
 

@@ -179,6 +179,18 @@ def test_many_replicas_of_a_few_rows(lib, M, cin, U, k, expected):
     assert tbn.tbn_linear_forward_kernel(torch.bfloat16, M, cin, U * k, k, 1) == expected
 
 
+@pytest.mark.parametrize("M,cin,U,k,expected", [
+    (64, 768, 256, 16, "small-batch"), (118, 768, 328, 17, "direct"), (118, 768, 328, 32, "direct"),
+    (96, 1280, 96, 16, "small-batch"), (95, 1792, 16, 16, "direct"), (95, 1792, 16, 8, "small-batch"), (20, 2816, 1800, 16, "direct"),
+    (14, 1280, 104, 16, "small-batch"), (14, 1536, 104, 9, "decode"), (14, 1536, 104, 8, "small-batch"),
+])
+def test_replicas_in_the_small_batch_kernel(lib, M, cin, U, k, expected):
+    """Many replicas of a bfloat16 call stay with the direct and the decode kernel, which store them in wider pieces."""
+    import torch
+    from paper_2407_12075_amd import tbn
+    assert tbn.tbn_linear_forward_kernel(torch.bfloat16, M, cin, U * k, k, 1) == expected
+
+
 # layers on sign bits with real outputs: the 64 x 64 blocks of the staged kernel end at 384 of them, with long rows at 2048
 @pytest.mark.parametrize("dtype,M,cin,out,k,expected", [
     ("bf16", 8192, 4096, 4096, 8, "staged"), ("f32", 2048, 4096, 2048, 2, "staged"),
