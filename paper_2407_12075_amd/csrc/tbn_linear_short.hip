@@ -24,7 +24,8 @@
 // 8192 x 512 -> 4096, k = 1 (the product of a column-tiled layer of 4096 x 4096, k = 8): 48 - 51 us in the block kernel, 39 here with
 // word loads, 34 now: 3 us to start and load the rows, 25 of multiplications (a pass keeps the matrix pipe 94 % busy, at 1.5 - 1.7 GHz:
 // the power limit), the rest stores that nothing runs under.  8192 x 128 / 256 / 320 / 576 -> 4096: 21.6 / 24.9 / 27.5 / 42.3 before,
-// 18.7 / 23.6 / 25.5 / 39.9 now; 2000 x 384 -> 4096 15.7 / 13.7; with two replicas of 4096 columns of 256 elements 33.1 / 34.0.
+// 18.7 / 23.6 / 25.5 / 39.9 now; 2000 x 384 -> 4096 15.7 / 13.7; with two replicas of 4096 columns of 256 elements
+// 34.6 / 34.3 (36.3 with all waves starting together).
 // Tried: 64 rows per workgroup (55 us: twice the vector instructions per matrix instruction), non-temporal stores and wave
 // priorities (no difference).
 #include "tbn_common.h"
@@ -47,6 +48,9 @@ constexpr int kThreads = 512, kWaves = 8;
 constexpr int TM = 4, kRows = 32 * TM;   // rows per workgroup, all of them taken by every wave
 constexpr int kCols = 64;         // columns per wave and pass
 constexpr int kLdsMax = 160 * 1024;
+// Two replicas, rows of at most this many chunks: wave after wave starts (80 drawn layers, together / one after another: 64 - 256 elements 1.05
+// times as fast on the mean, to 384 0.98 - 1.16, 544 and 576 0.94 - 0.99; 8192 x 256 -> 8192 36.3 us / 34.3, 10531 x 96 -> 8192 41.3 / 33.9)
+constexpr int kStaggerChunks = 6;
 
 union Frag {
     bf16x8_t v;
@@ -190,6 +194,11 @@ __global__ __launch_bounds__(kThreads, 2) void linear_short_kernel(const uint16_
         }
     }
     __syncthreads();
+
+    // Two replicas: the waves' stores are as long as their multiplications, and only those that start apart run under another
+    // wave's.  (The word by word loads of tile bits had spread the waves by the time they queued.)
+    if (P.reps > 1 && P.chunks <= kStaggerChunks)
+        for (int i = 0; i < wave; ++i) __builtin_amdgcn_s_sleep(16);   // 1024 cycles each
 
     uint32_t signs = 0x80008000u, ones = 0x3f803f80u;
     asm volatile("" : "+s"(signs), "+s"(ones));   // scalar registers: an and-or takes no constants of this size
