@@ -64,7 +64,8 @@ static LinearKernel choose_linear(const LinearArgs &a) {
     if (!(a.flags & TBN_FLAG_FORCE_GENERIC)) {
         // at most 16 batch rows: the decode kernel (a workgroup per two distinct columns reads all of X).  With many distinct columns the
         // kernels whose workgroups share X among more columns are faster: bfloat16 with K in four slices or more the one with one wave per 32
-        // rows (rules and figures in tbn_linear_tile.hip), otherwise and in float32, at 8 - 16 rows, the small-batch kernel or the direct one
+        // rows (rules and figures in tbn_linear_tile.hip), bfloat16 of 5 - 16 short rows or many outputs the small-batch kernel
+        // (linear_skinny_over_decode); with more than 16384 outputs of Z either type takes the small-batch kernel or the direct one
         // (graph replays, 2048 distinct columns, batch 16, float32, in = 1024 / 4096 / 8192: 9.1 / 16.5 / 26.1 us in the decode kernel, 5.9 / 12.2 /
         // 21.5 here; bfloat16, in = 1280 / 4224: 8.8 / 12.4 and 4.6 / 7.5; batch 8: 4096 columns, float32, 5.3 / 10.7 / 17.7 and 5.9 / 10.0 / 16.5)
         const bool tile = !(a.flags & (TBN_FLAG_BLOCK_KERNEL | TBN_FLAG_STREAM_KERNEL));   // these keep the tile kernel out

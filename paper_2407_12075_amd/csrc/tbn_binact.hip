@@ -14,14 +14,16 @@
 //     up in a table of 64 KiB in LDS, four address and four read instructions and a table to fill per workgroup:
 //     8192 x 4096 -> 4096, k = 8, sign bits out 17.4 us against 15.1, bfloat16 out 23.8 against 21.2; one row 13.2 against 9.4;
 //     8192 x 256 -> 4096, k = 2, sign bits out 20.6 against 12.5.)  What bounds it now is the loads of the bits, 16 bytes from
-//     each of 32 rows per instruction; sending them through LDS in stages of 1024 bits measured the same at 4096 columns
-//     (141 us against 150 at 16384, k = 2) and 2 us slower at one row, fetching them three super-steps ahead 1 us slower.  Both operands
+//     each of 32 rows per instruction; in its 128 x 128 blocks sending them through LDS in stages of 1024 bits measured the same at 4096 columns
+//     (141 us against 150 at 16384, k = 2) and 2 us slower at one row (binact_staged, which does it, has a quarter of the block's
+//     products per wave besides), fetching them three super-steps ahead 1 us slower.  Both operands
 //     use the same assignment of K to lanes and registers, so a dot product does not depend on what that
 //     assignment is.  The distinct columns are computed once and every replica is written as alpha[t] * Z in whole
 //     128-byte lines after a turn through LDS (Section "CNN Architectures": only one of the tile computations needs
 //     to be executed).
-//   * binact_staged: the same product for small and middle layers, in blocks of 64 x 64 whose four waves share K and whose bits
-//     pass through LDS (the reasons stand at the kernel, the line between the two at binact_staged_preferred).
+//   * binact_staged: the same product for small and middle layers and for long rows up to 2048 blocks, in blocks of 64
+//     x 64 whose four waves share K and whose bits pass through LDS (the reasons stand at the kernel, the line between
+//     the two at binact_staged_preferred).
 //   * binact_generic: every other legal shape, one thread per output, XOR and population count on whole words
 //     where a word lies inside one tile copy, bit by bit where it crosses a tile end.
 #include "tbn_common.h"
@@ -534,15 +536,17 @@ __global__ __launch_bounds__(256, 2) void binact_mfma_kernel(const uint32_t *__r
     }
 }
 
-// ---- matrix-core forward of small and middle layers: sign bits through LDS, K dealt to the waves ------------
-// What bounds it: latency.  One block per CU at most (or two), so a layer takes what one workgroup takes from its first load
-// to its last store.  binact_mfma_kernel's 128 x 128 block is 256 matrix instructions per wave behind loads that touch 32
-// lines each; here a block is 64 x 64, its four waves share K (64 instructions each at in = 4096), and the bits come as
-// whole lines, once per workgroup, 32 KiB at a time through registers into one of two LDS slots, so that a stage's loads run
-// under the products of the one before.  Stamps of 1024 x 4096 -> 4096, k = 8, sign bits out: 1.1 us to the first stage, 2.1 of products, 0.5 to
-// exchange the sums, 1.5 for the words; kernel 13.1 us before and 6.3 now, one row 9.3 / 5.8.  Tried: blocks of 128 x 128 with K dealt to two
-// pairs of waves (13.6 us at any number of rows), products and expansions ordered instruction by instruction through inline
-// assembly (6.2; at 8192 rows 16.7 against 16.3), LDS writes and loads dealt one behind each product (8.5).
+// ---- matrix-core forward of small and middle layers and of long rows: sign bits through LDS, K dealt to the waves ------------
+// What bounds it: latency.  On small and middle layers there is one block per CU at most (or two), so a layer takes what one workgroup
+// takes from its first load to its last store; long rows go through it in up to four rounds of two blocks per CU, whose stores and loads
+// run under each other's products (8192 x 4096 -> 4096, k = 8, bfloat16 out: 1024 blocks, a wave multiplies 13 % of its time).
+// binact_mfma_kernel's 128 x 128 block is 256 matrix instructions per wave behind loads that touch 32 lines each; here a block is 64 x 64,
+// its four waves share K (64 instructions each at in = 4096), and the bits come as whole lines, once per workgroup, 32 KiB at a time
+// through registers into one of two LDS slots, so that a stage's loads run under the products of the one before.  Stamps of 1024 x 4096 ->
+// 4096, k = 8, sign bits out: 1.1 us to the first stage, 2.1 of products, 0.5 to exchange the sums, 1.5 for the words; kernel 13.1 us
+// before and 6.3 now, one row 9.3 / 5.8.  Tried: blocks of 128 x 128 with K dealt to two pairs of waves (13.6 us at any number of rows),
+// products and expansions ordered instruction by instruction through inline assembly (6.2; at 8192 rows 16.7 against 16.3), LDS writes and
+// loads dealt one behind each product (8.5).
 
 struct BinactStagedParams {
     int64_t M;
@@ -894,8 +898,9 @@ bool binact_mfma_supported(const BinactArgs &a) {
 // 4096 elements and columns, k = 2, 4, 8, as graph replays): a workgroup takes a quarter of the time, so while there is a CU for
 // each of them the larger blocks leave CUs idle (geometric mean 1.41 times as fast at up to 256 blocks, 1024 x 4096 -> 4096, k = 8,
 // bfloat16 out 14.6 us against 7.1, sign bits 13.1 / 6.3).  With two per CU they still win with sign bits out (4096 rows 13.6 / 9.0; 385
-// - 512 blocks 1.16 - 1.36 in the mean) and, up to 384, with real outputs of at least three super-steps; beyond, the operands that
-// are expanded twice as often per product cost more than the filling gains (8192 x 1024 -> 1024, k = 2: 8.0 / 9.5).  Real outputs of up to 64 short
+// - 512 blocks 1.16 - 1.36 in the mean) and, up to 384, with real outputs of at least three super-steps; beyond, what
+// every block pays beside its products (the first stage, the four sums of each output through LDS) costs short rows more than the filling
+// gains (8192 x 1024 -> 1024, k = 2: 8.0 / 9.5).  Drawn again, 381 layers inside these lines: 1.34 on the mean, one more than 3 % slower.  Real outputs of up to 64 short
 // rows: 14 x 256 -> 1536, k = 4: 4.1 / 4.6.
 bool binact_staged_preferred(const BinactArgs &a) {
     const int64_t U = a.p / a.in, blocks = ((a.M + kStBM - 1) / kStBM) * ((U + kStBN - 1) / kStBN);

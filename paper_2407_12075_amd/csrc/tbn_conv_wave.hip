@@ -288,7 +288,8 @@ __global__ __launch_bounds__(64 * kMaxWaves, (wave_bound(sizeof(XT) == 4, MT, T,
     }
     // One load per window: the lanes' windows lie in lines of their own, and a load takes the CU's load path as many cycles as it
     // touches lines, whatever its width.  Against four loads of a word (3x3, bfloat16): 27 x 512 x 35^2 -> 256, k = 2 122 us before,
-    // 103 now; 5 x 512 x 8 x 7 -> 256, k = 4 12.2 / 10.3; 128 x 256 x 14^2 -> 256, k = 8, float32 27.4 / 26.6.
+    // 103 now; 5 x 512 x 8 x 7 -> 256, k = 4, stride 2 11.7 / 9.8; 128 x 256 x 14^2 -> 256, k = 8, float32 26.8 / 26.9 (graph replays; through the
+    // wrapper, at a higher clock, 24.7 / 24.5); 99 drawn bfloat16 layers 1.025 times as fast on the mean, 101 float32 ones 1.004.
     // Nothing is read past the tile: a lane whose window ends there takes the last words and moves them down before it uses them.
     // (1x1: two words, where the moving costs what a load does.)
     const int32_t last_words = P.n_words - 4;
@@ -704,7 +705,8 @@ ConvArgs as_rows(ConvArgs a) {
 // constant, the chunks of 32 channels, the replicas and the pixel blocks / 256.  Least squares over 9169 random layers
 // of common sizes, 10 - 15 % off on the average, so the other kernel has to be estimated 9 % faster.  Of 16550 layers (also
 // larger ones) 1543 were more than 4 % slower here than there with this kernel always; by this rule 663 are, and 67 are
-// slower there than here (margin 3 %: 550 and 207).
+// slower there than here (margin 3 %: 550 and 207).  (The 3x3 rows of the table are from before one load fetched a window: this kernel
+// takes 0.98 of that time on the mean in bfloat16 and the same in float32.)
 bool prefer_wave(const ConvArgs &a, const WavePlan &pl) {
     struct Model { double wave[4], block[4]; };
     static const Model models[2][2] = {   // [bfloat16][3x3]

@@ -21,10 +21,11 @@
 //   * The +-1 operand is the row operand of v_mfma_f32_32x32x16_bf16 with its lanes numbered so that a lane ends up with eight
 //     adjacent columns of one row of Y; two register sets trade halves (v_permlane16_swap) so that a store instruction
 //     writes 64 bytes of 16 rows, without another pass through LDS.
-// 8192 x 512 -> 4096, k = 1 (the product of a column-tiled layer of 4096 x 4096, k = 8): 48 - 51 us in the block kernel, 39 here with
-// word loads, 34 now: 3 us to start and load the rows, 25 of multiplications (a pass keeps the matrix pipe 94 % busy, at 1.5 - 1.7 GHz:
-// the power limit), the rest stores that nothing runs under.  8192 x 128 / 256 / 320 / 576 -> 4096: 21.6 / 24.9 / 27.5 / 42.3 before,
-// 18.7 / 23.6 / 25.5 / 39.9 now; 2000 x 384 -> 4096 15.7 / 13.7; with two replicas of 4096 columns of 256 elements
+// 8192 x 512 -> 4096, k = 1 (the product of a column-tiled layer of 4096 x 4096, k = 8): 48 - 51 us in the block kernel; here, with
+// word loads / now, 37 / 34 in calls through the wrapper and 41.5 / 39.3 in graph replays, which leave no gaps and run at a lower clock: 3 us to start
+// and load the rows, 25 of multiplications (a pass keeps the matrix pipe 94 % busy, at 1.5 - 1.7 GHz: the power limit), the rest stores
+// that nothing runs under.  8192 x 128 / 256 / 320 / 576 -> 4096, graph replays: 20.5 / 24.5 / 26.7 / 41.0 before, 17.6 / 22.2 / 24.2 / 37.5 now;
+// 2000 x 384 -> 4096 16.7 / 14.1; with two replicas of 4096 columns of 256 elements
 // 34.6 / 34.3 (36.3 with all waves starting together).
 // Tried: 64 rows per workgroup (55 us: twice the vector instructions per matrix instruction), non-temporal stores and wave
 // priorities (no difference).
@@ -340,7 +341,8 @@ tbn_status launch_one(const LinearArgs &a, const ShortParams &P, int lds) {
 int64_t lds_bytes(int64_t in) { return kRows * (((in + 63) / 64) * 128 + 16) + 128; }
 
 // Column ranges per row block: a workgroup costs about 4 us to start and load its rows and 10.6 us per pass over K = 512
-// (two waves per SIMD, 64 columns each), its stores 1.2 us per pass and replica; one workgroup per CU at a time.
+// (two waves per SIMD, 64 columns each), its stores 1.2 us per pass and replica; one workgroup per CU at a time.  (Drawn with tile words
+// one by one.  A fit to 200 layers since gives 4.8 us, 8.6 us and, stores, 4.0 us; three of them would get other ranges by it.)
 int64_t column_splits(int64_t row_blocks, int64_t passes, int64_t in, int64_t reps) {
     const double pass = 0.0207 * static_cast<double>(in) + 1.2 * static_cast<double>(reps);
     int64_t best = 1;
@@ -365,7 +367,8 @@ bool linear_short_supported(const LinearArgs &a) {
 }
 
 // Where this kernel beats the block and the general kernel (graph replays, microseconds per call, the other kernel / this
-// one): the share of the chip's wave passes (256 CUs, eight waves each) that have columns to work on must not be small.
+// one with tile words one by one; 200 drawn layers since: the other kernel takes 1.37 times as long on the mean with one replica and 1.19 with two,
+// and three layers 0.89 - 0.97 times): the share of the chip's wave passes (256 CUs, eight waves each) that have columns to work on must not be small.
 // One replica: 8192 x 128 / 256 / 320 / 512 / 576 -> 4096 columns 30 / 20, 37 / 24, 41 / 27, 50 / 40 - 45, 56 / 43;
 // 12638 x 72 -> 824 15.6 / 9.7; 6853 x 448 -> 2616 (share 0.54) 29.4 / 28.2; 2049 x 512 -> 3912 (0.51) 17.4 / 18.4.  Two
 // replicas: 12000 x 200 -> 1400 29.2 / 24.7; 7815 x 576 -> 2584 (0.62) 44 / 40; 13011 x 504 -> 1344 (0.52) 35.6 / 37.0.  With
