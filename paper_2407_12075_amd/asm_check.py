@@ -1,6 +1,6 @@
 """Static check of the gfx950 assembly that hipcc produces for the kernels whose LDS reads are
 written as inline assembly with hand-placed ``s_waitcnt lgkmcnt`` (tbn_linear_stream.hip,
-tbn_linear_mfma.hip, tbn_conv_mfma.hip).
+tbn_linear_mfma.hip, tbn_conv_mfma.hip, tbn_binact.hip).
 
 Such a read hands its destination registers to the compiler as if they were already filled; the
 data arrives later, and the source only promises it after the wait that covers the read.  That
@@ -13,6 +13,9 @@ operations, retires entries at every ``s_waitcnt`` that carries an lgkmcnt, and 
   * any scalar memory load while reads are pending (scalar loads share the counter but return
     out of order, so a non-zero count would no longer name the reads that have landed),
   * reads still pending at ``s_endpgm``.
+
+Reads that the compiler placed itself (outside the markers it writes around inline assembly, where there are any) have waits of its
+own and are only counted.
 
 Usage: ``python -m paper_2407_12075_amd.asm_check`` compiles the sources with ``-S`` and checks
 them (exit status 1 on a finding); ``check_asm_text`` is the entry point for tests.
@@ -28,6 +31,7 @@ from typing import Dict, List, Optional, Tuple
 
 _REG = re.compile(r"\b([va])(?:(\d+)|\[(\d+):(\d+)\])")
 _LABEL = re.compile(r"^([.\w$]+):")
+_MANAGED = " managed"   # behind an LDS operation of the compiler's own
 _LGKM = re.compile(r"lgkmcnt\((\d+)\)")
 
 
@@ -47,7 +51,10 @@ def _split_kernels(asm: str) -> Dict[str, List[str]]:
     kernels: Dict[str, List[str]] = {}
     name: Optional[str] = None
     body: List[str] = []
+    marked, by_hand = "#ASMSTART" in asm, False   # no markers at all: every read counts as placed by hand
     for raw in asm.splitlines():
+        if marked and "#ASM" in raw:
+            by_hand = "#ASMSTART" in raw
         line = raw.split(";", 1)[0].rstrip()
         if not line.strip():
             continue
@@ -64,7 +71,7 @@ def _split_kernels(asm: str) -> Dict[str, List[str]]:
                     kernels[name] = body
                 name = None
             continue
-        body.append(s)
+        body.append(s if by_hand or not marked else s + _MANAGED if s.startswith("ds_") else s)
     return kernels
 
 
@@ -122,7 +129,7 @@ def check_kernel(name: str, body: List[str], max_states: int = 200000) -> List[s
                 touched = _regs(operands)
                 if touched & busy:
                     findings.append(f"{name}: '{text}' uses registers of a pending LDS read (instruction {i})")
-                if op.startswith("ds_read") or op.startswith("ds_load"):
+                if (op.startswith("ds_read") or op.startswith("ds_load")) and not text.endswith(_MANAGED):
                     dst = _regs(operands.split(",")[0])
                     pend = pend + (dst,)
                 else:
@@ -171,7 +178,7 @@ def compile_to_asm(src: str) -> str:
         return open(out).read()
 
 
-CHECKED_SOURCES = ("tbn_linear_block.hip", "tbn_linear_stream.hip", "tbn_linear_mfma.hip", "tbn_conv_mfma.hip")
+CHECKED_SOURCES = ("tbn_linear_block.hip", "tbn_linear_stream.hip", "tbn_linear_mfma.hip", "tbn_conv_mfma.hip", "tbn_binact.hip")
 
 
 def main() -> int:

@@ -7,20 +7,24 @@
 //   * sign_pack: real activations -> rows of sign bits (one pass over X, 16 bytes per lane where rows are whole
 //     words, a wave ballot otherwise).
 //   * binact_mfma (tile of whole weight rows, in % 256 == 0): Z = S T^T on the matrix cores in the 4-bit float
-//     format (E2M1 holds +1 and -1 exactly; v_mfma_f32_32x32x64_f8f6f4, the form without block scales, multiplies 64
-//     elements of K per instruction, four times the bfloat16 rate; the float32 sums of +-1 products are exact).
-//     A lane's operand for one instruction is 32 sign bits, which four shifts and and-ors (seven instructions) spread into
-//     four registers of eight 4-bit values: bit 4n + j is the sign of value n of register j.  (Before, each byte was looked
-//     up in a table of 64 KiB in LDS, four address and four read instructions and a table to fill per workgroup:
-//     8192 x 4096 -> 4096, k = 8, sign bits out 17.4 us against 15.1, bfloat16 out 23.8 against 21.2; one row 13.2 against 9.4;
-//     8192 x 256 -> 4096, k = 2, sign bits out 20.6 against 12.5.)  What bounds it now is the loads of the bits, 16 bytes from
-//     each of 32 rows per instruction; in its 128 x 128 blocks sending them through LDS in stages of 1024 bits measured the same at 4096 columns
-//     (141 us against 150 at 16384, k = 2) and 2 us slower at one row (binact_staged, which does it, has a quarter of the block's
-//     products per wave besides), fetching them three super-steps ahead 1 us slower.  Both operands
-//     use the same assignment of K to lanes and registers, so a dot product does not depend on what that
-//     assignment is.  The distinct columns are computed once and every replica is written as alpha[t] * Z in whole
-//     128-byte lines after a turn through LDS (Section "CNN Architectures": only one of the tile computations needs
-//     to be executed).
+//     format (E2M1 holds +1 and -1 exactly; v_mfma_f32_32x32x64_f8f6f4 multiplies 64 elements of K per instruction, four
+//     times the bfloat16 rate; the float32 sums of such products are exact).  A lane's operand for one instruction is 32 sign
+//     bits in four registers of eight 4-bit values.  Both operands use the same assignment of K to lanes and registers, so a
+//     dot product does not depend on what that assignment is.  The distinct columns are computed once and every replica is
+//     written as alpha[t] * Z in whole 128-byte lines after a turn through LDS (Section "CNN Architectures": only one of the
+//     tile computations needs to be executed); sign bits are formed in the accumulators' layout.  Two forms of the loop:
+//       - STAGED (sign bits out, and long rows on many blocks): bits through LDS, one vector instruction per operand register (see
+//         `operand`).  A wave issues an instruction every four cycles and a matrix instruction takes 32, so that seven vector
+//         instructions per operand made 38 cycles of every product, and loads of 16 bytes from each of 32 rows, which the load path
+//         takes 64 cycles for, made 55 - 62; here it is 47 with one workgroup per CU (five vector instructions per product, one of
+//         them for the counts of set bits; 43 without the LDS reads) and 29 with two.  8192 x 4096 -> 16384, k = 2: sign bits out 140
+//         us before and 97 now, bfloat16 out 152 / 113; 8192 x 4096 -> 4096, k = 8, sign bits out 13.8 / 10.6 (the words formed
+//         by comparisons and lane exchanges behind a turn through LDS took 4.7 of it, 1.9 now); 8192 x 256 -> 4096, k = 2, sign bits
+//         out 11.9 / 8.4.  Tried: K dealt to two groups of four waves (37 cycles, but 1.1 us to add the sums and a later start: 12.2
+//         us against 10.9 with sign bits out); 32-byte pieces of rows, whose LDS addresses are immediate (121 us against 113).
+//       - else (real outputs of other rows): four shifts and and-ors, seven instructions, spread a word over four registers, the loads
+//         go straight to registers and no wave waits for another: what staging adds per block costs short rows with real outputs
+//         more than it gains (8192 x 256 -> 4096, k = 2, bfloat16 out 13.4 us and 15.8 staged).
 //   * binact_staged: the same product for small and middle layers and for long rows up to 2048 blocks, in blocks of 64
 //     x 64 whose four waves share K and whose bits pass through LDS (the reasons stand at the kernel, the line between
 //     the two at binact_staged_preferred).
@@ -295,7 +299,34 @@ __global__ __launch_bounds__(kDirRows) void binact_direct_kernel(const uint32_t 
 
 constexpr int kTurnStride = 68;                   // floats per row of a wave's 64 x 64 sums in LDS
 constexpr int kTurnBytes = 64 * kTurnStride * 4;  // per wave
-constexpr int kMfmaLds = 4 * kTurnBytes;
+// Stages of sign bits (STAGED), two super-steps of 256 batch and tile rows, 64 bytes a row, a ring of four.  Behind the loop the turn
+// round, or the words of sign bits, take their place; the counts of set bits lie behind that.
+constexpr int kStageBytes = 256 * 64;
+constexpr int kRing = 4;
+constexpr int count_off(bool sign) { return sign || kRing * kStageBytes > 4 * kTurnBytes ? kRing * kStageBytes : 4 * kTurnBytes; }
+constexpr int mfma_lds(bool sign, bool staged) { return staged ? count_off(sign) + 256 * 4 : 4 * kTurnBytes; }
+
+// s_waitcnt that waits for the vector-memory counter only (gfx9 encoding: vmcnt in bits 3:0 and 15:14)
+constexpr int vmcnt_imm(int n) { return (n & 15) | ((n >> 4) << 14) | (7 << 4) | (15 << 8); }
+// Reads of the stages are inline assembly: the compiler would make each wait for every global -> LDS load in flight.  The register is
+// handed to the compiler by tie() behind the wait that covers the read.
+template <int OFF>
+__device__ __forceinline__ void lds_read16(u32x4_t &dst, uint32_t addr) {
+    asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(dst) : "v"(addr), "n"(OFF));
+}
+template <int N>
+__device__ __forceinline__ void lds_wait() {
+    asm volatile("s_waitcnt lgkmcnt(%0)" : : "n"(N) : "memory");
+}
+__device__ __forceinline__ void tie(u32x4_t &r) { asm volatile("" : "+v"(r)); }
+// An operand is formed, and a matrix instruction issued (the tie of its accumulators behind it), where it stands: left alone the compiler forms three
+// operands in one slot and puts eight matrix instructions in a row.
+__device__ __forceinline__ void pin(i32x8_t &f) {
+    int f0 = f[0], f1 = f[1], f2 = f[2], f3 = f[3];
+    asm volatile("" : "+v"(f0), "+v"(f1), "+v"(f2), "+v"(f3));
+    f[0] = f0, f[1] = f1, f[2] = f2, f[3] = f3;
+}
+template <int V> using Int = std::integral_constant<int, V>;
 
 struct BinactMfmaParams {
     int64_t M;
@@ -311,7 +342,10 @@ struct BinactMfmaParams {
 
 // 256 threads = 4 waves in 2 x 2; a wave owns 64 batch rows x 64 distinct columns (2 x 2 MFMA tiles) over all of K.
 // SIGN: the sign bits of the outputs are written instead of the outputs (U % 32 == 0; YT is then not used).
-template <typename YT, bool RELU, bool SIGN>
+// STAGED: the bits pass through LDS as 64-byte pieces of rows, operands cost a vector instruction per register and half of them are
+// counted; otherwise every lane loads for itself, seven vector instructions per operand, and no wave ever waits for another one,
+// which is what short rows with real outputs want.
+template <typename YT, bool RELU, bool SIGN, bool STAGED>
 __global__ __launch_bounds__(256, 2) void binact_mfma_kernel(const uint32_t *__restrict__ xbits, YT *__restrict__ y,
                                                              const uint32_t *__restrict__ tile,
                                                              const float *__restrict__ alpha, BinactMfmaParams P) {
@@ -338,42 +372,18 @@ __global__ __launch_bounds__(256, 2) void binact_mfma_kernel(const uint32_t *__r
             tile_m = (P.xcd_order ? (P.tiles_m / 8) * 8 : 0u) + q;
         }
     }
-    const int64_t m0 = int64_t(tile_m) * 128 + (wave >> 1) * 64;   // this wave's first batch row
-    const int32_t n0 = static_cast<int32_t>(tile_n) * 128 + (wave & 1) * 64;   // and first distinct column
+    const int wm = wave >> 1, wn = wave & 1;
+    const int64_t mb = int64_t(tile_m) * 128, m0 = mb + wm * 64;   // the block's and this wave's first batch row
+    const int32_t nb = static_cast<int32_t>(tile_n) * 128, n0 = nb + wn * 64;   // and first distinct column
 
     // alpha of replica t in lane t (replicas past the 64th are fetched one by one in the epilogue)
     const float alpha_lanes = alpha[P.n_alpha == 1 ? 0 : (lane < P.reps ? lane : P.reps - 1)];
 
-    // Operand rows.  Activations (second operand): lane (ln, lh) supplies batch row 32*tm + ln.  Tile rows (first
-    // operand): lane ln supplies distinct column 32*tn + 16*((ln >> 2) & 1) + 4*(ln >> 3) + (ln & 3); the
-    // instruction leaves row 8*(r / 4) + 4*lh + r % 4 of its result in register r, so that register r of a lane
-    // is column 32*tn + 16*lh + r: sixteen adjacent columns.  K: bytes 32*S + 16*lh .. + 15 of the row for the
-    // four instructions of super-step S, word i for instruction i.
-    const unsigned char *a_row[2], *b_row[2];
-#pragma unroll
-    for (int t = 0; t < 2; ++t) {
-        int64_t m = m0 + 32 * t + ln;
-        m = m < P.M ? m : P.M - 1;
-        a_row[t] = reinterpret_cast<const unsigned char *>(xbits) + m * P.row_bytes + 16 * lh;
-        int32_t u = n0 + 32 * t + 16 * ((ln >> 2) & 1) + 4 * (ln >> 3) + (ln & 3);
-        u = u < P.U ? u : P.U - 1;
-        b_row[t] = reinterpret_cast<const unsigned char *>(tile) + int64_t(u) * P.row_bytes + 16 * lh;
-    }
-    auto load = [&](u32x4_t (&r)[4], int32_t S) {
-        r[0] = *reinterpret_cast<const u32x4_t *>(a_row[0] + S * 32);
-        r[1] = *reinterpret_cast<const u32x4_t *>(a_row[1] + S * 32);
-        r[2] = *reinterpret_cast<const u32x4_t *>(b_row[0] + S * 32);
-        r[3] = *reinterpret_cast<const u32x4_t *>(b_row[1] + S * 32);
-    };
-    // 32 sign bits -> 32 four-bit floats: bit 4n + j becomes the sign of value n of register j (0x2 is +1.0, 0xA is -1.0).
-    // A set bit gives -1 in both operands alike, so their products are those of the signs.
-    uint32_t sign_bits = 0x88888888u, one_bits = 0x22222222u;
-    asm volatile("" : "+v"(sign_bits), "+v"(one_bits));   // registers: an and-or takes no constants of this size
-    auto expand = [&](i32x8_t &f, uint32_t word) {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) f[j] = static_cast<int>(((word << (3 - j)) & sign_bits) | one_bits);
-    };
-
+    // The instruction leaves row 8*(r / 4) + 4*lh + r % 4 of its result in register r: with tile row column_of(l) from operand lane l,
+    // register r of a lane is column 16*lh + r of the tile, sixteen adjacent columns.
+    auto column_of = [](int l) { return 16 * ((l >> 2) & 1) + 4 * (l >> 3) + (l & 3); };
+    // Operand t of either kind is the wave's batch rows 32*(t ^ row_turn) on, or its columns 32*(t ^ col_turn) on.
+    const int row_turn = STAGED ? wn : 0, col_turn = STAGED ? wm : 0;
     f32x16_t acc[2][2];
 #pragma unroll
     for (int a = 0; a < 2; ++a)
@@ -381,122 +391,290 @@ __global__ __launch_bounds__(256, 2) void binact_mfma_kernel(const uint32_t *__r
         for (int b = 0; b < 2; ++b)
 #pragma unroll
             for (int i = 0; i < 16; ++i) acc[a][b][i] = 0.f;
+    float *const counts = reinterpret_cast<float *>(lds + count_off(SIGN));   // STAGED: 2 * set bits of the block's rows, then of its columns
+    if constexpr (STAGED) {
+        // ---- the sign bits of a stage: 16 wave-loads of 16 rows x 64 bytes, four per wave (waves 0 and 1: batch rows) -----
+        // LDS row 128 + 64 w + 32 t + l holds distinct column 64 w + 32 t + column_of(l) of the block.  Rows past M and columns past U repeat the last one.  Piece c of LDS row r lies in slot c ^ (r / 4) % 4 of
+        // the row's four: operand reads free of bank conflicts.
+        const unsigned char *const src = wave < 2 ? reinterpret_cast<const unsigned char *>(xbits) + mb * P.row_bytes
+                                                : reinterpret_cast<const unsigned char *>(tile) + int64_t(nb) * P.row_bytes;
+        uint32_t from[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int r = 64 * wn + 16 * j + (lane >> 2);   // LDS row, from the first batch row or the first tile row on
+            const int64_t left = wave < 2 ? P.M - 1 - mb : int64_t(P.U - 1 - nb);
+            const int want = wave < 2 ? r : (r & ~31) + column_of(r & 31);
+            from[j] = static_cast<uint32_t>(want < left ? want : static_cast<int>(left)) * static_cast<uint32_t>(P.row_bytes);
+        }
+        const uint32_t piece = static_cast<uint32_t>((lane ^ (lane >> 4)) & 3) * 16u;
+        const uint32_t last_piece = static_cast<uint32_t>(P.row_bytes) - 16u;
+        auto fetch = [&](int32_t stage) __attribute__((always_inline)) {   // behind a row's end: its last piece, never used
+            unsigned char *const dst = lds + (stage % kRing) * kStageBytes + wave * 4096;
+            const uint32_t at = static_cast<uint32_t>(stage) * 64u + piece;
+            const uint32_t off = at < last_piece ? at : last_piece;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) __builtin_amdgcn_global_load_lds(src + (from[j] + off), dst + j * 1024, 16, 0, 0);
+        };
 
-    // Sign bits are fetched two super-steps ahead into three rotating register sets (a super-step is 16
-    // instructions, about a quarter of a microsecond: one would not cover a miss in the XCD's L2).
-    const int32_t last = P.n_super - 1;
-    u32x4_t raw[3][4];
-    load(raw[0], 0);
-    load(raw[1], 1 < last ? 1 : last);
-    i32x8_t F[2][4] = {};   // [operand set][A0, A1, B0, B1]; the upper four words of an operand are not read in this format
+        // ---- operands ---------------------------------------------------------------------------------------------------
+        // Activations are the second operand, tile rows the first; operand 0 / 1 are the wave's batch rows 32*(t ^ row_turn) on, 2 / 3
+        // its columns 32*(t ^ col_turn) on, so that each of the block's eight operands is the first of its kind in one wave, which
+        // counts its bits.  A lane's words of a super-step are bytes 32*S + 16*lh .. + 15 of its row, and instruction c takes bits 4n + c of all four:
+        //   c = 0, 1, 2: the bits where they are are the 4-bit floats 0.5, 1 and 2 (or 0), the block scales make every product of two set
+        //                bits a 4: with s = 2a - 1 and t = 2b - 1 that is st = 4ab - 2a - 2b + 1, the rest from the counts of set bits;
+        //   c = 3:       the bit is the sign of +-1 (0x2 or 0xA; a set bit gives -1 in both operands alike).
+        // One vector instruction per register instead of seven per four.
+        uint32_t rd[4];   // of a stage's first super-step; the second one's: ^ 32
 #pragma unroll
-    for (int f = 0; f < 4; ++f) expand(F[0][f], raw[0][f][0]);
-    constexpr int kOne = 0;   // both scale operands zero: the compiler takes the form of the instruction without block scales
-    // One super-step: four groups of four instructions.  In front of each instruction one operand of the next group is
-    // expanded (seven vector instructions, 28 of the 32 cycles the matrix instruction before it runs).  The last
-    // super-step loads itself once more and expands operands nobody multiplies: the body stays one straight line of code.
-    auto step = [&](auto c_c, int32_t S) __attribute__((always_inline)) {
-        constexpr int C = decltype(c_c)::value, N1 = (C + 1) % 3, N2 = (C + 2) % 3;
-        load(raw[N2], S + 2 < last ? S + 2 : last);
+        for (int t = 0; t < 2; ++t) {
+            auto at = [&](int r) { return static_cast<uint32_t>(r * 64 + ((lh ^ ((r >> 2) & 3)) << 4)); };
+            rd[t] = at(64 * wm + 32 * (t ^ row_turn) + ln);
+            rd[2 + t] = at(128 + 64 * wn + 32 * (t ^ col_turn) + ln);
+        }
+        uint32_t mask0 = 0x11111111u, mask1 = 0x22222222u, mask2 = 0x44444444u, mask3 = 0x88888888u, counted = 0x77777777u;
+        asm volatile("" : "+v"(mask0), "+v"(mask1), "+v"(mask2), "+v"(mask3), "+v"(counted));   // registers: an and-or takes no constants of this size
+        auto operand = [&](i32x8_t &f, const u32x4_t &w, auto c_c) __attribute__((always_inline)) {
+            constexpr int C = decltype(c_c)::value;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int s = i & 1, n = s ^ 1;
+            for (int j = 0; j < 4; ++j)
+                f[j] = static_cast<int>(C == 3 ? ((w[j] & mask3) | mask1) : (w[j] & (C == 0 ? mask0 : C == 1 ? mask1 : mask2)));
+            pin(f);
+        };
+
+        uint32_t count[2] = {0, 0};      // set bits of operands 0 and 2, those of instruction 3 left out
+        u32x4_t raw[2][4];
+        i32x8_t F[2][4] = {};            // the upper four words of an operand are not read in this format
+        // One super-step: four groups of four instructions.  In front of each instruction one operand of the next group is formed; the
+        // words of the next super-step are requested in the first group and taken in the last one.
+        auto step = [&](auto s_c, const uint32_t (&next)[4]) __attribute__((always_inline)) {   // S: half of the stage
+            constexpr int S = decltype(s_c)::value, N = S ^ 1;
+            auto group = [&](auto i_c) __attribute__((always_inline)) {
+                constexpr int I = decltype(i_c)::value, C = (I + 1) & 3;
+                uint32_t bits = 0;
+                if constexpr (I == 3) lds_wait<0>();
+                auto one = [&](auto q_c) __attribute__((always_inline)) {
+                    constexpr int Q = decltype(q_c)::value;
+                    if constexpr (I == 0) lds_read16<0>(raw[N][Q], next[Q]);
+                    if constexpr (I == 3) tie(raw[N][Q]);
+                    operand(F[(I & 1) ^ 1][Q], I < 3 ? raw[S][Q] : raw[N][Q], Int<C>{});
+                    if constexpr ((Q & 1) == 0) bits = raw[S][Q][I] & counted;
+                    else count[Q >> 1] += static_cast<uint32_t>(__builtin_popcount(bits));
+                    asm volatile("" : "+v"(bits), "+v"(count[0]), "+v"(count[1]));
+                    __builtin_amdgcn_sched_barrier(0);
+                    constexpr int tm = Q >> 1, tn = Q & 1;
+                    acc[tm][tn] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(F[I & 1][2 + tn], F[I & 1][tm], acc[tm][tn], 4, 4, 0,
+                                                                                  I == 0 ? 129 : I == 1 ? 128 : 0, 0, I == 0 ? 129 : I == 1 ? 128 : 0);
+                    asm volatile("" : "+v"(acc[tm][tn]));   // issued here
+                    __builtin_amdgcn_sched_barrier(0);
+                };
+                one(Int<0>{}); one(Int<1>{}); one(Int<2>{}); one(Int<3>{});
+            };
+            group(Int<0>{}); group(Int<1>{}); group(Int<2>{}); group(Int<3>{});
+        };
+
+        // Stage s + 1 is readable behind the barrier of stage s, which also frees the slot of stage s - 1 for stage s + 3.
+        // (both scale operands zero: the form of the instruction without block scales, one issue slot instead of two)
+        const int32_t n_stages = (P.n_super + 1) / 2;
+        fetch(0);
+        if (n_stages > 1) fetch(1);
+        if (n_stages > 2) fetch(2);
+        if (n_stages > 2) __builtin_amdgcn_s_waitcnt(vmcnt_imm(8));
+        else if (n_stages > 1) __builtin_amdgcn_s_waitcnt(vmcnt_imm(4));
+        else __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+        __builtin_amdgcn_s_barrier();
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                constexpr int kOrder[4] = {0, 2, 3, 1};
-                const int f = kOrder[q];
-                expand(F[n][f], i < 3 ? raw[C][f][i + 1] : raw[N1][f][0]);
-                __builtin_amdgcn_sched_barrier(0);
-                const int tm = q >> 1, tn = q & 1;
-                acc[tm][tn] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(F[s][2 + tn], F[s][tm], acc[tm][tn], 4, 4, 0, kOne, 0, kOne);
-                __builtin_amdgcn_sched_barrier(0);
+        for (int f = 0; f < 4; ++f) lds_read16<0>(raw[0][f], rd[f]);
+        lds_wait<0>();
+#pragma unroll
+        for (int f = 0; f < 4; ++f) {
+            tie(raw[0][f]);
+            operand(F[0][f], raw[0][f], Int<0>{});
+        }
+        for (int32_t st = 0; st < n_stages; ++st) {
+            if (st + 2 < n_stages) __builtin_amdgcn_s_waitcnt(vmcnt_imm(4));
+            else __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+            __builtin_amdgcn_s_barrier();
+            if (st + 3 < n_stages) fetch(st + 3);
+            const int32_t super = 2 * st;
+            uint32_t here[4], next[4];
+#pragma unroll
+            for (int f = 0; f < 4; ++f) {
+                here[f] = (rd[f] ^ 32u) + static_cast<uint32_t>((st % kRing) * kStageBytes);
+                next[f] = rd[f] + static_cast<uint32_t>(((st + 1) % kRing) * kStageBytes);
+            }
+            step(Int<0>{}, here);
+            if (super + 1 < P.n_super) step(Int<1>{}, next);
+        }
+
+        // ---- counts of set bits ---------------------------------------------------------------------------------------
+#pragma unroll
+        for (int i = 0; i < 2; ++i) count[i] += static_cast<uint32_t>(__shfl_xor(static_cast<int>(count[i]), 32));
+        if (lh == 0) {
+            counts[64 * wm + 32 * wn + ln] = static_cast<float>(2 * count[0]);
+            counts[128 + 64 * wn + 32 * wm + column_of(ln)] = static_cast<float>(2 * count[1]);
+        }
+        __syncthreads();   // the counts are there, and every wave is done with the stages
+    } else {
+        // Operand rows.  Activations (second operand): lane (ln, lh) supplies batch row 32*tm + ln.  Tile rows (first
+        // operand): lane ln supplies distinct column 32*tn + column_of(ln).  K: bytes 32*S + 16*lh .. + 15 of the row for the
+        // four instructions of super-step S, word i for instruction i.
+        const unsigned char *a_row[2], *b_row[2];
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            int64_t m = m0 + 32 * t + ln;
+            m = m < P.M ? m : P.M - 1;
+            a_row[t] = reinterpret_cast<const unsigned char *>(xbits) + m * P.row_bytes + 16 * lh;
+            int32_t u = n0 + 32 * t + column_of(ln);
+            u = u < P.U ? u : P.U - 1;
+            b_row[t] = reinterpret_cast<const unsigned char *>(tile) + int64_t(u) * P.row_bytes + 16 * lh;
+        }
+        auto load = [&](u32x4_t (&r)[4], int32_t S) {
+            r[0] = *reinterpret_cast<const u32x4_t *>(a_row[0] + S * 32);
+            r[1] = *reinterpret_cast<const u32x4_t *>(a_row[1] + S * 32);
+            r[2] = *reinterpret_cast<const u32x4_t *>(b_row[0] + S * 32);
+            r[3] = *reinterpret_cast<const u32x4_t *>(b_row[1] + S * 32);
+        };
+        // 32 sign bits -> 32 four-bit floats: bit 4n + j becomes the sign of value n of register j (0x2 is +1.0, 0xA is -1.0).
+        // A set bit gives -1 in both operands alike, so their products are those of the signs.
+        uint32_t sign_bits = 0x88888888u, one_bits = 0x22222222u;
+        asm volatile("" : "+v"(sign_bits), "+v"(one_bits));   // registers: an and-or takes no constants of this size
+        auto expand = [&](i32x8_t &f, uint32_t word) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) f[j] = static_cast<int>(((word << (3 - j)) & sign_bits) | one_bits);
+        };
+
+
+        // Sign bits are fetched two super-steps ahead into three rotating register sets (a super-step is 16
+        // instructions, about a quarter of a microsecond: one would not cover a miss in the XCD's L2).
+        const int32_t last = P.n_super - 1;
+        u32x4_t raw[3][4];
+        load(raw[0], 0);
+        load(raw[1], 1 < last ? 1 : last);
+        i32x8_t F[2][4] = {};   // [operand set][A0, A1, B0, B1]; the upper four words of an operand are not read in this format
+#pragma unroll
+        for (int f = 0; f < 4; ++f) expand(F[0][f], raw[0][f][0]);
+        constexpr int kOne = 0;   // both scale operands zero: the compiler takes the form of the instruction without block scales
+        // One super-step: four groups of four instructions.  In front of each instruction one operand of the next group is
+        // expanded (seven vector instructions, 28 of the 32 cycles the matrix instruction before it runs).  The last
+        // super-step loads itself once more and expands operands nobody multiplies: the body stays one straight line of code.
+        auto step = [&](auto c_c, int32_t S) __attribute__((always_inline)) {
+            constexpr int C = decltype(c_c)::value, N1 = (C + 1) % 3, N2 = (C + 2) % 3;
+            load(raw[N2], S + 2 < last ? S + 2 : last);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int s = i & 1, n = s ^ 1;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    constexpr int kOrder[4] = {0, 2, 3, 1};
+                    const int f = kOrder[q];
+                    expand(F[n][f], i < 3 ? raw[C][f][i + 1] : raw[N1][f][0]);
+                    __builtin_amdgcn_sched_barrier(0);
+                    const int tm = q >> 1, tn = q & 1;
+                    acc[tm][tn] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(F[s][2 + tn], F[s][tm], acc[tm][tn], 4, 4, 0, kOne, 0, kOne);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+        };
+        int32_t S = 0;
+        for (; S + 3 <= P.n_super; S += 3) {
+            step(std::integral_constant<int, 0>{}, S);
+            step(std::integral_constant<int, 1>{}, S + 1);
+            step(std::integral_constant<int, 2>{}, S + 2);
+        }
+        if (S < P.n_super) {   // one or two super-steps are left; the register sets are back in their first roles
+            step(std::integral_constant<int, 0>{}, S);
+            if (S + 1 < P.n_super) step(std::integral_constant<int, 1>{}, S + 1);
+        }
+    }
+    const float rest = 192.f * static_cast<float>(P.n_super);   // three quarters of K
+    auto of_row = [&](int tm) __attribute__((always_inline)) { return rest - counts[64 * wm + 32 * (tm ^ row_turn) + ln]; };
+    auto of_cols = [&](int tn, int a) __attribute__((always_inline)) {   // of columns 16*lh + 4*a .. + 3 of the tile
+        return *reinterpret_cast<const f32x4_t *>(counts + 128 + 64 * wn + 32 * (tn ^ col_turn) + 16 * lh + 4 * a);
+    };
+
+    if constexpr (SIGN) {
+        // alpha[t] * z is positive where z and alpha[t] have the same sign.  A lane shifts the signs of z ("negative") and of -z
+        // ("positive") of its sixteen columns of a row into two halves of a register; the lane halves trade theirs, so that a lane
+        // holds whole words of 32 columns, and every replica takes the "positive" or the "negative" word by the sign of its alpha
+        // (zero or not a number: no bit).
+        uint32_t *yb = reinterpret_cast<uint32_t *>(y);
+        const int64_t out_words = P.out >> 5;
+        const int32_t words_per_replica = P.U >> 5;
+        uint32_t half[2][2];   // sixteen columns: "positive" in the low half, "negative" in the high half
+#pragma unroll
+        for (int tm = 0; tm < 2; ++tm) {
+            const float r = of_row(tm);
+#pragma unroll
+            for (int tn = 0; tn < 2; ++tn) {
+                uint32_t pos = 0, neg = 0;
+#pragma unroll
+                for (int a = 3; a >= 0; --a) {
+                    const f32x4_t c = of_cols(tn, a);
+#pragma unroll
+                    for (int e = 3; e >= 0; --e) {
+                        const float d = r - c[e], z = acc[tm][tn][4 * a + e] + d, minus = (c[e] - r) - acc[tm][tn][4 * a + e];   // (never -0)
+                        neg = __builtin_amdgcn_alignbit(neg, __float_as_uint(z), 31);
+                        pos = __builtin_amdgcn_alignbit(pos, __float_as_uint(minus), 31);
+                    }
+                }
+                half[tm][tn] = pos | (neg << 16);
             }
         }
-    };
-    int32_t S = 0;
-    for (; S + 3 <= P.n_super; S += 3) {
-        step(std::integral_constant<int, 0>{}, S);
-        step(std::integral_constant<int, 1>{}, S + 1);
-        step(std::integral_constant<int, 2>{}, S + 2);
-    }
-    if (S < P.n_super) {   // one or two super-steps are left; the register sets are back in their first roles
-        step(std::integral_constant<int, 0>{}, S);
-        if (S + 1 < P.n_super) step(std::integral_constant<int, 1>{}, S + 1);
+        // the lanes with lh = 0 take the words of the first row tile, those with lh = 1 those of the second; the block's words meet in LDS, [row][pos, neg][4 words], so that a store writes the 128 columns of a row and replica at once
+        uint32_t *const words = reinterpret_cast<uint32_t *>(lds);
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const auto v = __builtin_amdgcn_permlane32_swap(half[0][i], half[1][i], false, false);   // low columns, high columns
+            const int row = 64 * wm + 32 * (lh ^ row_turn) + ln, word = 2 * wn + (i ^ col_turn);
+            words[row * 8 + word] = (v[0] & 0xffffu) | (v[1] << 16);
+            words[row * 8 + 4 + word] = (v[0] >> 16) | (v[1] & 0xffff0000u);
+        }
+        __syncthreads();
+        const int row = tid & 127;
+        const int64_t m = mb + row;
+        if (m >= P.M) return;
+        const u32x4_t wp = *reinterpret_cast<const u32x4_t *>(words + row * 8), wneg = *reinterpret_cast<const u32x4_t *>(words + row * 8 + 4);
+        uint32_t *const yrow = yb + m * out_words + (nb >> 5);
+        const int32_t left = (P.U - nb) >> 5;
+        for (int32_t t = wave >> 1; t < P.reps; t += 2) {
+            const float al = t < 64 ? __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, alpha_lanes), t))
+                                    : alpha[P.n_alpha == 1 ? 0 : t];
+            const u32x4_t zero = {0u, 0u, 0u, 0u}, w = al > 0.f ? wp : (al < 0.f ? wneg : zero);
+            uint32_t *dst = yrow + int64_t(t) * words_per_replica;
+            if (left >= 4) {
+                typedef uint32_t u32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));
+                *reinterpret_cast<u32x4_a4 *>(dst) = w;
+            } else {
+#pragma unroll
+                for (int i = 0; i < 3; ++i)
+                    if (i < left) dst[i] = w[i];
+            }
+        }
+        return;
     }
 
     // ---- turn the sums round through the wave's own LDS and write every replica ----------------------------
     float *zt = reinterpret_cast<float *>(lds + wave * kTurnBytes);
 #pragma unroll
-    for (int tm = 0; tm < 2; ++tm)
+    for (int tm = 0; tm < 2; ++tm) {
+        const int row = 32 * (tm ^ row_turn) + ln;
+        const float r = STAGED ? of_row(tm) : 0.f;
 #pragma unroll
         for (int tn = 0; tn < 2; ++tn)
 #pragma unroll
             for (int a = 0; a < 4; ++a) {
-                const f32x4_t v = {acc[tm][tn][4 * a], acc[tm][tn][4 * a + 1], acc[tm][tn][4 * a + 2], acc[tm][tn][4 * a + 3]};
-                *reinterpret_cast<f32x4_t *>(zt + (32 * tm + ln) * kTurnStride + 32 * tn + 16 * lh + 4 * a) = v;
+                f32x4_t v = {acc[tm][tn][4 * a], acc[tm][tn][4 * a + 1], acc[tm][tn][4 * a + 2], acc[tm][tn][4 * a + 3]};
+                if constexpr (STAGED) {
+                    const f32x4_t c = of_cols(tn, a);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) v[e] += r - c[e];
+                }
+                *reinterpret_cast<f32x4_t *>(zt + row * kTurnStride + 32 * (tn ^ col_turn) + 16 * lh + 4 * a) = v;
             }
+    }
     // a lane takes eight adjacent columns of one row; eight lanes cover the 64 columns of a row
     const int c8 = lane & 7, rsub = lane >> 3;
     const int32_t col = n0 + 8 * c8;
-    if constexpr (SIGN) {
-        // alpha[t] * z is positive where z and alpha[t] have the same sign: the eight bits "z > 0" and the eight bits
-        // "z < 0" of a lane are formed once per row and the four lanes of a word OR their bytes together (every lane takes
-        // part in the exchanges).  A pass over eight rows has 16 words per replica; they are dealt to the lanes so that
-        // one store instruction writes the words of four replicas: lane l stores word l % 16 of the pass (row l / 2 % 8,
-        // half l % 2) for replicas l / 16, l / 16 + 4, ..., taking the "positive" or the "negative" word by the sign of
-        // that replica's alpha (zero or not a number: no bit).
-        uint32_t *yb = reinterpret_cast<uint32_t *>(y);
-        const int64_t out_words = P.out >> 5;
-        const int slot = lane & 15, t_first = lane >> 4;
-        const int owner = (slot >> 1) * 8 + (slot & 1) * 4;   // a lane that holds word `slot` after the exchanges
-        const int32_t colw = n0 + 32 * (slot & 1);
-        const int32_t words_per_replica = P.U >> 5;
-        // the alphas of this lane's first four replicas (up to 16 replicas in all) are fetched once
-        float al_own[4];
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            const int32_t t = t_first + 4 * c;
-            al_own[c] = alpha[P.n_alpha == 1 ? 0 : (t < P.reps ? t : P.reps - 1)];
-        }
-#pragma unroll
-        for (int q = 0; q < 8; ++q) {
-            const int row = 8 * q + rsub;
-            const f32x4_t z0 = *reinterpret_cast<const f32x4_t *>(zt + row * kTurnStride + 8 * c8);
-            const f32x4_t z1 = *reinterpret_cast<const f32x4_t *>(zt + row * kTurnStride + 8 * c8 + 4);
-            uint32_t wp = 0, wn = 0;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                wp |= (z0[i] > 0.f ? 1u : 0u) << i;
-                wp |= (z1[i] > 0.f ? 1u : 0u) << (4 + i);
-                wn |= (z0[i] < 0.f ? 1u : 0u) << i;
-                wn |= (z1[i] < 0.f ? 1u : 0u) << (4 + i);
-            }
-            uint32_t both = (wp | (wn << 8)) << (16 * (c8 & 1));   // two lanes share a register for the first exchange
-            both |= __shfl_xor(both, 1);                           // bytes: pos(c8 even), neg(even), pos(odd), neg(odd)
-            const uint32_t pair_p = (both & 0xffu) | ((both >> 8) & 0xff00u), pair_n = ((both >> 8) & 0xffu) | ((both >> 16) & 0xff00u);
-            const uint32_t pn = pair_p | (pair_n << 16);           // low half: 16 "positive" bits of the lane pair, high half: "negative"
-            const uint32_t other = __shfl_xor(pn, 2);
-            const bool upper = (c8 & 2) != 0;                      // this pair holds bits 16 .. 31 of the word
-            const uint32_t lo = upper ? other : pn, hi = upper ? pn : other;
-            wp = (lo & 0xffffu) | (hi << 16);
-            wn = (lo >> 16) | (hi & 0xffff0000u);
-            const uint32_t sp = __shfl(wp, owner), sn = __shfl(wn, owner);   // the word this lane stores
-            const int64_t m = m0 + 8 * q + (slot >> 1);
-            if (m < P.M && colw < P.U) {
-                uint32_t *dst = yb + m * out_words + (colw >> 5);
-#pragma unroll
-                for (int c = 0; c < 4; ++c) {
-                    const int32_t t = t_first + 4 * c;
-                    if (t < P.reps) dst[int64_t(t) * words_per_replica] = al_own[c] > 0.f ? sp : (al_own[c] < 0.f ? sn : 0u);
-                }
-                for (int32_t t = t_first + 16; t < P.reps; t += 4) {
-                    const float al = alpha[P.n_alpha == 1 ? 0 : t];
-                    dst[int64_t(t) * words_per_replica] = al > 0.f ? sp : (al < 0.f ? sn : 0u);
-                }
-            }
-        }
-        return;
-    }
     if (col < P.U) {
 #pragma unroll 1
         for (int q = 0; q < 8; ++q) {
@@ -544,7 +722,8 @@ __global__ __launch_bounds__(256, 2) void binact_mfma_kernel(const uint32_t *__r
 // its four waves share K (64 instructions each at in = 4096), and the bits come as whole lines, once per workgroup, 32 KiB at a time
 // through registers into one of two LDS slots, so that a stage's loads run under the products of the one before.  Stamps of 1024 x 4096 ->
 // 4096, k = 8, sign bits out: 1.1 us to the first stage, 2.1 of products, 0.5 to exchange the sums, 1.5 for the words; kernel 13.1 us
-// before and 6.3 now, one row 9.3 / 5.8.  Tried: blocks of 128 x 128 with K dealt to two pairs of waves (13.6 us at any number of rows),
+// before and 6.3, one row 9.3 / 5.8; with operands and matrix instructions pinned to their places (see pin; the compiler put
+// eight matrix instructions in a row behind their operands) 6.0, one row 5.4, 8192 x 4096 -> 4096, k = 8, bfloat16 out 17.9 against 17.2.  Tried: blocks of 128 x 128 with K dealt to two pairs of waves (13.6 us at any number of rows),
 // products and expansions ordered instruction by instruction through inline assembly (6.2; at 8192 rows 16.7 against 16.3), LDS writes and
 // loads dealt one behind each product (8.5).
 
@@ -569,7 +748,10 @@ constexpr int kStStride = kStBN + 4;                // floats per row of a group
 constexpr int kStPlane = kStBM * kStStride;         // floats
 constexpr int kStLds = kGroups * kStPlane * 4 > 2 * kStStage ? kGroups * kStPlane * 4 : 2 * kStStage;
 
-template <typename YT, bool RELU, bool SIGN>
+// PIN: operands and matrix instructions stay where they stand, and sign bits' first alphas are fetched in front of the loop (387 drawn layers
+// with sign bits out on 257 - 512 blocks, without / with: rows of 1280 - 2048 elements 0.98 in the mean, 2304 - 3072 0.99, 3328 - 4096
+// 1.02, longer ones 1.06; with real outputs 1.00 - 1.04 at any length).
+template <typename YT, bool RELU, bool SIGN, bool PIN>
 __global__ __launch_bounds__(256, 2) void binact_staged_kernel(const uint32_t *__restrict__ xbits, YT *__restrict__ y,
                                                                             const uint32_t *__restrict__ tile,
                                                                             const float *__restrict__ alpha, BinactStagedParams P) {
@@ -660,6 +842,7 @@ __global__ __launch_bounds__(256, 2) void binact_staged_kernel(const uint32_t *_
     auto expand = [&](i32x8_t &f, uint32_t word) __attribute__((always_inline)) {
 #pragma unroll
         for (int j = 0; j < 4; ++j) f[j] = static_cast<int>(((word << (3 - j)) & sign_bits) | one_bits);
+        if constexpr (PIN) pin(f);
     };
 
     f32x16_t acc[TM][TN];
@@ -675,6 +858,18 @@ __global__ __launch_bounds__(256, 2) void binact_staged_kernel(const uint32_t *_
 #pragma unroll
     for (int i = 0; i < kPasses; ++i) put(i, 0);
     if (n_stages > 1) fetch_all(1);
+    // alpha of replica t in lane t (replicas past the 64th are fetched one by one below); sign bits out: a lane's first eight
+    // replicas (up to 16 replicas in all)
+    float alpha_lanes = 0.f, al_own[8] = {};
+    auto first_alphas = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int c = 0; c < 8; ++c) {
+            const int32_t t = lh + 2 * c;
+            al_own[c] = alpha[P.n_alpha == 1 ? 0 : (t < P.reps ? t : P.reps - 1)];
+        }
+    };
+    if constexpr (!SIGN) alpha_lanes = alpha[P.n_alpha == 1 ? 0 : (lane < P.reps ? lane : P.reps - 1)];
+    else if constexpr (PIN) first_alphas();
     lds_barrier();
     u32x4_t raw[2][NF];
     read(raw[0], 0, 0);
@@ -693,6 +888,7 @@ __global__ __launch_bounds__(256, 2) void binact_staged_kernel(const uint32_t *_
                 __builtin_amdgcn_sched_barrier(0);
                 const int tm = q >> 1, tn = q & 1;
                 acc[tm][tn] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(F[s][TM + tn], F[s][tm], acc[tm][tn], 4, 4, 0, kOne, 0, kOne);
+                if constexpr (PIN) asm volatile("" : "+v"(acc[tm][tn]));   // issued here
                 __builtin_amdgcn_sched_barrier(0);
             }
         }
@@ -731,8 +927,6 @@ __global__ __launch_bounds__(256, 2) void binact_staged_kernel(const uint32_t *_
                     *reinterpret_cast<f32x4_t *>(zt + (32 * tm + ln) * STR + 32 * tn + 16 * lh + 4 * a) = v;
                 }
     }
-    // alpha of replica t in lane t (replicas past the 64th are fetched one by one below)
-    float alpha_lanes = alpha[P.n_alpha == 1 ? 0 : (lane < P.reps ? lane : P.reps - 1)];
     asm volatile("" : "+v"(alpha_lanes));   // loaded by every lane here, not by those with columns below
     lds_barrier();
     // a wave takes a quarter of the rows
@@ -744,16 +938,10 @@ __global__ __launch_bounds__(256, 2) void binact_staged_kernel(const uint32_t *_
         uint32_t *yb = reinterpret_cast<uint32_t *>(y);
         const int64_t out_words = P.out >> 5;
         constexpr int WPR = BN / 32, RPP = 32 / WPR;          // words of a row, rows per pass
+        if constexpr (!PIN) first_alphas();
         const int slot_w = lane & 31, t_first = lane >> 5;
         const int32_t colw = n0 + 32 * (slot_w % WPR);
         const int32_t words_per_replica = P.U >> 5;
-        // the alphas of this lane's first eight replicas (up to 16 replicas in all) are fetched once
-        float al_own[8];
-#pragma unroll
-        for (int c = 0; c < 8; ++c) {
-            const int32_t t = t_first + 2 * c;
-            al_own[c] = alpha[P.n_alpha == 1 ? 0 : (t < P.reps ? t : P.reps - 1)];
-        }
 #pragma unroll 1
         for (int q = 0; q < BM / 4 / RPP; ++q) {
             const int row0 = wave * (BM / 4) + q * RPP;
@@ -851,16 +1039,16 @@ __global__ __launch_bounds__(256, 2) void binact_staged_kernel(const uint32_t *_
     }
 }
 
-template <typename YT, bool RELU, bool SIGN = false>
+template <typename YT, bool RELU, bool SIGN = false, bool PIN = true>
 static tbn_status launch_staged_t(const BinactArgs &a, const BinactStagedParams &P) {
-    static const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&binact_staged_kernel<YT, RELU, SIGN>),
+    static const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&binact_staged_kernel<YT, RELU, SIGN, PIN>),
                                                     hipFuncAttributeMaxDynamicSharedMemorySize, kStLds);
     if (e != hipSuccess) {
         set_error("tbn_linear_forward_binact: the matrix-core kernel was refused %d bytes of LDS", kStLds);
         (void)hipGetLastError();
         return TBN_ERR_DEVICE;
     }
-    hipLaunchKernelGGL((binact_staged_kernel<YT, RELU, SIGN>), dim3(P.tiles_m * static_cast<uint32_t>(P.tiles_n)), dim3(256),
+    hipLaunchKernelGGL((binact_staged_kernel<YT, RELU, SIGN, PIN>), dim3(P.tiles_m * static_cast<uint32_t>(P.tiles_n)), dim3(256),
                        kStLds, a.stream, a.xbits, static_cast<YT *>(a.y), a.tile, a.alpha, P);
     return check_launch("tbn_linear_forward_binact (matrix-core kernel)");
 }
@@ -878,7 +1066,7 @@ static tbn_status launch_binact_staged(const BinactArgs &a) {
     P.n_super = static_cast<int32_t>(a.in / 256);
     P.row_bytes = static_cast<int32_t>(a.in / 8);
     const bool relu = (a.flags & TBN_FLAG_RELU) != 0;
-    if (a.flags & TBN_FLAG_SIGN_OUT) return launch_staged_t<float, false, true>(a, P);
+    if (a.flags & TBN_FLAG_SIGN_OUT) return a.in > 3072 ? launch_staged_t<float, false, true>(a, P) : launch_staged_t<float, false, true, false>(a, P);
     if (a.dt == TBN_F32) return relu ? launch_staged_t<float, true>(a, P) : launch_staged_t<float, false>(a, P);
     return relu ? launch_staged_t<uint16_t, true>(a, P) : launch_staged_t<uint16_t, false>(a, P);
 }
@@ -894,17 +1082,31 @@ bool binact_mfma_supported(const BinactArgs &a) {
     return blocks <= 0x7fffffffLL;
 }
 
+constexpr int64_t kCountedRows = int64_t(1) << 22;   // sums of four times the set bits both operands have are exact in float32 up to here
+
+// Real outputs: long rows on more than one and a half blocks per CU take the 128 x 128 blocks with staged bits (205 drawn layers of more
+// than 1024 blocks of 64 x 64, as graph replays against the other kernels: rows of 2304 - 3072 elements 1.02 - 1.11 in the mean, longer ones
+// 1.08 - 1.23; up to 2048 elements 0.84 - 1.03, and on fewer blocks 0.91 - 1.0, with more than 4096 elements 1.04 - 1.14 there, not taken).  Rows
+// of Y that do not start on lines lose (4765 x 3328 -> 13184, k = 8, float32: 62.6 us and 70.4).
+bool binact_long_rows(const BinactArgs &a) {
+    const int64_t U = a.p / a.in;
+    return a.in > 2048 && a.in <= kCountedRows && U % 64 == 0 && ((a.M + 127) / 128) * ((U + 127) / 128) > 384;
+}
+
 // Where the staged kernel's blocks of 64 x 64 beat the 128 x 128 of binact_mfma_kernel (400 drawn layers of 1 - 8192 rows, 256 -
 // 4096 elements and columns, k = 2, 4, 8, as graph replays): a workgroup takes a quarter of the time, so while there is a CU for
 // each of them the larger blocks leave CUs idle (geometric mean 1.41 times as fast at up to 256 blocks, 1024 x 4096 -> 4096, k = 8,
-// bfloat16 out 14.6 us against 7.1, sign bits 13.1 / 6.3).  With two per CU they still win with sign bits out (4096 rows 13.6 / 9.0; 385
-// - 512 blocks 1.16 - 1.36 in the mean) and, up to 384, with real outputs of at least three super-steps; beyond, what
+// bfloat16 out 14.6 us against 7.1, sign bits 13.1 / 6.3).  With two per CU they still win with sign bits out
+// of rows of more than 1024 elements or with column blocks of 128 to fill (4096 x 4096 13.6 / 9.0; shorter rows, 95 drawn layers of 257 - 512
+// blocks: these take 1.18 times the 128 x 128 blocks' time up to 512 elements, 1.08 up to 1024; 1536 - 2048 0.9 in the mean; 1508 x 512 -> 5888,
+// k = 8, 736 columns: 6.5 / 5.8) and, up to 384, with real outputs of at least three super-steps; beyond, what
 // every block pays beside its products (the first stage, the four sums of each output through LDS) costs short rows more than the filling
 // gains (8192 x 1024 -> 1024, k = 2: 8.0 / 9.5).  Drawn again, 381 layers inside these lines: 1.34 on the mean, one more than 3 % slower.  Real outputs of up to 64 short
 // rows: 14 x 256 -> 1536, k = 4: 4.1 / 4.6.
 bool binact_staged_preferred(const BinactArgs &a) {
     const int64_t U = a.p / a.in, blocks = ((a.M + kStBM - 1) / kStBM) * ((U + kStBN - 1) / kStBN);
-    if (a.flags & TBN_FLAG_SIGN_OUT) return blocks <= 512;
+    if (a.flags & TBN_FLAG_SIGN_OUT) return blocks <= (a.in > 1024 || U % 128 != 0 ? 512 : 256) || a.in > kCountedRows;
+    if (binact_long_rows(a)) return false;
     if (a.in < 768) return a.M > 64 && blocks <= 256;
     if (blocks <= 384) return true;
     // Real outputs of long rows, 385 - 2048 blocks, by rounds of two blocks per CU (2 x 420 layers of 2048 - 16384 elements and 1 - 16
@@ -918,24 +1120,24 @@ bool binact_staged_preferred(const BinactArgs &a) {
     return a.dt == TBN_F32 || (blocks - 1) % 512 < 256 || (a.in >= 4096 && reps >= 8);
 }
 
-// the permission for more than 64 KiB of LDS, once per process
-template <typename YT, bool RELU, bool SIGN>
-static hipError_t allow_lds() {
-    static const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&binact_mfma_kernel<YT, RELU, SIGN>),
-                                                    hipFuncAttributeMaxDynamicSharedMemorySize, kMfmaLds);
-    return e;
-}
-
-template <typename YT, bool RELU, bool SIGN = false>
-static tbn_status launch_mfma_t(const BinactArgs &a, const BinactMfmaParams &P, unsigned blocks) {
-    if (allow_lds<YT, RELU, SIGN>() != hipSuccess) {
-        set_error("tbn_linear_forward_binact: the matrix-core kernel was refused %d bytes of LDS", kMfmaLds);
+template <typename YT, bool RELU, bool SIGN, bool STAGED>
+static tbn_status launch_mfma_s(const BinactArgs &a, const BinactMfmaParams &P, unsigned blocks) {
+    constexpr int bytes = mfma_lds(SIGN, STAGED);
+    // the permission for more than 64 KiB of LDS, once per process
+    static const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&binact_mfma_kernel<YT, RELU, SIGN, STAGED>),
+                                                    hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+    if (e != hipSuccess) {
+        set_error("tbn_linear_forward_binact: the matrix-core kernel was refused %d bytes of LDS", bytes);
         (void)hipGetLastError();
         return TBN_ERR_DEVICE;
     }
-    hipLaunchKernelGGL((binact_mfma_kernel<YT, RELU, SIGN>), dim3(blocks), dim3(256), kMfmaLds, a.stream, a.xbits,
+    hipLaunchKernelGGL((binact_mfma_kernel<YT, RELU, SIGN, STAGED>), dim3(blocks), dim3(256), bytes, a.stream, a.xbits,
                        static_cast<YT *>(a.y), a.tile, a.alpha, P);
     return check_launch("tbn_linear_forward_binact (matrix-core kernel)");
+}
+template <typename YT, bool RELU>
+static tbn_status launch_mfma_t(const BinactArgs &a, const BinactMfmaParams &P, unsigned blocks) {
+    return binact_long_rows(a) ? launch_mfma_s<YT, RELU, false, true>(a, P, blocks) : launch_mfma_s<YT, RELU, false, false>(a, P, blocks);
 }
 
 tbn_status launch_binact_mfma(const BinactArgs &a) {
@@ -956,7 +1158,7 @@ tbn_status launch_binact_mfma(const BinactArgs &a) {
     P.row_bytes = static_cast<int32_t>(a.in / 8);
     const unsigned blocks = static_cast<unsigned>(((a.M + 127) / 128) * P.tiles_n);
     const bool relu = (a.flags & TBN_FLAG_RELU) != 0;
-    if (a.flags & TBN_FLAG_SIGN_OUT) return launch_mfma_t<float, false, true>(a, P, blocks);
+    if (a.flags & TBN_FLAG_SIGN_OUT) return launch_mfma_s<float, false, true, true>(a, P, blocks);
     if (a.dt == TBN_F32) return relu ? launch_mfma_t<float, true>(a, P, blocks) : launch_mfma_t<float, false>(a, P, blocks);
     return relu ? launch_mfma_t<uint16_t, true>(a, P, blocks) : launch_mfma_t<uint16_t, false>(a, P, blocks);
 }
