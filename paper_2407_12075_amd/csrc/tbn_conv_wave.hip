@@ -76,26 +76,30 @@ struct WaveConvParams {
     int32_t sh, sw, ph, pw;
     int32_t n_words, aligned, n_alpha, relu;
     int32_t rows, cols, n_colblk, n_blk;   // pixel block, column blocks per row of blocks, blocks per image
-    int32_t PR, PC;         // patch rows and columns in LDS
+    int32_t PR, PC, pitch;  // patch rows and columns in LDS, LDS pixels from one row to the next
     int32_t step;           // tile bits from one chunk of a wave to its next, modulo p
-    FastDiv d_img, d_blk, d_col, d_cols, d_items;   // workgroups per image, blocks per grid row, column blocks, columns, loads per patch row
+    FastDiv d_img, d_blk, d_col, d_cols, d_items, d_group;   // workgroups per image, blocks per grid row, column blocks, columns, loads per patch row and channel
+    int32_t even;           // bfloat16, 3x3: loads begin at even elements of a plane
     int32_t ks_log2, ps;    // channel slices (power of two) and pixel blocks per workgroup
     int32_t n_chunks;
 };
 
-// px: neighbouring pixels in the 4 bytes that a lane loads of a channel
+// px: neighbouring pixels in the 4 bytes that a lane of a 1x1 layer loads of a channel
 template <typename XT> struct WTraits;
 template <> struct WTraits<float> { static constexpr int planes = 3, px = 1; };
 template <> struct WTraits<uint16_t> { static constexpr int planes = 1, px = 2; };
 
-// LDS pixels of a patch (the last one takes the stores of idle lanes) and the loads per lane and channel that cover them
-constexpr int loads_of(bool f32, int CAP) { return f32 ? (CAP - 1 + 63) / 64 : (CAP - 1 + 127) / 128; }
+// LDS pixels of a patch (the last one takes the stores of idle lanes) and the loads per lane and channel that cover them: pixels or pairs
+// of one channel group after the other, or (RUNS) runs of four pixels of all groups at once, at most run_limit per group.
+constexpr int kCapF32 = 100;   // two workgroups of eight waves per CU
+constexpr int slots_of(int CAP) { return CAP == kCapF32 ? 104 : CAP; }
+constexpr int loads_of(bool f32, int MT, int CAP, bool RUNS) { return RUNS ? 1 : f32 ? (CAP - 1 + 63) / 64 : (CAP - 1 + 127) / 128; }
+constexpr int kRunLimit = 32;
 // registers: what the LDS lets share a SIMD anyway
 constexpr int wave_bound(bool f32, int MT, int T, int PW, int NFT, int CAP) {
-    const int IT = loads_of(f32, CAP);
     if (NFT * PW > 64) return 2;
     if (T == 1) return MT == 16 ? 3 : 4;
-    return f32 ? (CAP <= 100 ? 4 : IT == 2 ? 3 : 2) : IT == 1 ? 4 : 3;
+    return f32 ? (CAP <= 100 ? 4 : CAP == 128 ? 3 : 2) : CAP == 128 ? 4 : 3;
 }
 
 __device__ __forceinline__ uint32_t load_raw(const char *p) {   // 4 bytes, 2-byte aligned for bfloat16 pairs
@@ -130,16 +134,16 @@ template <> struct Acc<16> {
 
 // XT: input and output type; MT: filters (and pixels) of an MFMA tile; T: taps; PW: pixels per wave; NFT: filter tiles
 // per wave; kCap: LDS pixels of a patch; ALL: float32, add what the split of small activations leaves out
-template <typename XT, int MT, int T, int PW, int NFT, int kCap, bool ALL = false>
+template <typename XT, int MT, int T, int PW, int NFT, int kCap, bool RUNS, bool ALL = false>
 __global__ __launch_bounds__(64 * kMaxWaves, (wave_bound(sizeof(XT) == 4, MT, T, PW, NFT, kCap) - (ALL ? 1 : 0))) void conv_wave_kernel(const XT *__restrict__ x, XT *__restrict__ y,
                                                                                          const uint32_t *__restrict__ tile,
                                                                                          const float *__restrict__ alpha, WaveConvParams P) {
     constexpr int NP = WTraits<XT>::planes;
     constexpr int G = 64 / MT, CK = 8 * G;          // channel groups of 8 per MFMA step, channels per chunk
     constexpr int J = PW / MT;                      // pixel tiles per wave
-    constexpr int LP = WTraits<XT>::px;             // pixels per load
-    constexpr int IT = loads_of(sizeof(XT) == 4, kCap);
-    constexpr int kGroup = kCap * 16, kPlane = G * kGroup, kRegion = NP * kPlane;
+    constexpr int LP = RUNS ? 4 : WTraits<XT>::px;  // pixels per load
+    constexpr int IT = loads_of(sizeof(XT) == 4, MT, kCap, RUNS);
+    constexpr int kSlots = slots_of(kCap), kGroup = kSlots * 16, kPlane = G * kGroup, kRegion = NP * kPlane;
     constexpr int NA = Acc<MT>::n;
     extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
 
@@ -178,30 +182,56 @@ __global__ __launch_bounds__(64 * kMaxWaves, (wave_bound(sizeof(XT) == 4, MT, T,
     const int PX = live ? rows * P.cols : 0;
     const int64_t u0 = int64_t(blk_z) * (MT * NFT);
 
-    // ---- staging: which input element a lane reads and where it goes ------------------------------------
-    // A load covers LP neighbouring pixels of an image row (one where a 1x1 layer strides); at the edges of the image
-    // a pair is moved by a pixel, so that nothing outside the row is read; positions outside the image stay zero.
-    uint32_t goff[IT];     // byte offset inside a channel plane
-    uint32_t loff[IT][LP]; // byte offset inside a channel group of the patch
+    // ---- staging: which input elements a lane reads and where they go -----------------------------------
+    // RUNS: a lane takes a run of four neighbouring pixels of a patch row in one channel group, one load per channel: a load takes
+    // the CU's load path about ten cycles however little a lane takes of it, and 512 of them per chunk and CU (16 waves, 16 channels of
+    // two pixels a lane, float32) were 1.9 us in front of the first product, 0.7 now, and as much beside the second chunk's (128 x 256 x
+    // 14^2 -> 256, k = 8: 22.6 us before, 21.3 now; 16 x 512 x 7^2 -> 512, k = 8 19.2 / 17.3).  Else a load covers LP neighbouring pixels of an image row (one where a 1x1 layer
+    // strides).  A load is moved so that it stays inside the plane (1x1: inside the row), and bfloat16 loads of 3x3 layers begin at
+    // even elements where all planes do (pairs at odd ones took 10 cycles instead of 7: 32 x 64 x 56^2 -> 64, k = 4 13.2 us / 12.0; runs
+    // for its tiles of 16 filters, two per lane, cost the registers of the operand reads, 12.4 - 13.8).  183 drawn layers of stride 1
+    // 1.03 times as fast on the mean, 51 of stride 2 1.03.  Positions outside the image stay zero.
+    uint32_t goff[IT];     // byte offset inside a channel plane (RUNS: with that of the lane's channel group)
+    uint32_t loff[IT][(LP + 1) / 2];   // byte offsets inside a channel group of the patch (RUNS: with that of the group), two to a word
+    auto lds_off = [&](int it, int h) __attribute__((always_inline)) { return LP == 1 ? loff[it][0] : h & 1 ? loff[it][h / 2] >> 16 : loff[it][h / 2] & 0xffffu; };
+    const int per_group = P.PR * static_cast<int>(P.d_items.d);   // RUNS: loads per channel of a group
+    auto group_of = [&](int it) { return P.d_group.div(it * 64 + lane); };
     {
         const int iy0 = row0 * P.sh - P.ph, ix0 = col0 * P.sw - P.pw;
         const int sy = T == 1 ? P.sh : 1, sx = T == 1 ? P.sw : 1;         // image steps between patch positions
-        const int per = LP == 2 && sx == 1 ? 2 : 1;                       // patch pixels per load
-        const int n_items = live ? P.PR * static_cast<int>(P.d_items.d) : 0;
+        const int per = T == 9 ? LP : LP == 2 && sx == 1 ? 2 : 1;         // patch pixels per load
+        const int n_items = live ? (RUNS ? G : 1) * per_group : 0;
 #pragma unroll
         for (int it = 0; it < IT; ++it) {
-            const int v = it * 64 + lane;
-            const int py = P.d_items.div(v), px = (v - py * static_cast<int>(P.d_items.d)) * per;
+            const int v = it * 64 + lane, g = RUNS ? group_of(it) : 0, w = v - g * per_group;
+            const int py = P.d_items.div(w), px = (w - py * static_cast<int>(P.d_items.d)) * per;
             const int iy = iy0 + py * sy, ix = ix0 + px * sx;
-            const bool ok = v < n_items && iy >= 0 && iy < P.H && ix > -per && ix < P.W;   // some of its pixels lie in the image
-            int sx0 = ix;                                                 // image column where the load starts
-            if (LP == 2) sx0 = ix < 0 ? 0 : ix > P.W - 2 ? P.W - 2 : ix;
-            goff[it] = ok ? static_cast<uint32_t>((iy * P.W + sx0) * static_cast<int>(sizeof(XT))) : 0u;
+            if constexpr (T == 9 && LP > 1) {
+                const bool ok = v < n_items && iy >= 0 && iy < P.H;
+                const int flat = iy * P.W, last = static_cast<int>(P.HW) - LP;
+                int at = flat + ix - ((flat + ix0) & P.even);
+                at = at < 0 ? 0 : at > last ? last : at;
+                goff[it] = ok ? static_cast<uint32_t>(at) * static_cast<uint32_t>(sizeof(XT)) + static_cast<uint32_t>(8 * g) * static_cast<uint32_t>(P.HW * sizeof(XT)) : 0u;
+                const int c0 = at - flat, p0 = c0 - ix0;                 // image and patch column of the load's first element
+                const uint32_t base = static_cast<uint32_t>((g * kSlots + py * P.pitch + p0) * 16);
 #pragma unroll
-            for (int h = 0; h < LP; ++h) {
-                const int d = sx0 + h - ix;                              // which of the load's patch pixels this half is
-                const bool use = ok && d >= 0 && d < per && px + d < P.PC;
-                loff[it][h] = static_cast<uint32_t>((use ? py * P.PC + px + d : kCap - 1) * 16);
+                for (int h = 0; h < LP; ++h) {   // (a moved load's elements may be another one's too)
+                    const bool use = ok && static_cast<unsigned>(c0 + h) < static_cast<unsigned>(P.W) && static_cast<unsigned>(p0 + h) < static_cast<unsigned>(P.PC);
+                    const uint32_t off = use ? base + 16u * h : (kSlots - 1) * 16u;
+                    loff[it][h / 2] = h & 1 ? loff[it][h / 2] | (off << 16) : off;
+                }
+            } else {
+                const bool ok = v < n_items && iy >= 0 && iy < P.H && ix > -per && ix < P.W;   // some of its pixels lie in the image
+                int sx0 = ix;                                             // image column where the load starts
+                if (LP == 2) sx0 = ix < 0 ? 0 : ix > P.W - 2 ? P.W - 2 : ix;
+                goff[it] = ok ? static_cast<uint32_t>((iy * P.W + sx0) * static_cast<int>(sizeof(XT))) : 0u;
+#pragma unroll
+                for (int h = 0; h < LP; ++h) {
+                    const int d = sx0 + h - ix;                          // which of the load's patch pixels this element is
+                    const bool use = ok && d >= 0 && d < per && px + d < P.PC;
+                    const uint32_t off = static_cast<uint32_t>((use ? py * P.PC + px + d : kSlots - 1) * 16);
+                    loff[it][h / 2] = h & 1 ? loff[it][h / 2] | (off << 16) : off;
+                }
             }
         }
     }
@@ -212,19 +242,42 @@ __global__ __launch_bounds__(64 * kMaxWaves, (wave_bound(sizeof(XT) == 4, MT, T,
 
     // Loads of a 1x1 layer run two chunks ahead (a chunk is a handful of MFMAs), those of a 3x3 layer one.
     constexpr int kSets = T == 1 ? 2 : 1;
-    uint32_t staged[kSets][G][IT][8];
+    constexpr int GL = RUNS ? 1 : G, RW = RUNS ? static_cast<int>(sizeof(XT)) : 1;   // groups a lane loads of, words per load
+    uint32_t staged[kSets][GL][IT][8][RW];
     auto load_chunk = [&](int chunk, auto set_c) {
         auto &st = staged[decltype(set_c)::value];
         const int c0 = chunk * CK;
         const char *b = x_img + c0 * hwb;
+        if constexpr (RUNS) {
+            const int c_left = P.C - c0;
+            if (c_left >= CK) {
 #pragma unroll
-        for (int g = 0; g < G; ++g)
+                for (int j = 0; j < 8; ++j) {
 #pragma unroll
-            for (int j = 0; j < 8; ++j) {
+                    for (int it = 0; it < IT; ++it) __builtin_memcpy(st[0][it][j], b + goff[it], 4 * RW);
+                    b += hwb;
+                }
+            } else {   // past the last channel: that one again, dropped below
 #pragma unroll
-                for (int it = 0; it < IT; ++it) st[g][it][j] = load_raw(b + goff[it]);
-                b += c0 + g * 8 + j + 1 < P.C ? hwb : 0;   // past the last channel: that one again, dropped below
+                for (int it = 0; it < IT; ++it)
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) {
+                        const int over = 8 * group_of(it) + j - (c_left - 1);
+                        const char *at = b + j * hwb + goff[it];
+                        if (goff[it] != 0u && over > 0) at -= over * hwb;
+                        __builtin_memcpy(st[0][it][j], j < c_left || goff[it] != 0u ? at : b, 4 * RW);
+                    }
             }
+        } else {
+#pragma unroll
+            for (int g = 0; g < G; ++g)
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+#pragma unroll
+                    for (int it = 0; it < IT; ++it) st[g][it][j][0] = load_raw(b + goff[it]);
+                    b += c0 + g * 8 + j + 1 < P.C ? hwb : 0;   // past the last channel: that one again, dropped below
+                }
+        }
     };
     uint32_t low_bits = 0u;   // ALL: of the third terms; the low 16 have no place in a bfloat16 (activations below 2^-110)
     auto store_chunk = [&](int chunk, auto set_c) __attribute__((always_inline)) {
@@ -232,42 +285,45 @@ __global__ __launch_bounds__(64 * kMaxWaves, (wave_bound(sizeof(XT) == 4, MT, T,
         const int c_left = P.C - chunk * CK;
         if (c_left < CK) {   // channels past the last one are zeros
 #pragma unroll
-            for (int g = 0; g < G; ++g)
+            for (int g = 0; g < GL; ++g)
 #pragma unroll
                 for (int j = 0; j < 8; ++j)
 #pragma unroll
-                    for (int it = 0; it < IT; ++it) st[g][it][j] = g * 8 + j < c_left ? st[g][it][j] : 0u;
+                    for (int it = 0; it < IT; ++it)
+#pragma unroll
+                        for (int e = 0; e < RW; ++e)
+                            st[g][it][j][e] = 8 * (RUNS ? group_of(it) : g) + j < c_left ? st[g][it][j][e] : 0u;
         }
 #pragma unroll
-        for (int g = 0; g < G; ++g)
+        for (int g = 0; g < GL; ++g)
 #pragma unroll
             for (int it = 0; it < IT; ++it) {
-                uint32_t *s = st[g][it];
-                if constexpr (NP == 1) {   // channel pairs of the two pixels
 #pragma unroll
-                    for (int h = 0; h < LP; ++h) {
+                for (int h = 0; h < LP; ++h) {
+                    unsigned char *dst = region + lds_off(it, h) + (RUNS ? 0 : g * kGroup);
+                    if constexpr (NP == 1) {   // channel pairs of one pixel
                         u32x4_t v;
 #pragma unroll
-                        for (int e = 0; e < 4; ++e) v[e] = __builtin_amdgcn_perm(s[2 * e + 1], s[2 * e], h ? 0x07060302u : 0x05040100u);
-                        *reinterpret_cast<u32x4_t *>(region + loff[it][h] + g * kGroup) = v;
-                    }
-                } else {   // exact three-term split: the top 8 significand bits, the next 8, the rest
-                    unsigned char *dst = region + loff[it][0] + g * kGroup;
-                    u32x4_t v0, v1, v2;
+                        for (int e = 0; e < 4; ++e) v[e] = __builtin_amdgcn_perm(st[g][it][2 * e + 1][h / 2], st[g][it][2 * e][h / 2], h & 1 ? 0x07060302u : 0x05040100u);
+                        *reinterpret_cast<u32x4_t *>(dst) = v;
+                    } else {   // exact three-term split: the top 8 significand bits, the next 8, the rest
+                        u32x4_t v0, v1, v2;
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const float a = __uint_as_float(s[2 * e]), b = __uint_as_float(s[2 * e + 1]);
-                        const float a1 = a - __uint_as_float(s[2 * e] & 0xffff0000u), b1 = b - __uint_as_float(s[2 * e + 1] & 0xffff0000u);
-                        const float a2 = a1 - __uint_as_float(__float_as_uint(a1) & 0xffff0000u);
-                        const float b2 = b1 - __uint_as_float(__float_as_uint(b1) & 0xffff0000u);
-                        if (ALL) low_bits |= __float_as_uint(a2) | __float_as_uint(b2);
-                        v0[e] = pack_hi16(s[2 * e], s[2 * e + 1]);
-                        v1[e] = pack_hi16(__float_as_uint(a1), __float_as_uint(b1));
-                        v2[e] = pack_hi16(__float_as_uint(a2), __float_as_uint(b2));
+                        for (int e = 0; e < 4; ++e) {
+                            const uint32_t sa = st[g][it][2 * e][h], sb = st[g][it][2 * e + 1][h];
+                            const float a = __uint_as_float(sa), b = __uint_as_float(sb);
+                            const float a1 = a - __uint_as_float(sa & 0xffff0000u), b1 = b - __uint_as_float(sb & 0xffff0000u);
+                            const float a2 = a1 - __uint_as_float(__float_as_uint(a1) & 0xffff0000u);
+                            const float b2 = b1 - __uint_as_float(__float_as_uint(b1) & 0xffff0000u);
+                            if (ALL) low_bits |= __float_as_uint(a2) | __float_as_uint(b2);
+                            v0[e] = pack_hi16(sa, sb);
+                            v1[e] = pack_hi16(__float_as_uint(a1), __float_as_uint(b1));
+                            v2[e] = pack_hi16(__float_as_uint(a2), __float_as_uint(b2));
+                        }
+                        *reinterpret_cast<u32x4_t *>(dst) = v0;
+                        *reinterpret_cast<u32x4_t *>(dst + kPlane) = v1;
+                        *reinterpret_cast<u32x4_t *>(dst + 2 * kPlane) = v2;
                     }
-                    *reinterpret_cast<u32x4_t *>(dst) = v0;
-                    *reinterpret_cast<u32x4_t *>(dst + kPlane) = v1;
-                    *reinterpret_cast<u32x4_t *>(dst + 2 * kPlane) = v2;
                 }
             }
     };
@@ -320,7 +376,7 @@ __global__ __launch_bounds__(64 * kMaxWaves, (wave_bound(sizeof(XT) == 4, MT, T,
         const int yo = P.d_cols.div(px), xo = px - yo * P.cols;
 #pragma unroll
         for (int dy = 0; dy < DY; ++dy)
-            rd[j][dy] = region + q * kGroup + (T == 1 ? yo * P.PC + xo : (yo * P.sh + dy) * P.PC + xo * P.sw) * 16;
+            rd[j][dy] = region + q * kGroup + (T == 1 ? yo * P.PC + xo : (yo * P.sh + dy) * P.pitch + xo * P.sw) * 16;
     }
     const int n_tiles = (PX + MT - 1) / MT;          // pixel tiles with pixels (uniform)
     uint32_t sign_mask = 0x80008000u, one_bits = 0x3f803f80u;
@@ -576,13 +632,14 @@ __global__ __launch_bounds__(64 * kMaxWaves, (wave_bound(sizeof(XT) == 4, MT, T,
 }
 
 constexpr double kLineCost = 6;   // cycles per output line of a wave
-constexpr int kCapF32 = 100;   // two workgroups of eight waves per CU
 
 struct WavePlan {
     bool ok;
-    int mt, pw, nft, cap, rows, cols, n_colblk, n_rowblk, PR, PC, ks_log2, ps, n_chunks, waves;
+    int mt, pw, nft, cap, rows, cols, n_colblk, n_rowblk, PR, PC, pitch, ks_log2, ps, n_chunks, waves;
     size_t lds;
     int64_t total_waves;
+    bool runs;        // staged four pixels at a time
+    bool even;        // bfloat16 loads begin at even elements
     bool all_bits;
     bool preferred;   // over tbn_conv_mfma.hip
 };
@@ -667,7 +724,13 @@ WavePlan plan_wave_for(const ConvArgs &a, int nft) {
     // Channel slices, each at least one chunk: until the chip (1024 SIMDs) has about four waves per SIMD, which cover each
     // other's waits.  A float32 patch of more than 100 pixels takes 12 - 18 KiB of LDS per wave: workgroups of eight waves
     // would leave room for one per CU, so eight slices are for grids that would leave SIMDs empty.
+    // Runs of four pixels: 3x3, patches of up to 128 pixels whose runs fit, planes that hold one, offsets over 32 channels in 32 bits
+    const int row_px = pl.PC + (f32 || a.H * a.W % 2 != 0 ? 0 : 1);
+    pl.runs = three && pl.cap == 128 && pl.mt == 32 && pl.PR * ((row_px + 3) / 4) <= kRunLimit && a.H * a.W >= 4 && a.H * a.W < (int64_t(1) << 25);
+    pl.even = three && !f32 && a.H * a.W % 2 == 0 && (pl.runs || pl.PR * ((row_px + 1) / 2) <= (pl.cap == 128 ? 64 : 128));
     if (f32 && !one && pl.cap == 128 && pl.PR * pl.PC <= kCapF32 - 1) pl.cap = kCapF32;
+    // an odd number of LDS pixels per row where one is free: the runs that 16 lanes store then lie on different banks
+    pl.pitch = pl.runs && pl.PC % 4 == 0 && pl.PR * (pl.PC + 1) <= slots_of(pl.cap) - 1 ? pl.PC + 1 : pl.PC;
     int ks_log2 = 0;
     const int64_t units = blocks * a.N * fblocks, want8 = f32 && !one && pl.cap != kCapF32 ? 1024 : 4096;
     while (ks_log2 < 3 && (2 << ks_log2) <= pl.n_chunks && units << ks_log2 < (ks_log2 == 2 ? want8 : 4096)) {
@@ -680,7 +743,7 @@ WavePlan plan_wave_for(const ConvArgs &a, int nft) {
     pl.ps = ks_log2 >= 2 ? 1 : 4 >> ks_log2;
     if (pl.ps > blocks) pl.ps = static_cast<int>(blocks);
     pl.waves = pl.ps << ks_log2;
-    const size_t region = size_t(np) * (64 / pl.mt) * pl.cap * 16;
+    const size_t region = size_t(np) * (64 / pl.mt) * slots_of(pl.cap) * 16;
     const size_t red = size_t(pl.waves) * pl.mt * pl.pw * 4;
     pl.lds = std::max(region * pl.waves, red);
     pl.ok = pl.lds <= 160 * 1024;
@@ -771,17 +834,17 @@ WavePlan plan_wave(const ConvArgs &a) {
     return e.plan;
 }
 
-template <typename XT, int MT, int T, int PW, int NFT, int CAP, bool ALL = false>
+template <typename XT, int MT, int T, int PW, int NFT, int CAP, bool RUNS = false, bool ALL = false>
 tbn_status launch_wave_t(const ConvArgs &a, const WaveConvParams &P, const WavePlan &pl, dim3 grid) {
     if constexpr (sizeof(XT) == 4 && !ALL)
-        if (pl.all_bits) return launch_wave_t<XT, MT, T, PW, NFT, CAP, true>(a, P, pl, grid);
-    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(&conv_wave_kernel<XT, MT, T, PW, NFT, CAP, ALL>),
+        if (pl.all_bits) return launch_wave_t<XT, MT, T, PW, NFT, CAP, RUNS, true>(a, P, pl, grid);
+    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(&conv_wave_kernel<XT, MT, T, PW, NFT, CAP, RUNS, ALL>),
                                                        hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     if (attr != hipSuccess) {
         set_error("tbn_conv2d_forward: cannot reserve %zu bytes of LDS", pl.lds);
         return TBN_ERR_DEVICE;
     }
-    hipLaunchKernelGGL((conv_wave_kernel<XT, MT, T, PW, NFT, CAP, ALL>), grid, dim3(64 * pl.waves), pl.lds, a.stream,
+    hipLaunchKernelGGL((conv_wave_kernel<XT, MT, T, PW, NFT, CAP, RUNS, ALL>), grid, dim3(64 * pl.waves), pl.lds, a.stream,
                        static_cast<const XT *>(a.x), static_cast<XT *>(a.y), a.tile, a.alpha, P);
     return check_launch("tbn_conv2d_forward (one wave per pixel block)");
 }
@@ -796,9 +859,11 @@ tbn_status launch_wave_shape(const ConvArgs &a, const WaveConvParams &P, const W
         if (pl.pw == 32) return launch_wave_t<XT, MT, 9, 32, NFT, kLarge>(a, P, pl, grid);
         if (pl.cap == kLarge) return launch_wave_t<XT, MT, 9, 64, NFT, kLarge>(a, P, pl, grid);
     }
+    if constexpr (MT == 16) return launch_wave_t<XT, MT, 9, 64, NFT, 128>(a, P, pl, grid);
     if constexpr (f32)
-        if (pl.cap == kCapF32) return launch_wave_t<XT, MT, 9, 64, NFT, kCapF32>(a, P, pl, grid);
-    return launch_wave_t<XT, MT, 9, 64, NFT, 128>(a, P, pl, grid);
+        if (pl.cap == kCapF32)
+            return pl.runs ? launch_wave_t<XT, MT, 9, 64, NFT, kCapF32, true>(a, P, pl, grid) : launch_wave_t<XT, MT, 9, 64, NFT, kCapF32>(a, P, pl, grid);
+    return pl.runs ? launch_wave_t<XT, MT, 9, 64, NFT, 128, true>(a, P, pl, grid) : launch_wave_t<XT, MT, 9, 64, NFT, 128>(a, P, pl, grid);
     }
 }
 
@@ -834,7 +899,7 @@ tbn_status launch_conv_wave(const ConvArgs &layer) {
     P.n_alpha = a.n_alpha;
     P.relu = (a.flags & TBN_FLAG_RELU) ? 1 : 0;
     P.rows = pl.rows; P.cols = pl.cols; P.n_colblk = pl.n_colblk; P.n_blk = pl.n_rowblk * pl.n_colblk;
-    P.PR = pl.PR; P.PC = pl.PC;
+    P.PR = pl.PR; P.PC = pl.PC; P.pitch = pl.pitch;
     const int CK = 8 * (64 / pl.mt);
     P.step = static_cast<int32_t>(((int64_t(CK) << pl.ks_log2) * a.kh * a.kw) % a.p);
     P.ks_log2 = pl.ks_log2; P.ps = pl.ps; P.n_chunks = pl.n_chunks;
@@ -844,7 +909,10 @@ tbn_status launch_conv_wave(const ConvArgs &layer) {
     P.d_blk = FastDiv(gx);
     P.d_col = FastDiv(pl.n_colblk);
     P.d_cols = FastDiv(pl.cols);
-    P.d_items = FastDiv(a.dt == TBN_F32 || (a.kh == 1 && a.sw > 1) ? pl.PC : (pl.PC + 1) / 2);
+    P.even = pl.even && (reinterpret_cast<uintptr_t>(a.x) & 3u) == 0 ? 1 : 0;
+    const int row_px = pl.PC + (pl.even ? 1 : 0);
+    P.d_items = FastDiv(pl.runs ? (row_px + 3) / 4 : a.dt == TBN_F32 || (a.kh == 1 && a.sw > 1) ? pl.PC : (row_px + 1) / 2);
+    P.d_group = FastDiv(int64_t(P.PR) * P.d_items.d);
     const dim3 grid(static_cast<unsigned>(gx), static_cast<unsigned>(a.N), static_cast<unsigned>(fblocks));
     tbn_status st;
     if (a.dt == TBN_F32)
