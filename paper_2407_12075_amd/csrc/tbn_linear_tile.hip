@@ -27,6 +27,12 @@
 //   * the sums are turned round through LDS, 32 x 32 at a time, so that a store instruction writes whole
 //     lines of Y (a lane of the accumulator layout holds four adjacent columns of one row only).
 //
+// float32: the K loop as a pipeline over steps (see there) and two chunks in flight for long rows in one slice, 150 drawn layers
+// of 157 - 12200 rows: 1.105 times as fast on the mean, 0.98 - 1.4 each (8192 x 4096 -> 4096, k = 8: 130.8 us before, 129.6 now;
+// 826 x 3712 -> 2624 distinct columns 77.1 / 59.3; 4304 x 2176 -> 128 34.4 / 29.0; 12608 x 384 -> 1536 and 1536 -> 384, k = 4,
+// 43.4 / 42.3 together).  On big layers the matrix pipe then runs at its limit of power: 60 cycles per product at 1.76 GHz before, 54 at
+// 1.62 now.
+//
 // bfloat16 with K split, graph replays, 4096 -> 512 distinct columns, batch 300: 9.0 us before, 6.4 now (8192: 14.0 / 10.7;
 // 1024: 5.3 / 4.2).  A wave per 32 columns where that leaves a workgroup per CU (8.7 -> 6.9), sums and stores by all waves, the table
 // filled behind the first loads and barriers that order LDS only (-> 6.4); the alphas of 64 replicas in lanes, no branch in the
@@ -73,25 +79,6 @@ struct TileParams {
     int32_t k_per_wave;   // K slice of a wave (whole chunks)
 };
 
-// truncation split of eight floats into three bf16x8 operands: term 0 = top 8 significand bits, term 1 = the next 8,
-// term 2 = the rest (at most 8 bits, so its truncation to bfloat16 is exact)
-__device__ __forceinline__ void split8(const float (&x)[8], Frag (&t)[3]) {
-    uint32_t h[3][8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        const uint32_t t0 = __float_as_uint(x[i]) & 0xffff0000u;
-        const float r1 = x[i] - __uint_as_float(t0);
-        const uint32_t t1 = __float_as_uint(r1) & 0xffff0000u;
-        const float r2 = r1 - __uint_as_float(t1);
-        h[0][i] = t0; h[1][i] = t1; h[2][i] = __float_as_uint(r2);
-    }
-#pragma unroll
-    for (int j = 0; j < 3; ++j)
-#pragma unroll
-        for (int v = 0; v < 4; ++v)   // high halves of two words in one: (lo >> 16) | (hi & 0xffff0000)
-            t[j].q[v] = __builtin_amdgcn_perm(h[j][2 * v + 1], h[j][2 * v], 0x07060302u);
-}
-
 // barrier that orders LDS only: __syncthreads would wait for the loads in flight
 __device__ __forceinline__ void lds_barrier() {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
@@ -116,8 +103,16 @@ struct Lds {
     static constexpr int kBytes = 4096 + KW * kRegion;
 };
 
-template <typename XT, bool RELU, int NT, int KW>
-__global__ __launch_bounds__(64 * KW) void linear_tile_kernel(const XT *__restrict__ x, XT *__restrict__ y,
+// float32, one wave per workgroup: chunks of K above which two of them are on their way instead of one.  A lone wave per SIMD has
+// 8 KiB in flight with one (10685 x 5952 -> 64 distinct columns, 93 chunks: 111 us with one, 82 with two).  Two take 40 registers and a
+// longer beginning and end: 7 - 8 / 9 - 12 chunks 2.5 / 1 % slower than with one, 13 - 20 / 21 - 40 / more 7 / 12 / 17 % faster on the
+// mean.  With K split among waves there is enough in flight, and two are 1 - 5 % slower (282 drawn layers; one column tile and at most a
+// wave per SIMD alone would gain, 5 %).
+constexpr int32_t kLongSlice = 12;
+
+// (float32: at most 256 registers, or the sums go to accumulation registers, which a tie would move them out of and back)
+template <typename XT, bool RELU, int NT, int KW, int AHEAD>
+__global__ __launch_bounds__(64 * KW, (std::is_same<XT, float>::value || KW == 8 ? 2 : 1)) void linear_tile_kernel(const XT *__restrict__ x, XT *__restrict__ y,
                                                               const uint32_t *__restrict__ tile,
                                                               const float *__restrict__ alpha, TileParams P) {
     typedef Lds<NT, KW> L;
@@ -152,7 +147,7 @@ __global__ __launch_bounds__(64 * KW) void linear_tile_kernel(const XT *__restri
     }
     const int64_t m0 = int64_t(rt) * 32;
     const int32_t u0 = cg * (NT * 32);
-    const int32_t k_begin = wave * P.k_per_wave;
+    const int32_t k_begin = __builtin_amdgcn_readfirstlane(wave) * P.k_per_wave;
 
     // loads: instruction (i, h) of a chunk reads rows 8i + lane/8, bytes 128h + 16*(lane%8) .. + 15 of the chunk's 256:
     // eight lanes cover a whole 128-byte line.  Rows past M repeat the last one; they are never written.
@@ -179,12 +174,12 @@ __global__ __launch_bounds__(64 * KW) void linear_tile_kernel(const XT *__restri
             rd_pos[s4][j] = static_cast<uint32_t>(ln * 256 + (((8 * lg + kReads * s4 + j) ^ (ln & 15)) << 4));
 
     // tile words of this lane's column in every column tile: bit u * in + k; a lane half covers kWords words per chunk
-    const uint32_t *tp[NT];
+    const unsigned char *t_blk = reinterpret_cast<const unsigned char *>(tile + ((int64_t(u0) * P.in + k_begin) >> 5));
+    uint32_t t_off[NT];   // byte offsets from t_blk
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
-        int32_t u = u0 + 32 * t + ln;
-        u = u < P.U ? u : P.U - 1;   // columns past U repeat the last one; never written
-        tp[t] = tile + ((int64_t(u) * P.in + k_begin) >> 5) + kWords * lg;
+        const int32_t u = 32 * t + ln, u_last = P.U - 1 - u0;   // columns past U repeat the last one; never written
+        t_off[t] = (static_cast<uint32_t>(u < u_last ? u : u_last) * static_cast<uint32_t>(P.in) >> 3) + 4 * kWords * lg;
     }
 
     f32x16_t acc[NT];
@@ -193,9 +188,10 @@ __global__ __launch_bounds__(64 * KW) void linear_tile_kernel(const XT *__restri
 #pragma unroll
         for (int e = 0; e < 16; ++e) acc[t][e] = 0.f;
 
-    u32x4_t xr[8];        // the chunk in flight: [i][h]
-    uint32_t wr[NT][kWords];
-    auto load_chunk = [&](int32_t c) {
+    static_assert(AHEAD == 1 || (kF32 && AHEAD == 2), "");
+    u32x4_t xr[AHEAD][8];   // the chunks in flight: [i][h]
+    uint32_t wr[AHEAD][NT][kWords];
+    auto load_chunk = [&](int32_t c, u32x4_t (&xr)[8], uint32_t (&wr)[NT][kWords]) __attribute__((always_inline)) {
         const unsigned char *src = x_blk + c * kChunkBytes;
 #pragma unroll
         for (int i = 0; i < 4; ++i)
@@ -204,11 +200,11 @@ __global__ __launch_bounds__(64 * KW) void linear_tile_kernel(const XT *__restri
 #pragma unroll
         for (int t = 0; t < NT; ++t)
 #pragma unroll
-            for (int w = 0; w < kWords; ++w) wr[t][w] = tp[t][c * 2 * kWords + w];
+            for (int w = 0; w < kWords; ++w) wr[t][w] = reinterpret_cast<const uint32_t *>(t_blk + c * 8 * kWords + t_off[t])[w];
     };
 
     const int32_t chunks = P.k_per_wave / kCE;   // >= 1
-    load_chunk(0);
+    load_chunk(0, xr[0], wr[0]);
     const int32_t reps = P.reps;
     float av = alpha[P.n_alpha == 1 || lane >= reps ? 0 : lane];   // alphas of the first 64 replicas, one per lane
 
@@ -222,52 +218,161 @@ __global__ __launch_bounds__(64 * KW) void linear_tile_kernel(const XT *__restri
     }
     lds_barrier();
 
-    // A chunk goes to LDS, the next one is requested, then this one is multiplied from LDS.  bfloat16: the last chunk requests
+    // bfloat16: a chunk goes to LDS, the next one is requested, then this one is multiplied from LDS.  The last chunk requests
     // nothing and stands by itself, because with a condition around the loads the compiler cannot count them in its waits (batch
     // 300, 4096 -> 512 distinct columns 6.4 us against 6.6); it then has to be kept from moving them down, which four waves pay for
     // with every chunk (312 x 8704 -> 976 distinct columns: 15.5 us with the condition, 17.5 with the loads moved down, 14.1 now; 177 x
-    // 5632 -> 1664: 11.8 / 13.0 / 10.6; eight waves are level: 300 x 8192 -> 512 14.3 / 10.5 / 10.6).  float32, at many rows: the
-    // shorter code is the faster (12608 x 384 -> 384 distinct columns 23.3 against 24.0).
+    // 5632 -> 1664: 11.8 / 13.0 / 10.6; eight waves are level: 300 x 8192 -> 512 14.3 / 10.5 / 10.6).
     auto multiply_chunk = [&](int32_t c, auto more) {
         uint32_t wc[NT][kWords];
 #pragma unroll
         for (int t = 0; t < NT; ++t)
 #pragma unroll
-            for (int w = 0; w < kWords; ++w) wc[t][w] = wr[t][w];
+            for (int w = 0; w < kWords; ++w) wc[t][w] = wr[0][t][w];
 #pragma unroll
         for (int i = 0; i < 4; ++i)
 #pragma unroll
-            for (int h = 0; h < 2; ++h) *reinterpret_cast<u32x4_t *>(region_b + st_pos[i][h]) = xr[2 * i + h];
+            for (int h = 0; h < 2; ++h) *reinterpret_cast<u32x4_t *>(region_b + st_pos[i][h]) = xr[0][2 * i + h];
         __builtin_amdgcn_wave_barrier();   // lanes read what other lanes of the wave wrote (LDS operations of a wave stay in order)
-        if (decltype(more)::value && (!kF32 || c + 1 < chunks)) load_chunk(c + 1);
-        // bfloat16: left to itself the compiler moves these loads behind most of the products below, which they are to run under
-        if constexpr (!kF32) __builtin_amdgcn_sched_barrier(0);
+        if (decltype(more)::value) load_chunk(c + 1, xr[0], wr[0]);
+        // left to itself the compiler moves these loads behind most of the products below, which they are to run under
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int s4 = 0; s4 < kSteps; ++s4) {
-            constexpr int kTerms = kF32 ? 3 : 1;
-            Frag xt[kTerms];
-            if constexpr (kF32) {
-                const f32x4_t a = *reinterpret_cast<const f32x4_t *>(region_b + rd_pos[s4][0]);
-                const f32x4_t b = *reinterpret_cast<const f32x4_t *>(region_b + rd_pos[s4][kReads - 1]);
-                const float xs[8] = {a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
-                split8(xs, xt);
-            } else {
-                xt[0].q = *reinterpret_cast<const u32x4_t *>(region_b + rd_pos[s4][0]);
-            }
+            Frag xt;
+            xt.q = *reinterpret_cast<const u32x4_t *>(region_b + rd_pos[s4][0]);
 #pragma unroll
             for (int t = 0; t < NT; ++t) {
                 Frag sg;
                 sg.q = s_table[(wc[t][s4 / 4] >> (8 * (s4 % 4))) & 0xffu];
-#pragma unroll
-                for (int j = 0; j < kTerms; ++j)
-                    acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(sg.v, xt[j].v, acc[t], 0, 0, 0);
+                acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(sg.v, xt.v, acc[t], 0, 0, 0);
             }
         }
         __builtin_amdgcn_wave_barrier();   // the next chunk overwrites the region
     };
-    int32_t c = 0;
-    for (; c + (kF32 ? 0 : 1) < chunks; ++c) multiply_chunk(c, std::true_type{});
-    if constexpr (!kF32) multiply_chunk(c, std::false_type{});
+    if constexpr (kF32) {
+        // float32: the split of a step's activations into terms takes 44 vector instructions, as long as six of its products.  One
+        // after the other (many rows and distinct columns leave one wave per SIMD) that was 60 cycles per product of 32; here the
+        // next step's split is dealt to the slots behind this step's matrix instructions (pinned there: the compiler would put the
+        // split in front of all of them), its signs and the activations of the step after next are read meanwhile, and the next
+        // chunk goes to LDS in the slots of the second step.  The sums are formed in the order they had: the same bits.
+        constexpr int kSlots = 3 * NT, kUnits = 12;   // units of the split: element, element, their pair's six halves
+        float xs[2][8];              // activations of a step, by its parity
+        Frag xt[2][3], sg[2][NT];    // terms and signs of a step, by its parity
+        uint32_t wc[NT], wn[NT];     // tile words of this chunk and the next
+        uint32_t ww[AHEAD][NT];      // of the chunks that are on their way
+        uint32_t hold[2][3];         // terms of the pair that is being split
+        auto request = [&](int32_t c, u32x4_t (&xn)[8], uint32_t (&wx)[NT]) __attribute__((always_inline)) {
+            const unsigned char *src = x_blk + c * kChunkBytes, *words = t_blk + c * 8;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                asm volatile("" : "+v"(ld_off[i]));   // or the compiler keeps 64-bit addresses of all of them in registers
+#pragma unroll
+                for (int h = 0; h < 2; ++h) xn[2 * i + h] = *reinterpret_cast<const u32x4_t *>(src + ld_off[i] + 128 * h);
+            }
+#pragma unroll
+            for (int t = 0; t < NT; ++t) {
+                asm volatile("" : "+v"(t_off[t]));
+                wx[t] = *reinterpret_cast<const uint32_t *>(words + t_off[t]);
+            }
+        };
+        auto store = [&](int n, const u32x4_t (&v)[8]) __attribute__((always_inline)) {
+            *reinterpret_cast<u32x4_t *>(region_b + st_pos[n >> 1][n & 1]) = v[n];
+        };
+        auto read = [&](float (&v)[8], int s4) __attribute__((always_inline)) {
+            const f32x4_t a = *reinterpret_cast<const f32x4_t *>(region_b + rd_pos[s4][0]);
+            const f32x4_t b = *reinterpret_cast<const f32x4_t *>(region_b + rd_pos[s4][kReads - 1]);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) { v[i] = a[i]; v[4 + i] = b[i]; }
+        };
+        auto signs = [&](Frag &g, uint32_t word, int s4) __attribute__((always_inline)) { g.q = s_table[(word >> (8 * s4)) & 0xffu]; };
+        auto unit = [&](int n, const float (&v)[8], Frag (&t)[3]) __attribute__((always_inline)) {
+            // truncation: term 0 = top 8 significand bits, term 1 = the next 8, term 2 = the rest (at most 8 bits: exact)
+            const int pair = n / 3, k = n % 3;
+            if (k < 2) {
+                const float a = v[2 * pair + k];
+                const uint32_t t0 = __float_as_uint(a) & 0xffff0000u;
+                const float r1 = a - __uint_as_float(t0);
+                const float r2 = r1 - __uint_as_float(__float_as_uint(r1) & 0xffff0000u);
+                hold[k][0] = __float_as_uint(a); hold[k][1] = __float_as_uint(r1); hold[k][2] = __float_as_uint(r2);
+                asm volatile("" : "+v"(hold[k][0]), "+v"(hold[k][1]), "+v"(hold[k][2]));
+            } else {   // high halves of two words in one
+#pragma unroll
+                for (int j = 0; j < 3; ++j) t[j].q[pair] = __builtin_amdgcn_perm(hold[1][j], hold[0][j], 0x07060302u);
+                uint32_t p0 = t[0].q[pair], p1 = t[1].q[pair], p2 = t[2].q[pair];
+                asm volatile("" : "+v"(p0), "+v"(p1), "+v"(p2));
+                t[0].q[pair] = p0; t[1].q[pair] = p1; t[2].q[pair] = p2;
+            }
+        };
+        if constexpr (AHEAD == 2) request(1, xr[1], ww[1]);
+#pragma unroll
+        for (int n = 0; n < 8; ++n) store(n, xr[0]);
+        __builtin_amdgcn_wave_barrier();   // lanes read what other lanes of the wave wrote (LDS operations of a wave stay in order)
+        read(xs[0], 0);
+        read(xs[1], 1);
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+            wc[t] = wr[0][t][0];
+            signs(sg[0][t], wc[t], 0);
+        }
+        if (AHEAD == 2 || chunks > 1) request(AHEAD, xr[0], ww[0]);   // two ahead: chunks > 4
+#pragma unroll
+        for (int n = 0; n < kUnits; ++n) unit(n, xs[0], xt[0]);
+        auto chunk = [&](int32_t c, u32x4_t (&xn)[8], uint32_t (&wx)[NT], auto all) __attribute__((always_inline)) {
+#pragma unroll
+            for (int s4 = 0; s4 < kSteps; ++s4) {
+                const int cur = s4 & 1, nxt = cur ^ 1;
+                read(xs[cur], (s4 + 2) & 3);   // (behind the last chunk: what is there, not used)
+                if (s4 == 2) {   // the chunk after those that are on their way
+#pragma unroll
+                    for (int t = 0; t < NT; ++t) wn[t] = wx[t];
+                    if (decltype(all)::value || c + 1 + AHEAD < chunks) request(c + 1 + AHEAD, xn, wx);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int i = 0; i < kSlots; ++i) {
+                    const int j = i / NT, t = i % NT;
+                    acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(sg[cur][t].v, xt[cur][j].v, acc[t], 0, 0, 0);
+                    asm volatile("" : "+v"(acc[t]));
+                    if (i < NT) signs(sg[nxt][i], s4 < 3 ? wc[i] : wn[i], (s4 + 1) & 3);
+                    // the next chunk to LDS, behind the reads of this one's last step (behind the last chunk: what is there)
+                    if (s4 == 1) {
+#pragma unroll
+                        for (int n = 0; n < 8; ++n)
+                            if (n * kSlots / 8 == i) store(n, xn);
+                    }
+#pragma unroll
+                    for (int n = 0; n < kUnits; ++n)
+                        if (n * kSlots / kUnits == i) unit(n, xs[nxt], xt[nxt]);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                if (s4 == 1) __builtin_amdgcn_wave_barrier();
+            }
+#pragma unroll
+            for (int t = 0; t < NT; ++t) wc[t] = wn[t];
+        };
+        int32_t c = 0;
+        if constexpr (AHEAD == 2) {
+            // With a condition around the loads the compiler cannot count them, and a wait for one chunk waits for both: the chunks
+            // that still have two pairs ahead go without.  (Loading the same 16 bytes for a chunk that is not there costs 5 %.)
+            do {
+                chunk(c, xr[1], ww[1], std::true_type{});
+                chunk(c + 1, xr[0], ww[0], std::true_type{});
+                c += 2;
+            } while (c + 4 < chunks);
+            for (; c < chunks; c += 2) {
+                chunk(c, xr[1], ww[1], std::false_type{});
+                if (c + 1 < chunks) chunk(c + 1, xr[0], ww[0], std::false_type{});
+            }
+        } else {
+            for (; c < chunks; ++c) chunk(c, xr[0], ww[0], std::false_type{});
+        }
+        __builtin_amdgcn_wave_barrier();
+    } else {
+        int32_t c = 0;
+        for (; c + 1 < chunks; ++c) multiply_chunk(c, std::true_type{});
+        multiply_chunk(c, std::false_type{});
+    }
 
     // ---- bfloat16, K split: every thread adds CP neighbouring outputs of one row over the waves, in wave order (results are the
     // same from run to run), and writes them.  (One wave adding and writing a column tile while the others idle: see the top.)
@@ -444,28 +549,31 @@ __global__ __launch_bounds__(64 * KW) void linear_tile_kernel(const XT *__restri
     }
 }
 
-template <typename XT, bool RELU, int NT, int KW>
+template <typename XT, bool RELU, int NT, int KW, int AHEAD>
 tbn_status launch_one(const LinearArgs &a, const TileParams &P, unsigned grid) {
     typedef Lds<NT, KW> L;
     // dynamic LDS above the default limit has to be allowed once per kernel (thread-safe static initialisation)
     static const hipError_t attr = L::kBytes > 65536
-        ? hipFuncSetAttribute(reinterpret_cast<const void *>(&linear_tile_kernel<XT, RELU, NT, KW>),
+        ? hipFuncSetAttribute(reinterpret_cast<const void *>(&linear_tile_kernel<XT, RELU, NT, KW, AHEAD>),
                               hipFuncAttributeMaxDynamicSharedMemorySize, L::kBytes)
         : hipSuccess;
     if (attr != hipSuccess) {
         set_error("tbn_linear_forward: cannot reserve %d bytes of LDS", L::kBytes);
         return TBN_ERR_DEVICE;
     }
-    hipLaunchKernelGGL((linear_tile_kernel<XT, RELU, NT, KW>), dim3(grid), dim3(64 * KW), L::kBytes, a.stream,
+    hipLaunchKernelGGL((linear_tile_kernel<XT, RELU, NT, KW, AHEAD>), dim3(grid), dim3(64 * KW), L::kBytes, a.stream,
                        static_cast<const XT *>(a.x), static_cast<XT *>(a.y), a.tile, a.alpha, P);
     return check_launch("tbn_linear_forward (one wave per 32 batch rows)");
 }
 
 template <typename XT, bool RELU, int NT>
 tbn_status launch_kw(const LinearArgs &a, const TileParams &P, unsigned grid, int kw) {
-    if (kw == 8) return launch_one<XT, RELU, NT, 8>(a, P, grid);
-    if (kw == 4) return launch_one<XT, RELU, NT, 4>(a, P, grid);
-    return launch_one<XT, RELU, NT, 1>(a, P, grid);
+    if (kw == 8) return launch_one<XT, RELU, NT, 8, 1>(a, P, grid);
+    if (kw == 4) return launch_one<XT, RELU, NT, 4, 1>(a, P, grid);
+    if constexpr (std::is_same<XT, float>::value) {
+        if (P.k_per_wave > kLongSlice * chunk_elems<float>()) return launch_one<XT, RELU, NT, 1, 2>(a, P, grid);
+    }
+    return launch_one<XT, RELU, NT, 1, 1>(a, P, grid);
 }
 
 template <typename XT, bool RELU>

@@ -1,0 +1,35 @@
+"""float32 layers whose tile holds whole weight rows, one wave per 32 batch rows: the loop over chunks of 64 elements, of which one or two are
+on their way while one is multiplied, at every count where its beginning and end differ, for one to four column tiles per wave, K in one
+slice or several, rows and columns that end inside a tile.  Exact arithmetic: half of the rows hold integers of 13 bits, whose sums
+float32 holds, the other half one integer of 24 bits, which takes all three terms of the split."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def tbn():
+    from paper_2407_12075_amd import tbn as binding
+    binding.lib()
+    return binding
+
+
+@pytest.mark.parametrize("U", [32, 60, 96, 100, 256])
+@pytest.mark.parametrize("chunks", [1, 2, 3, 4, 5, 6, 7, 11, 13, 14, 15, 17,   # K in one slice; two chunks on their way from 13 on
+                                    8, 12, 16, 24])                            # four or eight slices of two or three
+def test_chunks_of_the_float32_loop(tbn, chunks, U):
+    M, cin, k = 301, 64 * chunks, 2
+    g = torch.Generator().manual_seed(chunks * 1000 + U)
+    x = torch.randint(-4096, 4097, (M, cin), generator=g).double()
+    x[1::2] = 0
+    rows = torch.arange(1, M, 2)
+    x[rows, (rows * 37) % cin] = (torch.randint(2 ** 22, 2 ** 23, (len(rows),), generator=g) * 2 + 1).double()
+    words = torch.randint(-2 ** 31, 2 ** 31, (U * cin // 32,), generator=g).to(torch.int32)
+    signs = ((words.view(-1, 1) >> torch.arange(32)) & 1).reshape(U, cin).double() * 2 - 1
+    alpha = torch.tensor([0.5, -2.0])
+    want = torch.cat([x @ signs.T * a for a in alpha.double()], 1).float()
+    flags = tbn.TBN_FLAG_LARGE_BATCH
+    assert tbn.tbn_linear_forward_kernel(torch.float32, M, cin, U * k, k, k, flags) == "tile"
+    y = tbn.tbn_linear_forward(x.float().cuda(), words.cuda(), alpha.cuda(), U * k, k, flags=flags)
+    assert torch.equal(y.cpu(), want)
