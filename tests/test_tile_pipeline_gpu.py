@@ -1,7 +1,8 @@
 """float32 layers whose tile holds whole weight rows, one wave per 32 batch rows: the loop over chunks of 64 elements, of which one or two are
 on their way while one is multiplied, at every count where its beginning and end differ, for one to four column tiles per wave, K in one
 slice or several, rows and columns that end inside a tile.  Exact arithmetic: half of the rows hold integers of 13 bits, whose sums
-float32 holds, the other half one integer of 24 bits, which takes all three terms of the split."""
+float32 holds, the other half one integer of 24 bits, which takes all three terms of the split.  Below, the kernel for any row length where
+its workgroups of four column tiles would need a second round of the CUs and take one or two tiles."""
 import pytest
 import torch
 
@@ -32,4 +33,23 @@ def test_chunks_of_the_float32_loop(tbn, chunks, U):
     flags = tbn.TBN_FLAG_LARGE_BATCH
     assert tbn.tbn_linear_forward_kernel(torch.float32, M, cin, U * k, k, k, flags) == "tile"
     y = tbn.tbn_linear_forward(x.float().cuda(), words.cuda(), alpha.cuda(), U * k, k, flags=flags)
+    assert torch.equal(y.cpu(), want)
+
+
+@pytest.mark.parametrize("M,cin,U,k", [
+    (8225, 65, 100, 2),       # 258 workgroups of four column tiles: one tile instead
+    (8193, 768, 97, 1),       # twelve chunks, the most with one
+    (8225, 772, 100, 1),      # thirteen: two
+    (611, 777, 1633, 1),      # 52 tiles of columns, the last one holds one
+    (10977, 776, 72, 1),      # three tiles: as they are
+])
+def test_direct_kernel_in_two_rounds_of_workgroups(tbn, M, cin, U, k):
+    g = torch.Generator().manual_seed(M + cin)
+    x = torch.randint(-4096, 4097, (M, cin), generator=g).double()
+    words = torch.randint(-2 ** 31, 2 ** 31, ((U * cin + 31) // 32,), generator=g).to(torch.int32)
+    signs = ((words.view(-1, 1) >> torch.arange(32)) & 1).reshape(-1)[: U * cin].view(U, cin).double() * 2 - 1
+    alpha = torch.tensor([0.5, -2.0])[:k]
+    want = torch.cat([x @ signs.T * a for a in alpha.double()], 1).float()
+    assert tbn.tbn_linear_forward_kernel(torch.float32, M, cin, U * k, k, k) == "direct"
+    y = tbn.tbn_linear_forward(x.float().cuda(), words.cuda(), alpha.cuda(), U * k, k)
     assert torch.equal(y.cpu(), want)
