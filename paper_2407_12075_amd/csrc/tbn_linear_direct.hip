@@ -608,12 +608,15 @@ struct DirectPlan {
 // W = 32 x 32 tiles of Z.  Up to 1024 of them a workgroup takes one and as many waves as bring the chip to 3072 (12 per
 // CU; 8192 x 196 -> 96: 8.0 us with four waves, 9.0 with two, 10.9 with eight).  Beyond that float32 takes four column
 // tiles and at least four waves: more columns share the split of an activation (2500 x 520 -> 1400: 23.5 us against 27.7
-// with two tiles; 6000 x 2504 -> 640: 65.8 against 80.1), unless those are 257 - 384 workgroups: eight waves of four tiles hold 132 KB of
-// LDS, so that they run one to a CU and the second round finds most CUs without one.  Up to 12 chunks of K one tile, from there two (80
-// drawn layers 1.13 times as fast on the mean, 1.00 at the least: 2319 x 368 -> 465 12.7 us with four, 10.4 with one; 2340 x 579 -> 477 17.0 /
-// 14.3; 2132 x 2968 -> 502 41.9 with four, 39.3 with two; three tiles from 13 chunks on stay: 5533 x 1816 -> 161 26.2 / 27.7).  bfloat16 takes two (12000 x 520 -> 152: 10.8 us against 13.4
+// with two tiles; 6000 x 2504 -> 640: 65.8 against 80.1).  bfloat16 takes two (12000 x 520 -> 152: 10.8 us against 13.4
 // with four), and above 4096 as many as leave the fewest empty ones (8192 x 2050 -> 513: 41.9 us with three, 45.3 with
 // four).
+// float32 takes eight waves only while every workgroup has a CU to itself: their registers (134 a lane with one tile) or their LDS
+// (132 KB with four) leave room for one of them per CU, so that of 257 - 384 the second round finds most CUs without one; of four waves three
+// (two with four tiles) run at once.  One tile: 120 drawn layers 1.19 times as fast on the mean, 1.04 at the least (3556 x 382 -> 90 7.5 us with
+// eight, 6.4 with four).  Four tiles: with up to 12 chunks of K, where load and sums are most of the time, one tile per workgroup instead
+// (2319 x 368 -> 465 12.7 us with eight waves of four tiles, 10.4 now; 2340 x 579 -> 477 17.0 / 14.3); longer rows 1.06 on the mean over
+// 70 against four waves of two tiles, which beat eight waves of four by 1.02 - 1.18.
 DirectPlan plan(const LinearArgs &a) {
     DirectPlan pl;
     const bool f32 = a.dt == TBN_F32;
@@ -627,7 +630,7 @@ DirectPlan plan(const LinearArgs &a) {
     const int64_t fours = pl.row_tiles * ((tiles + kMaxNT - 1) / kMaxNT);
     int nt = kMaxNT;
     if (W <= 1024 || pl.wide) nt = 1;
-    else if (f32 && fours <= 384 && (pl.chunks <= 12 || W > 3 * fours)) nt = pl.chunks <= 12 ? 1 : 2;
+    else if (f32 && fours <= 384 && pl.chunks <= 12) nt = 1;
     else if (!f32 && W <= 4096) nt = 2;
     else if (!f32)
         for (int cand = kMaxNT - 1; cand >= 2; --cand)
@@ -635,7 +638,7 @@ DirectPlan plan(const LinearArgs &a) {
     pl.groups = (tiles + nt - 1) / nt;
     pl.nt = static_cast<int>((tiles + pl.groups - 1) / pl.groups);
     pl.kw = 8;
-    while (!pl.wide && pl.kw > (f32 ? 4 : 1) && pl.row_tiles * pl.groups * pl.kw > 3072) pl.kw /= 2;
+    while (!pl.wide && pl.kw > (f32 ? 4 : 1) && pl.row_tiles * pl.groups * pl.kw > (f32 ? 2048 : 3072)) pl.kw /= 2;
     return pl;
 }
 

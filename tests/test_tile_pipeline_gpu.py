@@ -2,7 +2,7 @@
 on their way while one is multiplied, at every count where its beginning and end differ, for one to four column tiles per wave, K in one
 slice or several, rows and columns that end inside a tile.  Exact arithmetic: half of the rows hold integers of 13 bits, whose sums
 float32 holds, the other half one integer of 24 bits, which takes all three terms of the split.  Below, the kernel for any row length where
-its workgroups of four column tiles would need a second round of the CUs and take one or two tiles."""
+its workgroups of eight waves would need a second round of the CUs and take four waves, or one column tile instead of four."""
 import pytest
 import torch
 
@@ -39,9 +39,11 @@ def test_chunks_of_the_float32_loop(tbn, chunks, U):
 @pytest.mark.parametrize("M,cin,U,k", [
     (8225, 65, 100, 2),       # 258 workgroups of four column tiles: one tile instead
     (8193, 768, 97, 1),       # twelve chunks, the most with one
-    (8225, 772, 100, 1),      # thirteen: two
+    (8225, 772, 100, 1),      # thirteen: four tiles, four waves
     (611, 777, 1633, 1),      # 52 tiles of columns, the last one holds one
-    (10977, 776, 72, 1),      # three tiles: as they are
+    (10977, 776, 72, 1),      # three tiles
+    (8193, 300, 31, 2),       # 257 workgroups of one tile: four waves
+    (3041, 1300, 100, 1),     # 384
 ])
 def test_direct_kernel_in_two_rounds_of_workgroups(tbn, M, cin, U, k):
     g = torch.Generator().manual_seed(M + cin)
