@@ -605,8 +605,8 @@ struct DirectPlan {
     int64_t groups, row_tiles, chunks;
 };
 
-// W = 32 x 32 tiles of Z.  Up to 1024 of them a workgroup takes one and as many waves as bring the chip to 3072 (12 per
-// CU; 8192 x 196 -> 96: 8.0 us with four waves, 9.0 with two, 10.9 with eight).  Beyond that float32 takes four column
+// W = 32 x 32 tiles of Z.  Up to 1024 of them a workgroup takes one and as many waves as bring the chip to 3072 in bfloat16 (12 per
+// CU; 8192 x 196 -> 96: 8.0 us with four waves, 9.0 with two, 10.9 with eight), to 2048 in float32, see below.  Beyond that float32 takes four column
 // tiles and at least four waves: more columns share the split of an activation (2500 x 520 -> 1400: 23.5 us against 27.7
 // with two tiles; 6000 x 2504 -> 640: 65.8 against 80.1).  bfloat16 takes two (12000 x 520 -> 152: 10.8 us against 13.4
 // with four), and above 4096 as many as leave the fewest empty ones (8192 x 2050 -> 513: 41.9 us with three, 45.3 with
@@ -617,6 +617,11 @@ struct DirectPlan {
 // eight, 6.4 with four).  Four tiles: with up to 12 chunks of K, where load and sums are most of the time, one tile per workgroup instead
 // (2319 x 368 -> 465 12.7 us with eight waves of four tiles, 10.4 now; 2340 x 579 -> 477 17.0 / 14.3); longer rows 1.06 on the mean over
 // 70 against four waves of two tiles, which beat eight waves of four by 1.02 - 1.18.
+// The error against 64-bit sums decides where that ends.  Four waves add fewer partial sums at the end, but twice as many steps go into each sum:
+// measured over six sizes of 257 - 384 workgroups, four waves' error over eight waves' is 0.81 at 2051 elements, 0.85 at 4099, 0.92 at 8196, 0.97 at
+// 12000, 0.99 at 14001, 1.01 at 16001, 1.04 at 20001, 1.12 at 32001 and 1.29 at 65540.  So rows of more than 216 chunks (13824 elements) keep eight waves.
+constexpr int64_t kFewWavesChunks = 216;
+
 DirectPlan plan(const LinearArgs &a) {
     DirectPlan pl;
     const bool f32 = a.dt == TBN_F32;
@@ -638,7 +643,8 @@ DirectPlan plan(const LinearArgs &a) {
     pl.groups = (tiles + nt - 1) / nt;
     pl.nt = static_cast<int>((tiles + pl.groups - 1) / pl.groups);
     pl.kw = 8;
-    while (!pl.wide && pl.kw > (f32 ? 4 : 1) && pl.row_tiles * pl.groups * pl.kw > (f32 ? 2048 : 3072)) pl.kw /= 2;
+    const int64_t waves = f32 && pl.chunks <= kFewWavesChunks ? 2048 : 3072;
+    while (!pl.wide && pl.kw > (f32 ? 4 : 1) && pl.row_tiles * pl.groups * pl.kw > waves) pl.kw /= 2;
     return pl;
 }
 

@@ -55,3 +55,17 @@ def test_direct_kernel_in_two_rounds_of_workgroups(tbn, M, cin, U, k):
     assert tbn.tbn_linear_forward_kernel(torch.float32, M, cin, U * k, k, k) == "direct"
     y = tbn.tbn_linear_forward(x.float().cuda(), words.cuda(), alpha.cuda(), U * k, k)
     assert torch.equal(y.cpu(), want)
+
+
+@pytest.mark.parametrize("M,cin,U,part", [
+    (2100, 20001, 100, 1024),     # 264 workgroups of one column tile, 128 in the part
+    (3041, 13825, 400, 512),      # 384 of four column tiles, 208 of one
+])
+def test_long_rows_keep_the_sums_of_eight_waves(tbn, M, cin, U, part):
+    """Rows of more than 13824 elements: more workgroups than CUs take no longer sums, whose error would be the larger, than fewer do."""
+    g = torch.Generator(device="cuda").manual_seed(cin)
+    x = torch.randn(M, cin, generator=g, device="cuda")
+    words = torch.randint(-2 ** 31, 2 ** 31, ((U * cin + 31) // 32,), generator=g, device="cuda", dtype=torch.int64).int()
+    one = torch.ones(1, device="cuda")
+    assert all(tbn.tbn_linear_forward_kernel(torch.float32, m, cin, U, 1) == "direct" for m in (M, part))
+    assert torch.equal(tbn.tbn_linear_forward(x, words, one, U, 1)[:part], tbn.tbn_linear_forward(x[:part], words, one, U, 1))
