@@ -326,6 +326,9 @@ __device__ __forceinline__ void pin(i32x8_t &f) {
     asm volatile("" : "+v"(f0), "+v"(f1), "+v"(f2), "+v"(f3));
     f[0] = f0, f[1] = f1, f[2] = f2, f[3] = f3;
 }
+// A register that readlane reads later is loaded by every lane of the wave here: left alone the compiler may move the load to where it is
+// read, behind a branch that the lanes which hold the wanted values did not take.
+__device__ __forceinline__ void hold_in_all_lanes(float &v) { asm volatile("; held in all lanes: %0" : "+v"(v)); }
 template <int V> using Int = std::integral_constant<int, V>;
 
 struct BinactMfmaParams {
@@ -377,7 +380,7 @@ __global__ __launch_bounds__(256, 2) void binact_mfma_kernel(const uint32_t *__r
     const int32_t nb = static_cast<int32_t>(tile_n) * 128, n0 = nb + wn * 64;   // and first distinct column
 
     // alpha of replica t in lane t (replicas past the 64th are fetched one by one in the epilogue)
-    const float alpha_lanes = alpha[P.n_alpha == 1 ? 0 : (lane < P.reps ? lane : P.reps - 1)];
+    float alpha_lanes = alpha[P.n_alpha == 1 ? 0 : (lane < P.reps ? lane : P.reps - 1)];
 
     // The instruction leaves row 8*(r / 4) + 4*lh + r % 4 of its result in register r: with tile row column_of(l) from operand lane l,
     // register r of a lane is column 16*lh + r of the tile, sixteen adjacent columns.
@@ -586,6 +589,7 @@ __global__ __launch_bounds__(256, 2) void binact_mfma_kernel(const uint32_t *__r
             if (S + 1 < P.n_super) step(std::integral_constant<int, 1>{}, S + 1);
         }
     }
+    hold_in_all_lanes(alpha_lanes);   // rows past M and columns past U are left out below
     const float rest = 192.f * static_cast<float>(P.n_super);   // three quarters of K
     auto of_row = [&](int tm) __attribute__((always_inline)) { return rest - counts[64 * wm + 32 * (tm ^ row_turn) + ln]; };
     auto of_cols = [&](int tn, int a) __attribute__((always_inline)) {   // of columns 16*lh + 4*a .. + 3 of the tile
@@ -927,7 +931,7 @@ __global__ __launch_bounds__(256, 2) void binact_staged_kernel(const uint32_t *_
                     *reinterpret_cast<f32x4_t *>(zt + (32 * tm + ln) * STR + 32 * tn + 16 * lh + 4 * a) = v;
                 }
     }
-    asm volatile("" : "+v"(alpha_lanes));   // loaded by every lane here, not by those with columns below
+    hold_in_all_lanes(alpha_lanes);   // columns past U are left out below
     lds_barrier();
     // a wave takes a quarter of the rows
     if constexpr (SIGN) {

@@ -3,6 +3,7 @@ destination registers of an LDS read before the wait that covers it.  These CPU 
 that was validated, run the static check on what this compiler generates, and show on small planted mistakes
 that the check sees what it is meant to see."""
 import os
+import re
 from concurrent.futures import ThreadPoolExecutor
 
 import pytest
@@ -108,3 +109,26 @@ def test_tile_kernel_requests_a_chunk_before_the_products_of_the_one_before():
                 assert loads[-1] < products[0], f"{name}: loads behind the first of {len(products)} matrix instructions"
             block = []
     assert loops == 12   # with and without ReLU, one and two column tiles, one, four and eight slices of K
+
+
+def test_registers_that_lanes_are_read_from_are_held_in_all_lanes():
+    """The kernels on sign bits keep the scalar of replica t in lane t and read it by v_readlane where only some lanes may be on.  Behind the
+    products, where all are, the source marks the register as used; the marked register has to be the one that is read, every narrowing of
+    the execution mask between the last product and the mark undone, and nothing may load the register again behind it."""
+    text = asm_check.compile_to_asm(os.path.join(hip_build.CSRC, "tbn_binact.hip"))
+    checked = 0
+    for body in re.findall(r"^(_Z\w*binact_(?:mfma|staged)_kernel\w*):.*?\n(.*?)s_endpgm\n\s*\.section", text, re.S | re.M):
+        lines = body[1].splitlines()
+        read = {re.search(r"v_readlane_b32 \S+ (v\d+)", l).group(1) for l in lines if "v_readlane_b32" in l}
+        if not read:
+            continue
+        marks = [i for i, l in enumerate(lines) if "held in all lanes:" in l]
+        last = max(i for i, l in enumerate(lines) if l.strip().startswith("v_mfma"))
+        assert len(marks) == 1 and read == {lines[marks[0]].split(":")[1].strip()}, (body[0], read)
+        between = lines[last:marks[0]]
+        masks = [l for l in between if "_saveexec" in l or re.match(r"\s*s_or_b64 exec, exec,", l)]
+        assert marks[0] > last and not any("s_endpgm" in l for l in between) and not ("_saveexec" in masks[-1] if masks else False), body[0]
+        register = lines[marks[0]].split(":")[1].strip()
+        assert not any(re.match(r"\s*(?!v_readlane)\S+ " + register + r"\b", l) for l in lines[marks[0] + 1:]), body[0]
+        checked += 1
+    assert checked == 13   # nine of the 128 x 128 blocks, four of the 64 x 64 with real outputs
