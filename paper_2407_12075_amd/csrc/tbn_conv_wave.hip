@@ -93,7 +93,7 @@ template <> struct WTraits<uint16_t> { static constexpr int planes = 1, px = 2; 
 // of one channel group after the other, or (RUNS) runs of four pixels of all groups at once, at most run_limit per group.
 constexpr int kCapF32 = 100;   // two workgroups of eight waves per CU
 constexpr int slots_of(int CAP) { return CAP == kCapF32 ? 104 : CAP; }
-constexpr int loads_of(bool f32, int MT, int CAP, bool RUNS) { return RUNS ? 1 : f32 ? (CAP - 1 + 63) / 64 : (CAP - 1 + 127) / 128; }
+constexpr int loads_of(bool f32, int CAP, bool RUNS) { return RUNS ? 1 : f32 ? (CAP - 1 + 63) / 64 : (CAP - 1 + 127) / 128; }
 constexpr int kRunLimit = 32;
 // registers: what the LDS lets share a SIMD anyway
 constexpr int wave_bound(bool f32, int MT, int T, int PW, int NFT, int CAP) {
@@ -142,7 +142,7 @@ __global__ __launch_bounds__(64 * kMaxWaves, (wave_bound(sizeof(XT) == 4, MT, T,
     constexpr int G = 64 / MT, CK = 8 * G;          // channel groups of 8 per MFMA step, channels per chunk
     constexpr int J = PW / MT;                      // pixel tiles per wave
     constexpr int LP = RUNS ? 4 : WTraits<XT>::px;  // pixels per load
-    constexpr int IT = loads_of(sizeof(XT) == 4, MT, kCap, RUNS);
+    constexpr int IT = loads_of(sizeof(XT) == 4, kCap, RUNS);
     constexpr int kSlots = slots_of(kCap), kGroup = kSlots * 16, kPlane = G * kGroup, kRegion = NP * kPlane;
     constexpr int NA = Acc<MT>::n;
     extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
@@ -859,11 +859,14 @@ tbn_status launch_wave_shape(const ConvArgs &a, const WaveConvParams &P, const W
         if (pl.pw == 32) return launch_wave_t<XT, MT, 9, 32, NFT, kLarge>(a, P, pl, grid);
         if (pl.cap == kLarge) return launch_wave_t<XT, MT, 9, 64, NFT, kLarge>(a, P, pl, grid);
     }
-    if constexpr (MT == 16) return launch_wave_t<XT, MT, 9, 64, NFT, 128>(a, P, pl, grid);
-    if constexpr (f32)
-        if (pl.cap == kCapF32)
-            return pl.runs ? launch_wave_t<XT, MT, 9, 64, NFT, kCapF32, true>(a, P, pl, grid) : launch_wave_t<XT, MT, 9, 64, NFT, kCapF32>(a, P, pl, grid);
-    return pl.runs ? launch_wave_t<XT, MT, 9, 64, NFT, 128, true>(a, P, pl, grid) : launch_wave_t<XT, MT, 9, 64, NFT, 128>(a, P, pl, grid);
+    if constexpr (MT == 16) {   // (no runs)
+        return launch_wave_t<XT, MT, 9, 64, NFT, 128>(a, P, pl, grid);
+    } else {
+        if constexpr (f32)
+            if (pl.cap == kCapF32)
+                return pl.runs ? launch_wave_t<XT, MT, 9, 64, NFT, kCapF32, true>(a, P, pl, grid) : launch_wave_t<XT, MT, 9, 64, NFT, kCapF32>(a, P, pl, grid);
+        return pl.runs ? launch_wave_t<XT, MT, 9, 64, NFT, 128, true>(a, P, pl, grid) : launch_wave_t<XT, MT, 9, 64, NFT, 128>(a, P, pl, grid);
+    }
     }
 }
 
