@@ -210,9 +210,11 @@ tbn_status tbn_conv2d_forward(const void *x, void *y, tbn_dtype dt, int64_t N, i
  * nothing is launched, no pointer is dereferenced.
  *
  * Returns "direct", "block", "generic", or "wave" followed by the plan of the kernel with one wave per pixel block (filter
- * tiles per wave x filters per tile, pixels per wave, pixels of a patch in LDS, channel slices, and "all-bits" for its
- * instance that keeps the bits of small float32 activations); "" on sizes tbn_conv2d_forward would reject.  The string is
- * valid until the calling thread's next call.
+ * tiles per wave x filters per tile, pixels per wave, pixels of a patch in LDS, channel slices, waves, output rows x columns
+ * of a block, LDS pixels from one patch row to the next, how a patch is staged -- "pixels", "pairs" or "runs" of four of a
+ * channel per load, "even-" where loads begin at even elements of x --, and "all-bits" for its instance that keeps the bits
+ * of small float32 activations); "" on sizes tbn_conv2d_forward would reject.  The string is valid until the calling
+ * thread's next call.
  */
 const char *tbn_conv2d_forward_kernel(const void *x, const void *y, tbn_dtype dt, int64_t N, int64_t C, int64_t H, int64_t W,
                                       int64_t O, int32_t kh, int32_t kw, int32_t stride_h, int32_t stride_w, int32_t pad_h,

@@ -538,7 +538,7 @@ tbn_status tbn_conv2d_forward(const void *x, void *y, tbn_dtype dt, int64_t N, i
 const char *tbn_conv2d_forward_kernel(const void *x, const void *y, tbn_dtype dt, int64_t N, int64_t C, int64_t H, int64_t W,
                                       int64_t O, int32_t kh, int32_t kw, int32_t stride_h, int32_t stride_w, int32_t pad_h,
                                       int32_t pad_w, int32_t k, int32_t n_alpha, uint32_t flags) {
-    static thread_local char text[96];
+    static thread_local char text[192];
     ConvArgs a;
     char last[sizeof(g_err)];   // the query leaves tbn_last_error alone
     std::memcpy(last, g_err, sizeof(g_err));

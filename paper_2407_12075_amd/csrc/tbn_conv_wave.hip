@@ -878,8 +878,10 @@ int64_t conv_wave_searches() { return n_searches; }
 
 void conv_wave_describe(const ConvArgs &a, char *text, size_t size) {
     const WavePlan pl = plan_wave(a);
-    std::snprintf(text, size, "wave filters=%dx%d pixels=%d patch=%d slices=%d waves=%lld%s", pl.nft, pl.mt, pl.pw, pl.cap,
-                  1 << pl.ks_log2, static_cast<long long>(pl.total_waves), pl.all_bits ? " all-bits" : "");
+    const bool pairs = a.dt != TBN_F32 && (a.kh == 3 || a.sw == 1);
+    std::snprintf(text, size, "wave filters=%dx%d pixels=%d patch=%d slices=%d waves=%lld block=%dx%d pitch=%d staged=%s%s%s", pl.nft, pl.mt,
+                  pl.pw, pl.cap, 1 << pl.ks_log2, static_cast<long long>(pl.total_waves), pl.rows, pl.cols, pl.pitch, pl.even ? "even-" : "",
+                  pl.runs ? "runs" : pairs ? "pairs" : "pixels", pl.all_bits ? " all-bits" : "");
 }
 
 tbn_status launch_conv_wave(const ConvArgs &layer) {
