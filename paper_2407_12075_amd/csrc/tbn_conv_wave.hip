@@ -195,7 +195,6 @@ __global__ __launch_bounds__(64 * kMaxWaves, (wave_bound(sizeof(XT) == 4, MT, T,
     uint32_t loff[IT][(LP + 1) / 2];   // byte offsets inside a channel group of the patch (RUNS: with that of the group), two to a word
     auto lds_off = [&](int it, int h) __attribute__((always_inline)) { return LP == 1 ? loff[it][0] : h & 1 ? loff[it][h / 2] >> 16 : loff[it][h / 2] & 0xffffu; };
     const int per_group = P.PR * static_cast<int>(P.d_items.d);   // RUNS: loads per channel of a group
-    auto group_of = [&](int it) { return P.d_group.div(it * 64 + lane); };
     {
         const int iy0 = row0 * P.sh - P.ph, ix0 = col0 * P.sw - P.pw;
         const int sy = T == 1 ? P.sh : 1, sx = T == 1 ? P.sw : 1;         // image steps between patch positions
@@ -203,7 +202,7 @@ __global__ __launch_bounds__(64 * kMaxWaves, (wave_bound(sizeof(XT) == 4, MT, T,
         const int n_items = live ? (RUNS ? G : 1) * per_group : 0;
 #pragma unroll
         for (int it = 0; it < IT; ++it) {
-            const int v = it * 64 + lane, g = RUNS ? group_of(it) : 0, w = v - g * per_group;
+            const int v = it * 64 + lane, g = RUNS ? P.d_group.div(v) : 0, w = v - g * per_group;
             const int py = P.d_items.div(w), px = (w - py * static_cast<int>(P.d_items.d)) * per;
             const int iy = iy0 + py * sy, ix = ix0 + px * sx;
             if constexpr (T == 9 && LP > 1) {
@@ -239,6 +238,16 @@ __global__ __launch_bounds__(64 * kMaxWaves, (wave_bound(sizeof(XT) == 4, MT, T,
     const int64_t hw = P.HW;
     const char *x_img = reinterpret_cast<const char *>(x + img * P.C * hw);
     const int64_t hwb = hw * static_cast<int64_t>(sizeof(XT));
+    // RUNS: the first channel in its chunk of this lane's load, worked out where the last channels need it.  With one filter tile and float32 patches
+    // of up to 100 pixels the kernel has 128 registers for four waves per SIMD: held over the loop, this and the unpacked LDS offsets (below) were
+    // two too many, and spilled; without either it takes 127 and the same time (128 x 256 x 14^2 -> 256, k = 8 21.9 us).
+    constexpr bool kTight = RUNS && sizeof(XT) == 4 && kCap == kCapF32 && NFT * PW <= 64;
+    static_assert(!RUNS || IT == 1, "");
+    auto first_channel = [&]() __attribute__((always_inline)) {
+        int l = lane;
+        asm volatile("" : "+v"(l));
+        return 8 * P.d_group.div(l);
+    };
 
     // Loads of a 1x1 layer run two chunks ahead (a chunk is a handful of MFMAs), those of a 3x3 layer one.
     constexpr int kSets = T == 1 ? 2 : 1;
@@ -263,16 +272,13 @@ __global__ __launch_bounds__(64 * kMaxWaves, (wave_bound(sizeof(XT) == 4, MT, T,
                 // of the first load, took back what runs give one-chunk waves (float32, 8 x 16 x 68^2 -> 512, k = 4 52.4 us by pixels, 55.1 with
                 // them, 51.6 now; bfloat16, 2 x 24 x 7^2 -> 96, k = 2 5.5 / 5.9 / 5.5).
                 const uint32_t plane = static_cast<uint32_t>(hwb);
+                const int first = first_channel();
+                uint32_t at = goff[0];
+                if (first >= c_left && at != 0u) at -= static_cast<uint32_t>(first - (c_left - 1)) * plane;
 #pragma unroll
-                for (int it = 0; it < IT; ++it) {
-                    const int first = 8 * group_of(it);
-                    uint32_t at = goff[it];
-                    if (first >= c_left && at != 0u) at -= static_cast<uint32_t>(first - (c_left - 1)) * plane;
-#pragma unroll
-                    for (int j = 0; j < 8; ++j) {
-                        __builtin_memcpy(st[0][it][j], b + at, 4 * RW);
-                        at += first + j + 1 < c_left ? plane : 0u;
-                    }
+                for (int j = 0; j < 8; ++j) {
+                    __builtin_memcpy(st[0][0][j], b + at, 4 * RW);
+                    at += first + j + 1 < c_left ? plane : 0u;
                 }
             }
         } else {
@@ -290,7 +296,9 @@ __global__ __launch_bounds__(64 * kMaxWaves, (wave_bound(sizeof(XT) == 4, MT, T,
     auto store_chunk = [&](int chunk, auto set_c) __attribute__((always_inline)) {
         auto &st = staged[decltype(set_c)::value];
         const int c_left = P.C - chunk * CK;
+        if constexpr (kTight) asm volatile("" : "+v"(loff[0][0]), "+v"(loff[0][1]));   // unpacked here, for each chunk
         if (c_left < CK) {   // channels past the last one are zeros
+            const int first = RUNS ? first_channel() : 0;
 #pragma unroll
             for (int g = 0; g < GL; ++g)
 #pragma unroll
@@ -299,7 +307,7 @@ __global__ __launch_bounds__(64 * kMaxWaves, (wave_bound(sizeof(XT) == 4, MT, T,
                     for (int it = 0; it < IT; ++it)
 #pragma unroll
                         for (int e = 0; e < RW; ++e)
-                            st[g][it][j][e] = 8 * (RUNS ? group_of(it) : g) + j < c_left ? st[g][it][j][e] : 0u;
+                            st[g][it][j][e] = (RUNS ? first : 8 * g) + j < c_left ? st[g][it][j][e] : 0u;
         }
 #pragma unroll
         for (int g = 0; g < GL; ++g)

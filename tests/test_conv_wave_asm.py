@@ -26,3 +26,10 @@ def test_runs_cost_no_64_bit_products(instances):
     assert len(runs) == 11
     for key in runs:
         assert products(instances[key]) <= products(instances[key[:6] + ("0",) + key[7:]]), key
+
+
+def test_3x3_instances_keep_their_registers(instances):
+    """Nothing of a 3x3 layer goes to scratch memory."""
+    for key, lines in instances.items():
+        if key[2] == "9":
+            assert not any(l.startswith(("scratch_", "buffer_store", "buffer_load")) for l in lines), key
