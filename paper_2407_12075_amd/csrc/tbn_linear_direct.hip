@@ -579,14 +579,19 @@ tbn_status launch_one(const LinearArgs &a, DirectLinearParams P) {
     return check_launch("tbn_linear_forward (direct kernel)");
 }
 
-template <typename XT, int NT>
+// What `plan` gives: float32 four or eight waves, of eight at most 384 workgroups (two column tiles come only with more than 512 row tiles); bfloat16
+// eight waves with one column tile, four with up to two, since more tiles come with more than 1024 workgroups.
+constexpr bool planned(bool f32, int NT, int KW) {
+    return f32 ? KW == 4 || (KW == 8 && NT != 2) : KW <= 2 || (KW == 4 && NT <= 2) || (KW == 8 && NT == 1);
+}
+
+template <typename XT, int NT, int KW = 8>
 tbn_status launch_kw(const LinearArgs &a, const DirectLinearParams &P, int kw) {
-    switch (kw) {
-        case 8: return launch_one<XT, NT, 8>(a, P);
-        case 4: return launch_one<XT, NT, 4>(a, P);
-        case 2: return launch_one<XT, NT, 2>(a, P);
-    }
-    return launch_one<XT, NT, 1>(a, P);
+    if constexpr (planned(std::is_same<XT, float>::value, NT, KW))
+        if (kw == KW) return launch_one<XT, NT, KW>(a, P);
+    if constexpr (KW > 1) return launch_kw<XT, NT, KW / 2>(a, P, kw);
+    set_error("tbn_linear_forward: the direct kernel has no instance of %d column tiles and %d waves", NT, kw);
+    return TBN_ERR_UNSUPPORTED;
 }
 
 template <typename XT>
