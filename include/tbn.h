@@ -328,6 +328,8 @@ const char *tbn_linear_forward_binact_kernel(const uint32_t *xbits, const void *
  *                           instruction of tbn_linear_forward_binact.
  *   tbn_diag_conv_plan_searches : how often the calling thread has searched for the plan of a convolution (a shape that it
  *                           has used lately is not searched for again).
+ *   tbn_diag_binact_counted : 1 if the "matrix-core" kernel would take these arguments in its form that multiplies set bits and
+ *                           counts them, 0 otherwise (aligned pointers assumed; nothing is launched).
  * Errors: TBN_ERR_NULL, TBN_ERR_SHAPE, TBN_ERR_DEVICE.
  */
 tbn_status tbn_diag_empty_launch(void *stream);
@@ -335,6 +337,7 @@ tbn_status tbn_diag_stream(const void *src, void *dst, size_t bytes, void *sink,
 tbn_status tbn_diag_mfma(int32_t blocks, int32_t iters, float *out, void *stream);
 tbn_status tbn_diag_mfma_fp4(int32_t blocks, int32_t iters, float *out, void *stream);
 int64_t tbn_diag_conv_plan_searches(void);
+int32_t tbn_diag_binact_counted(tbn_dtype y_dt, int64_t M, int64_t in, int64_t out, int32_t k, int32_t n_alpha, uint32_t flags);
 
 #ifdef __cplusplus
 }

@@ -475,13 +475,22 @@ tbn_status tbn_linear_forward_binact(const uint32_t *xbits, void *y, tbn_dtype y
                                 static_cast<hipStream_t>(stream));
 }
 
+static bool binact_sizes_ok(tbn_dtype y_dt, int64_t M, int64_t in, int64_t out, int32_t k, int32_t n_alpha, int64_t *n) {
+    return (y_dt == TBN_F32 || y_dt == TBN_BF16) && M > 0 && in > 0 && out > 0 && k > 0 && mul_ok(in, out, n) && *n % k == 0 &&
+           (n_alpha == 1 || n_alpha == k);
+}
+
 const char *tbn_linear_forward_binact_kernel(const uint32_t *xbits, const void *y, tbn_dtype y_dt, int64_t M, int64_t in,
                                              int64_t out, int32_t k, int32_t n_alpha, uint32_t flags) {
     int64_t n;
-    if ((y_dt != TBN_F32 && y_dt != TBN_BF16) || M <= 0 || in <= 0 || out <= 0 || k <= 0 || !mul_ok(in, out, &n) || n % k != 0 ||
-        (n_alpha != 1 && n_alpha != k))
-        return "";
+    if (!binact_sizes_ok(y_dt, M, in, out, k, n_alpha, &n)) return "";
     return linear_binact_kernel_name(xbits, y, (int)y_dt, M, in, out, n / k, k, n_alpha, flags);
+}
+
+int32_t tbn_diag_binact_counted(tbn_dtype y_dt, int64_t M, int64_t in, int64_t out, int32_t k, int32_t n_alpha, uint32_t flags) {
+    int64_t n;
+    return binact_sizes_ok(y_dt, M, in, out, k, n_alpha, &n) &&
+           linear_binact_counted(nullptr, nullptr, (int)y_dt, M, in, out, n / k, k, n_alpha, flags);
 }
 
 tbn_status tbn_diag_empty_launch(void *stream) { return launch_diag_empty(static_cast<hipStream_t>(stream)); }

@@ -1124,6 +1124,9 @@ bool binact_staged_preferred(const BinactArgs &a) {
     return a.dt == TBN_F32 || (blocks - 1) % 512 < 256 || (a.in >= 4096 && reps >= 8);
 }
 
+// Does binact_mfma_kernel count set bits (its STAGED form)?
+bool binact_counted(const BinactArgs &a) { return (a.flags & TBN_FLAG_SIGN_OUT) != 0 || binact_long_rows(a); }
+
 template <typename YT, bool RELU, bool SIGN, bool STAGED>
 static tbn_status launch_mfma_s(const BinactArgs &a, const BinactMfmaParams &P, unsigned blocks) {
     constexpr int bytes = mfma_lds(SIGN, STAGED);
@@ -1141,7 +1144,7 @@ static tbn_status launch_mfma_s(const BinactArgs &a, const BinactMfmaParams &P, 
 }
 template <typename YT, bool RELU>
 static tbn_status launch_mfma_t(const BinactArgs &a, const BinactMfmaParams &P, unsigned blocks) {
-    return binact_long_rows(a) ? launch_mfma_s<YT, RELU, false, true>(a, P, blocks) : launch_mfma_s<YT, RELU, false, false>(a, P, blocks);
+    return binact_counted(a) ? launch_mfma_s<YT, RELU, false, true>(a, P, blocks) : launch_mfma_s<YT, RELU, false, false>(a, P, blocks);
 }
 
 tbn_status launch_binact_mfma(const BinactArgs &a) {
@@ -1286,6 +1289,12 @@ const char *linear_binact_kernel_name(const uint32_t *xbits, const void *y, int 
         case BinactKernel::Generic: break;
     }
     return "generic";
+}
+
+bool linear_binact_counted(const uint32_t *xbits, const void *y, int dt, int64_t M, int64_t in, int64_t out, int64_t p, int32_t k,
+                           int32_t n_alpha, uint32_t flags) {
+    const BinactArgs a{xbits, const_cast<void *>(y), dt, M, in, out, nullptr, p, k, nullptr, n_alpha, flags, nullptr};
+    return choose_binact(a) == BinactKernel::MatrixCore && binact_counted(a);
 }
 
 }  // namespace tbn

@@ -101,6 +101,8 @@ tbn_status launch_linear_binact(const uint32_t *xbits, void *y, int dt, int64_t 
                                 uint32_t flags, hipStream_t stream);
 const char *linear_binact_kernel_name(const uint32_t *xbits, const void *y, int dt, int64_t M, int64_t in, int64_t out, int64_t p,
                                       int32_t k, int32_t n_alpha, uint32_t flags);
+bool linear_binact_counted(const uint32_t *xbits, const void *y, int dt, int64_t M, int64_t in, int64_t out, int64_t p, int32_t k,
+                           int32_t n_alpha, uint32_t flags);   // the kernel of that name, in its form that counts set bits
 
 tbn_status launch_conv_generic(const ConvArgs &a);
 tbn_status launch_conv_generic_tile_ends(const ConvArgs &a);   // only the channels whose filter holds a tile end

@@ -102,6 +102,8 @@ def lib() -> ctypes.CDLL:
         L.tbn_diag_mfma_fp4.argtypes = [_c_i32, _c_i32, _c_vp, _c_vp]
         L.tbn_diag_conv_plan_searches.restype = _c_i64
         L.tbn_diag_conv_plan_searches.argtypes = []
+        L.tbn_diag_binact_counted.restype = _c_i32
+        L.tbn_diag_binact_counted.argtypes = [ctypes.c_int, _c_i64, _c_i64, _c_i64, _c_i32, _c_i32, _c_u32]
         L.tbn_linear_forward_binact_kernel.restype = ctypes.c_char_p
         L.tbn_linear_forward_binact_kernel.argtypes = [_c_vp, _c_vp, ctypes.c_int, _c_i64, _c_i64, _c_i64, _c_i32, _c_i32, _c_u32]
         L.tbn_conv2d_forward_kernel.restype = ctypes.c_char_p

@@ -209,6 +209,27 @@ def test_kernel_choice_of_layers_on_sign_bits(lib, dtype, M, cin, out, k, expect
     assert tbn.tbn_linear_forward_binact_kernel(dt, M, cin, out, k, 1) == expected
 
 
+# layers on sign bits: the form of the 128 x 128 blocks that counts set bits takes all sign bits out that the 64 x 64 blocks leave, and real
+# outputs of long rows on more than 384 blocks, both up to rows of 2^22
+@pytest.mark.parametrize("dtype,M,cin,U,k,flags,expected,counted", [
+    ("f32", 1024, 1024, 1024, 2, 0x4000, "staged", 0), ("f32", 1025, 1024, 1024, 2, 0x4000, "matrix-core", 1),    # 256 and 272 blocks of 64 x 64
+    ("f32", 2048, 1280, 1024, 2, 0x4000, "staged", 0), ("f32", 2049, 1280, 1024, 2, 0x4000, "matrix-core", 1),    # rows of more than 1024: 512 and 528
+    ("f32", 2048, 1024, 992, 2, 0x4000, "staged", 0), ("f32", 2049, 1024, 992, 2, 0x4000, "matrix-core", 1),      # column blocks of 128 to fill
+    ("f32", 4200, 1 << 22, 1024, 1, 0x4000, "matrix-core", 1), ("f32", 4200, (1 << 22) + 256, 1024, 1, 0x4000, "staged", 0),
+    ("bf16", 6144, 2304, 1024, 1, 0, "matrix-core", 0), ("bf16", 6145, 2304, 1024, 1, 0, "matrix-core", 1),       # 384 and 392 blocks of 128 x 128
+    ("bf16", 6145, 2048, 1024, 1, 0, "matrix-core", 0), ("f32", 6145, 2304, 1000, 1, 0, "matrix-core", 0),        # row length; rows of Y off the lines
+    ("f32", 6145, 1 << 22, 1024, 1, 1, "matrix-core", 1), ("f32", 6145, (1 << 22) + 256, 1024, 1, 1, "staged", 0),
+])
+def test_counted_form_of_layers_on_sign_bits(lib, dtype, M, cin, U, k, flags, expected, counted):
+    import torch
+    from paper_2407_12075_amd import tbn
+    dt = torch.float32 if dtype == "f32" else torch.bfloat16
+    assert tbn.tbn_linear_forward_binact_kernel(dt, M, cin, U * k, k, k, flags) == expected
+    assert tbn.lib().tbn_diag_binact_counted(tbn.TBN_F32 if dtype == "f32" else tbn.TBN_BF16, M, cin, U * k, k, k, flags) == counted
+    assert tbn.lib().tbn_diag_binact_counted(tbn.TBN_F32, 0, cin, U * k, k, k, flags) == 0
+    assert tbn.lib().tbn_diag_binact_counted(tbn.TBN_F32, M, cin, U * k, k, k + 1, flags) == 0
+
+
 # bfloat16, rows in multiples of 8 that the general and the windowed kernel both take: M, in, out, k, n_alpha, expected
 WINDOW_CHOICE = [
     (3141, 3608, 80, 11, 1, "general"),       # 17.6 tile starts among a block's rows
