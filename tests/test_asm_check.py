@@ -26,6 +26,8 @@ def test_generated_assembly_has_no_early_use_of_pending_reads():
     for src, text in zip(srcs, texts):
         names, findings = asm_check.check_asm_text(text)
         assert names, f"no kernel found in the assembly of {src}"
+        followed = sum(l.startswith("ds_read") and not l.endswith(asm_check._MANAGED) for body in asm_check._split_kernels(text).values() for l in body)
+        assert followed >= 20, f"{src}: {followed} reads placed by hand"
         assert not findings, f"{src}:\n" + "\n".join(findings[:20])
 
 
@@ -87,6 +89,59 @@ kernel_a:
     .end_amdhsa_kernel
 """
     assert any("touches registers" in f for f in _check(text))
+
+
+# As hipcc writes it: reads placed by hand between markers, one of the compiler's own (v[16:19]) with a wait of its own.
+_MARKED = """
+kernel_a:
+    ds_read_b128 v[16:19], v2
+    ;;#ASMSTART
+    ds_read_b128 v[4:7], v1
+    ;;#ASMEND
+    ;;#ASMSTART
+    ds_read_b128 v[8:11], v1 offset:16
+    ;;#ASMEND
+    s_waitcnt lgkmcnt(2)
+    v_add_f32_e32 v20, v16, v17
+    ;;#ASMSTART
+    s_waitcnt lgkmcnt(0)
+    ;;#ASMEND
+    v_mfma_f32_32x32x16_bf16 a[0:15], v[4:7], v[8:11], a[0:15]
+    ds_read_b32 v3, v2
+    s_waitcnt lgkmcnt(0)
+    s_endpgm
+    .end_amdhsa_kernel
+"""
+
+
+def test_checker_tells_reads_placed_by_hand_from_the_compilers():
+    assert _check(_MARKED) == []
+    # a read of the compiler's own is not followed: its use is the compiler's business
+    assert _check(_MARKED.replace("lgkmcnt(2)", "lgkmcnt(3)")) == []
+    assert _check(_MARKED.replace("    ds_read_b32 v3, v2\n    s_waitcnt lgkmcnt(0)\n", "    ds_read_b32 v3, v2\n")) == []
+    # without the markers every read is
+    bare = "\n".join(l for l in _MARKED.splitlines() if "#ASM" not in l)
+    assert _check(bare) == []
+    assert any("touches registers" in f for f in _check(bare.replace("lgkmcnt(2)", "lgkmcnt(3)")))
+
+
+@pytest.mark.parametrize("old,new,what", [
+    # the product in front of the wait, and behind one that leaves the second read pending
+    ("s_waitcnt lgkmcnt(0)\n    ;;#ASMEND\n    v_mfma", "s_nop 0\n    ;;#ASMEND\n    v_mfma", "touches registers of a pending LDS read"),
+    ("s_waitcnt lgkmcnt(0)\n    ;;#ASMEND\n    v_mfma", "s_waitcnt lgkmcnt(1)\n    ;;#ASMEND\n    v_mfma", "touches registers of a pending LDS read"),
+    # the compiler's instruction, inside or outside the markers, on a register of a pending read
+    ("v_add_f32_e32 v20, v16, v17", "v_mov_b32_e32 v20, v9", "touches registers of a pending LDS read"),
+    # a read of the compiler's own: its destination, then its address in registers of a pending one
+    ("    s_waitcnt lgkmcnt(2)\n", "    ds_read_b32 v5, v2\n    s_waitcnt lgkmcnt(3)\n", "uses registers of a pending LDS read"),
+    ("    s_waitcnt lgkmcnt(2)\n", "    ds_read_b32 v22, v10\n    s_waitcnt lgkmcnt(3)\n", "uses registers of a pending LDS read"),
+    # a read by hand behind one of the compiler's own that has not landed either: the wait counts both
+    ("    s_waitcnt lgkmcnt(2)\n", "    ds_read_b32 v22, v2\n    s_waitcnt lgkmcnt(1)\n    v_mov_b32_e32 v21, v8\n    v_mov_b32_e32 v23, v4\n    s_waitcnt lgkmcnt(0)\n", None),
+    ("    s_waitcnt lgkmcnt(2)\n", "    ds_read_b32 v22, v2\n    s_waitcnt lgkmcnt(2)\n    v_mov_b32_e32 v21, v8\n    s_waitcnt lgkmcnt(0)\n", "touches registers of a pending LDS read"),
+])
+def test_checker_sees_planted_mistakes_between_markers(old, new, what):
+    assert _MARKED.count(old) == 1
+    findings = _check(_MARKED.replace(old, new))
+    assert any(what in f for f in findings) if what else findings == [], findings
 
 
 def test_tile_kernel_requests_a_chunk_before_the_products_of_the_one_before():
