@@ -16,9 +16,12 @@
 //       - STAGED (sign bits out, and long rows on many blocks): bits through LDS, one vector instruction per operand register (see
 //         `operand`).  A wave issues an instruction every four cycles and a matrix instruction takes 32, so that seven vector
 //         instructions per operand made 38 cycles of every product, and loads of 16 bytes from each of 32 rows, which the load path
-//         takes 64 cycles for, made 55 - 62; here it is 47 with one workgroup per CU (five vector instructions per product, one of
-//         them for the counts of set bits; 43 without the LDS reads) and 29 with two.  8192 x 4096 -> 16384, k = 2: sign bits out 140
-//         us before and 97 now, bfloat16 out 152 / 113; 8192 x 4096 -> 4096, k = 8, sign bits out 13.8 / 10.6 (the words formed
+//         takes 64 cycles for, made 55 - 62 by time stamps; here it is 47 with one workgroup per CU (five vector instructions per product, one of
+//         them for the counts of set bits; 43 without the LDS reads).  What 12288 elements of K more take, over the products of a SIMD and
+//         at 2.4 GHz: 50 cycles with one workgroup per CU (8192 x 4096 and 16384 -> 512, k = 1; 66 in the other form), 46 where two
+//         share it (-> 8192; 73).  Graph replays on two cards: 8192 x 4096 -> 16384, k = 2: sign bits out 140 and 155
+//         us before, 97 and 106 now, bfloat16 out 152 / 113 and 159 / 116 (eager calls 99 - 116 and 114 - 132, by how many follow one another: the clock
+//         moves with the power); 8192 x 4096 -> 4096, k = 8, sign bits out 13.8 / 10.6 and 13.2 / 10.3 (the words formed
 //         by comparisons and lane exchanges behind a turn through LDS took 4.7 of it, 1.9 now); 8192 x 256 -> 4096, k = 2, sign bits
 //         out 11.9 / 8.4.  Tried: K dealt to two groups of four waves (37 cycles, but 1.1 us to add the sums and a later start: 12.2
 //         us against 10.9 with sign bits out); 32-byte pieces of rows, whose LDS addresses are immediate (121 us against 113).
@@ -1090,8 +1093,9 @@ constexpr int64_t kCountedRows = int64_t(1) << 22;   // sums of four times the s
 
 // Real outputs: long rows on more than one and a half blocks per CU take the 128 x 128 blocks with staged bits (205 drawn layers of more
 // than 1024 blocks of 64 x 64, as graph replays against the other kernels: rows of 2304 - 3072 elements 1.02 - 1.11 in the mean, longer ones
-// 1.08 - 1.23; up to 2048 elements 0.84 - 1.03, and on fewer blocks 0.91 - 1.0, with more than 4096 elements 1.04 - 1.14 there, not taken).  Rows
-// of Y that do not start on lines lose (4765 x 3328 -> 13184, k = 8, float32: 62.6 us and 70.4).
+// 1.08 - 1.23; up to 2048 elements 0.84 - 1.03, and on fewer blocks 0.91 - 1.0, with more than 4096 elements 1.04 - 1.14 there, where no line
+// has been drawn: those stay with the blocks of 64 x 64).  Rows of Y that do not start on lines lose (4765 x 3328 -> 13184, k = 8, float32: 62.6 us
+// and 70.4); U % 64 sees to that for both types, float32 with U % 64 == 32 was not drawn by itself and stays where it was.
 bool binact_long_rows(const BinactArgs &a) {
     const int64_t U = a.p / a.in;
     return a.in > 2048 && a.in <= kCountedRows && U % 64 == 0 && ((a.M + 127) / 128) * ((U + 127) / 128) > 384;

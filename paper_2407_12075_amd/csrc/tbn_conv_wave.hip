@@ -189,8 +189,10 @@ __global__ __launch_bounds__(64 * kMaxWaves, (wave_bound(sizeof(XT) == 4, MT, T,
     // 14^2 -> 256, k = 8: 22.6 us before, 21.3 now; 16 x 512 x 7^2 -> 512, k = 8 19.2 / 17.3).  Else a load covers LP neighbouring pixels of an image row (one where a 1x1 layer
     // strides).  A load is moved so that it stays inside the plane (1x1: inside the row), and bfloat16 loads of 3x3 layers begin at
     // even elements where all planes do (pairs at odd ones took 10 cycles instead of 7: 32 x 64 x 56^2 -> 64, k = 4 13.2 us / 12.0; runs
-    // for its tiles of 16 filters, two per lane, cost the registers of the operand reads, 12.4 - 13.8).  183 drawn layers of stride 1
-    // 1.03 times as fast on the mean, 51 of stride 2 1.03.  Positions outside the image stay zero.
+    // for its tiles of 16 filters, two per lane, cost the registers of the operand reads, 12.4 - 13.8).  738 drawn layers with runs: 1.04 times as
+    // fast as with pixels and pairs on the mean; three are more than 3 % slower, float32 with full patches on 3000 and more waves (26 x 512 x 37 x
+    // 36 -> 64, k = 4 0.91; neighbours of these are faster, by no rule that was found).  Even pairs: 1.02 - 1.1 on the mean of a form,
+    // single layers 0.94 (7 x 160 x 66 x 64 -> 128, k = 2 19.9 us / 21.2).  Positions outside the image stay zero.
     uint32_t goff[IT];     // byte offset inside a channel plane (RUNS: with that of the lane's channel group)
     uint32_t loff[IT][(LP + 1) / 2];   // byte offsets inside a channel group of the patch (RUNS: with that of the group), two to a word
     auto lds_off = [&](int it, int h) __attribute__((always_inline)) { return LP == 1 ? loff[it][0] : h & 1 ? loff[it][h / 2] >> 16 : loff[it][h / 2] & 0xffffu; };
@@ -676,7 +678,9 @@ WavePlan plan_wave_for(const ConvArgs &a, int nft) {
     pl.nft = nft;
     // Pixel block: rows x cols output pixels of at most pw (64, or 32 where a 64-pixel patch would not fit) whose patch fits
     // the LDS pixels that `it` loads per lane cover.  The cost of a map is its number of blocks times what a wave spends
-    // on 32 channels of a block, in cycles: staging per load, operand expansion per filter tile, MFMAs per pixel tile.
+    // on 32 channels of a block, in cycles: staging per load, operand expansion per filter tile, MFMAs per pixel tile.  (Fitted to loads of
+    // single pixels and pairs, as are the limits of `fits`: whether a map allows runs is not known here, and where it does the staging
+    // costs less.)
     double best = 0;
     for (int mt : {16, 32}) {
         if (mt == 16 && (f32 || R > 16)) continue;
@@ -783,8 +787,8 @@ ConvArgs as_rows(ConvArgs a) {
 // constant, the chunks of 32 channels, the replicas and the pixel blocks / 256.  Least squares over 9169 random layers
 // of common sizes, 10 - 15 % off on the average, so the other kernel has to be estimated 9 % faster.  Of 16550 layers (also
 // larger ones) 1543 were more than 4 % slower here than there with this kernel always; by this rule 663 are, and 67 are
-// slower there than here (margin 3 %: 550 and 207).  (The 3x3 rows of the table are from before one load fetched a window: this kernel
-// takes 0.98 of that time on the mean in bfloat16 and the same in float32.)
+// slower there than here (margin 3 %: 550 and 207).  (The 3x3 rows of the table are from before one load fetched a window, which took this
+// kernel to 0.98 of that time on the mean in bfloat16 and the same in float32, and from before runs and even pairs, 0.96 - 0.97 of it in both.)
 bool prefer_wave(const ConvArgs &a, const WavePlan &pl) {
     struct Model { double wave[4], block[4]; };
     static const Model models[2][2] = {   // [bfloat16][3x3]

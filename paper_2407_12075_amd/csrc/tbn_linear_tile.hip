@@ -28,10 +28,10 @@
 //     lines of Y (a lane of the accumulator layout holds four adjacent columns of one row only).
 //
 // float32: the K loop as a pipeline over steps (see there) and two chunks in flight for long rows in one slice, 150 drawn layers
-// of 157 - 12200 rows: 1.105 times as fast on the mean, 0.98 - 1.4 each (8192 x 4096 -> 4096, k = 8: 130.8 us before, 129.6 now;
+// of 157 - 12200 rows: 1.105 times as fast on the mean, 0.98 - 1.4 each (8192 x 4096 -> 4096, k = 8: 130.8 us before, 129.6 now, on another card 108.8 and 100.9;
 // 826 x 3712 -> 2624 distinct columns 77.1 / 59.3; 4304 x 2176 -> 128 34.4 / 29.0; 12608 x 384 -> 1536 and 1536 -> 384, k = 4,
-// 43.4 / 42.3 together).  On big layers the matrix pipe then runs at its limit of power: 60 cycles per product at 1.76 GHz before, 54 at
-// 1.62 now.
+// 43.4 / 42.3 together).  On big layers the matrix pipe then runs at its limit of power: on the first card 60 cycles per product at 1.76 GHz
+// before, 54 at 1.62 now.
 //
 // bfloat16 with K split, graph replays, 4096 -> 512 distinct columns, batch 300: 9.0 us before, 6.4 now (8192: 14.0 / 10.7;
 // 1024: 5.3 / 4.2).  A wave per 32 columns where that leaves a workgroup per CU (8.7 -> 6.9), sums and stores by all waves, the table
