@@ -27,7 +27,7 @@
 //   * the sums are turned round through LDS, 32 x 32 at a time, so that a store instruction writes whole
 //     lines of Y (a lane of the accumulator layout holds four adjacent columns of one row only).
 //
-// float32: the K loop as a pipeline over steps (see there) and two chunks in flight for long rows in one slice, 150 drawn layers
+// float32: the K loop as a pipeline over steps (see there; not where plain_loop says) and two chunks in flight for long rows in one slice, 150 drawn layers
 // of 157 - 12200 rows: 1.105 times as fast on the mean, 0.98 - 1.4 each (8192 x 4096 -> 4096, k = 8: 130.8 us before, 129.6 now, on another card 108.8 and 100.9;
 // 826 x 3712 -> 2624 distinct columns 77.1 / 59.3; 4304 x 2176 -> 128 34.4 / 29.0; 12608 x 384 -> 1536 and 1536 -> 384, k = 4,
 // 43.4 / 42.3 together).  On big layers the matrix pipe then runs at its limit of power: on the first card 60 cycles per product at 1.76 GHz
@@ -110,13 +110,40 @@ struct Lds {
 // wave per SIMD alone would gain, 5 %).
 constexpr int32_t kLongSlice = 12;
 
-// (float32: at most 256 registers, or the sums go to accumulation registers, which a tie would move them out of and back)
+// float32, K split and few columns: the plain loop.  The three or six products of a step cover little of the next step's 44 vector instructions, and
+// the pipeline stores a chunk two steps before it is multiplied, so that its loads have three steps to arrive instead of four.
+// Pipeline, over the plain loop's speed, 900 drawn layers of 256 - 8192 elements: one column tile and four waves 0.90 - 0.98 in the mean at up to
+// 1024 waves, by rows' length, 0.96 - 1.01 beyond (4611 x 2304 -> 8 distinct columns 9.5 us plain, 11.6), eight waves 0.91 - 0.97, two column
+// tiles and eight waves 0.95 - 0.98; two and four 1.04 - 1.09, three and eight 0.98 - 1.06, the rest above that.
+constexpr bool plain_loop(int NT, int KW) { return (KW == 4 && NT == 1) || (KW == 8 && NT <= 2); }
+
+// truncation split of eight floats into three bf16x8 operands: term 0 = top 8 significand bits, term 1 = the next 8,
+// term 2 = the rest (at most 8 bits, so its truncation to bfloat16 is exact)
+__device__ __forceinline__ void split8(const float (&x)[8], Frag (&t)[3]) {
+    uint32_t h[3][8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        const uint32_t t0 = __float_as_uint(x[i]) & 0xffff0000u;
+        const float r1 = x[i] - __uint_as_float(t0);
+        const uint32_t t1 = __float_as_uint(r1) & 0xffff0000u;
+        const float r2 = r1 - __uint_as_float(t1);
+        h[0][i] = t0; h[1][i] = t1; h[2][i] = __float_as_uint(r2);
+    }
+#pragma unroll
+    for (int j = 0; j < 3; ++j)
+#pragma unroll
+        for (int v = 0; v < 4; ++v)   // high halves of two words in one: (lo >> 16) | (hi & 0xffff0000)
+            t[j].q[v] = __builtin_amdgcn_perm(h[j][2 * v + 1], h[j][2 * v], 0x07060302u);
+}
+
+// AHEAD: float32, chunks in flight in the pipeline over steps; 0 and bfloat16: the plain loop, one chunk in flight.
+// (pipeline: at most 256 registers, or the sums go to accumulation registers, which a tie would move them out of and back)
 template <typename XT, bool RELU, int NT, int KW, int AHEAD>
-__global__ __launch_bounds__(64 * KW, (std::is_same<XT, float>::value || KW == 8 ? 2 : 1)) void linear_tile_kernel(const XT *__restrict__ x, XT *__restrict__ y,
+__global__ __launch_bounds__(64 * KW, ((std::is_same<XT, float>::value && AHEAD > 0) || KW == 8 ? 2 : 1)) void linear_tile_kernel(const XT *__restrict__ x, XT *__restrict__ y,
                                                               const uint32_t *__restrict__ tile,
                                                               const float *__restrict__ alpha, TileParams P) {
     typedef Lds<NT, KW> L;
-    constexpr bool kF32 = std::is_same<XT, float>::value;
+    constexpr bool kF32 = std::is_same<XT, float>::value, kPipe = kF32 && AHEAD > 0;
     constexpr int kCE = chunk_elems<XT>();          // elements of K per chunk
     constexpr int kSteps = kCE / 16;                // MFMA steps per chunk
     constexpr int kWords = kCE / 64;                // tile words per lane half, column and chunk
@@ -147,7 +174,7 @@ __global__ __launch_bounds__(64 * KW, (std::is_same<XT, float>::value || KW == 8
     }
     const int64_t m0 = int64_t(rt) * 32;
     const int32_t u0 = cg * (NT * 32);
-    const int32_t k_begin = (kF32 ? __builtin_amdgcn_readfirstlane(wave) : wave) * P.k_per_wave;
+    const int32_t k_begin = (kPipe ? __builtin_amdgcn_readfirstlane(wave) : wave) * P.k_per_wave;
 
     // loads: instruction (i, h) of a chunk reads rows 8i + lane/8, bytes 128h + 16*(lane%8) .. + 15 of the chunk's 256:
     // eight lanes cover a whole 128-byte line.  Rows past M repeat the last one; they are never written.
@@ -174,7 +201,7 @@ __global__ __launch_bounds__(64 * KW, (std::is_same<XT, float>::value || KW == 8
             rd_pos[s4][j] = static_cast<uint32_t>(ln * 256 + (((8 * lg + kReads * s4 + j) ^ (ln & 15)) << 4));
 
     // tile words of this lane's column in every column tile: bit u * in + k; a lane half covers kWords words per chunk
-    // (float32: one address per wave and 32-bit offsets, for the registers; in bfloat16 that is 0.7 % slower at batch 300)
+    // (pipeline: one address per wave and 32-bit offsets, for the registers; in bfloat16 that is 0.7 % slower at batch 300)
     const uint32_t *tp[NT];
     const unsigned char *t_blk = reinterpret_cast<const unsigned char *>(tile + ((int64_t(u0) * P.in + k_begin) >> 5));
     uint32_t t_off[NT];   // byte offsets from t_blk
@@ -192,9 +219,10 @@ __global__ __launch_bounds__(64 * KW, (std::is_same<XT, float>::value || KW == 8
 #pragma unroll
         for (int e = 0; e < 16; ++e) acc[t][e] = 0.f;
 
-    static_assert(AHEAD == 1 || (kF32 && AHEAD == 2), "");
-    u32x4_t xr[AHEAD][8];   // the chunks in flight: [i][h]
-    uint32_t wr[AHEAD][NT][kWords];
+    static_assert(kF32 ? AHEAD >= 0 && AHEAD <= 2 : AHEAD == 0, "");
+    constexpr int kBufs = AHEAD == 2 ? 2 : 1;
+    u32x4_t xr[kBufs][8];   // the chunks in flight: [i][h]
+    uint32_t wr[kBufs][NT][kWords];
     auto load_chunk = [&](int32_t c, u32x4_t (&xr)[8], uint32_t (&wr)[NT][kWords]) __attribute__((always_inline)) {
         const unsigned char *src = x_blk + c * kChunkBytes;
 #pragma unroll
@@ -205,7 +233,7 @@ __global__ __launch_bounds__(64 * KW, (std::is_same<XT, float>::value || KW == 8
         for (int t = 0; t < NT; ++t)
 #pragma unroll
             for (int w = 0; w < kWords; ++w) {
-                if constexpr (kF32) wr[t][w] = reinterpret_cast<const uint32_t *>(t_blk + c * 8 * kWords + t_off[t])[w];
+                if constexpr (kPipe) wr[t][w] = reinterpret_cast<const uint32_t *>(t_blk + c * 8 * kWords + t_off[t])[w];
                 else wr[t][w] = tp[t][c * 2 * kWords + w];
             }
     };
@@ -229,7 +257,8 @@ __global__ __launch_bounds__(64 * KW, (std::is_same<XT, float>::value || KW == 8
     // nothing and stands by itself, because with a condition around the loads the compiler cannot count them in its waits (batch
     // 300, 4096 -> 512 distinct columns 6.4 us against 6.6); it then has to be kept from moving them down, which four waves pay for
     // with every chunk (312 x 8704 -> 976 distinct columns: 15.5 us with the condition, 17.5 with the loads moved down, 14.1 now; 177 x
-    // 5632 -> 1664: 11.8 / 13.0 / 10.6; eight waves are level: 300 x 8192 -> 512 14.3 / 10.5 / 10.6).
+    // 5632 -> 1664: 11.8 / 13.0 / 10.6; eight waves are level: 300 x 8192 -> 512 14.3 / 10.5 / 10.6).  float32 here (few columns, K
+    // split) keeps the condition.
     auto multiply_chunk = [&](int32_t c, auto more) {
         uint32_t wc[NT][kWords];
 #pragma unroll
@@ -241,23 +270,33 @@ __global__ __launch_bounds__(64 * KW, (std::is_same<XT, float>::value || KW == 8
 #pragma unroll
             for (int h = 0; h < 2; ++h) *reinterpret_cast<u32x4_t *>(region_b + st_pos[i][h]) = xr[0][2 * i + h];
         __builtin_amdgcn_wave_barrier();   // lanes read what other lanes of the wave wrote (LDS operations of a wave stay in order)
-        if (decltype(more)::value) load_chunk(c + 1, xr[0], wr[0]);
-        // left to itself the compiler moves these loads behind most of the products below, which they are to run under
-        __builtin_amdgcn_sched_barrier(0);
+        if (decltype(more)::value && (!kF32 || c + 1 < chunks)) load_chunk(c + 1, xr[0], wr[0]);
+        // bfloat16: left to itself the compiler moves these loads behind most of the products below, which they are to run under
+        if constexpr (!kF32) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int s4 = 0; s4 < kSteps; ++s4) {
-            Frag xt;
-            xt.q = *reinterpret_cast<const u32x4_t *>(region_b + rd_pos[s4][0]);
+            constexpr int kTerms = kF32 ? 3 : 1;
+            Frag xt[kTerms];
+            if constexpr (kF32) {
+                const f32x4_t a = *reinterpret_cast<const f32x4_t *>(region_b + rd_pos[s4][0]);
+                const f32x4_t b = *reinterpret_cast<const f32x4_t *>(region_b + rd_pos[s4][kReads - 1]);
+                const float xs[8] = {a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
+                split8(xs, xt);
+            } else {
+                xt[0].q = *reinterpret_cast<const u32x4_t *>(region_b + rd_pos[s4][0]);
+            }
 #pragma unroll
             for (int t = 0; t < NT; ++t) {
                 Frag sg;
                 sg.q = s_table[(wc[t][s4 / 4] >> (8 * (s4 % 4))) & 0xffu];
-                acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(sg.v, xt.v, acc[t], 0, 0, 0);
+#pragma unroll
+                for (int j = 0; j < kTerms; ++j)
+                    acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(sg.v, xt[j].v, acc[t], 0, 0, 0);
             }
         }
         __builtin_amdgcn_wave_barrier();   // the next chunk overwrites the region
     };
-    if constexpr (kF32) {
+    if constexpr (kPipe) {
         // float32: the split of a step's activations into terms takes 44 vector instructions, as long as six of its products.  One
         // after the other (many rows and distinct columns leave one wave per SIMD) that was 60 cycles per product of 32; here the
         // next step's split is dealt to the slots behind this step's matrix instructions (pinned there: the compiler would put the
@@ -377,8 +416,8 @@ __global__ __launch_bounds__(64 * KW, (std::is_same<XT, float>::value || KW == 8
         __builtin_amdgcn_wave_barrier();
     } else {
         int32_t c = 0;
-        for (; c + 1 < chunks; ++c) multiply_chunk(c, std::true_type{});
-        multiply_chunk(c, std::false_type{});
+        for (; c + (kF32 ? 0 : 1) < chunks; ++c) multiply_chunk(c, std::true_type{});
+        if constexpr (!kF32) multiply_chunk(c, std::false_type{});
     }
 
     // ---- bfloat16, K split: every thread adds CP neighbouring outputs of one row over the waves, in wave order (results are the
@@ -575,12 +614,13 @@ tbn_status launch_one(const LinearArgs &a, const TileParams &P, unsigned grid) {
 
 template <typename XT, bool RELU, int NT>
 tbn_status launch_kw(const LinearArgs &a, const TileParams &P, unsigned grid, int kw) {
-    if (kw == 8) return launch_one<XT, RELU, NT, 8, 1>(a, P, grid);
-    if (kw == 4) return launch_one<XT, RELU, NT, 4, 1>(a, P, grid);
-    if constexpr (std::is_same<XT, float>::value) {
+    constexpr bool f32 = std::is_same<XT, float>::value;
+    if (kw == 8) return launch_one<XT, RELU, NT, 8, (f32 && !plain_loop(NT, 8) ? 1 : 0)>(a, P, grid);
+    if (kw == 4) return launch_one<XT, RELU, NT, 4, (f32 && !plain_loop(NT, 4) ? 1 : 0)>(a, P, grid);
+    if constexpr (f32) {
         if (P.k_per_wave > kLongSlice * chunk_elems<float>()) return launch_one<XT, RELU, NT, 1, 2>(a, P, grid);
     }
-    return launch_one<XT, RELU, NT, 1, 1>(a, P, grid);
+    return launch_one<XT, RELU, NT, 1, (f32 ? 1 : 0)>(a, P, grid);
 }
 
 template <typename XT, bool RELU>

@@ -166,6 +166,14 @@ def test_tile_kernel_requests_a_chunk_before_the_products_of_the_one_before():
     assert loops == 12   # with and without ReLU, one and two column tiles, one, four and eight slices of K
 
 
+def test_float32_tile_kernel_keeps_the_plain_loop_for_few_columns_with_k_split():
+    """One column tile with four or eight slices of K and two with eight are faster without the pipeline over steps."""
+    text = asm_check.compile_to_asm(os.path.join(hip_build.CSRC, "tbn_linear_tile.hip"))
+    built = {tuple(map(int, m)) for m in re.findall(r"linear_tile_kernelIfLb[01]ELi(\d)ELi(\d)ELi(\d)E", text)}   # column tiles, slices, chunks ahead
+    split = {(nt, kw, 0 if (nt, kw) in {(1, 4), (1, 8), (2, 8)} else 1) for nt in (1, 2, 3, 4) for kw in (4, 8)}
+    assert built == split | {(nt, 1, ahead) for nt in (1, 2, 3, 4) for ahead in (1, 2)}
+
+
 def test_registers_that_lanes_are_read_from_are_held_in_all_lanes():
     """The kernels on sign bits keep the scalar of replica t in lane t and read it by v_readlane where only some lanes may be on.  Behind the
     products, where all are, the source marks the register as used; the marked register has to be the one that is read, every narrowing of

@@ -1,6 +1,6 @@
 """float32 layers whose tile holds whole weight rows, one wave per 32 batch rows: the loop over chunks of 64 elements, of which one or two are
 on their way while one is multiplied, at every count where its beginning and end differ, for one to four column tiles per wave, K in one
-slice or several, rows and columns that end inside a tile.  Exact arithmetic: half of the rows hold integers of 13 bits, whose sums
+slice or several (there one or two column tiles keep a plain loop), rows and columns that end inside a tile.  Exact arithmetic: half of the rows hold integers of 13 bits, whose sums
 float32 holds, the other half one integer of 24 bits, which takes all three terms of the split.  Below, the kernel for any row length where
 its workgroups of eight waves would need a second round of the CUs and take four waves, or one column tile instead of four."""
 import pytest
@@ -18,7 +18,7 @@ def tbn():
 
 @pytest.mark.parametrize("U", [32, 60, 96, 100, 256])
 @pytest.mark.parametrize("chunks", [1, 2, 3, 4, 5, 6, 7, 11, 13, 14, 15, 17,   # K in one slice; two chunks on their way from 13 on
-                                    8, 12, 16, 24])                            # four or eight slices of two or three
+                                    8, 12, 16, 24, 28, 40])                    # four or eight slices of two, three, seven or five
 def test_chunks_of_the_float32_loop(tbn, chunks, U):
     M, cin, k = 301, 64 * chunks, 2
     g = torch.Generator().manual_seed(chunks * 1000 + U)
