@@ -757,7 +757,7 @@ constexpr int kStLds = kGroups * kStPlane * 4 > 2 * kStStage ? kGroups * kStPlan
 
 // PIN: operands and matrix instructions stay where they stand, and sign bits' first alphas are fetched in front of the loop (387 drawn layers
 // with sign bits out on 257 - 512 blocks, without / with: rows of 1280 - 2048 elements 0.98 in the mean, 2304 - 3072 0.99, 3328 - 4096
-// 1.02, longer ones 1.06; with real outputs 1.00 - 1.04 at any length).
+// 1.02, longer ones 1.06; with real outputs 1.00 - 1.04 at any length; from before the alphas came without branches, which gave either 1.02 - 1.04).
 template <typename YT, bool RELU, bool SIGN, bool PIN>
 __global__ __launch_bounds__(256, 2) void binact_staged_kernel(const uint32_t *__restrict__ xbits, YT *__restrict__ y,
                                                                             const uint32_t *__restrict__ tile,
@@ -868,11 +868,14 @@ __global__ __launch_bounds__(256, 2) void binact_staged_kernel(const uint32_t *_
     // alpha of replica t in lane t (replicas past the 64th are fetched one by one below); sign bits out: a lane's first eight
     // replicas (up to 16 replicas in all)
     float alpha_lanes = 0.f, al_own[8] = {};
+    const int32_t last_alpha = P.n_alpha == 1 ? 0 : P.reps - 1;
     auto first_alphas = [&]() __attribute__((always_inline)) {
 #pragma unroll
         for (int c = 0; c < 8; ++c) {
             const int32_t t = lh + 2 * c;
-            al_own[c] = alpha[P.n_alpha == 1 ? 0 : (t < P.reps ? t : P.reps - 1)];
+            // (With the choice between one scalar and many made here, the compiler put a branch around every load and they came one after the
+            // other: 2600 drawn layers with sign bits out 1.03 - 1.04 times as fast without, 16 x 512 -> 8192, k = 8 4.47 us / 4.2.)
+            al_own[c] = alpha[t < last_alpha ? t : last_alpha];
         }
     };
     if constexpr (!SIGN) alpha_lanes = alpha[P.n_alpha == 1 ? 0 : (lane < P.reps ? lane : P.reps - 1)];

@@ -174,14 +174,25 @@ def test_float32_tile_kernel_keeps_the_plain_loop_for_few_columns_with_k_split()
     assert built == split | {(nt, 1, ahead) for nt in (1, 2, 3, 4) for ahead in (1, 2)}
 
 
+def test_scalars_of_sign_bits_out_are_loaded_without_branches():
+    """The 64 x 64 blocks with sign bits out load eight scalars per lane; a branch around each, for layers with a single one, makes eight round
+    trips of them.  (Such a branch loads the single one by a scalar load.)"""
+    text = asm_check.compile_to_asm(os.path.join(hip_build.CSRC, "tbn_binact.hip"))
+    bodies = [b for n, b in asm_check._split_kernels(text).items() if "binact_staged_kernelIfLb0ELb1E" in n]
+    assert len(bodies) == 2 and not any(l.startswith("s_load_dword ") for b in bodies for l in b)
+
+
 def test_registers_that_lanes_are_read_from_are_held_in_all_lanes():
     """The kernels on sign bits keep the scalar of replica t in lane t and read it by v_readlane where only some lanes may be on.  Behind the
     products, where all are, the source marks the register as used; the marked register has to be the one that is read, every narrowing of
     the execution mask between the last product and the mark undone, and nothing may load the register again behind it."""
     text = asm_check.compile_to_asm(os.path.join(hip_build.CSRC, "tbn_binact.hip"))
     checked = 0
-    for body in re.findall(r"^(_Z\w*binact_(?:mfma|staged)_kernel\w*):.*?\n(.*?)s_endpgm\n\s*\.section", text, re.S | re.M):
-        lines = body[1].splitlines()
+    functions = re.split(r"^(_Z\w+):.*$", text, flags=re.M)      # what stands before the first, then name, text, name, text ...
+    for body in zip(functions[1::2], functions[2::2]):
+        lines = re.split(r"^\s*\.section", body[1], maxsplit=1, flags=re.M)[0].splitlines()
+        if not re.search(r"binact_(?:mfma|staged)_kernel", body[0]):
+            continue
         read = {re.search(r"v_readlane_b32 \S+ (v\d+)", l).group(1) for l in lines if "v_readlane_b32" in l}
         if not read:
             continue
