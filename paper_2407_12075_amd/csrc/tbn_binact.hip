@@ -1116,7 +1116,16 @@ bool binact_long_rows(const BinactArgs &a) {
 // rows: 14 x 256 -> 1536, k = 4: 4.1 / 4.6.
 bool binact_staged_preferred(const BinactArgs &a) {
     const int64_t U = a.p / a.in, blocks = ((a.M + kStBM - 1) / kStBM) * ((U + kStBN - 1) / kStBN);
-    if (a.flags & TBN_FLAG_SIGN_OUT) return blocks <= (a.in > 1024 || U % 128 != 0 ? 512 : 256) || a.in > kCountedRows;
+    if (a.flags & TBN_FLAG_SIGN_OUT) {
+        // Short rows whose columns fill blocks of 128, but not with eight replicas or more on 8 - 13 row blocks: eight are the fewest whose column blocks
+        // share an XCD, which completes the lines of the many stores there; blocks of 128 reach that with twice the rows.  These blocks' time
+        // over the others', 1400 drawn layers, by 8, 9, 10, 11, 12, 13 row blocks: rows of 1024 elements 0.88, 0.91, 0.95, 0.96, 0.99, 0.99, of 768
+        // 0.91, 0.94, 0.96, 0.99, 0.99, 0.95, of 512 0.97, 0.98, 0.97, 1.05, 1.07, 1.10; up to seven 1.15 - 1.3, from 14 on 1.02 - 1.3, fewer replicas
+        // 1.0 - 1.25 at any number (488 x 1024 -> 32768, k = 8: 5.9 us and 6.9).
+        const int64_t row_blocks = (a.M + kStBM - 1) / kStBM;
+        const bool eight = a.in >= 512 && a.out / U >= 8 && row_blocks >= 8 && row_blocks <= (a.in > 512 ? 13 : 10);
+        return blocks <= (a.in > 1024 || U % 128 != 0 || eight ? 512 : 256) || a.in > kCountedRows;
+    }
     if (binact_long_rows(a)) return false;
     if (a.in < 768) return a.M > 64 && blocks <= 256;
     if (blocks <= 384) return true;

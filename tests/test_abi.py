@@ -215,6 +215,11 @@ def test_kernel_choice_of_layers_on_sign_bits(lib, dtype, M, cin, out, k, expect
     ("f32", 1024, 1024, 1024, 2, 0x4000, "staged", 0), ("f32", 1025, 1024, 1024, 2, 0x4000, "matrix-core", 1),    # 256 and 272 blocks of 64 x 64
     ("f32", 2048, 1280, 1024, 2, 0x4000, "staged", 0), ("f32", 2049, 1280, 1024, 2, 0x4000, "matrix-core", 1),    # rows of more than 1024: 512 and 528
     ("f32", 2048, 1024, 992, 2, 0x4000, "staged", 0), ("f32", 2049, 1024, 992, 2, 0x4000, "matrix-core", 1),      # column blocks of 128 to fill
+    ("f32", 449, 1024, 4096, 8, 0x4000, "staged", 0), ("f32", 448, 1024, 4096, 8, 0x4000, "matrix-core", 1),      # eight replicas, 8 - 13 blocks of 64 rows
+    ("f32", 832, 768, 2048, 8, 0x4000, "staged", 0), ("f32", 833, 768, 2048, 8, 0x4000, "matrix-core", 1),
+    ("f32", 640, 512, 2048, 8, 0x4000, "staged", 0), ("f32", 641, 512, 2048, 8, 0x4000, "matrix-core", 1),        # up to 10
+    ("f32", 449, 1024, 4096, 7, 0x4000, "matrix-core", 1), ("f32", 449, 256, 4096, 8, 0x4000, "matrix-core", 1),
+    ("f32", 513, 1024, 4096, 8, 0x4000, "matrix-core", 1),                                                        # 576
     ("f32", 4200, 1 << 22, 1024, 1, 0x4000, "matrix-core", 1), ("f32", 4200, (1 << 22) + 256, 1024, 1, 0x4000, "staged", 0),
     ("bf16", 6144, 2304, 1024, 1, 0, "matrix-core", 0), ("bf16", 6145, 2304, 1024, 1, 0, "matrix-core", 1),       # 384 and 392 blocks of 128 x 128
     ("bf16", 6145, 2048, 1024, 1, 0, "matrix-core", 0), ("f32", 6145, 2304, 1000, 1, 0, "matrix-core", 0),        # row length; rows of Y off the lines
